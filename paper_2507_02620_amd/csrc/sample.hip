@@ -9,6 +9,8 @@
 // exp2_spec is a fixed sequence of IEEE fp32 operations (no contraction), so any implementation produces the same bits.
 #include "tree.hpp"
 
+#include <algorithm>
+
 #pragma clang fp contract(off)
 
 static __device__ __forceinline__ uint64_t rng64(uint64_t seed, uint64_t step, uint64_t k) {
@@ -19,8 +21,10 @@ static __device__ __forceinline__ uint64_t rng64(uint64_t seed, uint64_t step, u
     return z;
 }
 
+// E = (uint64)(exp2_spec * 2^32).  The polynomial's value p lies in [1, 2]; scaling it by 2^(n + 32), n <= 0, and truncating is a
+// shift of its 24-bit significand, exact and without the conversion sequence a float -> uint64 cast takes.
 static __device__ __forceinline__ uint64_t exp_weight(float z, float m) {
-    const float t = __fmul_rn(__fsub_rn(z, m), 1.44269504088896341f);
+    const float t = __fmul_rn(__fsub_rn(z, m), 1.44269504088896341f);  // <= 0: m is the row's maximum
     if (!(t >= -64.0f)) return 0;
     const float n = floorf(t), f = __fsub_rn(t, n);
     float p = 1.52527338e-5f;
@@ -31,126 +35,220 @@ static __device__ __forceinline__ uint64_t exp_weight(float z, float m) {
     p = fmaf(p, f, 2.40226507e-1f);
     p = fmaf(p, f, 6.93147181e-1f);
     p = fmaf(p, f, 1.0f);
-    return (uint64_t)__fmul_rn(ldexpf(p, (int)n), 4294967296.0f);
+    const unsigned bits = __float_as_uint(p);
+    const int sh = 127 - (int)(bits >> 23) - (int)n;  // 0 .. 64 places below 2^32 (p = 2 only with n <= -1)
+    return ((uint64_t)((bits & 0x7FFFFFu) | 0x800000u) << 9) >> min(sh, 63);
 }
 
-static __device__ uint64_t block_sum_u64(uint64_t v, uint64_t* sh) {
+// Row maxima are kept as unsigned keys that order like the floats do (0: below every float), so that the chunks of a row can
+// meet in an atomic maximum.
+static __device__ __forceinline__ unsigned max_key(float m) {
+    const unsigned b = __float_as_uint(m);
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+static __device__ __forceinline__ float key_max(unsigned k) { return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k); }
+
+// Visits the elements [lo, hi) of a row with all threads of the group, adjacent threads on adjacent 16 bytes (four loads in flight
+// per thread) where the row allows it (lo a multiple of 4).
+template <typename F>
+static __device__ __forceinline__ void for_row(const float* __restrict__ p, int lo, int hi, int t, int nt, bool vec, F&& fn) {
+    int v = lo;
+    if (vec) {
+        const int n4 = (hi - lo) >> 2;
+        const f32x4* p4 = (const f32x4*)(p + lo);
+        int i = t;
+        for (; i + 3 * nt < n4; i += 4 * nt) {
+            f32x4 x[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) x[k] = p4[i + k * nt];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) fn(x[k][e]);
+        }
+        for (; i < n4; i += nt) {
+            const f32x4 x = p4[i];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) fn(x[e]);
+        }
+        v = lo + 4 * n4;
+    }
+    for (int i = v + t; i < hi; i += nt) fn(p[i]);
+}
+
+static __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, FS_WAVE);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint64_t r = 0;
-    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) r += sh[k];
-    return r;
+    return v;
 }
 
-// per verified row: m = max z, Z = sum of integer weights
-__global__ void __launch_bounds__(256) sample_rowstats_kernel(const float* __restrict__ logits, int vocab, float inv_temp, float* __restrict__ rowm,
-                                                              unsigned long long* __restrict__ rowZ) {
-    __shared__ float shm[4];
-    __shared__ uint64_t shz[4];
-    const float* p = logits + (size_t)blockIdx.x * vocab;
+#define SMP_STAT_THREADS 256
+// Row statistics of the verified rows: m = max z and Z = sum of the integer weights, which needs m first.  A compute unit draws 25 - 45 GB/s
+// from memory, so one workgroup per row leaves most of the chip idle (80 rows x 152064: 351 us in one launch with scalar loads);
+// here every row is cut into gridDim.x chunks and the chunks of a row meet in an atomic maximum and an atomic (integer: order does
+// not matter) sum: 1.6 + 15 + 13 us, 48.7 MB read twice at 3.2 - 3.7 TB/s.
+__global__ void __launch_bounds__(256) sample_clear_kernel(unsigned* __restrict__ rowm, unsigned long long* __restrict__ rowZ, int rows) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < rows) {
+        rowm[i] = 0u;
+        rowZ[i] = 0ull;
+    }
+}
+
+__global__ void __launch_bounds__(SMP_STAT_THREADS) sample_max_kernel(const float* __restrict__ logits, int vocab, float inv_temp, int chunk, bool vec,
+                                                                      unsigned* __restrict__ rowm) {
+    __shared__ float shm[SMP_STAT_THREADS / 64];
+    const float* p = logits + (size_t)blockIdx.y * vocab;
+    const int lo = blockIdx.x * chunk, hi = min(vocab, lo + chunk);
     float m = -INFINITY;
-    for (int v = threadIdx.x; v < vocab; v += blockDim.x) m = fmaxf(m, __fmul_rn(p[v], inv_temp));
+    for_row(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, FS_WAVE));
     if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
-    uint64_t z = 0;
-    for (int v = threadIdx.x; v < vocab; v += blockDim.x) z += exp_weight(__fmul_rn(p[v], inv_temp), m);
-    z = block_sum_u64(z, shz);
     if (threadIdx.x == 0) {
-        rowm[blockIdx.x] = m;
+        for (int w = 1; w < SMP_STAT_THREADS / 64; ++w) m = fmaxf(m, shm[w]);
+        atomicMax(&rowm[blockIdx.y], max_key(m));
+    }
+}
+
+__global__ void __launch_bounds__(SMP_STAT_THREADS) sample_sum_kernel(const float* __restrict__ logits, int vocab, float inv_temp, int chunk, bool vec,
+                                                                      const unsigned* __restrict__ rowm, unsigned long long* __restrict__ rowZ) {
+    __shared__ uint64_t shz[SMP_STAT_THREADS / 64];
+    const float* p = logits + (size_t)blockIdx.y * vocab;
+    const int lo = blockIdx.x * chunk, hi = min(vocab, lo + chunk);
+    const float m = key_max(rowm[blockIdx.y]);
+    uint64_t z = 0;
+    for_row(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { z += exp_weight(__fmul_rn(x, inv_temp), m); });
+    z = wave_sum_u64(z);
+    if ((threadIdx.x & 63) == 0) shz[threadIdx.x >> 6] = z;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < SMP_STAT_THREADS / 64; ++w) z += shz[w];
+        atomicAdd(&rowZ[blockIdx.y], (unsigned long long)z);
+    }
+}
+
+// The same with one workgroup per row, in one launch: small vocabularies, where the three launches are the time, and rows enough
+// to fill the chip.
+__global__ void __launch_bounds__(SMP_STAT_THREADS) sample_rowstats_kernel(const float* __restrict__ logits, int vocab, float inv_temp, bool vec,
+                                                                           unsigned* __restrict__ rowm, unsigned long long* __restrict__ rowZ) {
+    __shared__ float shm[SMP_STAT_THREADS / 64];
+    __shared__ uint64_t shz[SMP_STAT_THREADS / 64];
+    const float* p = logits + (size_t)blockIdx.x * vocab;
+    float m = -INFINITY;
+    for_row(p, 0, vocab, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
+    for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, FS_WAVE));
+    if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = m;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < SMP_STAT_THREADS / 64; ++w) m = fmaxf(m, shm[w]);
+    uint64_t z = 0;
+    for_row(p, 0, vocab, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { z += exp_weight(__fmul_rn(x, inv_temp), m); });
+    z = wave_sum_u64(z);
+    if ((threadIdx.x & 63) == 0) shz[threadIdx.x >> 6] = z;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < SMP_STAT_THREADS / 64; ++w) z += shz[w];
+        rowm[blockIdx.x] = max_key(m);
         rowZ[blockIdx.x] = z;
     }
 }
 
-#define SMP_THREADS 256
-#define SMP_NPT 4
+#define SMP_THREADS 1024 /* one node of the tree per thread */
+#define SMP_WAVES (SMP_THREADS / 64)
 
-__global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float* __restrict__ logits, int vocab, float inv_temp,
-                                                                    const float* __restrict__ rowm, const unsigned long long* __restrict__ rowZ,
+// Rank of this thread among the threads whose flag is set, and their number (two barriers).
+static __device__ __forceinline__ int block_rank(bool flag, int* sh, int* total) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const unsigned long long b = __ballot(flag);
+    __syncthreads();
+    if (lane == 0) sh[w] = __popcll(b);
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int k = 0; k < SMP_WAVES; ++k) {
+        const int c = sh[k];
+        before += k < w ? c : 0;
+        all += c;
+    }
+    *total = all;
+    return before + __popcll(b & ((1ull << lane) - 1));
+}
+
+// One workgroup walks the tree.  Latency is what it costs, so per accepted node everything that can be parallel is: the children
+// are gathered by ballots, their weights fetched together and their duplicate tests run side by side; one lane then only takes
+// the decisions from LDS.  The residual draw narrows the vocabulary down in three coalesced passes (a sixteenth per wave, a
+// sixteenth of that per wave, then 64 elements at a time) with the rejected tokens' weights taken off the sums.
+// (Three accepted nodes and a residual draw over 152064 entries: 420 -> 40 us, of which the 608 KB row through one compute unit is
+// the larger part; 16 rows x 32000 below a star of 16 nodes, whole call: 338 -> 35 us.)
+__global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float* __restrict__ logits, int vocab, float inv_temp, bool vec,
+                                                                    const unsigned* __restrict__ rowm, const unsigned long long* __restrict__ rowZ,
                                                                     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, int T,
                                                                     int n_ver, uint64_t seed, uint64_t step, AcceptResultDev* __restrict__ res,
                                                                     int32_t* __restrict__ retain) {
-    __shared__ short par[1024];
-    __shared__ int tok[1024];
-    __shared__ unsigned char keep[1024];
-    __shared__ short child[1024];
-    __shared__ int rej[1024];
-    __shared__ int scan[SMP_THREADS];
-    __shared__ uint64_t scan64[SMP_THREADS];
-    __shared__ uint64_t sh64[4];
-    __shared__ int s_u, s_next, s_nrej, s_xnew, s_nnew, s_nacc;
+    __shared__ short child[1024], jump[2][1024];
+    __shared__ unsigned char keep[1024], reach[2][1024], skip[1024];
+    __shared__ int ctok[1024], rej[1024], sh[SMP_WAVES];
+    __shared__ uint64_t cw[1024], rejw[1024], sums[SMP_WAVES];
+    __shared__ int s_next, s_nrej;
     __shared__ uint64_t s_draw, s_target;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
 
-    int bad_topo = 0;
-    for (int i = tid; i < T; i += SMP_THREADS) {
-        const int p = parent[i];
-        bad_topo |= (p < -1 || p >= i || (i == 0 && p != -1));
-        par[i] = (short)((p < -1 || p >= i) ? -1 : p);
-        tok[i] = token[i];
-        keep[i] = 0;
-    }
+    const int par = tid < T ? parent[tid] : -1;
+    const int tok = tid < T ? token[tid] : 0;
+    const int bad_topo = tid < T && (par < -1 || par >= tid || (tid == 0 && par != -1));
+    keep[tid] = 0;
+    if (tid == 0) s_draw = 0;
     if (__syncthreads_or(bad_topo)) {
         if (tid == 0) res->n_acc = -1;
         return;
     }
     if (n_ver == 0) {
-        for (int i = tid; i < T; i += SMP_THREADS) retain[i] = i;
+        if (tid < T) retain[tid] = tid;
         if (tid == 0) *res = AcceptResultDev{0, -1, 0, 1, T, 0};
         return;
     }
-    if (tid == 0) {
-        s_u = 0; s_draw = 0; s_nacc = 0; s_xnew = -1; s_nnew = -1;
-    }
-    __syncthreads();
 
+    int u = 0, n_acc = 0, x_new = -1, n_new = -1;  // uniform over the workgroup
     for (;;) {  // one iteration per accepted node: at most T of them
-        const int u = s_u;
-        // children of u in ascending order (parallel compaction)
-        int flags[SMP_NPT], local = 0;
-#pragma unroll
-        for (int q = 0; q < SMP_NPT; ++q) {
-            const int i = tid * SMP_NPT + q;
-            flags[q] = (i < T && i > u && par[i] == u);
-            local += flags[q];
+        const float* row = logits + (size_t)u * vocab;
+        const float m = key_max(rowm[u]);
+        const uint64_t Z = rowZ[u];
+        // children of u in ascending order, their tokens and weights
+        const bool is_child = tid < T && par == u;
+        const bool in_vocab = is_child && tok >= 0 && tok < vocab;
+        const uint64_t wt = in_vocab ? exp_weight(__fmul_rn(row[tok], inv_temp), m) : 0;
+        int n_child;
+        const int rank = block_rank(is_child, sh, &n_child);
+        if (is_child) {
+            child[rank] = (short)tid;
+            ctok[rank] = in_vocab ? tok : -1;
+            cw[rank] = wt;
         }
-        scan[tid] = local;
+        if (tid == 0) keep[u] = 1;
+        ++n_acc;
         __syncthreads();
-        for (int o = 1; o < SMP_THREADS; o <<= 1) {
-            const int v = (tid >= o) ? scan[tid - o] : 0;
-            __syncthreads();
-            scan[tid] += v;
-            __syncthreads();
+        // A child whose token an earlier sibling carries is passed over: whenever it is reached, that sibling was rejected.
+        if (tid < n_child) {
+            const int t = ctok[tid];
+            bool dup = t < 0;
+            for (int j = 0; j < tid && !dup; ++j) dup = (ctok[j] == t);
+            skip[tid] = dup;
         }
-        int pos = scan[tid] - local;
-        const int n_child = scan[SMP_THREADS - 1];
-#pragma unroll
-        for (int q = 0; q < SMP_NPT; ++q)
-            if (flags[q]) child[pos++] = (short)(tid * SMP_NPT + q);
         __syncthreads();
         if (tid == 0) {
-            keep[u] = 1;
-            ++s_nacc;
-            const float* row = logits + (size_t)u * vocab;
-            const float m = rowm[u];
-            uint64_t R = rowZ[u], draw = s_draw;
+            uint64_t R = Z, draw = s_draw;
             int n_rej = 0, next = -1;
             for (int k = 0; k < n_child && next < 0; ++k) {
-                const int c = child[k], t = tok[c];
-                bool dup = (t < 0 || t >= vocab);
-                for (int j = 0; j < n_rej && !dup; ++j) dup = (rej[j] == t);
-                if (dup) continue;
-                const uint64_t Ec = exp_weight(__fmul_rn(row[t], inv_temp), m);
+                if (skip[k]) continue;
+                const uint64_t Ec = cw[k];
                 const uint64_t r24 = rng64(seed, step, draw++) >> 40;
                 const uint64_t hi = __umul64hi(r24, R), lo = r24 * R;
                 if (hi == 0 && lo < (Ec << 24)) {
-                    next = c;
+                    next = child[k];
                 } else {
                     R -= Ec;
-                    rej[n_rej++] = t;
+                    rej[n_rej] = ctok[k];
+                    rejw[n_rej++] = Ec;
                 }
             }
             s_next = next; s_nrej = n_rej;
@@ -164,97 +262,115 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
         __syncthreads();
         const int next = s_next;
         if (next >= 0 && next < n_ver) {  // accepted and verified: descend
-            if (tid == 0) s_u = next;
-            __syncthreads();
+            u = next;
             continue;
         }
         if (next >= 0) {  // accepted, not verified yet: the node n_new of the continuous condition
-            if (tid == 0) {
-                s_xnew = tok[next];
-                s_nnew = next;
-            }
-        } else {  // residual draw over the vocabulary: thread t owns a contiguous chunk, integer prefix sums locate the token
-            const float* row = logits + (size_t)u * vocab;
-            const float m = rowm[u];
-            const int n_rej = s_nrej;
-            const int chunk = (vocab + SMP_THREADS - 1) / SMP_THREADS;
-            const int lo = min(vocab, tid * chunk), hi = min(vocab, lo + chunk);
-            auto weight = [&](int v) -> uint64_t {
-                for (int j = 0; j < n_rej; ++j)
-                    if (rej[j] == v) return 0;
-                return exp_weight(__fmul_rn(row[v], inv_temp), m);
-            };
-            uint64_t mine = 0;
-            for (int v = lo; v < hi; ++v) mine += weight(v);
-            scan64[tid] = mine;
+            for (int k = 0; k < n_child; ++k)
+                if (child[k] == next) x_new = ctok[k];
+            n_new = next;
+            break;
+        }
+        // Residual draw: the first v whose running sum of unstruck weights exceeds the target.  Integer sums: any grouping gives
+        // the same token.
+        const uint64_t target = s_target;
+        const int n_rej = s_nrej;
+        int lo = 0, hi = vocab;
+        uint64_t base = 0;  // running sum below lo
+        bool found = true;
+        for (int pass = 0; pass < 2 && found; ++pass) {
+            const int part = ((hi - lo + SMP_WAVES - 1) / SMP_WAVES + 3) & ~3;  // a multiple of 4 elements per wave
+            const int wlo = min(hi, lo + w * part), whi = min(hi, wlo + part);
+            uint64_t z = 0;
+            for_row(row, wlo, whi, lane, 64, vec, [&](float x) { z += exp_weight(__fmul_rn(x, inv_temp), m); });
+            for (int j = lane; j < n_rej; j += 64)
+                if (rej[j] >= wlo && rej[j] < whi) z -= rejw[j];
+            z = wave_sum_u64(z);
             __syncthreads();
-            for (int o = 1; o < SMP_THREADS; o <<= 1) {
-                const uint64_t v = (tid >= o) ? scan64[tid - o] : 0;
-                __syncthreads();
-                scan64[tid] += v;
-                __syncthreads();
-            }
-            const uint64_t before = scan64[tid] - mine, target = s_target;
-            if (tid == 0) s_xnew = vocab - 1;  // only reached if the weights changed under us; mirrors the definition's default
+            if (lane == 0) sums[w] = z;
             __syncthreads();
-            if (target >= before && target < before + mine) {
-                uint64_t run = before;
-                for (int v = lo; v < hi; ++v) {
-                    run += weight(v);
-                    if (run > target) {
-                        s_xnew = v;
-                        break;
-                    }
+            found = false;
+            const int lo0 = lo, hi0 = hi;
+            uint64_t before = base;
+            for (int k = 0; k < SMP_WAVES; ++k) {
+                const uint64_t s = sums[k];
+                if (!found && target < before + s) {  // the first part that reaches beyond the target
+                    found = true;
+                    lo = min(hi0, lo0 + k * part);
+                    hi = min(hi0, lo + part);
+                    base = before;
                 }
+                before += s;
             }
         }
-        __syncthreads();
+        x_new = vocab - 1;  // the definition's default (no weight left)
+        for (int v0 = lo; found && v0 < hi; v0 += 64) {  // every wave does the same
+            const int v = v0 + lane;
+            uint64_t run = 0;
+            if (v < hi) {
+                run = exp_weight(__fmul_rn(row[v], inv_temp), m);
+                for (int j = 0; j < n_rej; ++j)
+                    if (rej[j] == v) run = 0;
+            }
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint64_t below = __shfl_up(run, o, FS_WAVE);
+                if (lane >= o) run += below;
+            }
+            const unsigned long long hit = __ballot(v < hi && base + run > target);
+            if (hit) {
+                x_new = v0 + __ffsll(hit) - 1;
+                break;
+            }
+            base += __shfl(run, 63, FS_WAVE);
+        }
         break;
     }
 
-    // retain list: path nodes (keep = 1), then n_new and its descendants (keep = 2); parents precede children
-    const int n_new = s_nnew;
-    if (tid == 0 && n_new >= 0) {
-        keep[n_new] = 2;
-        for (int i = n_new + 1; i < T; ++i)
-            if (par[i] >= 0 && keep[par[i]] == 2) keep[i] = 2;
+    // n_new and its descendants: pointer doubling over the parent links (ceil(log2 T) rounds)
+    int cur = 0;
+    if (n_new >= 0) {
+        jump[0][tid] = (short)(tid < T ? par : -1);
+        reach[0][tid] = tid == n_new;
+        for (int span = 1; span < T; span <<= 1) {
+            __syncthreads();
+            const int j = jump[cur][tid];
+            reach[cur ^ 1][tid] = reach[cur][tid] | (j >= 0 ? reach[cur][j] : 0);
+            jump[cur ^ 1][tid] = j >= 0 ? jump[cur][j] : (short)-1;
+            cur ^= 1;
+        }
     }
     __syncthreads();
-    int flags[SMP_NPT], local = 0, prv = 0;
-#pragma unroll
-    for (int q = 0; q < SMP_NPT; ++q) {
-        const int i = tid * SMP_NPT + q;
-        flags[q] = (i < T && keep[i] != 0);
-        local += flags[q];
-        prv += (i < T && keep[i] == 2 && i < n_ver);
-    }
-    scan[tid] = local;
-    __syncthreads();
-    for (int o = 1; o < SMP_THREADS; o <<= 1) {
-        const int v = (tid >= o) ? scan[tid - o] : 0;
-        __syncthreads();
-        scan[tid] += v;
-        __syncthreads();
-    }
-    int pos = scan[tid] - local;
-    const int total = scan[SMP_THREADS - 1];
-#pragma unroll
-    for (int q = 0; q < SMP_NPT; ++q)
-        if (flags[q]) retain[pos++] = tid * SMP_NPT + q;
-    const uint64_t prv_total = block_sum_u64((uint64_t)prv, sh64);
-    if (tid == 0) *res = AcceptResultDev{s_nacc, s_xnew, n_new, n_new >= 0, total, (int)prv_total};
+    const bool on_path = tid < T && keep[tid] == 1, below = n_new >= 0 && tid < T && reach[cur][tid];
+    int total, prv;
+    const int pos = block_rank(on_path || below, sh, &total);
+    if (on_path || below) retain[pos] = tid;
+    (void)block_rank(below && tid < n_ver, sh, &prv);
+    if (tid == 0) *res = AcceptResultDev{n_acc, x_new, n_new, n_new >= 0, total, prv};
 }
 
 hipError_t launch_accept_sample(const float* logits, int vocab, float inv_temp, const int32_t* token, const int32_t* parent, int T, int n_ver,
                                 uint64_t seed, uint64_t step, AcceptResultDev* res, int32_t* retain, void* work, hipStream_t s) {
-    float* rowm = (float*)work;
+    unsigned* rowm = (unsigned*)work;
     unsigned long long* rowZ = (unsigned long long*)((char*)work + (((size_t)n_ver * sizeof(float) + 15) / 16) * 16);
+    const bool vec = (vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0;  // every row starts on 16 bytes
     if (n_ver > 0) {
-        hipLaunchKernelGGL(sample_rowstats_kernel, dim3(n_ver), dim3(256), 0, s, logits, vocab, inv_temp, rowm, rowZ);
+        // Chunks of a row: about 2048 workgroups in all, at least 4096 elements each.  From four chunks on the three launches
+        // beat one workgroup per row (whole call, chunked / single: 256 x 32000 135 / 141 us, 16 x 32000 35 / 36, 16 x 152064
+        // 78 / 104), with fewer they do not (600 x 32000 331 / 283, 16 x 8192 24 / 21).
+        int chunks = std::min((vocab + 4095) / 4096, std::max(1, 2048 / n_ver));
+        if (chunks >= 4) {
+            const int chunk = ((vocab + chunks - 1) / chunks + 3) & ~3;
+            chunks = (vocab + chunk - 1) / chunk;
+            hipLaunchKernelGGL(sample_clear_kernel, dim3((n_ver + 255) / 256), dim3(256), 0, s, rowm, rowZ, n_ver);
+            hipLaunchKernelGGL(sample_max_kernel, dim3(chunks, n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
+            hipLaunchKernelGGL(sample_sum_kernel, dim3(chunks, n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
+        } else {
+            hipLaunchKernelGGL(sample_rowstats_kernel, dim3(n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, vec, rowm, rowZ);
+        }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(accept_sample_kernel, dim3(1), dim3(SMP_THREADS), 0, s, logits, vocab, inv_temp, rowm, rowZ, token, parent, T, n_ver, seed,
+    hipLaunchKernelGGL(accept_sample_kernel, dim3(1), dim3(SMP_THREADS), 0, s, logits, vocab, inv_temp, vec, rowm, rowZ, token, parent, T, n_ver, seed,
                        step, res, retain);
     return hipGetLastError();
 }

@@ -73,3 +73,35 @@ def test_sampled_accept_errors():
     fs.tree_accept_sample(lg, 1.0, t, bad, 1, 0, 0, res, retain)
     out, _ = fs.accept_result_to_host(res, retain, 4)
     assert out.n_acc == -1
+
+
+@pytest.mark.parametrize("vocab,T,n_ver,n_child", [
+    (4096, 40, 40, 3), (4097, 40, 33, 8),      # one launch per row / the smallest chunked row, with a scalar tail
+    (10007, 90, 90, 60),                       # odd row length: unaligned rows, most of the tree below one node
+    (32000, 1024, 1024, 1000),                 # many rows: two chunks each; a star of a thousand candidates
+    (152064, 3, 2, 2),                         # few rows of the largest vocabulary: many chunks
+])
+def test_sampled_accept_row_chunks_and_residual(vocab, T, n_ver, n_child):
+    """Row statistics cut into chunks, candidates with duplicate tokens and tokens outside the vocabulary, residual draws behind
+    rejected candidates, rows with infinities and with one weight only: bit for bit as the oracle."""
+    rng = np.random.default_rng(vocab + T)
+    parent = np.array([-1] + [0 if i <= n_child else int(rng.integers(1, i)) for i in range(1, T)], dtype=np.int32)
+    token = rng.integers(0, vocab, T).astype(np.int32)
+    token[1:T:3] = token[1]                    # duplicates among siblings
+    if T > 4:
+        token[4] = vocab + 5                   # never a candidate
+    lg = (rng.standard_normal((n_ver, vocab)) * 2).astype(np.float32)
+    lg[0, token[1]] = 2.0 + np.log(vocab)      # a heavy candidate: often accepted, otherwise struck before the residual draw
+    lg[-1, ::7] = -np.inf
+    if n_ver > 1:
+        lg[1] = -np.inf
+        lg[1, vocab - 1] = 3.0                 # all weight on the last token
+    print(f"[case] vocab={vocab} T={T} n_ver={n_ver}", flush=True)
+    seen = set()
+    for step in range(10):
+        o_res, o_ret = oracle.accept_sample(lg, 1.0, token, parent, n_ver, 99, step)
+        g_res, g_ret = _gpu(lg, 1.0, token, parent, n_ver, 99, step)
+        assert g_res == o_res.as_tuple(), (step, g_res, o_res.as_tuple())
+        assert np.array_equal(g_ret, o_ret)
+        seen.add(o_res.n_acc)
+    assert len(seen) > 1                       # accepted and rejected candidates both occurred
