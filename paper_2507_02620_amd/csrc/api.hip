@@ -212,6 +212,19 @@ int valid_kv(const fs_stage_desc& d, const fs_kv_cache& kv) {
     return FS_OK;
 }
 
+constexpr int kShortTree = 32;  // levels up to which a tree's masks are found by walking to the root
+
+// Levels below the roots of a topologically ordered tree.
+int tree_depth(const int32_t* parent, int T) {
+    short depth[FS_MAX_TREE];
+    int deepest = 0;
+    for (int j = 0; j < T; ++j) {
+        depth[j] = parent[j] < 0 ? 0 : (short)(depth[parent[j]] + 1);
+        if (depth[j] > deepest) deepest = depth[j];
+    }
+    return deepest;
+}
+
 int fill_idx(IdxList& L, const int32_t* v, int n) {
     if (n < 0 || n > 1024) return FS_ECAP;
     L.n = n;
@@ -561,28 +574,30 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
 
     // ---- per request: ancestor masks, positions (rotary table) and cache slots of its rows, into the stacked arrays ----
     int row0 = 0, rq = 0;
+    PrepBatch prep;
+    prep.a.inv_freq = st->at<double>(L.off_invf); prep.a.anc = anc; prep.a.rope = rope; prep.a.krow = krow; prep.a.hd = hd;
+    prep.a.tok_bytes = (unsigned long long)kv0->stride_tok * st->elem;
     for (int i = 0; i < n; ++i) {
         const fs_batch_item& it = items[i];
         if (it.l_s == 0) continue;
         const int T = it.seg_off + it.l_s;
-        short depth[FS_MAX_TREE];
-        int max_depth = 0;
-        depth[0] = 0;
-        for (int j = 1; j < T; ++j) {
-            depth[j] = it.parent[j] < 0 ? 0 : (short)(depth[it.parent[j]] + 1);
-            if (depth[j] > max_depth) max_depth = depth[j];
+        if (tree_depth(it.parent, T) <= kShortTree) {
+            if (!prep.fits(T)) HIP_TRY_K(st, FS_K_PREPARE, s, prep.launch(s));
+            prep.add(it.parent, T, PrepReq{(unsigned long long)(uintptr_t)it.kv.base, it.l_cache, it.l_glo, (short)row0, (short)it.l_s, (short)it.seg_off, 0});
+        } else {
+            IdxList pl;
+            int rc = fill_idx(pl, it.parent, T);
+            if (rc) return rc;
+            KRowArgs kr{krow + row0, (unsigned long long)(uintptr_t)it.kv.base, prep.a.tok_bytes, it.l_cache};
+            HIP_TRY_K(st, FS_K_PREPARE, s,
+                      launch_tree_prepare_deep(pl, it.l_glo, it.seg_off, it.l_s, hd, prep.a.inv_freq, st->at<uint64_t>(L.off_ancall),
+                                               anc + (size_t)row0 * FS_ANC_WORDS, rope + (size_t)row0 * (hd / 2), kr, s));
         }
-        IdxList pl;
-        int rc = fill_idx(pl, it.parent, T);
-        if (rc) return rc;
-        KRowArgs kr{krow + row0, (unsigned long long)(uintptr_t)it.kv.base, (unsigned long long)it.kv.stride_tok * st->elem, it.l_cache};
-        HIP_TRY_K(st, FS_K_PREPARE, s,
-                  launch_tree_prepare(pl, max_depth, it.l_glo, it.seg_off, it.l_s, hd, st->at<double>(L.off_invf), st->at<uint64_t>(L.off_ancall),
-                                      anc + (size_t)row0 * FS_ANC_WORDS, rope + (size_t)row0 * (hd / 2), kr, s));
         at.req[rq] = AttnReq{it.kv.base, row0, it.l_s, it.l_glo, it.l_cache + it.l_s};
         row0 += it.l_s;
         ++rq;
     }
+    if (prep.n) HIP_TRY_K(st, FS_K_PREPARE, s, prep.launch(s));
     int aMTW, aRB;
     attn_plan(st->elem, hd, max_M, G, d.n_kv_heads * n_live, max_L, kMaxSplits, st->tun.attn_wgs, st->tun.attn_mtw, st->tun.attn_nset, st->tun.attn_nwc,
               st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma);
@@ -673,22 +688,26 @@ int fs_tree_mask(fs_stage* st, int l_glo, int seg_off, int l_s, const int32_t* p
     const int T = seg_off + l_s;
     if (T > st->d.max_tree || l_s > st->d.max_seg) return FS_ECAP;
     if (parent[0] != -1) return FS_ETOPO;
-    short depth[FS_MAX_TREE];
-    int max_depth = 0;
-    depth[0] = 0;
-    for (int j = 1; j < T; ++j) {
+    for (int j = 1; j < T; ++j)
         if (parent[j] < -1 || parent[j] >= j) return FS_ETOPO;
-        depth[j] = parent[j] < 0 ? 0 : (short)(depth[parent[j]] + 1);
-        if (depth[j] > max_depth) max_depth = depth[j];
+    const Layout& L = st->L;
+    // the rows' cache-slot table is a by-product of the same kernels: it goes to the stage's own scratch
+    unsigned long long* krow = st->at<unsigned long long>(L.off_krow);
+    hipStream_t s = (hipStream_t)stream;
+    if (tree_depth(parent, T) <= kShortTree) {
+        PrepBatch prep;
+        prep.a.inv_freq = st->at<double>(L.off_invf); prep.a.anc = anc; prep.a.rope = (float2*)rope; prep.a.krow = krow; prep.a.hd = st->d.head_dim;
+        prep.a.tok_bytes = 0;
+        prep.add(parent, T, PrepReq{0ull, 0, l_glo, 0, (short)l_s, (short)seg_off, 0});
+        HIP_TRY(prep.launch(s));
+        return FS_OK;
     }
     IdxList pl;
     int rc = fill_idx(pl, parent, T);
     if (rc) return rc;
-    const Layout& L = st->L;
-    // the rows' cache-slot table is a by-product of the same kernels: it goes to the stage's own scratch
-    KRowArgs kr{st->at<unsigned long long>(L.off_krow), 0ull, 0ull, 0};
-    HIP_TRY(launch_tree_prepare(pl, max_depth, l_glo, seg_off, l_s, st->d.head_dim, st->at<double>(L.off_invf), st->at<uint64_t>(L.off_ancall), anc,
-                                (float2*)rope, kr, (hipStream_t)stream));
+    KRowArgs kr{krow, 0ull, 0ull, 0};
+    HIP_TRY(launch_tree_prepare_deep(pl, l_glo, seg_off, l_s, st->d.head_dim, st->at<double>(L.off_invf), st->at<uint64_t>(L.off_ancall), anc,
+                                     (float2*)rope, kr, s));
     return FS_OK;
 }
 

@@ -18,42 +18,76 @@ hipError_t launch_rope_freq(double* inv_freq, int hd, float theta, hipStream_t s
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) tree_prepare_kernel(const IdxList parent, int l_glo, int seg_off, int l_s, int hd,
-                                                           const double* __restrict__ inv_freq, uint64_t* __restrict__ anc,
-                                                           float2* __restrict__ rope, KRowArgs kr) {
-    for (int r = threadIdx.x; r < l_s; r += blockDim.x) kr.krow[r] = kr.base + (unsigned long long)(kr.slot0 + r) * kr.tok_bytes;
+// Grid (16-row slice of a segment, request): latency is all it costs, so the requests of a batch share a launch and the slices of a
+// segment run side by side (two 7B layers for 32 requests of 16 rows, one launch each / one for all: 813 / 656 us; 9 requests
+// 387 / 355 us; a single 64-row segment 467 / 464 us).
+#define PREP_ROWS 16
+__global__ void __launch_bounds__(256) tree_prepare_kernel(const PrepArgs a) {
+    const PrepReq q = a.req[blockIdx.y];
+    const int r0 = blockIdx.x * PREP_ROWS, rows = min(PREP_ROWS, (int)q.l_s - r0);
+    if (rows <= 0) return;
     __shared__ short par[1024];
-    __shared__ int pos[1024];
-    const int T = seg_off + l_s;
-    for (int i = threadIdx.x; i < T; i += blockDim.x) par[i] = parent.v[i];
+    __shared__ int pos[PREP_ROWS];
+    const int T = q.seg_off + r0 + rows;  // nodes up to the slice's last one
+    for (int i = threadIdx.x; i < T; i += blockDim.x) {
+        const int p = a.wide ? (int)((const unsigned short*)a.par)[q.par0 + i] : (int)a.par[q.par0 + i];
+        par[i] = (short)(p == i ? -1 : p);
+    }
     __syncthreads();
-    for (int r = threadIdx.x; r < l_s; r += blockDim.x) {
+    if (threadIdx.x < rows) {
+        const int r = r0 + threadIdx.x;
         uint64_t m[FS_ANC_WORDS];
 #pragma unroll
         for (int w = 0; w < FS_ANC_WORDS; ++w) m[w] = 0;
         int depth = -1;
         // parent[i] < i was checked on the host, so the walk ends after at most T steps
-        for (int j = seg_off + r; j >= 0; j = par[j]) {
+        for (int j = q.seg_off + r; j >= 0; j = par[j]) {
 #pragma unroll
             for (int w = 0; w < FS_ANC_WORDS; ++w)
                 if (w == (j >> 6)) m[w] |= 1ull << (j & 63);
             ++depth;
         }
 #pragma unroll
-        for (int w = 0; w < FS_ANC_WORDS; ++w) anc[(size_t)r * FS_ANC_WORDS + w] = m[w];
-        pos[r] = l_glo + depth;
+        for (int w = 0; w < FS_ANC_WORDS; ++w) a.anc[(size_t)(q.row0 + r) * FS_ANC_WORDS + w] = m[w];
+        pos[threadIdx.x] = q.l_glo + depth;
+        a.krow[q.row0 + r] = q.base + (unsigned long long)(q.slot0 + r) * a.tok_bytes;
     }
     __syncthreads();
-    const int half = hd >> 1;
-    for (int i = threadIdx.x; i < l_s * half; i += blockDim.x) {
+    const int half = a.hd >> 1;
+    for (int i = threadIdx.x; i < rows * half; i += blockDim.x) {
         const int r = i / half, t = i % half;
         const double two_pi = 6.283185307179586476925286766559;
-        double ang = (double)pos[r] * inv_freq[t];
+        double ang = (double)pos[r] * a.inv_freq[t];
         ang -= two_pi * floor(ang / two_pi);
         float sn, cs;
         sincosf((float)ang, &sn, &cs);
-        rope[i] = make_float2(cs, sn);
+        a.rope[(size_t)(q.row0 + r0 + r) * half + t] = make_float2(cs, sn);
     }
+}
+
+bool PrepBatch::fits(int T) const {
+    const bool w = wide_tree(T);
+    return n == 0 || (n < PREP_MAX_REQ && (a.wide != 0) == w && used + T * (w ? 2 : 1) <= PREP_BYTES);
+}
+void PrepBatch::add(const int32_t* parent, int T, const PrepReq& r) {
+    a.wide = wide_tree(T);
+    const int at = a.wide ? used / 2 : used;
+    for (int i = 0; i < T; ++i) {
+        const int p = parent[i] < 0 ? i : parent[i];
+        if (a.wide) ((unsigned short*)a.par)[at + i] = (unsigned short)p;
+        else a.par[at + i] = (unsigned char)p;
+    }
+    a.req[n] = r;
+    a.req[n].par0 = (short)at;
+    used += T * (a.wide ? 2 : 1);
+    max_ls = max_ls > r.l_s ? max_ls : r.l_s;
+    ++n;
+}
+hipError_t PrepBatch::launch(hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(tree_prepare_kernel, dim3((max_ls + PREP_ROWS - 1) / PREP_ROWS, n), dim3(256), 0, s, a);
+    n = used = max_ls = 0;
+    return hipGetLastError();
 }
 
 // Deep trees (more than 32 levels): walking to the root costs one dependent step per level, so the masks and depths are
@@ -142,20 +176,17 @@ __global__ void __launch_bounds__(256) tree_prepare_chain_kernel(int l_glo, int 
     }
 }
 
-hipError_t launch_tree_prepare(const IdxList& parent, int max_depth, int l_glo, int seg_off, int l_s, int hd, const double* inv_freq,
-                               uint64_t* anc_all, uint64_t* anc, float2* rope, const KRowArgs& kr, hipStream_t s) {
-    bool chain = max_depth > 32;  // only worth looking for where the pointer-doubling kernel would run
+hipError_t launch_tree_prepare_deep(const IdxList& parent, int l_glo, int seg_off, int l_s, int hd, const double* inv_freq, uint64_t* anc_all,
+                                    uint64_t* anc, float2* rope, const KRowArgs& kr, hipStream_t s) {
+    bool chain = true;
     for (int i = 0; chain && i < seg_off + l_s; ++i) chain = parent.v[i] == i - 1;
     if (chain) {
         const int n = l_s * (FS_ANC_WORDS > hd / 2 ? FS_ANC_WORDS : hd / 2);
         hipLaunchKernelGGL(tree_prepare_chain_kernel, dim3((n + 255) / 256), dim3(256), 0, s, l_glo, seg_off, l_s, hd, inv_freq, anc, rope, kr);
         return hipGetLastError();
     }
-    if (max_depth > 32)
-        hipLaunchKernelGGL(tree_prepare_deep_kernel, dim3(1), dim3(1024), 0, s, parent, l_glo, seg_off, l_s, hd, inv_freq, anc_all,
-                           anc_all + (size_t)(seg_off + l_s) * FS_ANC_WORDS, anc, rope, kr);
-    else
-        hipLaunchKernelGGL(tree_prepare_kernel, dim3(1), dim3(256), 0, s, parent, l_glo, seg_off, l_s, hd, inv_freq, anc, rope, kr);
+    hipLaunchKernelGGL(tree_prepare_deep_kernel, dim3(1), dim3(1024), 0, s, parent, l_glo, seg_off, l_s, hd, inv_freq, anc_all,
+                       anc_all + (size_t)(seg_off + l_s) * FS_ANC_WORDS, anc, rope, kr);
     return hipGetLastError();
 }
 

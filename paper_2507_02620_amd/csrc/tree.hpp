@@ -26,11 +26,39 @@ struct KRowArgs {
     int slot0;                 // l_cache
 };
 
-// anc [l_s][FS_ANC_WORDS], rope [l_s][hd/2], kr.krow [l_s]; max_depth (of the tree, from the host's validation pass) picks the walking kernel
-// or, for deep trees, the pointer-doubling one, which needs anc_all [2][seg_off + l_s][FS_ANC_WORDS] as scratch (two copies: each
-// round reads one and writes the other).
-hipError_t launch_tree_prepare(const IdxList& parent, int max_depth, int l_glo, int seg_off, int l_s, int hd, const double* inv_freq,
-                               uint64_t* anc_all, uint64_t* anc, float2* rope, const KRowArgs& kr, hipStream_t s);
+// Short trees (at most 32 levels): the requests of a batch share launches, their parent arrays travel packed as kernel arguments
+// (the argument segment holds 4 KiB).
+constexpr int PREP_MAX_REQ = 32, PREP_BYTES = 3072;
+struct PrepReq {
+    unsigned long long base;  // as KRowArgs
+    int slot0, l_glo;
+    short row0, l_s, seg_off, par0;  // first stacked row; par0: index of the first parent entry
+};
+struct PrepArgs {
+    const double* inv_freq;
+    uint64_t* anc;             // [rows][FS_ANC_WORDS]
+    float2* rope;              // [rows][hd/2]
+    unsigned long long* krow;  // [rows]
+    unsigned long long tok_bytes;
+    int hd, wide;              // parent entries of 16 bits, else of 8 (trees of at most 256 nodes); a root's entry is its own index
+    PrepReq req[PREP_MAX_REQ];
+    unsigned char par[PREP_BYTES];
+};
+// Collects requests into launches.
+struct PrepBatch {
+    PrepArgs a;
+    int n = 0, used = 0, max_ls = 0;  // requests, bytes of parent entries, longest segment
+    static bool wide_tree(int T) { return T > 256; }
+    bool fits(int T) const;
+    void add(const int32_t* parent, int T, const PrepReq& r);
+    hipError_t launch(hipStream_t s);  // everything collected; empties the batch
+};
+
+// Deep trees (more than 32 levels): anc [l_s][FS_ANC_WORDS], rope [l_s][hd/2], kr.krow [l_s].  A chain takes the closed form, any other
+// tree the pointer-doubling kernel, which needs anc_all [2][seg_off + l_s][FS_ANC_WORDS] as scratch (two copies: each round reads one
+// and writes the other).
+hipError_t launch_tree_prepare_deep(const IdxList& parent, int l_glo, int seg_off, int l_s, int hd, const double* inv_freq, uint64_t* anc_all,
+                                    uint64_t* anc, float2* rope, const KRowArgs& kr, hipStream_t s);
 hipError_t launch_argmax(const float* logits, int rows, int vocab, int chunks, int32_t* work, int32_t* amax, hipStream_t s);
 hipError_t launch_accept(const int32_t* amax, const int32_t* token, const int32_t* parent, int T, int n_ver, AcceptResultDev* res,
                          int32_t* retain, hipStream_t s);

@@ -157,3 +157,21 @@ def test_random_batches(i):
         for l in range(cfg.n_layers):
             g = kv[l][:, :, l_glo + seg_off:l_glo + seg_off + l_s].float().cpu().numpy()
             assert max_rel_err(g, orc.kv[l][:, :, l_glo + seg_off:l_glo + seg_off + l_s]) < TOL[cfg.dtype]
+
+
+def test_batch_packs_trees_of_all_sizes_into_launches():
+    """Tree preparation of a whole batch: byte-sized parent entries (trees of 1 and 256 nodes at the ends), 16-bit ones (257 nodes and
+    more), a deep tree in between, more entries than one launch's arguments hold, segments of one row and of several 16-row slices."""
+    from tests.gpu_util import TOL, max_rel_err
+    sizes = [(1, 1), (256, 37), (257, 16), (600, 33), (256, 1)] + [(250, 20)] * 13 + [(130, 49), (40, 17)]
+    specs = [(3 + 5 * i, T, 60 if T == 130 else 7, 1 if T == 130 else 3, T - n, n) for i, (T, n) in enumerate(sizes)]
+    cfg = synth.StageConfig("b-prep", "f32", 1, 64, 1, 1, 64, 64, 0, max(s[0] for s in specs), 600, 600, 8, 3)
+    print(f"[case] {len(specs)} requests, {sum(s[5] for s in specs)} rows", flush=True)
+    got, want, caches, _ = _run_batch(cfg, specs, seed=21)
+    row = 0
+    for r, w in enumerate(want):
+        assert max_rel_err(got[row:row + w.shape[0]], w) < TOL["f32"], specs[r]
+        row += w.shape[0]
+    for kv, orc, l_glo, seg_off, l_s in caches:
+        rows = slice(l_glo + seg_off, l_glo + seg_off + l_s)
+        assert max_rel_err(kv[0][:, :, rows].cpu().numpy(), orc.kv[0][:, :, rows]) < TOL["f32"]
