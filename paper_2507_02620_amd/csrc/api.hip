@@ -268,8 +268,8 @@ struct Tunables {
         attn_nwc = env_int("FLOWSPEC_ATTN_NWC", 0);    // > 0: at most this many row-tile waves per workgroup (more row blocks)
         attn_dma = env_int("FLOWSPEC_ATTN_DMA", 0);    // 1: never the direct-to-LDS attention kernel; 2 .. 4: always, with so many tile buffers
         attn_nset = env_int("FLOWSPEC_ATTN_NSET", 0);  // > 0: K/V tiles in flight per workgroup on long splits
-        wide_rows = env_int("FLOWSPEC_WIDE_ROWS", 65); // stacked rows from which every projection takes the many-row kernel
-        mid_rows = env_int("FLOWSPEC_MID_ROWS", 17);   // ... from which the wide projections do
+        wide_rows = env_int("FLOWSPEC_WIDE_ROWS", 129); // stacked rows from which every projection takes the many-row kernels (at most 129)
+        mid_rows = env_int("FLOWSPEC_MID_ROWS", 17);   // ... from which they may take the weight-streaming kernel fed through LDS
         compact_cb = env_int("FLOWSPEC_COMPACT_CB", 0);  // KV compaction: column blocks per row (0: by the grid size)
         block_gemm = env_int("FLOWSPEC_BLOCK_GEMM", -1);  // 256-row projection kernel: 0 never, 1 / 2 always (256- / 192-feature blocks), else by rule
     }
@@ -495,17 +495,19 @@ int fs_stage_profile_end(fs_stage* st, void* stream, double* total_ms, long long
     return FS_OK;
 }
 
-// One row block of the many-row kernel has a workgroup per 128 features: that is a good launch if they all run at once
-// (at most one per compute unit) or if there are many rounds of them, not if a few compute units get a second one
-// (measured: 296 workgroups, 60 us against 52 us with the few-row kernel; 216 workgroups, 49 against 57 us).
-static bool mid_cols_ok(int n_tiles) {
-    const int n_cols = (n_tiles + 7) / 8;
-    return n_cols <= 256 || n_cols >= 512;
+// Which kernels a dense bf16 projection of so many stacked rows takes; every other stage takes the few-row kernels.
+enum Route { ROUTE_FEW = 0, ROUTE_STREAM = 1, ROUTE_WIDE = 2 };
+static Route route_of(const fs_stage* st, int rows) {
+    if (st->d.dtype != FS_BF16 || st->d.weight_format != FS_WFMT_DENSE) return ROUTE_FEW;
+    if (rows >= st->tun.wide_rows || rows > 128) return ROUTE_WIDE;
+    return rows < st->tun.mid_rows ? ROUTE_FEW : ROUTE_STREAM;
 }
 
-// dense or 4-bit projection launch, by the stage's weight format; `wide`: through the many-row kernel
-static hipError_t launch_proj(const fs_stage* st, int epi, const GemmPlan& p, GemmArgs& g, hipStream_t s, bool wide = false) {
-    if (wide) return launch_gemm_wide(epi, p.NT, p.n_groups * p.NT, g, st->at<float>(st->L.off_part), st->L.part_bytes, st->tun.block_gemm, s);
+static hipError_t launch_proj(const fs_stage* st, int epi, const GemmPlan& p, GemmArgs& g, hipStream_t s, Route route) {
+    float* part = st->at<float>(st->L.off_part);
+    const int tiles = p.n_groups * p.NT;
+    if (route == ROUTE_STREAM && stream_pays(epi, g.M, tiles, p.nkt)) return launch_gemm_stream(epi, p.NT, tiles, g, part, st->L.part_bytes, s);
+    if (route == ROUTE_WIDE) return launch_gemm_wide(epi, p.NT, tiles, g, part, st->L.part_bytes, st->tun.block_gemm, s);
     if (p.w4) {
         g.Sp = p.sp;
         return launch_gemm_w4(epi, p.NT, p.NW, p.n_groups, g, s);
@@ -603,26 +605,20 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
               st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma);
 
     // 4-bit stages: activations entering a normed projection carry the norm's gain, and the rows' sums of squares
-    // travel beside them as partial sums (see GemmArgs::gain_next)
-    // 65 rows and more (chunked prefill, batches of segments) take the many-row projection kernel; it uses the same
-    // hand-over of fragment-major activations + partial sums of squares, without gains (they are folded into the bf16 weights).
+    // travel beside them as partial sums (see GemmArgs::gain_next).  The many-row kernels of dense stages use the same hand-over of
+    // fragment-major activations + partial sums of squares, without gains (they are folded into the bf16 weights); the kernels
+    // for fewer rows work the sums out themselves and take the stage's input as it is.
     const int l_s = rows;
     const bool w4 = d.weight_format == FS_WFMT_INT4_G128;
-    const bool wide = !w4 && d.dtype == FS_BF16 && l_s >= st->tun.wide_rows;
-    // In between (17 .. 64 stacked rows: more than one row tile, less than a row block and a half) the few-row kernel re-reads
-    // the activations once per workgroup and is bound by the L2; gate/up, the down projection (and the LM head) then go
-    // through the many-row kernel with one 64-row block of 128-feature column blocks, which works out its own RMSNorm scale
-    // (gate/up) or splits K (down); QKV and the attention output have too few column blocks for that and stay with the
-    // few-row kernel.
-    const bool mid = !w4 && !wide && d.dtype == FS_BF16 && l_s >= st->tun.mid_rows;
-    const bool mid_gu = mid && mid_cols_ok(L.layers[0].gu.n_groups * L.layers[0].gu.NT);
-    const bool mid_down = mid;
-    const bool handover = w4 || wide;
+    const Route route = route_of(st, rows);
+    const bool wide = route == ROUTE_WIDE, handover = w4 || wide;
     float* sspa = st->at<float>(L.off_sspa);
     float* sspb = st->at<float>(L.off_sspb);
     const int res_parts = wide ? wide_ssp_parts(l_s, d.d_model / 16) : d.d_model / 16;  // partial sums per row a residual epilogue leaves
     int ssp_n_first = 0;
-    if (handover)
+    // (row-major input costs the streaming kernel 64-byte pieces of 16 rows per load; from 33 rows on one conversion pass is cheaper)
+    const bool to_frag = handover || (route == ROUTE_STREAM && l_s > 32);
+    if (to_frag)
         HIP_TRY_K(st, FS_K_PREPARE, s,
                   launch_prenorm(hidden_in, d.d_model, l_s, d.d_model, w4 ? gains : nullptr, hb, sspa, L.ssp_stride, &ssp_n_first, s));
 
@@ -632,12 +628,12 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
         const bool first = (l == 0), last = (l == d.n_layers - 1);
         // RMSNorm + QKV + RoPE + cache append
         GemmArgs g{};
-        g.X = (first && !handover) ? hidden_in : hb; g.x_frag = (first && !handover) ? 0 : 1; g.ldx = d.d_model; g.M = l_s; g.K = p.qkv.K; g.nkt = p.qkv.nkt; g.N = p.qkv.N; g.Wp = p.qkv.wp;
+        g.X = (first && !to_frag) ? hidden_in : hb; g.x_frag = (first && !to_frag) ? 0 : 1; g.ldx = d.d_model; g.M = l_s; g.K = p.qkv.K; g.nkt = p.qkv.nkt; g.N = p.qkv.N; g.Wp = p.qkv.wp;
         g.eps = d.rms_eps; g.bias = p.qkv.bias; g.rope = rope; g.q_out = q; g.krow = krow; g.layer_off = layer_off;
         g.stride_kv = kv0->stride_kv; g.stride_head = kv0->stride_head;
         g.Hq = d.n_q_heads; g.Hkv = d.n_kv_heads; g.hd = hd;
         g.ssp_in = sspa; g.ssp_n = first ? ssp_n_first : res_parts; g.ssp_stride = L.ssp_stride;
-        HIP_TRY_K(st, FS_K_QKV, s, launch_proj(st, EPI_QKV, p.qkv, g, s, wide));
+        HIP_TRY_K(st, FS_K_QKV, s, launch_proj(st, EPI_QKV, p.qkv, g, s, route));
         // tree attention
         at.layer_off = layer_off;
         HIP_TRY_K(st, FS_K_ATTN, s, launch_attention(d.dtype, at, aMTW, aRB, s));
@@ -648,13 +644,13 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
         if (handover) {
             g.gain_next = w4 ? gains + (size_t)(2 * l + 1) * d.d_model : nullptr; g.ssp_out = sspb; g.ssp_stride = L.ssp_stride;
         }
-        HIP_TRY_K(st, FS_K_OPROJ, s, launch_proj(st, EPI_RESID, p.o, g, s, wide));
+        HIP_TRY_K(st, FS_K_OPROJ, s, launch_proj(st, EPI_RESID, p.o, g, s, route));
         // RMSNorm + gate/up + SiLU * up
         g = GemmArgs{};
         g.X = hb; g.x_frag = 1; g.ldx = d.d_model; g.M = l_s; g.K = p.gu.K; g.nkt = p.gu.nkt; g.N = 2 * p.gu.N; g.Wp = p.gu.wp; g.eps = d.rms_eps;
         g.act_out = act; g.F = d.d_ffn;
         g.ssp_in = sspb; g.ssp_n = res_parts; g.ssp_stride = L.ssp_stride;
-        HIP_TRY_K(st, FS_K_GATEUP, s, launch_proj(st, EPI_SWIGLU, p.gu, g, s, wide || mid_gu));
+        HIP_TRY_K(st, FS_K_GATEUP, s, launch_proj(st, EPI_SWIGLU, p.gu, g, s, route));
         // down projection + residual
         g = GemmArgs{};
         g.X = act; g.x_frag = 1; g.ldx = d.d_ffn; g.M = l_s; g.K = p.down.K; g.nkt = p.down.nkt; g.N = p.down.N; g.Wp = p.down.wp;
@@ -662,7 +658,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
         if (handover && !last) {
             g.gain_next = w4 ? gains + (size_t)(2 * l + 2) * d.d_model : nullptr; g.ssp_out = sspa; g.ssp_stride = L.ssp_stride;
         }
-        HIP_TRY_K(st, FS_K_DOWN, s, launch_proj(st, EPI_RESID, p.down, g, s, wide || mid_down));
+        HIP_TRY_K(st, FS_K_DOWN, s, launch_proj(st, EPI_RESID, p.down, g, s, route));
     }
     return FS_OK;
 }
@@ -721,16 +717,16 @@ int fs_tree_logits(fs_stage* st, const void* hidden, int l_s, float* logits, int
     const GemmPlan& p = st->L.head;
     GemmArgs g{};
     g.X = hidden; g.ldx = st->d.d_model; g.M = l_s; g.K = p.K; g.nkt = p.nkt; g.N = p.N; g.Wp = p.wp; g.eps = st->d.rms_eps; g.logits = logits;
-    const bool wide = !p.w4 && st->d.dtype == FS_BF16 &&  // many-row kernel (see verify_batch)
-                      (l_s >= st->tun.wide_rows || (l_s >= st->tun.mid_rows && mid_cols_ok(p.n_groups * p.NT)));
-    if (p.w4 || wide) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
+    Route route = route_of(st, l_s);
+    if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, p.n_groups * p.NT, p.nkt)) route = ROUTE_WIDE;
+    if (p.w4 || route == ROUTE_WIDE) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
         void* hb = st->at<void>(st->L.off_hb);
         float* ssp = st->at<float>(st->L.off_sspa);
         const bf16_t* gain = p.w4 ? st->at<bf16_t>(st->L.off_gain) + (size_t)(2 * st->d.n_layers) * st->d.d_model : nullptr;
         HIP_TRY_K(st, FS_K_PREPARE, s, launch_prenorm(hidden, st->d.d_model, l_s, st->d.d_model, gain, hb, ssp, st->L.ssp_stride, &g.ssp_n, s));
         g.X = hb; g.x_frag = 1; g.ssp_in = ssp; g.ssp_stride = st->L.ssp_stride;
     }
-    HIP_TRY_K(st, FS_K_HEAD, s, launch_proj(st, EPI_LOGITS, p, g, s, wide));
+    HIP_TRY_K(st, FS_K_HEAD, s, launch_proj(st, EPI_LOGITS, p, g, s, route));
     HIP_TRY_K(st, FS_K_ARGMAX, s, launch_argmax(logits, l_s, st->d.vocab, FS_ARGMAX_CHUNKS, st->at<int32_t>(st->L.off_amw), amax, s));
     return FS_OK;
 }

@@ -16,6 +16,8 @@
 // workgroup reads anyway (it covers the whole K range) and applied in the epilogue.
 #include "gemm.hpp"
 
+#include <algorithm>
+
 
 typedef __attribute__((ext_vector_type(2))) bf16_t bf16x2;
 struct bf16x2x4 {
@@ -354,7 +356,7 @@ hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const G
 // With more than a row tile or two the projections stop being a pure weight stream: the few-row kernel re-reads the
 // activations once per workgroup and ends up bound by the path from L2 into the compute units.  This kernel shares the
 // activations between the waves instead.  Workgroup = 4 waves; block = 128 rows x 256 features (from 384 rows), 128 rows
-// x 128 features (65 .. 383 rows) or 64 rows x 128 features (up to 64 rows); wave w owns a quarter of the features for
+// x 128 features (129 .. 383 rows; LM head from 65) or 64 rows x 128 features (LM head of up to 64 rows); wave w owns a quarter of the features for
 // all rows of the block (8 x 4, 8 x 2 or 4 x 2 accumulator tiles).
 //   * Weights are private to a wave, so they skip LDS: each wave streams its tiles per k-tile straight from the re-tiled
 //     copy into registers, a ring of PFW k-tiles deep (the same coalesced 1 KiB fragment loads as the few-row kernel).
@@ -371,9 +373,7 @@ hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const G
 //   * Projections too narrow to fill the chip (d_model outputs, a few row blocks) split K over `k_splits` workgroups;
 //     each writes its raw accumulator tiles (MFMA lane order, so 16 bytes per lane, contiguous per wave) to a scratch
 //     array and wide_fixup_kernel adds them up and runs the residual epilogue.
-//   * Which projections come here at which row count is the caller's choice (with one 64-row block: gate/up, the down
-//     projection and the LM head; QKV and the attention output have too few 128-feature blocks to fill the chip and a
-//     wave has only 8 MFMAs per k-tile to hide a barrier and an LDS round trip behind: 64 rows, QKV 31 -> 38 us).
+//   * Below 129 rows only an LM head of many rounds of blocks comes here (stream_pays).
 template <int EPI, bool PARTIAL, int BMT, int WNT, int WAVES, bool STREAMW>
 __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel(const GemmArgs a, int layout_nt, int n_tiles, int n_cols, int m_blocks, int k_splits,
                                                            float* part) {
@@ -817,6 +817,245 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_kernel(const GemmArgs
     }
 }
 
+// ---- 17 to 128 rows: one pass over the weights, both operands through LDS ------------------------------------------------
+// A weight byte is used by at most 128 rows, so the launch is bound by what a compute unit can draw: its share of the weights from
+// memory and the whole activation block from L2.  A workgroup that streams through registers has too little in flight for that
+// (96 workgroups of 4 waves: 2.5 TB/s, through direct-to-LDS loads 4.5 TB/s).  Workgroup = WM x WN x KG waves on a block of
+// all rows (16 * WM * MT) x 16 * WN * NT features; the KG wave groups take alternate k-tiles of the block (larger wave tiles, hence
+// fewer LDS reads per MFMA, than dividing it further) and add their tiles up through LDS at the end.
+//   * A stage is the block's fragments of S k-tiles; R stage buffers, all but one of them in flight.  Loads are 16 bytes per
+//     lane straight into LDS, a fixed number per wave and stage, so the explicit wait counts are exact; stages beyond the K
+//     range are still "loaded" (one cache line, into a buffer nobody reads).
+//   * Per stage one bare barrier: before it a wave waits for its own loads of stage s + 1 and for its LDS reads of stage s;
+//     behind it stage s + 1 is complete and the buffer of stage s free.  Fragments travel LDS -> registers one stage ahead.
+//   * RMSNorm: every wave adds up the squares of the activation fragments it multiplies anyway (the row scale is wanted per lane
+//     in exactly that layout), so no producer has to leave sums behind.
+// Before (few-row kernel, or 64 / 128-row blocks streamed through registers) -> now, 7B shapes, us: 32 rows QKV 25.5 -> 22.7, gate/up
+// 38.3 -> 32.4, down 28.5 -> 21.1; 64 rows QKV 34.7 -> 27.2, gate/up 41 -> 33.9, down 30.1 -> 24.3; 128 rows QKV 47.9 -> 35.7, output
+// 25.5 -> 19.3, gate/up 53.9 -> 47.7, down 34.7 -> 31.2.  MFMAs, LDS reads and RMSNorm sums are hidden (128 rows QKV: 1.3 us without
+// them, the epilogue another 4); above the 19 us in which the same loads run alone it is the activations, first read beyond L2.
+template <int EPI, bool PARTIAL, int WM, int WN, int KG, int MT, int NT, int S, int R>
+__global__ void __launch_bounds__(WM * WN * KG * 64) stream_gemm_kernel(const void* Wp, const void* X, int nkt, int ldx, int M, int flags, int n_tiles,
+                                                                        int kt_per, const GemmArgs a, float* part) {
+    using T = bf16_t;
+    using E = Elem<T>;
+    using frag_t = E::frag_t;
+    constexpr bool NORM = (EPI != EPI_RESID);
+    constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
+    constexpr int TPI = PAIR ? 2 : 1;
+    constexpr int NW = WM * WN * KG, BMT = WM * MT, BNT = WN * NT, H = MT / KG;
+    constexpr int AF = S * BMT, WF = S * BNT, LA = AF / NW, LW = WF / NW, LPS = LA + LW;  // fragments per stage, loads per wave and stage
+    static_assert(AF % NW == 0 && WF % NW == 0, "every wave issues the same loads");
+    static_assert(KG == 1 || (KG == 2 && S == 2 && MT % 2 == 0), "two wave groups take one k-tile of a stage each");
+    static_assert(S == KG, "one k-tile per wave and stage");
+    static_assert(R % 2 == 0 && R >= 4 && R <= 8, "register sets alternate with the stages; at most 8 buffers");
+    static_assert(R * (AF + WF) <= 158 && LPS * (R - 1) < 64, "160 KiB of LDS, 6-bit wait counter");
+    static_assert(KG == 1 || H * NT * WM * WN <= AF + WF, "exchange of half the tiles fits a stage buffer");
+    // one array per buffer: distinct objects, see block_gemm_kernel
+    __shared__ __align__(1024) unsigned char sb0[(AF + WF) * 1024];
+    __shared__ __align__(1024) unsigned char sb1[(AF + WF) * 1024];
+    __shared__ __align__(1024) unsigned char sb2[(AF + WF) * 1024];
+    __shared__ __align__(1024) unsigned char sb3[(AF + WF) * 1024];
+    __shared__ __align__(1024) unsigned char sb4[R > 4 ? (AF + WF) * 1024 : 16];
+    __shared__ __align__(1024) unsigned char sb5[R > 4 ? (AF + WF) * 1024 : 16];
+    __shared__ __align__(1024) unsigned char sb6[R > 6 ? (AF + WF) * 1024 : 16];
+    __shared__ __align__(1024) unsigned char sb7[R > 6 ? (AF + WF) * 1024 : 16];
+    __shared__ float ssx[KG == 2 ? 2 * BMT * 16 : 1];
+    auto buf_at = [&](int j) -> unsigned char* {
+        return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : (j == 3 ? sb3 : (j == 4 ? sb4 : (j == 5 ? sb5 : (j == 6 ? sb6 : sb7))))));
+    };
+
+    // grid (feature block, K slice); all rows are in one block.
+    // What the first loads depend on arrives in SGPRs, and the prologue is kept free of divisions: a launch of a few dozen stages
+    // feels every microsecond in front of its first load.
+    const int col = blockIdx.x, ks = blockIdx.y;
+    const int x_frag = flags & 1, lsh = flags >> 1;  // log2 of the weights' tiles per group
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), kg = w / (WM * WN), wm = (w / WN) % WM, wn = w % WN;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int kt_lo = ks * kt_per, n = min(kt_per, nkt - kt_lo);  // >= 1 (host)
+    const int ns = (n + S - 1) / S;
+    const int m_tiles = (M + 15) >> 4;
+
+    // This wave's fragments of a stage: i * NW + w of the activations (k-tile, row tile), then of the weights (k-tile, feature tile).
+    // A 32-bit offset per lane and load, advanced by one stage per issue; tiles beyond the matrix re-read the last one.  The issue
+    // path is kept to a handful of instructions per load: with one wave per SIMD it is not hidden by anything.
+    const unsigned char* const xb = (const unsigned char*)X;
+    const unsigned char* const wb = (const unsigned char*)Wp;
+    const unsigned xkt = x_frag ? 1024u : 64u, wkt = 1024u << lsh;  // bytes from one k-tile to the next
+    unsigned xo[LA], wo[LW];
+    int xn[LA], wn_[LW];  // stages in which the load's k-tile exists
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int f = i * NW + w, j = f / BMT, mt = min(f % BMT, m_tiles - 1);
+        const unsigned o = x_frag ? (unsigned)mt * (unsigned)nkt * 1024u + (unsigned)lane * 16u
+                                  : (unsigned)min(mt * 16 + r16, M - 1) * (unsigned)ldx * 2u + (unsigned)g * 16u;
+        xo[i] = o + (unsigned)(kt_lo + j) * xkt;
+        xn[i] = (n - j + S - 1) / S;
+    }
+#pragma unroll
+    for (int i = 0; i < LW; ++i) {
+        const int f = i * NW + w, j = f / BNT, pc = min(col * BNT + f % BNT, n_tiles - 1);
+        wo[i] = ((((unsigned)(pc >> lsh) * (unsigned)nkt + (unsigned)(kt_lo + j)) << lsh) + (unsigned)(pc & ((1 << lsh) - 1))) * 1024u + (unsigned)lane * 16u;
+        wn_[i] = (n - j + S - 1) / S;
+    }
+    const unsigned lane16 = (unsigned)lane * 16u;
+    int st = 0;  // next stage to issue
+    auto issue = [&](int j) {  // next stage -> buffer j; k-tiles beyond the range fetch the first line of the operand (no branch around a load)
+        unsigned char* dst = buf_at(j);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const unsigned live = (unsigned)((st - xn[i]) >> 31);  // uniform, all ones or zero
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + (i * NW + w) * 1024), 16, 0, 0);
+            xo[i] += S * xkt;
+        }
+#pragma unroll
+        for (int i = 0; i < LW; ++i) {
+            const unsigned live = (unsigned)((st - wn_[i]) >> 31);
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(wb + (wo[i] & live)), FS_LDS_PTR(dst + (AF + i * NW + w) * 1024), 16, 0, 2);
+            wo[i] += S * wkt;
+        }
+        ++st;
+    };
+
+    f32x4 acc[MT][NT];
+    float ss[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        ss[mt] = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    frag_t xf[2][MT], wf[2][NT];
+    auto read = [&](int set, int j) {  // this group's k-tile of the stage in buffer j
+        const unsigned char* b = buf_at(j) + lane16;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) wf[set][nt] = *(const frag_t*)(b + (AF + kg * BNT + wn * NT + nt) * 1024);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) xf[set][mt] = *(const frag_t*)(b + (kg * BMT + wm * MT + mt) * 1024);
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) issue(j);
+    FS_WAIT_VM_LGKM((R - 1) * LPS, 0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    read(0, 0);
+    int cur = 0;  // stage being multiplied
+    auto stage = [&](int ju) {  // the next stage, in buffer ju, its fragments in register set ju & 1
+        const int set = ju & 1;
+        asm volatile("" ::: "memory");
+        FS_WAIT_VM_LGKM((R - 2) * LPS, 0);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        issue(ju);
+        read(set ^ 1, (ju + 1) % R);
+        if (cur++ * S + kg < n) {  // uniform; the last stage may hold one k-tile only
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                if constexpr (NORM) {
+                    const bf16x2x4 pr = __builtin_bit_cast(bf16x2x4, xf[set][mt]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ss[mt] = __builtin_amdgcn_fdot2_f32_bf16(pr.v[e], pr.v[e], ss[mt], false);
+                }
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = E::mma(wf[set][nt], xf[set][mt], acc[mt][nt]);
+            }
+        }
+    };
+    int s0 = 0;
+    for (; s0 + R <= ns; s0 += R) {
+#pragma unroll
+        for (int ju = 0; ju < R; ++ju) stage(ju);
+    }
+#pragma unroll
+    for (int ju = 0; ju < R; ++ju) {
+        if (s0 + ju >= ns) break;
+        stage(ju);
+    }
+    // every load has landed and every wave has left the loop before LDS is reused or given back
+    FS_WAIT_VM_LGKM(0, 0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    // ---- the groups' tiles: each group finishes half of the row tiles ----
+    f32x4 own[H][NT];
+    float so[H];
+    if constexpr (KG == 2) {
+        f32x4* give = (f32x4*)(kg == 0 ? sb0 : sb1) + (size_t)(wm * WN + wn) * H * NT * 64 + lane;
+        const f32x4* take = (const f32x4*)(kg == 0 ? sb1 : sb0) + (size_t)(wm * WN + wn) * H * NT * 64 + lane;
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                own[h][nt] = kg == 0 ? acc[h][nt] : acc[H + h][nt];
+                give[(h * NT + nt) * 64] = kg == 0 ? acc[H + h][nt] : acc[h][nt];
+            }
+        if constexpr (NORM) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const float tot = wave_xor_add(wave_xor_add(ss[mt], 16), 32);
+                if (wn == 0 && g == 0) ssx[(kg * BMT + wm * MT + mt) * 16 + r16] = tot;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) own[h][nt] += take[(h * NT + nt) * 64];
+            const int rt = (wm * MT + kg * H + h) * 16 + r16;
+            so[h] = NORM ? ssx[rt] + ssx[BMT * 16 + rt] : 0.f;
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) own[h][nt] = acc[h][nt];
+            so[h] = NORM ? wave_xor_add(wave_xor_add(ss[h], 16), 32) : 0.f;
+        }
+    }
+    const int pt0 = col * BNT + wn * NT;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const int mt = wm * MT + kg * H + h;
+        if (mt >= m_tiles) break;
+        if constexpr (PARTIAL) {  // raw tiles: part[ks][m tile][n tile][lane]
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) ((f32x4*)part)[(((size_t)ks * m_tiles + mt) * (gridDim.x * BNT) + pt0 + nt) * 64 + lane] = own[h][nt];
+        } else {
+            const float rs = NORM ? 1.0f / sqrtf(so[h] / (float)a.K + a.eps) : 1.f;
+#pragma unroll
+            for (int ntp = 0; ntp < NT / TPI; ++ntp) {
+                float y[TPI][4];
+#pragma unroll
+                for (int tt = 0; tt < TPI; ++tt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) y[tt][v] = own[h][ntp * TPI + tt][v];
+                epilogue_item<T, EPI>(a, y, rs, mt * 16 + r16, pt0 + ntp * TPI, g);
+            }
+        }
+    }
+}
+
+// Sum of the K slices' raw tiles + residual epilogue, one wave per 16 x 16 tile.
+template <int KS>
+__global__ void __launch_bounds__(256) stream_fixup_kernel(const GemmArgs a, int nt_all, const float* part) {
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    const int m_tiles = (a.M + 15) >> 4;
+    const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (unit >= m_tiles * nt_all) return;
+    const int mt = unit / nt_all, ptile = unit % nt_all, m = mt * 16 + r16, n = ptile * 16 + g * 4;
+    f32x4 v[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) v[ks] = ((const f32x4*)part)[(((size_t)ks * m_tiles + mt) * nt_all + ptile) * 64 + lane];
+    f32x4 pre{0.f, 0.f, 0.f, 0.f};
+    if (m < a.M && n < a.N) pre = load_resid<bf16_t>(a, m, n);
+    f32x4 sum = v[0];
+#pragma unroll
+    for (int ks = 1; ks < KS; ++ks) sum += v[ks];
+    const float y[1][4] = {{sum[0], sum[1], sum[2], sum[3]}};
+    epilogue_item<bf16_t, EPI_RESID>(a, y, 1.f, m, ptile, g, &pre);
+}
+
 // Block geometry by projection kind and row count (see the kernel's header comment).
 struct WideShape {
     int bmt, wnt, waves;
@@ -827,8 +1066,8 @@ static int wide_narrow_rows() {
     return v;
 }
 static int env_int(const char* name, int dflt) { const char* e = getenv(name); return e ? atoi(e) : dflt; }
-static WideShape wide_shape(int, int M) {
-    if (M <= 64) return WideShape{4, 2, 4};  // one 64-row block (gate/up and LM head of segments of 33 to 64 rows)
+static WideShape wide_shape(int epi, int M) {
+    if (M <= 64 && epi == EPI_LOGITS) return WideShape{4, 2, 4};  // one 64-row block
     return M < wide_narrow_rows() ? WideShape{8, 2, 4} : WideShape{8, 4, 4};
 }
 
@@ -955,21 +1194,109 @@ hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs&
     }
     switch (epi) {
         case EPI_QKV:
-            if (half) return launch_wide_shape<EPI_QKV, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
             return narrow ? launch_wide_shape<EPI_QKV, 8, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s)
                           : launch_wide_shape<EPI_QKV, 8, 4, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
         case EPI_SWIGLU:
-            if (half) return launch_wide_shape<EPI_SWIGLU, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
             return narrow ? launch_wide_shape<EPI_SWIGLU, 8, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s)
                           : launch_wide_shape<EPI_SWIGLU, 8, 4, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
         case EPI_RESID:
-            if (half) return launch_wide_shape<EPI_RESID, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
             return narrow ? launch_wide_shape<EPI_RESID, 8, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s)
                           : launch_wide_shape<EPI_RESID, 8, 4, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
         case EPI_LOGITS:
             if (half) return launch_wide_shape<EPI_LOGITS, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
             return narrow ? launch_wide_shape<EPI_LOGITS, 8, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s)
                           : launch_wide_shape<EPI_LOGITS, 8, 4, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// ---- launch of the 17 to 128 row kernel -----------------------------------------------------------------------------------
+template <int EPI, int WM, int WN, int KG, int MT, int NT, int S, int R>
+static hipError_t launch_stream_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    constexpr int BNT = WN * NT;
+    const int n_cols = (n_tiles + BNT - 1) / BNT, m_tiles = (a.M + 15) / 16;
+    const int flags = a.x_frag | (layout_nt == 4 ? 4 : layout_nt == 2 ? 2 : 0);
+    const dim3 block(WM * WN * KG * 64);
+    if constexpr (EPI == EPI_RESID) {  // K slices until there is about one workgroup per compute unit
+        int ks = std::min(std::min(256 / n_cols, 8), a.nkt / 8);
+        while (ks > 1 && (size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) --ks;
+        if (ks > 1) {
+            const int per = ((a.nkt + ks - 1) / ks + S - 1) / S * S;
+            ks = (a.nkt + per - 1) / per;
+            hipLaunchKernelGGL((stream_gemm_kernel<EPI, true, WM, WN, KG, MT, NT, S, R>), dim3(n_cols, ks), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags,
+                               n_tiles, per, a, part);
+            const dim3 grid((m_tiles * n_cols * BNT + 3) / 4);
+#define FS_FIX(k) \
+    case k: hipLaunchKernelGGL((stream_fixup_kernel<k>), grid, dim3(256), 0, s, a, n_cols * BNT, part); break;
+            switch (ks) { FS_FIX(1) FS_FIX(2) FS_FIX(3) FS_FIX(4) FS_FIX(5) FS_FIX(6) FS_FIX(7) FS_FIX(8) }
+#undef FS_FIX
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((stream_gemm_kernel<EPI, false, WM, WN, KG, MT, NT, S, R>), dim3(n_cols), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags, n_tiles,
+                       (a.nkt + S - 1) / S * S, a, nullptr);
+    return hipGetLastError();
+}
+
+// Feature tiles per block: a compute unit holds one block at a time and draws its weights and the activations for it, so a launch
+// costs rounds x (feature tiles + row tiles); the residual projections fill the chip with K slices instead, where wider blocks
+// only pay by reading a long activation block less often (128 rows x 11008: 33.5 -> 31.2 us).
+static int stream_width(int epi, int M, int n_tiles, int nkt) {
+    const int bmt = M <= 64 ? 4 : 8;
+    if (epi == EPI_RESID) return (M > 64 && nkt > 256) ? 8 : 4;
+    int best = 4, cost = 1 << 30;
+    for (int bn = 4; bn <= 8; bn += 2) {
+        const int blocks = (n_tiles + bn - 1) / bn, c = (blocks + 255) / 256 * (bn + bmt);
+        if (c < cost) {
+            cost = c;
+            best = bn;
+        }
+    }
+    return best;
+}
+
+// Whether a projection takes this kernel at 17 to 128 rows (else: the few-row kernel, the LM head the kernel with blocks in
+// registers).  Measured, this kernel / the other one, us:
+//   * LM head: while its blocks run in one round (32000 rows x 4096: 64 rows 50 / 49 + 5 for the conversion pass the other one needs);
+//     with many rounds several workgroups per compute unit hide each other's ends (152064 x 3584, 64 rows: 242 / 220 + 5).
+//   * QKV of few heads (288 tiles, 72 blocks): from 65 rows on (80 rows 34 / 43, but 48 rows 23.4 / 21.6).
+//   * gate/up with more than one round of blocks: from 33 rows on (2368 tiles: 48 rows 54.7 / 62.2, but 32 rows 53.4 / 52.4).
+//   * attention output up to 32 rows with at most one few-row workgroup per compute unit: the second launch that adds the K slices
+//     costs more than it gives while K is short (4096 x 4096: 15 / 13; but 5120 x 5120 with its 320 tiles 15.4 / 18.4, and
+//     4096 x 11008 21.1 / 28).
+bool stream_pays(int epi, int M, int n_tiles, int nkt) {
+    if (epi == EPI_LOGITS) return M <= 64 && (n_tiles + 7) / 8 <= 256;
+    if (epi == EPI_QKV) return M > 64 || n_tiles >= 512;
+    if (epi == EPI_RESID) return M > 32 || n_tiles > 256 || nkt > 128;
+    return M > 32 || (n_tiles + 7) / 8 <= 256;
+}
+
+template <int EPI>
+static hipError_t launch_stream_epi(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    const int bn = stream_width(EPI, a.M, n_tiles, a.nkt);
+    if (a.M <= 32 && bn == 4) return launch_stream_shape<EPI, 1, 2, 2, 2, 2, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+    if (a.M <= 64) {
+        if (bn == 4) return launch_stream_shape<EPI, 2, 2, 2, 2, 2, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+        if constexpr (EPI != EPI_RESID) {
+            if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 2, 6, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+            return launch_stream_shape<EPI, 1, 2, 2, 4, 4, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+        }
+    }
+    if (bn == 4) return launch_stream_shape<EPI, 4, 1, 2, 2, 4, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+    if constexpr (EPI != EPI_RESID) {
+        if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 4, 6, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
+    }
+    return launch_stream_shape<EPI, 2, 2, 1, 4, 4, 1, 8>(layout_nt, n_tiles, a, part, part_bytes, s);
+}
+
+hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    // 32-bit byte offsets from the operands' bases
+    if ((unsigned long long)(n_tiles + 8) * a.nkt * 1024ull >= (1ull << 32) || a.M > 128) return hipErrorInvalidValue;
+    switch (epi) {
+        case EPI_QKV: return launch_stream_epi<EPI_QKV>(layout_nt, n_tiles, a, part, part_bytes, s);
+        case EPI_RESID: return launch_stream_epi<EPI_RESID>(layout_nt, n_tiles, a, part, part_bytes, s);
+        case EPI_SWIGLU: return launch_stream_epi<EPI_SWIGLU>(layout_nt, n_tiles, a, part, part_bytes, s);
+        case EPI_LOGITS: return launch_stream_epi<EPI_LOGITS>(layout_nt, n_tiles, a, part, part_bytes, s);
     }
     return hipErrorInvalidValue;
 }

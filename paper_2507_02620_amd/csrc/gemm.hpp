@@ -94,5 +94,10 @@ int wide_ssp_parts(int M, int n_tiles);
 size_t wide_partial_bytes(int max_rows, int n_tiles);
 // block_mode: 0 never / 1 whenever possible / anything else: by rule — use of the 256-row kernel (both operands through LDS) from 384 rows on
 hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, int block_mode, hipStream_t s);
+// bf16, 17 to 128 rows, row-major or fragment-major activations: the kernel that streams both operands through LDS; normed projections
+// work out their own row scale, residual projections leave no sums of squares.  `part` as for launch_gemm_wide.  stream_pays: whether it
+// is the faster choice for a projection.
+bool stream_pays(int epi, int M, int n_tiles, int nkt);
+hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
 // MT = ceil(M/16) in {1,2,4}, NT in {1,2,4} (even for QKV / SWIGLU), waves per workgroup NW
 hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const GemmArgs& a, hipStream_t s);

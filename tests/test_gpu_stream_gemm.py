@@ -1,0 +1,35 @@
+"""The projection kernel for 17 to 128 rows (both operands streamed through LDS) against the oracle: row counts at the edges of its
+row blocks, K ranges of an odd number of k-tiles and shorter than the ring of stage buffers, K slices, feature counts that leave
+the last block partly filled, row-major and fragment-major activations."""
+import numpy as np
+import pytest
+
+from paper_2507_02620_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows", [17, 32, 33, 64, 65, 113, 128])
+@pytest.mark.parametrize("d,hq,hkv,hd,f,vocab,bias", [
+    (480, 6, 3, 64, 1056, 1000, True),      # 15 and 33 k-tiles (an odd last stage), ragged feature blocks everywhere
+    (64, 1, 1, 64, 96, 40, False),          # 2 k-tiles: fewer stages than buffers
+    (1024, 64, 2, 128, 6400, 4000, False),  # QKV of 544 tiles through the kernel, gate/up of 800 tiles, several K slices
+])
+def test_rows_between_one_tile_and_a_block(rows, d, hq, hkv, hd, f, vocab, bias):
+    import torch
+    from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
+    cfg = synth.StageConfig(f"stream-{d}-{rows}", "bf16", 2, d, hq, hkv, hd, f, vocab, 37, rows + 3, rows, 6, 3, qkv_bias=bias)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, head=True)
+    tree = synth.config_tree(cfg, seed=rows)
+    hid = synth.hidden(cfg, tree.size, 0, rows)
+    o, g = pair.verify_tree(tree.parent, hid, rows)     # one segment of `rows` rows, then 3 rows
+    L = cfg.l_glo + tree.size
+    err = max_rel_err(g, o)
+    kerr = max_rel_err(pair.kv[:, :, :, cfg.l_glo:L].float().cpu().numpy(), pair.orc.kv[:, :, :, cfg.l_glo:L])
+    x = synth.storage(cfg, o[:rows].astype(np.float32))
+    lo, _ = pair.orc.logits(x.astype(np.float64))
+    lg, _ = pair.gpu.tree_logits(to_dev(x, torch.bfloat16))
+    lerr = max_rel_err(lg.cpu().numpy(), lo)
+    print(f"  hidden {err:.2e}, K/V {kerr:.2e}, logits {lerr:.2e}", flush=True)
+    assert err < TOL["bf16"] and kerr < TOL["bf16"] and lerr < TOL["bf16"]
