@@ -81,15 +81,15 @@ void plan_gemm(GemmPlan& g, int tiles, int K, int elem, bool pair, int max_seg, 
     g.nkt = (K + KT - 1) / KT;
     g.NT = choose_nt(tiles, pair, max_seg, env_nt, wide_n);
     if (w4) {
-        // a 4-bit tile is a quarter of the bytes: larger groups keep the per-workgroup stream long enough;
-        // 64-row segments stay at NT <= 2 (registers)
+        // a 4-bit tile is a quarter of the bytes: larger groups keep the per-workgroup stream long enough, whatever the longest
+        // segment (the kernel takes 32 rows at a time; 24 rows in a stage that also takes prompt chunks, 2 -> 4 tiles per group: QKV
+        // 27.7 -> 21.3 us, gate/up 48 -> 32 us)
         int nt = pair ? 2 : 1;
         // (QKV and the LM head already from 192 groups on: 24 rows, 960 tiles: QKV 27.4 -> 22.2 us; 16 rows, 768 tiles: 14.5 -> 13.8 us)
-        if ((tiles / 4 >= 256 || (wide_n && tiles / 4 >= 192)) && max_seg <= 32) nt = 4;
+        if (tiles / 4 >= 256 || (wide_n && tiles / 4 >= 192)) nt = 4;
         else if (tiles / 2 >= 128) nt = 2;
         const int o = env_int(env_nt, 0);
         if (o == 1 || o == 2 || o == 4) nt = (pair && o == 1) ? 2 : o;
-        if (max_seg > 32 && nt > 2) nt = 2;
         g.NT = nt;
     }
     g.n_groups = (tiles + g.NT - 1) / g.NT;
@@ -195,7 +195,7 @@ void make_layout(const fs_stage_desc* d, Layout& L) {
     L.off_sspb = take(ssp_bytes);
     // many-row segments: scratch for the K-split partial results of the two residual projections
     L.part_bytes = 0;
-    if (d->dtype == FS_BF16 && !w4 && d->max_seg > 16) L.part_bytes = wide_partial_bytes(d->max_seg, d->d_model / 16);
+    if (d->dtype == FS_BF16 && d->max_seg > 16) L.part_bytes = wide_partial_bytes(d->max_seg, d->d_model / 16);
     L.off_part = take(L.part_bytes);
     L.off_krow = take(M * sizeof(unsigned long long));  // cache slot address of every stacked row
     L.off_ancall = take((size_t)2 * d->max_tree * FS_ANC_WORDS * sizeof(uint64_t));  // two copies of every node's mask while a deep tree's are built
@@ -495,7 +495,7 @@ int fs_stage_profile_end(fs_stage* st, void* stream, double* total_ms, long long
     return FS_OK;
 }
 
-// Which kernels a dense bf16 projection of so many stacked rows takes; every other stage takes the few-row kernels.
+// Which kernels a dense bf16 projection of so many stacked rows takes (f32: always the few-row kernel; 4-bit weights: launch_gemm_w4).
 enum Route { ROUTE_FEW = 0, ROUTE_STREAM = 1, ROUTE_WIDE = 2 };
 static Route route_of(const fs_stage* st, int rows) {
     if (st->d.dtype != FS_BF16 || st->d.weight_format != FS_WFMT_DENSE) return ROUTE_FEW;
@@ -510,7 +510,7 @@ static hipError_t launch_proj(const fs_stage* st, int epi, const GemmPlan& p, Ge
     if (route == ROUTE_WIDE) return launch_gemm_wide(epi, p.NT, tiles, g, part, st->L.part_bytes, st->tun.block_gemm, s);
     if (p.w4) {
         g.Sp = p.sp;
-        return launch_gemm_w4(epi, p.NT, p.NW, p.n_groups, g, s);
+        return launch_gemm_w4(epi, p.NT, p.NW, p.n_groups, g, part, st->L.part_bytes, s);
     }
     return launch_gemm(st->d.dtype, epi, p.NT, p.NW, p.n_groups, g, s);
 }
@@ -614,7 +614,8 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     const bool wide = route == ROUTE_WIDE, handover = w4 || wide;
     float* sspa = st->at<float>(L.off_sspa);
     float* sspb = st->at<float>(L.off_sspb);
-    const int res_parts = wide ? wide_ssp_parts(l_s, d.d_model / 16) : d.d_model / 16;  // partial sums per row a residual epilogue leaves
+    // partial sums per row a residual epilogue leaves
+    const int res_parts = wide ? wide_ssp_parts(l_s, d.d_model / 16) : w4_ssp_parts(l_s, L.layers[0].o.n_groups * L.layers[0].o.NT);
     int ssp_n_first = 0;
     // (row-major input costs the streaming kernel 64-byte pieces of 16 rows per load; from 33 rows on one conversion pass is cheaper)
     const bool to_frag = handover || (route == ROUTE_STREAM && l_s > 32);

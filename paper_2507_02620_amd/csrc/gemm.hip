@@ -594,33 +594,55 @@ __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel
     }
 }
 
-// Sum of the K slices' raw tiles + residual epilogue.  One wave per (row tile, group of wnt feature tiles = what one
-// wave of the projection kernel owns): the same lane layout as the accumulators, the same partial sums of squares as the
-// direct epilogue.
-__global__ void __launch_bounds__(256) wide_fixup_kernel(const GemmArgs a, int nt_all, int wnt, int k_splits, const float* part) {
+// Sum of the K slices' raw tiles + residual epilogue.  One wave per (row tile, group of WNT feature tiles): the same lane layout as
+// the accumulators; a workgroup's 4 waves leave one partial sum of squares per row.  All loads of a wave go out together (a loop
+// of load - add per slice before: 512 rows x 4096 features, 4 slices 10.5 - 12.7 -> 9.8 - 10.9 us; 1024 rows, 2 slices 13.4 -> 12.6).
+template <int KS, int WNT>
+__global__ void __launch_bounds__(256) wide_fixup_kernel(const GemmArgs a, int nt_all, const float* part) {
     const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
-    const int m_tiles = (a.M + 15) >> 4, groups = nt_all / wnt;
+    const int m_tiles = (a.M + 15) >> 4, groups = nt_all / WNT;
     __shared__ float hs[4][16];
     const int wv = threadIdx.x >> 6;
-    const int unit = blockIdx.x * 4 + wv;  // groups is a multiple of 4: the workgroup's 4 units are the 4 waves' shares of one block
+    const int unit = blockIdx.x * 4 + wv;  // groups is a multiple of 4: the workgroup's 4 units are neighbours of one row tile
     if (unit >= m_tiles * groups) return;  // whole workgroup
     const int mt = unit / groups, grp = unit % groups;
     const int m = mt * 16 + r16;
+    f32x4 v[WNT][KS], pre[WNT];
+#pragma unroll
+    for (int nt = 0; nt < WNT; ++nt) {
+        const int ptile = grp * WNT + nt;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) v[nt][ks] = ((const f32x4*)part)[(((size_t)ks * m_tiles + mt) * nt_all + ptile) * 64 + lane];
+        pre[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int n = ptile * 16 + g * 4;
+        if (m < a.M && n < a.N) pre[nt] = load_resid<bf16_t>(a, m, n);
+    }
     float hsq = 0.f;
-    for (int nt = 0; nt < wnt; ++nt) {
-        const int ptile = grp * wnt + nt;
-        f32x4 sum{0.f, 0.f, 0.f, 0.f};
-        for (int ks = 0; ks < k_splits; ++ks) sum += ((const f32x4*)part)[(((size_t)ks * m_tiles + mt) * nt_all + ptile) * 64 + lane];
+#pragma unroll
+    for (int nt = 0; nt < WNT; ++nt) {
+        f32x4 sum = v[nt][0];
+#pragma unroll
+        for (int ks = 1; ks < KS; ++ks) sum += v[nt][ks];
         const float y[1][4] = {{sum[0], sum[1], sum[2], sum[3]}};
-        hsq += epilogue_item<bf16_t, EPI_RESID>(a, y, 1.f, m, ptile, g);
+        hsq += epilogue_item<bf16_t, EPI_RESID>(a, y, 1.f, m, grp * WNT + nt, g, &pre[nt]);
     }
     if (a.ssp_out) {
         hsq = wave_xor_add(wave_xor_add(hsq, 16), 32);
         if (g == 0) hs[wv][r16] = hsq;
         __syncthreads();
-        if (threadIdx.x < 16 && mt * 16 + (int)threadIdx.x < a.ssp_stride)
+        if (threadIdx.x < 16 && mt * 16 + (int)threadIdx.x < a.ssp_stride && (grp >> 2) * (64 * WNT) < a.N)  // not for padding blocks
             a.ssp_out[(size_t)(grp >> 2) * a.ssp_stride + mt * 16 + threadIdx.x] = hs[0][threadIdx.x] + hs[1][threadIdx.x] + hs[2][threadIdx.x] + hs[3][threadIdx.x];
     }
+}
+
+template <int WNT>
+static hipError_t launch_fixup(const GemmArgs& a, int nt_all, int k_splits, const float* part, hipStream_t s) {
+    const int units = ((a.M + 15) / 16) * (nt_all / WNT);
+#define FS_FIX(k) \
+    case k: hipLaunchKernelGGL((wide_fixup_kernel<k, WNT>), dim3((units + 3) / 4), dim3(256), 0, s, a, nt_all, part); break;
+    switch (k_splits) { FS_FIX(1) FS_FIX(2) FS_FIX(3) FS_FIX(4) FS_FIX(5) FS_FIX(6) FS_FIX(7) FS_FIX(8) default: return hipErrorInvalidValue; }
+#undef FS_FIX
+    return hipGetLastError();
 }
 
 // ---- many-row segments: 256-row blocks, both operands through LDS ------------------------------------------------------
@@ -1123,9 +1145,7 @@ static hipError_t launch_wide_shape(int layout_nt, int n_tiles, const GemmArgs& 
             else
                 hipLaunchKernelGGL((wide_gemm_kernel<EPI, true, BMT, WNT, WAVES, false>), dim3(grid), dim3(WAVES * 64), 0, s, a, layout_nt, n_tiles,
                                    g.n_cols, g.m_blocks, g.k_splits, part);
-            const int units = ((a.M + 15) / 16) * g.n_cols * WAVES;
-            hipLaunchKernelGGL(wide_fixup_kernel, dim3((units + 3) / 4), dim3(256), 0, s, a, g.n_cols * WAVES * WNT, WNT, g.k_splits, part);
-            return hipGetLastError();
+            return launch_fixup<WNT>(a, g.n_cols * WAVES * WNT, g.k_splits, part, s);
         }
     }
     if (stream)
@@ -1326,8 +1346,11 @@ __global__ void __launch_bounds__(512) skinny_gemm_w4_kernel(const GemmArgs a) {
     const int row0 = mb * MT * 16;
     const int nkc = a.nkt >> 2;                       // chunks of 4 k-tiles
     const int nsteps = (nkc - w + NW - 1) / NW;       // >= 1: the host never launches more waves than chunks
-    const unsigned char* wbase = (const unsigned char*)a.Wp + ((size_t)grp * nkc) * (size_t)(NT * 1024) + (size_t)lane * 16;
-    const bf16_t* sbase = (const bf16_t*)a.Sp + ((size_t)grp * nkc) * (size_t)(NT * 16) + g * 4;
+    // the workgroup's tiles: a whole group of the re-tiled weights, or half of one (w_shift: log2 of the tiles per group)
+    const int sh = a.w_shift, tile0 = grp * NT;
+    const size_t first = (((size_t)(tile0 >> sh) * nkc) << sh) + (tile0 & ((1 << sh) - 1));
+    const unsigned char* wbase = (const unsigned char*)a.Wp + first * 1024 + (size_t)lane * 16;
+    const bf16_t* sbase = (const bf16_t*)a.Sp + first * 16 + g * 4;
     const T* xrow[MT];
     const size_t xstep = a.x_frag ? (size_t)64 * E::EPF : (size_t)E::KT;
 #pragma unroll
@@ -1374,8 +1397,8 @@ __global__ void __launch_bounds__(512) skinny_gemm_w4_kernel(const GemmArgs a) {
         const int c = w + min(step, nsteps - 1) * NW;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-            cq[s][nt] = __builtin_nontemporal_load((const u32x4*)(wbase + ((size_t)c * NT + nt) * 1024));
-            sq[s][nt] = *(const bf16x4*)(sbase + ((size_t)c * NT + nt) * 16);
+            cq[s][nt] = __builtin_nontemporal_load((const u32x4*)(wbase + (((size_t)c << sh) + nt) * 1024));
+            sq[s][nt] = *(const bf16x4*)(sbase + (((size_t)c << sh) + nt) * 16);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1468,10 +1491,318 @@ static hipError_t launch_mt_nt_w4(int MT, int NT, int NW, int n_groups, const Ge
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, hipStream_t s) {
-    // at most 32 rows per workgroup (register budget); longer segments take a second row block, whose pass over
-    // the quarter-size weights mostly hits in L2
+// ---- 4-bit weights, many rows (prompt chunks, stacked requests) ------------------------------------------------------------
+// The few-row kernel above unpacks its weights again for every 32 rows and reads the activations once per workgroup of 32 or 64
+// features: at a few hundred rows it is bound by both (13B layer, 389 rows: 1048 us, now 528).  Here a workgroup of WM x WN waves owns
+// 16 * WM * MT rows x 16 * WN * NT features; a stage is one 128-column chunk: the rows' fragments of its four k-tiles, the feature
+// tiles' codes (a KiB each) and scales, all by direct-to-LDS loads, R buffers.  A wave unpacks its NT code tiles once per chunk
+// into 16 operand registers each (2 VALU operations per pair of weights) and multiplies them with MT row tiles; the chunk's result
+// gets -136 * sum of the activations added (one more MFMA per row tile and k-tile, shared by the NT feature tiles) and enters the
+// accumulators times the scale.  Per chunk and wave of 4 x 4 tiles: 80 MFMAs (64 of them products), about 250 VALU operations, 20 KB
+// of LDS reads.  A 128 x 256 block takes 2.2 us per chunk, of which 1.25 us is its MFMAs with two waves per SIMD: unpacking and
+// scaling share the issue slots with them (1024 rows x 27648 features x 5120: 1171 -> 349 us, 0.83 PFLOP/s).  Same arithmetic as the
+// few-row kernel: exact codes, f32 sums per chunk, f32 scaling.
+template <int EPI, bool PARTIAL, int WM, int WN, int MT, int NT, int R>
+__global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void* Wp, const void* X, const void* Sp, int nkc, int M, int lsh, int n_tiles,
+                                                                     int kc_per, const GemmArgs a, float* part) {
+    using T = bf16_t;
+    using E = Elem<T>;
+    using frag_t = E::frag_t;
+    constexpr bool NORM = (EPI != EPI_RESID);
+    constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
+    constexpr int TPI = PAIR ? 2 : 1;
+    constexpr int NW = WM * WN, BMT = WM * MT, BNT = WN * NT, ROWS = BMT * 16, THREADS = NW * 64;
+    constexpr int AF = 4 * BMT, LA = AF / NW, LW = BNT / NW, LPS = LA + LW + 1;
+    constexpr int SCALES = (AF + BNT) * 1024, STAGE = SCALES + NW * 256;
+    static_assert(AF % NW == 0 && BNT % NW == 0, "every wave issues the same loads");
+    static_assert(R >= 3 && R <= 6 && LPS * (R - 1) < 64 && R * STAGE + ROWS * 8 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
+    static_assert(NT <= 8 && THREADS % ROWS == 0, "a wave's scales fit one load; whole rows per pass of the row-scale sums");
+    __shared__ __align__(1024) unsigned char sb0[STAGE];
+    __shared__ __align__(1024) unsigned char sb1[STAGE];
+    __shared__ __align__(1024) unsigned char sb2[STAGE];
+    __shared__ __align__(1024) unsigned char sb3[R > 3 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char sb4[R > 4 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char sb5[R > 5 ? STAGE : 16];
+    __shared__ float rs_s[ROWS];
+    auto buf_at = [&](int j) -> unsigned char* { return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : (j == 3 ? sb3 : (j == 4 ? sb4 : sb5)))); };
+
+    // grid (8 * row blocks, feature blocks / 8, K slices): the row blocks of a feature block are neighbours on one XCD
+    const int mb = blockIdx.x >> 3, col = blockIdx.y * 8 + (blockIdx.x & 7), ks = blockIdx.z;
+    if (col * BNT >= n_tiles) return;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w / WN, wn = w % WN;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int kc_lo = ks * kc_per, ns = min(kc_per, nkc - kc_lo);  // >= 1 (host)
+    const int mt0 = mb * BMT, m_tiles = (M + 15) >> 4;
+
+    // RMSNorm: this thread's share of its row's partial sums of squares (the loads go out in front of the ring's)
+    constexpr int TPR = THREADS / ROWS, SL = 8;
+    float sp[SL], s_more = 0.f;
+    const int row = t % ROWS, sub = t / ROWS;
+    if (NORM) {
+        const int m = min(mt0 * 16 + row, M - 1);
+#pragma unroll
+        for (int i = 0; i < SL; ++i) sp[i] = a.ssp_in[(size_t)min(sub + i * TPR, a.ssp_n - 1) * a.ssp_stride + m];
+#pragma unroll 8
+        for (int j = sub + SL * TPR; j < a.ssp_n; j += TPR) s_more += a.ssp_in[(size_t)j * a.ssp_stride + m];
+    }
+
+    // this wave's loads of a stage: fragments i * NW + w of the activations (k-tile, row tile), code tiles i * NW + w, its own scales
+    const unsigned char* const xb = (const unsigned char*)X;
+    const unsigned char* const wb = (const unsigned char*)Wp;
+    const unsigned char* const sb = (const unsigned char*)Sp;
+    const unsigned wkc = 1024u << lsh, skc = 32u << lsh;  // bytes from one chunk to the next
+    unsigned xo[LA], wo[LW], so;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int f = i * NW + w, mt = min(mt0 + f % BMT, m_tiles - 1);
+        xo[i] = ((unsigned)mt * (unsigned)nkc * 4u + (unsigned)kc_lo * 4u + (unsigned)(f / BMT)) * 1024u + (unsigned)lane * 16u;
+    }
+#pragma unroll
+    for (int i = 0; i < LW; ++i) {
+        const int pc = min(col * BNT + i * NW + w, n_tiles - 1);
+        wo[i] = ((((unsigned)(pc >> lsh) * (unsigned)nkc + (unsigned)kc_lo) << lsh) + (unsigned)(pc & ((1 << lsh) - 1))) * 1024u + (unsigned)lane * 16u;
+    }
+    {  // 4 bytes per lane: lane = (tile of the wave, pair of rows); lanes beyond the wave's tiles repeat its last one
+        const int pc = min(col * BNT + wn * NT + min(lane >> 3, NT - 1), n_tiles - 1);
+        so = ((((unsigned)(pc >> lsh) * (unsigned)nkc + (unsigned)kc_lo) << lsh) + (unsigned)(pc & ((1 << lsh) - 1))) * 32u + (unsigned)(lane & 7) * 4u;
+    }
+    const unsigned lane16 = (unsigned)lane * 16u;
+    int st = 0;
+    auto issue = [&](int j) {  // next stage -> buffer j; stages beyond the range fetch the operands' first line (no branch around a load)
+        unsigned char* dst = buf_at(j);
+        const unsigned live = (unsigned)((st - ns) >> 31);  // uniform, all ones or zero
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + (i * NW + w) * 1024), 16, 0, 0);
+            xo[i] += 4096u;
+        }
+#pragma unroll
+        for (int i = 0; i < LW; ++i) {
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(wb + (wo[i] & live)), FS_LDS_PTR(dst + (AF + i * NW + w) * 1024), 16, 0, 0);
+            wo[i] += wkc;
+        }
+        __builtin_amdgcn_global_load_lds(FS_GLB_PTR(sb + (so & live)), FS_LDS_PTR(dst + SCALES + w * 256), 4, 0, 0);
+        so += skc;
+        ++st;
+    };
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    frag_t koff;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) koff[e] = (bf16_t)(-136.0f);
+    const f32x4 zero{0.f, 0.f, 0.f, 0.f};
+    // mask and exponent of the unpacking, one in a scalar and one in a vector register: a single and-or instruction takes both
+    unsigned nib = 0x000F000Fu, one28 = 0x43004300u;
+    asm volatile("" : "+s"(nib));
+    asm volatile("" : "+v"(one28));
+    const bool works = (mt0 + wm * MT) * 16 < M;  // uniform: a wave whose rows all lie beyond the matrix only loads
+
+#pragma unroll
+    for (int j = 0; j + 1 < R; ++j) issue(j);
+    if (NORM) {  // partial row sums meet in rs_s (one thread per row and pass of the loop below)
+        float tot = s_more;
+#pragma unroll
+        for (int i = 0; i < SL; ++i) tot += sub + i * TPR < a.ssp_n ? sp[i] : 0.f;
+        for (int k = 0; k < TPR; ++k) {  // uniform; TPR is 2 .. 4
+            if (sub == k) rs_s[row] = k == 0 ? tot : rs_s[row] + tot;
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+    }
+    auto stage = [&](int ju) {  // the next stage, in buffer ju
+        asm volatile("" ::: "memory");
+        FS_WAIT_VM_LGKM((R - 2) * LPS, 0);
+        __builtin_amdgcn_s_barrier();  // the stage is complete for every wave, and everybody is done with the one before
+        asm volatile("" ::: "memory");
+        issue((ju + R - 1) % R);
+        if (!works) return;
+        const unsigned char* b = buf_at(ju);
+        u32x4 c[NT];
+        bf16x4 s4[NT];
+        frag_t wf[2][NT], x[2][MT];
+        f32x4 tq[MT][NT], off[MT];
+        auto unpack = [&](int set, int q) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                unsigned pr[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) pr[j] = ((c[nt][q] >> (4 * j)) & nib) | one28;
+                wf[set][nt] = __builtin_bit_cast(frag_t, u32x4{pr[0], pr[1], pr[2], pr[3]});
+            }
+        };
+        auto read_x = [&](int set, int q) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) x[set][mt] = *(const frag_t*)(b + (q * BMT + wm * MT + mt) * 1024 + lane16);
+        };
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) c[nt] = *(const u32x4*)(b + (AF + wn * NT + nt) * 1024 + lane16);
+        read_x(0, 0);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) s4[nt] = *(const bf16x4*)(b + SCALES + w * 256 + nt * 32 + g * 8);
+        unpack(0, 0);
+        // k-tile by k-tile: the next one's operands are read and unpacked while this one's MFMAs run
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int cu = q & 1, nx = cu ^ 1;
+            if (q < 3) {
+                read_x(nx, q + 1);
+                unpack(nx, q + 1);
+            }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) tq[mt][nt] = E::mma(wf[cu][nt], x[cu][mt], q ? tq[mt][nt] : zero);
+                off[mt] = E::mma(koff, x[cu][mt], q ? off[mt] : zero);
+            }
+            if (q < 3) {
+                __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);  // the next k-tile's LDS reads first
+#pragma unroll
+                for (int k = 0; k < MT * (NT + 1); ++k) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // one MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x002, (7 * NT + MT * (NT + 1) - 1) / (MT * (NT + 1)), 0);  // its share of the unpacking
+                }
+            }
+        }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float sc = (float)s4[nt][v];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[mt][nt][v] += sc * (tq[mt][nt][v] + off[mt][v]);
+            }
+    };
+    int s0 = 0;
+    for (; s0 + R <= ns; s0 += R) {
+#pragma unroll
+        for (int ju = 0; ju < R; ++ju) stage(ju);
+    }
+#pragma unroll
+    for (int ju = 0; ju < R; ++ju) {
+        if (s0 + ju >= ns) break;
+        stage(ju);
+    }
+    // every load has landed and every wave has left the loop before LDS is reused or given back
+    FS_WAIT_VM_LGKM(0, 0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    const int pt0 = col * BNT + wn * NT;
+    if constexpr (PARTIAL) {  // raw tiles: part[ks][m tile][n tile][lane]
+        const int nt_all = (int)gridDim.y * 8 * BNT;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const int mtile = mt0 + wm * MT + mt;
+            if (mtile >= m_tiles) break;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) ((f32x4*)part)[(((size_t)ks * m_tiles + mtile) * nt_all + pt0 + nt) * 64 + lane] = acc[mt][nt];
+        }
+        return;
+    }
+    float* hs = (float*)sb0;  // residual projections: [WN feature waves][ROWS] sums of squares
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int lr = (wm * MT + mt) * 16 + r16, m = mt0 * 16 + lr;
+        const float rs = NORM ? 1.0f / sqrtf(rs_s[lr] / (float)a.K + a.eps) : 1.f;
+        float hsq = 0.f;
+#pragma unroll
+        for (int ntp = 0; ntp < NT / TPI; ++ntp) {
+            float y[TPI][4];
+#pragma unroll
+            for (int tt = 0; tt < TPI; ++tt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y[tt][v] = acc[mt][ntp * TPI + tt][v];
+            hsq += epilogue_item<T, EPI>(a, y, rs, m, pt0 + ntp * TPI, g);
+        }
+        if constexpr (EPI == EPI_RESID) {
+            hsq = wave_xor_add(wave_xor_add(hsq, 16), 32);
+            if (g == 0) hs[wn * ROWS + lr] = hsq;
+        }
+    }
+    if constexpr (EPI == EPI_RESID) {
+        if (a.ssp_out) {
+            __syncthreads();
+            for (int r = t; r < ROWS; r += THREADS) {
+                float sum = 0.f;
+#pragma unroll
+                for (int k = 0; k < WN; ++k) sum += hs[k * ROWS + r];
+                if (mt0 * 16 + r < a.ssp_stride) a.ssp_out[(size_t)col * a.ssp_stride + mt0 * 16 + r] = sum;
+            }
+        }
+    }
+}
+
+// Which 4-bit kernel: a round of this kernel's blocks takes 1.45 (64 rows) or 2.2 us (128 rows) per 128-column chunk, the few-row
+// kernel with four tiles per workgroup 0.37 ns per chunk, feature tile and 32-row block.  Both sides, us (few / this): 4096 x 12288,
+// 128 rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 64 rows 51 / 60, 128 rows
+// 101 / 89.  Residual projections (two tiles per workgroup there, K slices here): 4096 x 4096, 128 rows 18 / 25, 200 rows 30 / 28;
+// 13824 x 5120, 64 rows 42 / 32; 5120 x 5120, 65 rows 23 / 26.
+static bool block_w4_pays(int epi, int M, int n_tiles) {
+    if (M <= 32) return false;
+    const int work = n_tiles * ((M + 31) / 32), rounds = ((n_tiles + 15) / 16 * ((M + 127) / 128) + 255) / 256;
+    if (epi == EPI_RESID) return work > (M <= 64 ? 600 : 1100);
+    return work > (M <= 64 ? 4200 : 6000) * rounds;
+}
+
+int w4_ssp_parts(int M, int n_tiles) { return block_w4_pays(EPI_RESID, M, n_tiles) ? (n_tiles + 15) / 16 : n_tiles; }
+
+template <int EPI, int WM, int WN, int MT, int NT, int R>
+static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    constexpr int BMT = WM * MT, BNT = WN * NT;
+    static_assert(BNT == 16, "the residual projections' sums of squares come per 16 feature tiles");
+    const int m_tiles = (a.M + 15) / 16, m_blocks = (m_tiles + BMT - 1) / BMT, cols8 = ((n_tiles + BNT - 1) / BNT + 7) / 8, nkc = a.nkt / 4;
+    const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
+    const dim3 block(WM * WN * 64);
+    if constexpr (EPI == EPI_RESID) {
+        int ks = std::min(std::min(256 / ((n_tiles + BNT - 1) / BNT * m_blocks), 8), nkc / 4);
+        while (ks > 1 && (size_t)ks * m_tiles * cols8 * 8 * BNT * 1024 > part_bytes) --ks;
+        if (ks > 1) {
+            const int per = (nkc + ks - 1) / ks;
+            ks = (nkc + per - 1) / per;
+            hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, true, WM, WN, MT, NT, R>), dim3(8 * m_blocks, cols8, ks), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh,
+                               n_tiles, per, a, part);
+            return launch_fixup<4>(a, cols8 * 8 * BNT, ks, part, s);
+        }
+    }
+    hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, false, WM, WN, MT, NT, R>), dim3(8 * m_blocks, cols8, 1), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh, n_tiles,
+                       nkc, a, nullptr);
+    return hipGetLastError();
+}
+
+static hipError_t launch_block_w4(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    if (!a.x_frag || (unsigned long long)(n_tiles + 16) * a.nkt * 256ull >= (1ull << 32) || (unsigned long long)(a.M + 16) * a.nkt * 64ull >= (1ull << 32))
+        return hipErrorInvalidValue;
+#define FS_W4(e)                                                                                              \
+    if (epi == e) {                                                                                           \
+        if (a.M <= 64) return launch_w4_shape<e, 1, 8, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);  \
+        return launch_w4_shape<e, 2, 4, 4, 4, 3>(layout_nt, n_tiles, a, part, part_bytes, s);                 \
+    }
+    FS_W4(EPI_QKV) FS_W4(EPI_RESID) FS_W4(EPI_SWIGLU) FS_W4(EPI_LOGITS)
+#undef FS_W4
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a0, float* part, size_t part_bytes, hipStream_t s) {
+    if (block_w4_pays(epi, a0.M, n_groups * NT)) return launch_block_w4(epi, NT, n_groups * NT, a0, part, part_bytes, s);
+    // at most 32 rows per workgroup (register budget); longer segments take further row blocks, whose passes over
+    // the quarter-size weights mostly hit in L2
+    GemmArgs a = a0;
     const int MT = a.M <= 16 ? 1 : 2;
+    a.w_shift = NT == 4 ? 2 : NT == 2 ? 1 : 0;
+    if (NT == 4 && MT == 1) {
+        // one row tile: half a group per workgroup where whole groups would leave a last round of few workgroups (344 of them, two
+        // rounds of 256 compute units: gate/up 20.8 -> 18.6 us)
+        auto fill = [](int n) { return (double)n / ((n + 255) / 256 * 256); };
+        if (fill(2 * n_groups) > 1.2 * fill(n_groups)) {
+            NT = 2;
+            n_groups *= 2;
+        }
+    }
     if (NW > 8) NW = 8;
     if (MT * NT >= 8 && NW > 4) NW = 4;  // as in the dense launcher
     if (epi == EPI_QKV) return launch_mt_nt_w4<EPI_QKV>(MT, NT, NW, n_groups, a, s);

@@ -24,6 +24,7 @@ struct GemmArgs {
     const float* ssp_in;   // [ssp_n][ssp_stride]: partial sums of squares per row
     int ssp_n, ssp_stride;
     int ldx, M, K, nkt;
+    int w_shift;     // 4-bit few-row kernel, set by the launcher: log2 of the re-tiled weights' tiles per group
     int red_copies;  // set by the launcher: copies of the workgroup's tiles the cross-wave reduction keeps in LDS
     int N;           // valid output features (packed order)
     float eps;
@@ -82,8 +83,10 @@ void launch_pack_w4(const PackW4Args& a, hipStream_t s);
 // per 512-column slice, ssp[slice][ssp_stride]; returns the number of slices through n_slices.
 hipError_t launch_prenorm(const void* X, int ldx, int M, int K, const void* gain, void* xg, float* ssp, int ssp_stride, int* n_slices,
                              hipStream_t s);
-// 4-bit weights, bf16 activations: w[n][k] = scale[n][k/128] * (code - 8)
-hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, hipStream_t s);
+// 4-bit weights, bf16 activations (fragment-major, with their sums of squares): w[n][k] = scale[n][k/128] * (code - 8).  A residual
+// projection leaves w4_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
+int w4_ssp_parts(int M, int n_tiles);
+hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
 // bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block up to 64 rows).  layout_nt and n_tiles
 // describe the re-tiled weights (tiles per group, 16-feature tiles in total); normed projections need ssp_in from 384 rows on
 // (256-feature blocks; the 128-feature blocks add up the squares of the activations themselves).  `part` (may be null) is scratch for K-split partial results of the d_model-wide

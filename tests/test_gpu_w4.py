@@ -130,3 +130,36 @@ def test_w4_random_shapes(i):
         lerr = max_rel_err(lg.float().cpu().numpy(), lo)
         print(f"  logits max-rel-err {lerr:.3e}", flush=True)
         assert lerr < TOL["bf16"]
+
+
+@pytest.mark.parametrize("name,cfg,rows", [
+    # every projection in 128-row blocks (the last one holds one row tile), K slices for the residual ones
+    ("all", synth.StageConfig("w4b-all", "bf16", 2, 1024, 16, 16, 128, 3328, 0, 40, 577, 577, 577, 1, qkv_bias=True), 577),
+    # residual projections and LM head in 64-row blocks, the attention output with one K slice; the others in the few-row kernel
+    ("resid", synth.StageConfig("w4b-resid", "bf16", 2, 4992, 2, 2, 64, 1152, 34000, 30, 33, 33, 5, 3), 33),
+    ("resid", synth.StageConfig("w4b-resid", "bf16", 1, 4992, 2, 2, 64, 1152, 34000, 30, 64, 64, 5, 3), 64),
+    # gate/up only: 64-row blocks, and 128-row blocks whose last one holds a single row
+    ("gateup", synth.StageConfig("w4b-gu", "bf16", 2, 128, 2, 1, 64, 17024, 0, 30, 64, 64, 5, 3), 64),
+    ("gateup", synth.StageConfig("w4b-gu", "bf16", 2, 128, 2, 1, 64, 9728, 0, 30, 161, 161, 161, 1), 161),
+    # one row tile, 344 groups of four gate/up tiles: half a group per workgroup
+    ("half", synth.StageConfig("w4b-half", "bf16", 1, 128, 2, 1, 64, 11008, 0, 30, 16, 16, 5, 3), 16),
+])
+def test_w4_row_blocks(name, cfg, rows):
+    """The many-row 4-bit kernel where it takes over from the few-row one, alone and mixed with it in one layer."""
+    import torch
+    from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
+    print(f"[case] {name} rows={rows}", flush=True)
+    pair = Pair(cfg, seed=rows, head=cfg.vocab > 0, w4=True)
+    parent = np.arange(-1, rows - 1, dtype=np.int32) if cfg.max_branch == 1 else synth.config_tree(cfg, seed=rows).parent
+    hid = synth.hidden(cfg, rows, 0, rows)
+    o, g = pair.verify_tree(parent, hid, rows)
+    L = cfg.l_glo + rows
+    err = max_rel_err(g, o)
+    kerr = max_rel_err(pair.kv[:, :, :, cfg.l_glo:L].float().cpu().numpy(), pair.orc.kv[:, :, :, cfg.l_glo:L])
+    print(f"  hidden {err:.2e}, K/V {kerr:.2e}", flush=True)
+    assert err < TOL["bf16"] and kerr < TOL["bf16"]
+    if cfg.vocab:
+        x = synth.storage(cfg, o.astype(np.float32))
+        lo, _ = pair.orc.logits(x.astype(np.float64))
+        lg, _ = pair.gpu.tree_logits(to_dev(x, torch.bfloat16))
+        assert max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
