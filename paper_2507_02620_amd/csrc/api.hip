@@ -266,7 +266,7 @@ struct Tunables {
         attn_wgs = env_int("FLOWSPEC_ATTN_WGS", 0);    // > 0: workgroups the attention split plan aims for
         attn_mtw = env_int("FLOWSPEC_ATTN_MTW", 0);    // > 0: row tiles per wave of the attention kernel
         attn_nwc = env_int("FLOWSPEC_ATTN_NWC", 0);    // > 0: at most this many row-tile waves per workgroup (more row blocks)
-        attn_dma = env_int("FLOWSPEC_ATTN_DMA", 0);    // 1: never the direct-to-LDS attention kernel; 2 .. 4: always, with so many tile buffers
+        attn_dma = env_int("FLOWSPEC_ATTN_DMA", 0);    // 1: never the direct-to-LDS attention kernel; 2 .. 4: always, with so many tile buffers; 5: tiles in pairs
         attn_nset = env_int("FLOWSPEC_ATTN_NSET", 0);  // > 0: K/V tiles in flight per workgroup on long splits
         wide_rows = env_int("FLOWSPEC_WIDE_ROWS", 129); // stacked rows from which every projection takes the many-row kernels (at most 129)
         mid_rows = env_int("FLOWSPEC_MID_ROWS", 17);   // ... from which they may take the weight-streaming kernel fed through LDS
@@ -602,7 +602,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     if (prep.n) HIP_TRY_K(st, FS_K_PREPARE, s, prep.launch(s));
     int aMTW, aRB;
     attn_plan(st->elem, hd, max_M, G, d.n_kv_heads * n_live, max_L, kMaxSplits, st->tun.attn_wgs, st->tun.attn_mtw, st->tun.attn_nset, st->tun.attn_nwc,
-              st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma);
+              st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma, &at.pair);
 
     // 4-bit stages: activations entering a normed projection carry the norm's gain, and the rows' sums of squares
     // travel beside them as partial sums (see GemmArgs::gain_next).  The many-row kernels of dense stages use the same hand-over of

@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
 
 
 // ---- variant whose K/V tiles go straight from global memory into LDS ------------------------------------------------
-// bf16, head dim 128, one row tile per wave, 4 waves.  The tile fetch is the direct-to-LDS load: no registers hold a tile in
+// bf16, head dim 128, GROUPS x 4 waves of MTW row tiles.  The tile fetch is the direct-to-LDS load: no registers hold a tile in
 // flight, so NBUF - 1 whole tiles (32 KiB each) are in flight per workgroup, behind ONE barrier per tile:
 //     wait (own loads of tile t landed, own LDS reads of tile t - 1 done) -> barrier -> issue tile t + NBUF - 1 into the
 //     buffer tile t - 1 used -> compute tile t.
@@ -443,9 +443,20 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
 // of 16 rows over all banks as the padding does.  The barrier is the bare instruction with explicit wait counts: the fence
 // of __syncthreads would wait for every tile in flight.  One array per buffer: distinct objects, so that the compiler's
 // own tracking of the direct-to-LDS loads never ties a read of one buffer to a load into another.
-
-template <int NBUF, bool STREAM>
-__global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, const AttnArgs a) {
+//
+// GROUPS = 2 (prompt chunks, many stacked rows: bound by LDS reads, matrix instructions and exponentials together, not by the
+// stream): two groups of four waves hold the same 128 rows and take alternate tiles, each into buffers of its own, and the second
+// group's sums join the first one's through LDS at the end.  Two row tiles per wave halve the LDS bytes per row (32 KiB per wave and
+// tile), and eight waves per compute unit still hide one wave's exponentials behind another's matrix products — without partial
+// results in memory.  Tiles behind the last slot that a row block can see are not walked, and a masked tile that all rows of a wave
+// see whole takes the short form.  The first half of the V fragments is read ahead of the exponentials (54.0 -> 52.0 us); raising
+// the waves' priority around the matrix products made it 52.6 -> 54.6.  1024 rows, 32 heads, 1k / 4k context:
+// 63.5 / 146 -> 52.0 / 108 us (tree_attn_kernel with one row tile per wave -> this).
+//
+// The bound of 512 threads also for the 256-thread forms keeps the compiler from splitting the registers into two files, which
+// cost 4 moves per accumulator and tile (16k context, 64 rows: 55.4 -> 52.7 us).
+template <int NBUF, bool STREAM, int MTW, int GROUPS>
+__global__ void __launch_bounds__(512) tree_attn_dma_kernel(int row_blocks, const AttnArgs a) {
     using T = bf16_t;
     using E = Elem<T>;
     using frag_t = E::frag_t;
@@ -456,38 +467,57 @@ __global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, cons
     constexpr int LPT = 8;                      // direct-to-LDS loads per wave and tile (4 K + 4 V, 4 rows each)
     constexpr int AUX = STREAM ? 2 : 0;         // non-temporal when one row block reads the K/V once
     static_assert(NBUF >= 2 && NBUF <= 4 && LPT * (NBUF - 1) < 64, "vmcnt is a 6-bit counter");
-    __shared__ __align__(1024) unsigned char tb0[2 * KBYTES];
-    __shared__ __align__(1024) unsigned char tb1[2 * KBYTES];
+    static_assert(GROUPS == 1 || (GROUPS == 2 && NBUF == 2), "two groups: four tiles of 32 KiB in LDS");
+    __shared__ __align__(1024) unsigned char tb0[GROUPS * 2 * KBYTES];
+    __shared__ __align__(1024) unsigned char tb1[GROUPS * 2 * KBYTES];
     __shared__ __align__(1024) unsigned char tb2[NBUF >= 3 ? 2 * KBYTES : 16];
     __shared__ __align__(1024) unsigned char tb3[NBUF >= 4 ? 2 * KBYTES : 16];
-    auto buf_at = [&](int j) -> unsigned char* { return j == 0 ? tb0 : (j == 1 ? tb1 : (j == 2 ? tb2 : tb3)); };
 
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
+    const int grp = GROUPS > 1 ? __builtin_amdgcn_readfirstlane(tid >> 8) : 0;
+    auto buf_at = [&](int j) -> unsigned char* { return (j == 0 ? tb0 : (j == 1 ? tb1 : (j == 2 ? tb2 : tb3))) + grp * (2 * KBYTES); };
     const int r16 = lane & 15, g = lane >> 4;
-    const int split = blockIdx.x, kvh = blockIdx.y, rqi = blockIdx.z / row_blocks, rb = blockIdx.z % row_blocks;
+    const int split = blockIdx.x, kvh = blockIdx.y, rqi = blockIdx.z / row_blocks;
+    // two groups: the last row block sees the most slots (causal part), so it is started first
+    const int rb = GROUPS > 1 ? row_blocks - 1 - (int)blockIdx.z % row_blocks : (int)blockIdx.z % row_blocks;
     const AttnReq rq = a.req[rqi];
     const int M = rq.M, L = rq.L, l_glo = rq.l_glo, row0 = rq.row0;
     const int R = a.G * M;
-    const bool dead = rb * a.nwc * 16 >= R;  // a shorter request of the batch may have no such row block
-    const int ntiles = dead ? 0 : (L + BS - 1) / BS;
-    const int t0 = split * a.tiles_per_split, t1 = min(ntiles, t0 + a.tiles_per_split);
-    const bool computes = (w < a.nwc) && ((rb * a.nwc + w) * 16 < R);
-
-    const int rho = (rb * a.nwc + w) * 16 + r16;
-    const bool rok = computes && rho < R;
-    const int rr = rok ? rho : 0;
-    const int seg_r = row0 + rr % M;
-    frag_t qf[NKT];
-    {
-        const int qh = kvh * a.G + rr / M;
-        const T* qp = (const T*)a.q + (size_t)seg_r * (a.Hq * HD) + (size_t)qh * HD + g * EPF;
-#pragma unroll
-        for (int kt = 0; kt < NKT; ++kt) qf[kt] = rok ? *(const frag_t*)(qp + kt * KT) : E::zero();
+    const int rho0 = rb * a.nwc * MTW * 16;  // first stacked row of the workgroup
+    const bool dead = rho0 >= R;  // a shorter request of the batch may have no such row block
+    // Slots the row block can see: a row's ancestors precede it, so none of its rows sees a slot behind that of its last row.
+    int seen = L;
+    if (GROUPS > 1) {
+        const int rho1 = min(R, rho0 + a.nwc * MTW * 16) - 1;
+        if (!dead && rho0 / M == rho1 / M) seen = L - M + rho1 % M + 1;
     }
-    f32x4 acc[NHT];
+    const int ntiles = dead ? 0 : (seen + BS - 1) / BS;
+    const int t0 = split * a.tiles_per_split, t1 = min(ntiles, t0 + a.tiles_per_split);
+    const bool computes = (w < a.nwc) && (rho0 + w * MTW * 16 < R);
+
+    int rho[MTW], seg_r[MTW];
+    bool rok[MTW];
+    frag_t qf[MTW][NKT];
 #pragma unroll
-    for (int nt = 0; nt < NHT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float mrun = NEG_BIG, lrun = 0.f;
+    for (int i = 0; i < MTW; ++i) {
+        rho[i] = rho0 + (w * MTW + i) * 16 + r16;
+        rok[i] = computes && rho[i] < R;
+        const int rr = rok[i] ? rho[i] : 0;
+        seg_r[i] = row0 + rr % M;
+        const int qh = kvh * a.G + rr / M;
+        const T* qp = (const T*)a.q + (size_t)seg_r[i] * (a.Hq * HD) + (size_t)qh * HD + g * EPF;
+#pragma unroll
+        for (int kt = 0; kt < NKT; ++kt) qf[i][kt] = rok[i] ? *(const frag_t*)(qp + kt * KT) : E::zero();
+    }
+    f32x4 acc[MTW][NHT];
+    float mrun[MTW], lrun[MTW];
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) {
+        mrun[i] = NEG_BIG;
+        lrun[i] = 0.f;
+#pragma unroll
+        for (int nt = 0; nt < NHT; ++nt) acc[i][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 
     const unsigned char* kbase = (const unsigned char*)((const T*)rq.kbase + a.layer_off + (size_t)kvh * a.stride_head);
     const unsigned char* vbase = kbase + (size_t)a.stride_kv * sizeof(T);
@@ -516,12 +546,20 @@ __global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, cons
         }
     };
 
-    const uint64_t* am = a.anc + (size_t)seg_r * FS_ANC_WORDS;
-    uint64_t mw0 = 0, mw1 = 0;
+    const uint64_t* am[MTW];
+    uint64_t mw0[MTW], mw1[MTW], cw0[MTW], cw1[MTW];
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) {
+        am[i] = a.anc + (size_t)seg_r[i] * FS_ANC_WORDS;
+        mw0[i] = mw1[i] = cw0[i] = cw1[i] = 0;
+    }
     auto load_mask = [&](int tile) {
         const int wd = min(max((tile * BS - l_glo) >> 6, 0), FS_ANC_WORDS - 1), wd1 = min(wd + 1, FS_ANC_WORDS - 1);
-        mw0 = am[wd];
-        mw1 = am[wd1];
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) {
+            mw0[i] = am[i][wd];
+            mw1[i] = am[i][wd1];
+        }
     };
 
     // byte offsets of this lane's fragment reads inside a buffer (without the per-sub-tile strides)
@@ -534,107 +572,129 @@ __global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, cons
         for (int nt = 0; nt < NHT; ++nt) vread[nt] = (unsigned)(KBYTES + vr * ROWB + (((nt * 2 + ((r16 & 3) >> 1)) ^ vr) * 16) + (r16 & 1) * 8);
     }
 
-    auto process = [&](int tile, const unsigned char* buf, auto masked_tag) {
+    auto process = [&](int tile, const unsigned char* buf, auto masked_tag) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         const int s0 = tile * BS;
         if (!computes) return;
-        const bool need_mask = MASKED && (s0 + BS > l_glo);  // the tile touches draft slots or the tail beyond L
-        uint64_t vm = 0;
+        if (GROUPS > 1 && tile >= t1) return;  // the range has an odd number of tiles
+        bool need_mask = MASKED && (s0 + BS > l_glo);  // the tile touches draft slots or the tail beyond L
+        uint64_t vm[MTW];
         if (need_mask) {
             const int d0 = s0 - l_glo, valid = L - s0;  // valid >= 1
-            uint64_t m;
-            if (d0 >= 0) {
-                const int wd = d0 >> 6, sh = d0 & 63;
-                m = mw0 >> sh;
-                if (sh && wd + 1 < FS_ANC_WORDS) m |= mw1 << (64 - sh);
-            } else {
-                m = ((1ull << (-d0)) - 1) | (mw0 << (-d0));  // 0 < -d0 < BS <= 64
+            bool any = false, part = false;
+#pragma unroll
+            for (int i = 0; i < MTW; ++i) {
+                uint64_t m;
+                if (d0 >= 0) {
+                    const int wd = d0 >> 6, sh = d0 & 63;
+                    m = cw0[i] >> sh;
+                    if (sh && wd + 1 < FS_ANC_WORDS) m |= cw1[i] << (64 - sh);
+                } else {
+                    m = ((1ull << (-d0)) - 1) | (cw0[i] << (-d0));  // 0 < -d0 < BS <= 64
+                }
+                if (valid < 64) m &= (1ull << valid) - 1;
+                if (!rok[i]) m = 0;
+                vm[i] = m >> (g * 4);
+                any |= (m != 0);
+                part |= rok[i] && m != ~0ull;
             }
-            if (valid < 64) m &= (1ull << valid) - 1;
-            if (!rok) m = 0;
-            vm = m >> (g * 4);
-            if (__ballot(m != 0) == 0) return;  // wave-uniform: none of the wave's rows sees a slot of this tile
+            if (__ballot(any) == 0) return;  // wave-uniform: none of the wave's rows sees a slot of this tile
+            need_mask = __ballot(part) != 0;  // all of them see all of it (a chain's tiles below the diagonal): the short form below
         }
         // ---- S^T = K . Q^T ----
-        f32x4 st[BS / 16];
+        f32x4 st[MTW][BS / 16];
 #pragma unroll
         for (int j = 0; j < BS / 16; ++j) {
-            st[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < MTW; ++i) st[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < NKT; ++kt) {
                 const frag_t kf = *(const frag_t*)(buf + kread[kt] + j * 16 * ROWB);
-                st[j] = E::mma(kf, qf[kt], st[j]);
+#pragma unroll
+                for (int i = 0; i < MTW; ++i) st[i][j] = E::mma(kf, qf[i][kt], st[i][j]);
             }
         }
-        // ---- mask, online softmax (as in tree_attn_kernel) ----
-        float mx = NEG_BIG;
-        if (need_mask) {
+        auto vload = [&](int jj, int nt) __attribute__((always_inline)) {
+                const unsigned char* vp = buf + vread[nt] + jj * 32 * ROWB;
+                const s16x4 t0v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)vp);
+                const s16x4 t1v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vp + 16 * ROWB));
+                return __builtin_bit_cast(frag_t, __builtin_shufflevector(t0v, t1v, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
+        frag_t vf0[NHT];
+        if (MTW > 1) {
 #pragma unroll
-            for (int j = 0; j < BS / 16; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float sv = st[j][v] * a.scale_log2;
-                    const unsigned half = (j * 16 + v) < 32 ? (unsigned)vm : (unsigned)(vm >> 32);
-                    if (!(half & (1u << ((j * 16 + v) & 31)))) sv = NEG_BIG;
-                    st[j][v] = sv;
-                    mx = fmaxf(mx, sv);
-                }
-        } else {
-#pragma unroll
-            for (int j = 0; j < BS / 16; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) mx = fmaxf(mx, st[j][v]);
-            mx *= a.scale_log2;
+            for (int nt = 0; nt < NHT; ++nt) vf0[nt] = vload(0, nt);
+            __builtin_amdgcn_sched_barrier(0);
         }
-        mx = wave_xor_max(wave_xor_max(mx, 16), 32);
-        const float mnew = fmaxf(mrun, mx);
-        if (__ballot(mnew != mrun) != 0) {
-            const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
-            lrun *= alpha;
+        frag_t pf[MTW][NPF];
 #pragma unroll
-            for (int nt = 0; nt < NHT; ++nt)
+        for (int i = 0; i < MTW; ++i) {
+            float mx = NEG_BIG;
+            if (need_mask) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[nt][v] *= alpha;
-            mrun = mnew;
+                for (int j = 0; j < BS / 16; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        float sv = st[i][j][v] * a.scale_log2;
+                        const unsigned half = (j * 16 + v) < 32 ? (unsigned)vm[i] : (unsigned)(vm[i] >> 32);
+                        if (!(half & (1u << ((j * 16 + v) & 31)))) sv = NEG_BIG;
+                        st[i][j][v] = sv;
+                        mx = fmaxf(mx, sv);
+                    }
+            } else {
+#pragma unroll
+                for (int j = 0; j < BS / 16; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) mx = fmaxf(mx, st[i][j][v]);
+                mx *= a.scale_log2;
+            }
+            mx = wave_xor_max(wave_xor_max(mx, 16), 32);
+            const float mnew = fmaxf(mrun[i], mx);
+            if (__ballot(mnew != mrun[i]) != 0) {
+                const float alpha = __builtin_amdgcn_exp2f(mrun[i] - mnew);
+                lrun[i] *= alpha;
+#pragma unroll
+                for (int nt = 0; nt < NHT; ++nt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][nt][v] *= alpha;
+                mrun[i] = mnew;
+            }
+            float psum = 0.f;
+            float p[BS / 16][4];
+            if (need_mask) {
+#pragma unroll
+                for (int j = 0; j < BS / 16; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const float sv = st[i][j][v];
+                        const float e = (sv <= NEG_BIG) ? 0.f : __builtin_amdgcn_exp2f(sv - mnew);
+                        p[j][v] = e;
+                        psum += e;
+                    }
+            } else {
+#pragma unroll
+                for (int j = 0; j < BS / 16; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(st[i][j][v], a.scale_log2, -mnew));
+                        p[j][v] = e;
+                        psum += e;
+                    }
+            }
+            lrun[i] += psum;
+#pragma unroll
+            for (int jj = 0; jj < NPF; ++jj)
+#pragma unroll
+                for (int e = 0; e < EPF; ++e) pf[i][jj][e] = E::from_f(p[jj * NSUB + e / 4][e % 4]);
         }
-        float psum = 0.f;
-        float p[BS / 16][4];
-        if (need_mask) {
-#pragma unroll
-            for (int j = 0; j < BS / 16; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float sv = st[j][v];
-                    const float e = (sv <= NEG_BIG) ? 0.f : __builtin_amdgcn_exp2f(sv - mnew);
-                    p[j][v] = e;
-                    psum += e;
-                }
-        } else {
-#pragma unroll
-            for (int j = 0; j < BS / 16; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(st[j][v], a.scale_log2, -mnew));
-                    p[j][v] = e;
-                    psum += e;
-                }
-        }
-        lrun += psum;
-        frag_t pf[NPF];
-#pragma unroll
-        for (int jj = 0; jj < NPF; ++jj)
-#pragma unroll
-            for (int e = 0; e < EPF; ++e) pf[jj][e] = E::from_f(p[jj * NSUB + e / 4][e % 4]);
         // ---- O^T += V^T . P^T (transposing LDS load, rows jj * 32 + g * 4 + (r16 >> 2) and + 16) ----
 #pragma unroll
         for (int jj = 0; jj < NPF; ++jj)
 #pragma unroll
             for (int nt = 0; nt < NHT; ++nt) {
-                const unsigned char* vp = buf + vread[nt] + jj * 32 * ROWB;
-                const s16x4 t0v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)vp);
-                const s16x4 t1v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vp + 16 * ROWB));
-                const frag_t vf = __builtin_bit_cast(frag_t, __builtin_shufflevector(t0v, t1v, 0, 1, 2, 3, 4, 5, 6, 7));
-                acc[nt] = E::mma(vf, pf[jj], acc[nt]);
+                const frag_t vf = (MTW > 1 && jj == 0) ? vf0[nt] : vload(jj, nt);
+#pragma unroll
+                for (int i = 0; i < MTW; ++i) acc[i][nt] = E::mma(vf, pf[i][jj], acc[i][nt]);
             }
     };
 
@@ -642,20 +702,28 @@ __global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, cons
     using masked_t = std::integral_constant<bool, true>;
     if (t1 > t0) {  // uniform over the workgroup
 #pragma unroll
-        for (int k = 0; k + 1 < NBUF; ++k) issue(t0 + k, buf_at(k));
+        for (int k = 0; k + 1 < NBUF; ++k) issue(t0 + GROUPS * k + grp, buf_at(k));
         FS_WAIT_VM_LGKM(LPT * (NBUF - 1), 15);  // the Q fragments (issued before the tiles) are there; the tiles stay in flight
-        // tile `tile` sits in buffer k.  Loads return in order and every step issues one tile's worth, so at each wait all
-        // but the newest NBUF - 2 tiles' worth have landed (mask loads issued in between only make a wait stricter).
-        auto step = [&](int tile, auto kc, auto masked_tag) {
+        // tiles `tile` .. + GROUPS - 1 sit in the groups' buffers k.  Loads return in order and every step issues one tile's worth
+        // per group, so at each wait all but the newest NBUF - 2 tiles' worth have landed (mask loads issued in between only make
+        // a wait stricter).
+        auto step = [&](int tile, auto kc, auto masked_tag) __attribute__((always_inline)) {
             constexpr int k = decltype(kc)::value;
             constexpr bool MASKED = decltype(masked_tag)::value;
             asm volatile("" ::: "memory");
             FS_WAIT_VM_LGKM(LPT * (NBUF - 2), 0);
-            __builtin_amdgcn_s_barrier();  // tile `tile` complete for every wave; every wave is done with tile - 1
+            __builtin_amdgcn_s_barrier();  // the step's tiles are complete for every wave; every wave is done with the step before
             asm volatile("" ::: "memory");
-            if (MASKED) load_mask(tile);
-            issue(tile + NBUF - 1, buf_at((k + NBUF - 1) % NBUF));
-            process(tile, buf_at(k), masked_tag);
+            if (MASKED) {  // this step's words have arrived with its tiles; the next step's come with the next tiles
+#pragma unroll
+                for (int i = 0; i < MTW; ++i) {
+                    cw0[i] = mw0[i];
+                    cw1[i] = mw1[i];
+                }
+                load_mask(tile + GROUPS + grp);
+            }
+            issue(tile + GROUPS * (NBUF - 1) + grp, buf_at((k + NBUF - 1) % NBUF));
+            process(tile + grp, buf_at(k), masked_tag);
         };
         using b0 = std::integral_constant<int, 0>;
         using b1 = std::integral_constant<int, 1>;
@@ -663,18 +731,20 @@ __global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, cons
         using b3 = std::integral_constant<int, 3>;
         // The tile range has an unmasked part (slots below l_glo: [t0, tA)) and a masked part ([tA, t1): draft slots and the tail
         // beyond L); tA sits on a buffer-ring boundary, so the masked part may begin with tiles that need no mask.
+        constexpr int RING = NBUF * GROUPS;
         const int t_mask = max(t0, min(t1, l_glo / BS));
-        const int tA = t0 + (t_mask - t0) / NBUF * NBUF;
+        const int tA = t0 + (t_mask - t0) / RING * RING;
         int tile = t0;
-        for (; tile < tA; tile += NBUF) {
+        for (; tile < tA; tile += RING) {
             step(tile, b0{}, unmasked_t{});
-            step(tile + 1, b1{}, unmasked_t{});
+            step(tile + GROUPS, b1{}, unmasked_t{});
             if constexpr (NBUF >= 3) step(tile + 2, b2{}, unmasked_t{});
             if constexpr (NBUF >= 4) step(tile + 3, b3{}, unmasked_t{});
         }
-        for (; tile < t1; tile += NBUF) {  // the conditions are uniform over the workgroup
+        if (tile < t1) load_mask(tile + grp);
+        for (; tile < t1; tile += RING) {  // the conditions are uniform over the workgroup
             step(tile, b0{}, masked_t{});
-            if (tile + 1 < t1) step(tile + 1, b1{}, masked_t{});
+            if (tile + GROUPS < t1) step(tile + GROUPS, b1{}, masked_t{});
             if constexpr (NBUF >= 3)
                 if (tile + 2 < t1) step(tile + 2, b2{}, masked_t{});
             if constexpr (NBUF >= 4)
@@ -684,22 +754,54 @@ __global__ void __launch_bounds__(256) tree_attn_dma_kernel(int row_blocks, cons
         FS_WAIT_VM_LGKM(0, 0);
     }
 
+    float l[MTW];
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) l[i] = wave_xor_add(wave_xor_add(lrun[i], 16), 32);
+    if constexpr (GROUPS == 2) {
+        // ---- the second group's share joins the first one's, through the tile buffers (all loads into them have landed) ----
+        static_assert(4 * MTW * NHT * 64 * sizeof(f32x4) <= sizeof(tb0), "partial results of a group fit one ring slot");
+        f32x4* po = (f32x4*)tb0 + w * (MTW * NHT * 64) + lane;
+        float2* pml = (float2*)tb1 + w * (MTW * 64) + lane;
+        __syncthreads();
+        if (grp == 1) {
+#pragma unroll
+            for (int i = 0; i < MTW; ++i) {
+#pragma unroll
+                for (int nt = 0; nt < NHT; ++nt) po[(i * NHT + nt) * 64] = acc[i][nt];
+                pml[i * 64] = make_float2(mrun[i], l[i]);
+            }
+        }
+        __syncthreads();
+        if (grp == 1) return;
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) {
+            const float2 o = pml[i * 64];
+            const float mn = fmaxf(mrun[i], o.x);
+            const float w0 = exp2f(mrun[i] - mn), w1 = exp2f(o.x - mn);
+            l[i] = l[i] * w0 + o.y * w1;
+            mrun[i] = mn;
+#pragma unroll
+            for (int nt = 0; nt < NHT; ++nt) acc[i][nt] = acc[i][nt] * w0 + po[(i * NHT + nt) * 64] * w1;
+        }
+    }
     // ---- write out (as tree_attn_kernel) ----
-    const float l = wave_xor_add(wave_xor_add(lrun, 16), 32);
-    if (!rok) return;
-    if (a.n_splits == 1) {
-        const float inv = 1.0f / l;
-        const int qh = kvh * a.G + rho / M;
 #pragma unroll
-        for (int nt = 0; nt < NHT; ++nt)
-            *(typename E::out4_t*)((T*)a.o + frag_major_index<T>(seg_r, qh * HD + nt * 16 + g * 4, a.Hq * HD / KT)) =
-                E::pack4(acc[nt][0] * inv, acc[nt][1] * inv, acc[nt][2] * inv, acc[nt][3] * inv);
-    } else {
-        const size_t prow = ((size_t)split * a.Hkv + kvh) * a.Rpad + a.G * row0 + rho;
-        float* po = a.part_o + prow * HD + g * 4;
+    for (int i = 0; i < MTW; ++i) {
+        if (!rok[i]) continue;
+        if (a.n_splits == 1) {
+            const float inv = 1.0f / l[i];
+            const int qh = kvh * a.G + rho[i] / M;
 #pragma unroll
-        for (int nt = 0; nt < NHT; ++nt) *(f32x4*)(po + nt * 16) = acc[nt];
-        if (g == 0) *(float2*)(a.part_ml + prow * 2) = make_float2(mrun, l);
+            for (int nt = 0; nt < NHT; ++nt)
+                *(typename E::out4_t*)((T*)a.o + frag_major_index<T>(seg_r[i], qh * HD + nt * 16 + g * 4, a.Hq * HD / KT)) =
+                    E::pack4(acc[i][nt][0] * inv, acc[i][nt][1] * inv, acc[i][nt][2] * inv, acc[i][nt][3] * inv);
+        } else {
+            const size_t prow = ((size_t)split * a.Hkv + kvh) * a.Rpad + a.G * row0 + rho[i];
+            float* po = a.part_o + prow * HD + g * 4;
+#pragma unroll
+            for (int nt = 0; nt < NHT; ++nt) *(f32x4*)(po + nt * 16) = acc[i][nt];
+            if (g == 0) *(float2*)(a.part_ml + prow * 2) = make_float2(mrun[i], l[i]);
+        }
     }
 }
 
@@ -717,24 +819,27 @@ template <typename T, int HD>
 static hipError_t launch_hd(const AttnArgs& a, int MTW, int row_blocks, hipStream_t s) {
     const int nw = a.nwc <= 4 ? 4 : 8;  // every wave stages the tiles; the first a.nwc also compute
     dim3 grid(a.n_splits, a.Hkv, row_blocks * a.n_req), block(nw * 64);
+    if constexpr (sizeof(T) == 2 && HD == 128) {
+        if (a.pair) hipLaunchKernelGGL((tree_attn_dma_kernel<2, false, 2, 2>), grid, dim3(512), 0, s, row_blocks, a);
+    }
     // K/V tiles in flight per workgroup (a.nset, chosen by attn_plan): rings of 3 and 4 exist for 16-bit types with 4 waves only
     // (the 32-bit kernels would spill), rings of 2 only with one row tile per wave
     int ring = MTW == 1 ? a.nset : 1;
     if (ring > 2 && (sizeof(T) != 2 || nw != 4)) ring = 2;
     const bool deep = ring >= 2;
-    bool done = false;
+    bool done = a.pair != 0;
     if constexpr (sizeof(T) == 2 && HD == 128) {
-        if (a.dma >= 2 && MTW == 1 && nw == 4) {
+        if (!done && a.dma >= 2 && MTW == 1 && nw == 4) {
             const bool stream = row_blocks == 1;
             if (a.dma >= 4) {
-                if (stream) hipLaunchKernelGGL((tree_attn_dma_kernel<4, true>), grid, block, 0, s, row_blocks, a);
-                else hipLaunchKernelGGL((tree_attn_dma_kernel<4, false>), grid, block, 0, s, row_blocks, a);
+                if (stream) hipLaunchKernelGGL((tree_attn_dma_kernel<4, true, 1, 1>), grid, block, 0, s, row_blocks, a);
+                else hipLaunchKernelGGL((tree_attn_dma_kernel<4, false, 1, 1>), grid, block, 0, s, row_blocks, a);
             } else if (a.dma == 3) {
-                if (stream) hipLaunchKernelGGL((tree_attn_dma_kernel<3, true>), grid, block, 0, s, row_blocks, a);
-                else hipLaunchKernelGGL((tree_attn_dma_kernel<3, false>), grid, block, 0, s, row_blocks, a);
+                if (stream) hipLaunchKernelGGL((tree_attn_dma_kernel<3, true, 1, 1>), grid, block, 0, s, row_blocks, a);
+                else hipLaunchKernelGGL((tree_attn_dma_kernel<3, false, 1, 1>), grid, block, 0, s, row_blocks, a);
             } else {
-                if (stream) hipLaunchKernelGGL((tree_attn_dma_kernel<2, true>), grid, block, 0, s, row_blocks, a);
-                else hipLaunchKernelGGL((tree_attn_dma_kernel<2, false>), grid, block, 0, s, row_blocks, a);
+                if (stream) hipLaunchKernelGGL((tree_attn_dma_kernel<2, true, 1, 1>), grid, block, 0, s, row_blocks, a);
+                else hipLaunchKernelGGL((tree_attn_dma_kernel<2, false, 1, 1>), grid, block, 0, s, row_blocks, a);
             }
             done = true;
         }
@@ -781,7 +886,7 @@ static hipError_t launch_hd(const AttnArgs& a, int MTW, int row_blocks, hipStrea
 }
 
 void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_splits, int wgs_override, int mtw_override, int nset_override,
-               int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma) {
+               int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma, int* pair) {
     const int R = G * M, mtiles = (R + 15) / 16;
     const int BS = attn_tile_slots(elem_bytes, hd);
     const int ntiles = (L + BS - 1) / BS;
@@ -813,13 +918,27 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_spl
     // the direct-to-LDS kernel: 16-bit K/V, head dim 128, at most 4 one-tile waves
     const bool dma_shape = elem_bytes == 2 && hd == 128 && mtiles <= 4;
     int dma_bufs = 0;
-    if (dma_override >= 2 && dma_shape) {
-        dma_bufs = dma_override > 4 ? 4 : dma_override;
+    if (dma_override >= 2 && dma_override <= 4 && dma_shape) {
+        dma_bufs = dma_override;
         mtw = 1;
     }
+    // Tiles in pairs, 128 rows per workgroup (tree_attn_dma_kernel with two groups): from 5 row tiles on, where a context of at
+    // least 12 tiles gives one workgroup per compute unit 4 of them.  us with the merge, tile by tile -> in pairs (tiles to walk per
+    // workgroup in brackets): 32 heads, 1024 rows: 1k context [16] 64 -> 52, 4k 146 -> 108; 700 rows, 1k 59 -> 42; 256 rows, 4k
+    // 62 -> 47; 128 rows, 2k [4.2] 31.6 -> 27.4; 4 heads x 448 rows, 4k [4.1] 26.4 -> 24.5.  Below the line the longer way in and out of
+    // a workgroup shows: 4 heads x 1120 rows, 1k [2.7] 24.1 -> 27.7; 32 heads, 389 rows, 100 slots (8 tiles) [4] 22.6 -> 25.1.
+    const bool pair_shape = elem_bytes == 2 && hd == 128;
+    const bool pairs = pair_shape && (dma_override == 5 || (dma_override == 0 && mtw_override <= 0 && nwc_override <= 0 && nset_override <= 0 &&
+                                                             mtiles > 4 && ntiles >= 12 && (long long)ntiles * Hkv * ((mtiles + 7) / 8) >= 4 * 256));
     if (mtw_override > 0 && !dma_bufs) mtw = (mtw_override >= 2 && mtiles > 1) ? 2 : 1;
     if (wgs_override > 0) target = wgs_override;
-    if (nwc_override > 0) nw_cap = nwc_override < 8 ? nwc_override : 8;
+    if (nwc_override > 0 && !pairs) nw_cap = nwc_override < 8 ? nwc_override : 8;
+    if (pairs) {
+        mtw = 2;
+        nw_cap = 4;
+        if (wgs_override <= 0) target = 256;
+    }
+    *pair = pairs;
     int nw = (mtiles + mtw - 1) / mtw;
     if (nw > nw_cap) nw = nw_cap;
     *NWC = nw;
@@ -828,7 +947,7 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_spl
     const int per_split = Hkv * *row_blocks;  // workgroups per KV split
     int want = (target + per_split - 1) / per_split;
     // one workgroup per compute unit: a handful of workgroups beyond 256 would make a second round of their own
-    if (deep_ring && wgs_override <= 0 && want * per_split > 256 && want > 1) --want;
+    if ((deep_ring || pairs) && wgs_override <= 0 && want * per_split > 256 && want > 1) --want;
     if (want > max_splits) want = max_splits;
     if (want > ntiles) want = ntiles;
     if (want < 1) want = 1;

@@ -27,6 +27,7 @@ struct AttnArgs {
     int nwc;              // compute waves per workgroup (workgroups have at least 4 waves for staging)
     int nset;             // tiles in flight per workgroup for long splits with one row tile per wave (2 .. 4; set by attn_plan)
     int dma;              // >= 2: the direct-to-LDS kernel with that many tile buffers (bf16, head dim 128, one row tile per wave, <= 4 waves)
+    int pair;             // two groups of four waves with two row tiles each take alternate tiles (bf16, head dim 128; nwc <= 4)
     AttnReq req[ATTN_MAX_REQ];  // last: the fields above stay within the first cache lines of the kernel-argument segment
 };
 
@@ -35,7 +36,7 @@ static inline int attn_tile_slots(int elem_bytes, int hd) { return elem_bytes * 
 
 // wgs_override / mtw_override / nset_override > 0 replace the plan's own choice of the workgroup target, of the row tiles per wave and of
 // the K/V tiles in flight per workgroup (tuning knobs); dma_override: 0 = plan's choice, 1 = never the direct-to-LDS kernel, 2 .. 4 = that
-// kernel with so many tile buffers wherever its shape allows
+// kernel with so many tile buffers wherever its shape allows, 5 = its form that takes tiles in pairs
 void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_splits, int wgs_override, int mtw_override, int nset_override,
-               int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma);
+               int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma, int* pair);
 hipError_t launch_attention(int dtype, const AttnArgs& a, int MTW, int row_blocks, hipStream_t s);

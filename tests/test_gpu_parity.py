@@ -127,6 +127,42 @@ def test_long_kv_splits_direct_to_lds(name, cfg, seg, wgs, bufs, monkeypatch):
     _check_stage(cfg.with_(name=f"{name}-{bufs}", seg_len=seg), 5, seg)
 
 
+@pytest.mark.parametrize("name,cfg,seg,wgs,chain", [
+    # the kernel of two wave groups that take alternate K/V tiles, 128 stacked rows per workgroup: even and odd tile counts, one
+    # tile only, splits with and without tiles for the second group, row blocks that straddle query heads, a last block of a
+    # few rows, later segments of a tree (rows that see draft slots of earlier ones), and chains, whose row blocks stop at their
+    # own last slot and whose tiles below the diagonal are seen whole
+    ("pair-13-tiles", SMALL_BF16.with_(l_glo=790, tree_size=40), 16, 4, False),
+    ("pair-12-tiles-two-splits", SMALL_BF16.with_(l_glo=720, tree_size=48), 48, 8, False),
+    ("pair-one-tile", SMALL_BF16.with_(l_glo=3, tree_size=40), 40, None, False),
+    ("pair-mostly-draft-slots", SMALL_BF16.with_(l_glo=8, tree_size=640, max_depth=14), 129, 4, False),
+    ("pair-gqa-blocks-across-heads", SMALL_BF16.with_(n_q_heads=8, n_kv_heads=2, d_model=1024, l_glo=300, tree_size=170), 85, None, False),
+    ("pair-many-splits", SMALL_BF16.with_(l_glo=1000, tree_size=130, max_depth=10), 130, 512, False),
+    ("pair-chain-257", SMALL_BF16.with_(l_glo=77, tree_size=257, max_depth=257), 257, 4, True),
+    ("pair-chain-segments", SMALL_BF16.with_(l_glo=64, tree_size=420, max_depth=420), 200, 16, True),
+    ("pair-chain-gqa", SMALL_BF16.with_(n_q_heads=8, n_kv_heads=2, d_model=1024, l_glo=30, tree_size=190, max_depth=190), 190, None, True),
+    # by the split plan's own rule: 8 KV heads x 8 row blocks x 17 tiles
+    ("pair-by-rule-chain-1024", SMALL_BF16.with_(n_q_heads=8, n_kv_heads=8, d_model=1024, n_layers=1, l_glo=10, tree_size=1024, max_depth=1024), 1024,
+     -1, True),
+])
+def test_tiles_in_pairs(name, cfg, seg, wgs, chain, monkeypatch):
+    from tests.gpu_util import TOL, max_rel_err, row_rel_err
+    if wgs != -1:
+        monkeypatch.setenv("FLOWSPEC_ATTN_DMA", "5")
+    if wgs and wgs > 0:
+        monkeypatch.setenv("FLOWSPEC_ATTN_WGS", str(wgs))
+    cfg = cfg.with_(name=name, seg_len=seg)
+    if not chain:
+        _check_stage(cfg, 5, seg)
+        return
+    print(f"[case] {name}", flush=True)
+    p = _pair(cfg, 5)
+    hid = synth.hidden(cfg, cfg.tree_size, 0, 5)
+    o_out, g_out = p.verify_tree(np.arange(-1, cfg.tree_size - 1, dtype=np.int32), hid, seg)
+    assert np.isfinite(g_out).all()
+    assert max_rel_err(g_out, o_out) < TOL["bf16"] and row_rel_err(g_out, o_out) < 2 * TOL["bf16"]
+
+
 @pytest.mark.parametrize("name,cfg,seg,wgs", [
     # one case per tree-attention variant, each with a context so short (l_glo <= 16) that the draft slots — the part the
     # ancestor mask governs — carry most of the attention weight
@@ -139,6 +175,7 @@ def test_long_kv_splits_direct_to_lds(name, cfg, seg, wgs, bufs, monkeypatch):
     ("mask-gqa-row-blocks", SMALL_BF16.with_(n_q_heads=8, n_kv_heads=2, d_model=1024, l_glo=3, tree_size=200, max_depth=10), 80, None),
     ("mask-gqa-four-wave-row-blocks", SMALL_BF16.with_(n_q_heads=8, n_kv_heads=2, d_model=1024, l_glo=12, tree_size=200, max_depth=10), 48, -4),
     ("mask-direct-to-lds", SMALL_BF16.with_(l_glo=8, tree_size=300, max_depth=12), 16, -100),
+    ("mask-tiles-in-pairs", SMALL_BF16.with_(l_glo=8, tree_size=300, max_depth=12), 150, -200),
 ])
 def test_bf16_comparison_would_notice_a_wrong_mask(name, cfg, seg, wgs, monkeypatch):
     """The bf16 tolerance is wide, so these cases show that the comparison still discriminates: the HIP path's distance
@@ -146,7 +183,9 @@ def test_bf16_comparison_would_notice_a_wrong_mask(name, cfg, seg, wgs, monkeypa
     depths (same positions) but other ancestors."""
     from tests.gpu_util import max_rel_err
     from tests.helpers import make_oracle_stage, reparent_same_depth, verify_whole_tree
-    if wgs == -100:  # the direct-to-LDS kernel, three tile buffers, long splits
+    if wgs == -200:  # tiles in pairs, 128 rows per workgroup
+        monkeypatch.setenv("FLOWSPEC_ATTN_DMA", "5")
+    elif wgs == -100:  # the direct-to-LDS kernel, three tile buffers, long splits
         monkeypatch.setenv("FLOWSPEC_ATTN_DMA", "3")
         monkeypatch.setenv("FLOWSPEC_ATTN_WGS", "4")
     elif wgs and wgs < 0:  # at most -wgs one-tile waves per workgroup: row blocks of four-wave workgroups
