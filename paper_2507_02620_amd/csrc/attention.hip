@@ -18,8 +18,8 @@
 // attn_merge_kernel combines them in a fixed order (deterministic).  (Letting the last workgroup to arrive do
 // the merge was measured and rejected: the device-scope fences it needs write back and invalidate the whole
 // per-XCD L2 once per workgroup, several times the cost of a second launch.)
-// (tree_attn_dma_kernel below is the variant for 16-bit K/V of head dim 128 with at most four row tiles: its tiles go from
-// global memory straight into LDS.)
+// (tree_attn_dma_kernel below is the variant for 16-bit K/V of head dim 128 with at most four row tiles, and for many
+// stacked rows on long contexts: its tiles go from global memory straight into LDS.)
 // All threads of the workgroup (256 or 512) stage a tile together; the next tile's global loads — the next two for long
 // splits — are issued before the current tile is computed, so HBM latency overlaps the MFMA work.  The kernel is bound
 // by that stream: with the arithmetic removed it is only about 7 % faster at a 16k context.
@@ -449,7 +449,7 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
 // group's sums join the first one's through LDS at the end.  Two row tiles per wave halve the LDS bytes per row (32 KiB per wave and
 // tile), and eight waves per compute unit still hide one wave's exponentials behind another's matrix products — without partial
 // results in memory.  Tiles behind the last slot that a row block can see are not walked, and a masked tile that all rows of a wave
-// see whole takes the short form.  The first half of the V fragments is read ahead of the exponentials (54.0 -> 52.0 us); raising
+// see whole takes the short form.  The first half of the V fragments is read ahead of the exponentials (52.6 -> 52.0 us); raising
 // the waves' priority around the matrix products made it 52.6 -> 54.6.  1024 rows, 32 heads, 1k / 4k context:
 // 63.5 / 146 -> 52.0 / 108 us (tree_attn_kernel with one row tile per wave -> this).
 //
@@ -897,7 +897,7 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_spl
     const int ntiles = (L + BS - 1) / BS;
     // up to 8 compute waves per workgroup; with 4 to 16 row tiles every wave takes 2 of them (each K/V fragment read from
     // LDS then serves 32 rows).  Beyond that there are row blocks enough to fill the chip with few or no KV splits, and one
-    // tile per wave is faster (1024-row chunk: 74 -> 65 us, no merge pass).
+    // tile per wave is faster (1024-row chunk: 74 -> 65 us, no merge pass).  Where tiles go in pairs, below, neither holds.
     int mtw = (mtiles >= 4 && mtiles <= 16) ? 2 : 1;
     // about 2 workgroups per CU for long contexts, fewer and longer splits for short ones (latency-bound: C2 256)
     int target = ntiles <= 32 ? 256 : 512;
