@@ -601,8 +601,8 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     }
     if (prep.n) HIP_TRY_K(st, FS_K_PREPARE, s, prep.launch(s));
     int aMTW, aRB;
-    attn_plan(st->elem, hd, max_M, G, d.n_kv_heads * n_live, max_L, kMaxSplits, st->tun.attn_wgs, st->tun.attn_mtw, st->tun.attn_nset, st->tun.attn_nwc,
-              st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma, &at.pair);
+    attn_plan(st->elem, hd, max_M, G, d.n_kv_heads, max_L, at.req, n_live, kMaxSplits, st->tun.attn_wgs, st->tun.attn_mtw, st->tun.attn_nset,
+              st->tun.attn_nwc, st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma, &at.pair);
 
     // 4-bit stages: activations entering a normed projection carry the norm's gain, and the rows' sums of squares
     // travel beside them as partial sums (see GemmArgs::gain_next).  The many-row kernels of dense stages use the same hand-over of

@@ -27,6 +27,7 @@
 
 #include <stdlib.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #ifndef PADK
@@ -890,11 +891,33 @@ static hipError_t launch_hd(const AttnArgs& a, int MTW, int row_blocks, hipStrea
     return e;
 }
 
-void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_splits, int wgs_override, int mtw_override, int nset_override,
-               int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma, int* pair) {
+// KV splits for one workgroup per compute unit: a handful of workgroups beyond 256 would make a second round of their own.
+static int splits_one_round(int per_split, int ntiles) { return std::max(1, std::min(256 / per_split, ntiles)); }
+
+// Whether the requests of a batch are alike enough for the paired form.  Its plan has half the splits of the other one's, counted as if
+// every request were the longest: what the launch then waits for is the longest walk of a workgroup, here in units of a compute unit's
+// share of all tiles that there are to walk.  Up to 1.5 (at most 8 row tiles and more than 32 K/V tiles), 3.5 (9 to 16 row tiles, where
+// the other form has two per wave) or 2.1 (more, where it has as many row blocks) the paired form was the faster one in 113 of
+// 116 batches of 2 to 32 requests, mostly ragged ones, by up to 1.8 times (three slower by 6, 8 and 13 %).  Above, the other one was in 20 of 45, by up to
+// 1.96 times (the paired one in the rest, by up to 1.4; us, other / paired: one 128-row segment behind 8k and fifteen 8-row segments behind 64 slots, 12/2 heads [20] 73 / 143; 18 requests of
+// up to 22 rows behind up to 7.7k, 28/4 heads [3.6] 112 / 138; 16 requests of 1 to 46 rows behind 50 to 3050, 28/4 heads [3.4] 56 / 65;
+// 23 requests of up to 29 rows behind up to 7.4k, 32/8 heads [1.8] 110 / 136).
+static bool pairs_balanced(const AttnReq* req, int n_req, int G, int Hkv1, int BS, int mtiles, int ntiles) {
+    if (n_req == 1) return true;
+    long long walk = 0;
+    for (int i = 0; i < n_req; ++i) walk += (long long)((req[i].L + BS - 1) / BS) * Hkv1 * ((G * req[i].M + 127) / 128);
+    const int splits = splits_one_round(Hkv1 * n_req * ((mtiles + 7) / 8), ntiles);
+    const long long longest = (ntiles + splits - 1) / splits;
+    if (mtiles <= 8) return ntiles <= 32 || longest * 256 * 2 <= walk * 3;
+    return longest * 256 * 10 <= walk * (mtiles <= 16 ? 35 : 21);
+}
+
+void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const AttnReq* req, int n_req, int max_splits, int wgs_override, int mtw_override,
+               int nset_override, int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma, int* pair) {
     const int R = G * M, mtiles = (R + 15) / 16;
     const int BS = attn_tile_slots(elem_bytes, hd);
     const int ntiles = (L + BS - 1) / BS;
+    const int Hkv = Hkv1 * n_req;
     // up to 8 compute waves per workgroup; with 4 to 16 row tiles every wave takes 2 of them (each K/V fragment read from
     // LDS then serves 32 rows).  Beyond that there are row blocks enough to fill the chip with few or no KV splits, and one
     // tile per wave is faster (1024-row chunk: 74 -> 65 us, no merge pass).  Where tiles go in pairs, below, neither holds.
@@ -934,7 +957,8 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_spl
     // a workgroup shows: 4 heads x 1120 rows, 1k [2.7] 24.1 -> 27.7; 32 heads, 389 rows, 100 slots (8 tiles) [4] 22.6 -> 25.1.
     const bool pair_shape = elem_bytes == 2 && hd == 128;
     const bool pairs = pair_shape && (dma_override == 5 || (dma_override == 0 && mtw_override <= 0 && nwc_override <= 0 && nset_override <= 0 &&
-                                                             mtiles > 4 && ntiles >= 12 && (long long)ntiles * Hkv * ((mtiles + 7) / 8) >= 4 * 256));
+                                                             mtiles > 4 && ntiles >= 12 && (long long)ntiles * Hkv * ((mtiles + 7) / 8) >= 4 * 256 &&
+                                                             pairs_balanced(req, n_req, G, Hkv1, BS, mtiles, ntiles)));
     if (mtw_override > 0 && !dma_bufs) mtw = (mtw_override >= 2 && mtiles > 1) ? 2 : 1;
     if (wgs_override > 0) target = wgs_override;
     if (nwc_override > 0 && !pairs) nw_cap = nwc_override < 8 ? nwc_override : 8;
@@ -951,8 +975,7 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv, int L, int max_spl
     *row_blocks = (mtiles + nw * mtw - 1) / (nw * mtw);
     const int per_split = Hkv * *row_blocks;  // workgroups per KV split
     int want = (target + per_split - 1) / per_split;
-    // one workgroup per compute unit: a handful of workgroups beyond 256 would make a second round of their own
-    if ((deep_ring || pairs) && wgs_override <= 0 && want * per_split > 256 && want > 1) --want;
+    if ((deep_ring || pairs) && wgs_override <= 0) want = splits_one_round(per_split, ntiles);
     if (want > max_splits) want = max_splits;
     if (want > ntiles) want = ntiles;
     if (want < 1) want = 1;

@@ -175,3 +175,30 @@ def test_batch_packs_trees_of_all_sizes_into_launches():
     for kv, orc, l_glo, seg_off, l_s in caches:
         rows = slice(l_glo + seg_off, l_glo + seg_off + l_s)
         assert max_rel_err(kv[0][:, :, rows].cpu().numpy(), orc.kv[0][:, :, rows]) < TOL["f32"]
+
+
+@pytest.mark.parametrize("name,hq,hkv,specs,knob", [
+    # requests of one row, of 17 rows and of several row blocks in one launch: row blocks and KV splits that the shorter ones do not have,
+    # contexts from nothing to 2k, a chain among the trees, segments behind earlier ones
+    ("pair-ragged", 4, 4, [(700, 150, 9, 3, 7, 140), (0, 18, 5, 3, 1, 17), (2000, 30, 6, 3, 29, 1), (5, 300, 300, 1, 30, 129)], "5"),
+    ("pair-ragged-gqa", 8, 2, [(90, 20, 5, 3, 19, 1), (1500, 60, 7, 3, 20, 40), (64, 17, 4, 3, 0, 17), (333, 33, 33, 1, 0, 33)], "5"),
+    # by the split plan's own rule: 10 splits, of which the short request fills one
+    ("pair-by-rule-ragged", 16, 2, [(6000, 48, 6, 3, 8, 40), (100, 20, 5, 3, 19, 1), (5500, 41, 41, 1, 1, 40), (3000, 40, 6, 3, 0, 17)], None),
+])
+def test_tiles_in_pairs_over_a_ragged_batch(name, hq, hkv, specs, knob, monkeypatch):
+    from tests.gpu_util import TOL, max_rel_err
+    if knob:
+        monkeypatch.setenv("FLOWSPEC_ATTN_DMA", knob)
+    cfg = synth.StageConfig(name, "bf16", 1, 512, hq, hkv, 128, 512, 0, max(s[0] for s in specs), max(s[1] for s in specs),
+                            max(sum(s[5] for s in specs), max(s[4] for s in specs)), 6, 3)
+    print(f"[case] batch {name}: {len(specs)} requests, {sum(s[5] for s in specs)} stacked rows", flush=True)
+    got, want, caches, cfg = _run_batch(cfg, specs, seed=33)
+    row = 0
+    for r, w in enumerate(want):
+        err = max_rel_err(got[row:row + w.shape[0]], w)
+        print(f"  request {r}: {w.shape[0]} rows, hidden max-rel-err {err:.3e}", flush=True)
+        assert err < TOL["bf16"]
+        row += w.shape[0]
+    for kv, orc, l_glo, seg_off, l_s in caches:
+        rows = slice(l_glo + seg_off, l_glo + seg_off + l_s)
+        assert max_rel_err(kv[0][:, :, rows].float().cpu().numpy(), orc.kv[0][:, :, rows]) < TOL["bf16"]
