@@ -615,7 +615,8 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     float* sspa = st->at<float>(L.off_sspa);
     float* sspb = st->at<float>(L.off_sspb);
     // partial sums per row a residual epilogue leaves
-    const int res_parts = wide ? wide_ssp_parts(l_s, d.d_model / 16) : w4_ssp_parts(l_s, L.layers[0].o.n_groups * L.layers[0].o.NT);
+    auto res_parts = [&](const GemmPlan& p) { return wide ? wide_ssp_parts(l_s, d.d_model / 16) : w4_ssp_parts(l_s, p.n_groups * p.NT, p.nkt); };
+    const int o_parts = res_parts(L.layers[0].o), down_parts = res_parts(L.layers[0].down);
     int ssp_n_first = 0;
     // (row-major input costs the streaming kernel 64-byte pieces of 16 rows per load; from 33 rows on one conversion pass is cheaper)
     const bool to_frag = handover || (route == ROUTE_STREAM && l_s > 32);
@@ -633,7 +634,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
         g.eps = d.rms_eps; g.bias = p.qkv.bias; g.rope = rope; g.q_out = q; g.krow = krow; g.layer_off = layer_off;
         g.stride_kv = kv0->stride_kv; g.stride_head = kv0->stride_head;
         g.Hq = d.n_q_heads; g.Hkv = d.n_kv_heads; g.hd = hd;
-        g.ssp_in = sspa; g.ssp_n = first ? ssp_n_first : res_parts; g.ssp_stride = L.ssp_stride;
+        g.ssp_in = sspa; g.ssp_n = first ? ssp_n_first : down_parts; g.ssp_stride = L.ssp_stride;
         HIP_TRY_K(st, FS_K_QKV, s, launch_proj(st, EPI_QKV, p.qkv, g, s, route));
         // tree attention
         at.layer_off = layer_off;
@@ -650,7 +651,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
         g = GemmArgs{};
         g.X = hb; g.x_frag = 1; g.ldx = d.d_model; g.M = l_s; g.K = p.gu.K; g.nkt = p.gu.nkt; g.N = 2 * p.gu.N; g.Wp = p.gu.wp; g.eps = d.rms_eps;
         g.act_out = act; g.F = d.d_ffn;
-        g.ssp_in = sspb; g.ssp_n = res_parts; g.ssp_stride = L.ssp_stride;
+        g.ssp_in = sspb; g.ssp_n = o_parts; g.ssp_stride = L.ssp_stride;
         HIP_TRY_K(st, FS_K_GATEUP, s, launch_proj(st, EPI_SWIGLU, p.gu, g, s, route));
         // down projection + residual
         g = GemmArgs{};
@@ -719,7 +720,8 @@ int fs_tree_logits(fs_stage* st, const void* hidden, int l_s, float* logits, int
     GemmArgs g{};
     g.X = hidden; g.ldx = st->d.d_model; g.M = l_s; g.K = p.K; g.nkt = p.nkt; g.N = p.N; g.Wp = p.wp; g.eps = st->d.rms_eps; g.logits = logits;
     Route route = route_of(st, l_s);
-    if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, p.n_groups * p.NT, p.nkt)) route = ROUTE_WIDE;
+    const int tiles = p.n_groups * p.NT;
+    if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, tiles, p.nkt)) route = wide_fits(p.NT, tiles, l_s, p.nkt) ? ROUTE_WIDE : ROUTE_FEW;
     if (p.w4 || route == ROUTE_WIDE) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
         void* hb = st->at<void>(st->L.off_hb);
         float* ssp = st->at<float>(st->L.off_sspa);

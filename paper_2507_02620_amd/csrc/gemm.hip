@@ -1191,11 +1191,13 @@ static int block_gemm_width(int mode, int epi, int M, int n_tiles) {  // mode 0 
     return 0;
 }
 
+// the kernels address weights and activations with 32-bit byte offsets from their bases
+bool wide_fits(int layout_nt, int n_tiles, int M, int nkt) {
+    return (unsigned long long)(n_tiles + layout_nt) * nkt * 1024ull < (1ull << 32) && (unsigned long long)(M + 16) * nkt * 64ull < (1ull << 32);
+}
+
 hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, int block_mode, hipStream_t s) {
-    if (!a.x_frag) return hipErrorInvalidValue;
-    // the kernel addresses weights and activations with 32-bit byte offsets from their bases
-    if ((unsigned long long)(n_tiles + layout_nt) * a.nkt * 1024ull >= (1ull << 32) || (unsigned long long)(a.M + 16) * a.nkt * 64ull >= (1ull << 32))
-        return hipErrorInvalidValue;
+    if (!a.x_frag || !wide_fits(layout_nt, n_tiles, a.M, a.nkt)) return hipErrorInvalidValue;
     const WideShape sh = wide_shape(epi, a.M);
     const bool narrow = sh.wnt == 2, half = sh.bmt == 4;
     const int bw = (!narrow && !half) ? block_gemm_width(block_mode, epi, a.M, n_tiles) : 0;
@@ -1276,7 +1278,7 @@ static int stream_width(int epi, int M, int n_tiles, int nkt) {
 }
 
 // Whether a projection takes this kernel at 17 to 128 rows (else: the few-row kernel, the LM head the kernel with blocks in
-// registers).  Measured, this kernel / the other one, us:
+// registers).  Its offsets from the operands' bases have 32 bits: matrices of 4 GiB and more stay with the few-row kernel.  Measured, this kernel / the other one, us:
 //   * LM head: while its blocks run in one round (32000 rows x 4096: 64 rows 50 / 49 + 5 for the conversion pass the other one needs);
 //     with many rounds several workgroups per compute unit hide each other's ends (152064 x 3584, 64 rows: 242 / 220 + 5).
 //   * QKV of few heads (288 tiles, 72 blocks): from 65 rows on (80 rows 34 / 43, but 48 rows 23.4 / 21.6).
@@ -1284,7 +1286,9 @@ static int stream_width(int epi, int M, int n_tiles, int nkt) {
 //   * attention output up to 32 rows with at most one few-row workgroup per compute unit: the second launch that adds the K slices
 //     costs more than it gives while K is short (4096 x 4096: 15 / 13; but 5120 x 5120 with its 320 tiles 15.4 / 18.4, and
 //     4096 x 11008 21.1 / 28).
+static bool stream_fits(int n_tiles, int nkt) { return (unsigned long long)(n_tiles + 8) * nkt * 1024ull < (1ull << 32); }
 bool stream_pays(int epi, int M, int n_tiles, int nkt) {
+    if (!stream_fits(n_tiles, nkt)) return false;
     if (epi == EPI_LOGITS) return M <= 64 && (n_tiles + 7) / 8 <= 256;
     if (epi == EPI_QKV) return M > 64 || n_tiles >= 512;
     if (epi == EPI_RESID) return M > 32 || n_tiles > 256 || nkt > 128;
@@ -1310,8 +1314,7 @@ static hipError_t launch_stream_epi(int layout_nt, int n_tiles, const GemmArgs& 
 }
 
 hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
-    // 32-bit byte offsets from the operands' bases
-    if ((unsigned long long)(n_tiles + 8) * a.nkt * 1024ull >= (1ull << 32) || a.M > 128) return hipErrorInvalidValue;
+    if (!stream_fits(n_tiles, a.nkt) || a.M > 128) return hipErrorInvalidValue;
     switch (epi) {
         case EPI_QKV: return launch_stream_epi<EPI_QKV>(layout_nt, n_tiles, a, part, part_bytes, s);
         case EPI_RESID: return launch_stream_epi<EPI_RESID>(layout_nt, n_tiles, a, part, part_bytes, s);
@@ -1742,14 +1745,18 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
 // 128 rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 64 rows 51 / 60, 128 rows
 // 101 / 89.  Residual projections (two tiles per workgroup there, K slices here): 4096 x 4096, 128 rows 18 / 25, 200 rows 30 / 28;
 // 13824 x 5120, 64 rows 42 / 32; 5120 x 5120, 65 rows 23 / 26.
-static bool block_w4_pays(int epi, int M, int n_tiles) {
-    if (M <= 32) return false;
+// Its offsets from the operands' bases have 32 bits: 4 GiB of codes and more stay with the few-row kernel.
+static bool block_w4_fits(int M, int n_tiles, int nkt) {
+    return (unsigned long long)(n_tiles + 16) * nkt * 256ull < (1ull << 32) && (unsigned long long)(M + 16) * nkt * 64ull < (1ull << 32);
+}
+static bool block_w4_pays(int epi, int M, int n_tiles, int nkt) {
+    if (M <= 32 || !block_w4_fits(M, n_tiles, nkt)) return false;
     const int work = n_tiles * ((M + 31) / 32), rounds = ((n_tiles + 15) / 16 * ((M + 127) / 128) + 255) / 256;
     if (epi == EPI_RESID) return work > (M <= 64 ? 600 : 1100);
     return work > (M <= 64 ? 4200 : 6000) * rounds;
 }
 
-int w4_ssp_parts(int M, int n_tiles) { return block_w4_pays(EPI_RESID, M, n_tiles) ? (n_tiles + 15) / 16 : n_tiles; }
+int w4_ssp_parts(int M, int n_tiles, int nkt) { return block_w4_pays(EPI_RESID, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles; }
 
 template <int EPI, int WM, int WN, int MT, int NT, int R>
 static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
@@ -1775,8 +1782,7 @@ static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a,
 }
 
 static hipError_t launch_block_w4(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
-    if (!a.x_frag || (unsigned long long)(n_tiles + 16) * a.nkt * 256ull >= (1ull << 32) || (unsigned long long)(a.M + 16) * a.nkt * 64ull >= (1ull << 32))
-        return hipErrorInvalidValue;
+    if (!a.x_frag || !block_w4_fits(a.M, n_tiles, a.nkt)) return hipErrorInvalidValue;
 #define FS_W4(e)                                                                                              \
     if (epi == e) {                                                                                           \
         if (a.M <= 64) return launch_w4_shape<e, 1, 8, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);  \
@@ -1788,7 +1794,7 @@ static hipError_t launch_block_w4(int epi, int layout_nt, int n_tiles, const Gem
 }
 
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a0, float* part, size_t part_bytes, hipStream_t s) {
-    if (block_w4_pays(epi, a0.M, n_groups * NT)) return launch_block_w4(epi, NT, n_groups * NT, a0, part, part_bytes, s);
+    if (block_w4_pays(epi, a0.M, n_groups * NT, a0.nkt)) return launch_block_w4(epi, NT, n_groups * NT, a0, part, part_bytes, s);
     // at most 32 rows per workgroup (register budget); longer segments take further row blocks, whose passes over
     // the quarter-size weights mostly hit in L2
     GemmArgs a = a0;

@@ -84,8 +84,8 @@ void launch_pack_w4(const PackW4Args& a, hipStream_t s);
 hipError_t launch_prenorm(const void* X, int ldx, int M, int K, const void* gain, void* xg, float* ssp, int ssp_stride, int* n_slices,
                              hipStream_t s);
 // 4-bit weights, bf16 activations (fragment-major, with their sums of squares): w[n][k] = scale[n][k/128] * (code - 8).  A residual
-// projection leaves w4_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
-int w4_ssp_parts(int M, int n_tiles);
+// projection leaves w4_ssp_parts(M, n_tiles, nkt) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
+int w4_ssp_parts(int M, int n_tiles, int nkt);
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
 // bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block up to 64 rows).  layout_nt and n_tiles
 // describe the re-tiled weights (tiles per group, 16-feature tiles in total); normed projections need ssp_in from 384 rows on
@@ -95,6 +95,8 @@ hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs&
 // projection leaves wide_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out.
 int wide_ssp_parts(int M, int n_tiles);
 size_t wide_partial_bytes(int max_rows, int n_tiles);
+// wide_fits: whether its 32-bit offsets reach all of the operands.
+bool wide_fits(int layout_nt, int n_tiles, int M, int nkt);
 // block_mode: 0 never / 1 whenever possible / anything else: by rule — use of the 256-row kernel (both operands through LDS) from 384 rows on
 hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, int block_mode, hipStream_t s);
 // bf16, 17 to 128 rows, row-major or fragment-major activations: the kernel that streams both operands through LDS; normed projections
