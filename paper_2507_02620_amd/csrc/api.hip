@@ -721,7 +721,8 @@ int fs_tree_logits(fs_stage* st, const void* hidden, int l_s, float* logits, int
     g.X = hidden; g.ldx = st->d.d_model; g.M = l_s; g.K = p.K; g.nkt = p.nkt; g.N = p.N; g.Wp = p.wp; g.eps = st->d.rms_eps; g.logits = logits;
     Route route = route_of(st, l_s);
     const int tiles = p.n_groups * p.NT;
-    if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, tiles, p.nkt)) route = wide_fits(p.NT, tiles, l_s, p.nkt) ? ROUTE_WIDE : ROUTE_FEW;
+    if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, tiles, p.nkt))
+        route = head_few_rows(l_s, tiles, p.nkt) || !wide_fits(p.NT, tiles, l_s, p.nkt) ? ROUTE_FEW : ROUTE_WIDE;
     if (p.w4 || route == ROUTE_WIDE) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
         void* hb = st->at<void>(st->L.off_hb);
         float* ssp = st->at<float>(st->L.off_sspa);

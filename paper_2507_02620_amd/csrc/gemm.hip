@@ -1295,6 +1295,16 @@ bool stream_pays(int epi, int M, int n_tiles, int nkt) {
     return M > 32 || (n_tiles + 7) / 8 <= 256;
 }
 
+// LM head of 17 to 128 rows that the kernel above does not take: the kernel with blocks in registers has one 64-row block per 128
+// features, a good launch if they all run at once or in many rounds, not if a few compute units get a second one.  Few-row kernel
+// instead (us, blocks in registers / few-row) for 257 to 384 blocks up to 40 rows (33024 x 4096: 17 rows 74.7 / 60.9, 32 rows 75.6 / 67.3,
+// 40 rows 2 % more, 48 rows 3 % less) and for 385 to 511 up to 24, with a short K up to 32 (50257 x 4096: 17 rows 85.7 / 84.6, 32 rows
+// 85 / 93; x 1024: 17 rows 33.2 / 29.8, 32 rows 35.5 / 35.8; 61440 x 1024, 28 rows 38.2 / 36.3).
+bool head_few_rows(int M, int n_tiles, int nkt) {
+    const int blocks = (n_tiles + 7) / 8;
+    return blocks > 256 && blocks < 512 && M <= (blocks <= 384 ? 40 : nkt <= 64 ? 32 : 24);
+}
+
 template <int EPI>
 static hipError_t launch_stream_epi(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
     const int bn = stream_width(EPI, a.M, n_tiles, a.nkt);

@@ -103,6 +103,7 @@ hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs&
 // work out their own row scale, residual projections leave no sums of squares.  `part` as for launch_gemm_wide.  stream_pays: whether it
 // is the faster choice for a projection.
 bool stream_pays(int epi, int M, int n_tiles, int nkt);
+bool head_few_rows(int M, int n_tiles, int nkt);  // an LM head that it does not take: few-row kernel, else launch_gemm_wide
 hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
 // MT = ceil(M/16) in {1,2,4}, NT in {1,2,4} (even for QKV / SWIGLU), waves per workgroup NW
 hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const GemmArgs& a, hipStream_t s);

@@ -38,3 +38,19 @@ def test_logits_and_argmax(cfg, rows):
     # elsewhere the chosen entry must be within the bound of the oracle's maximum
     for r in np.nonzero(~clear)[0]:
         assert o_lg[r, g_am[r]] >= top2[r, 1] - 2 * TOL[cfg.dtype] * np.abs(o_lg).max()
+
+
+@pytest.mark.parametrize("vocab,rows", [(32768, 33), (32769, 40), (32769, 41), (49152, 17), (49153, 32), (49153, 33), (65408, 24), (65409, 17)])
+def test_head_of_17_to_48_rows_at_the_edges_of_its_routes(vocab, rows):
+    """256, 257, 384, 385, 511 and 512 blocks of 128 features, rows on both sides of the line between two kernels."""
+    import torch
+    from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
+    cfg = synth.StageConfig(f"lg-{vocab}", "bf16", 1, 256, 2, 2, 128, 256, vocab, 8, 16, rows, 4, 3)
+    print(f"[case] {cfg.name} rows={rows}", flush=True)
+    p = Pair(cfg, 3, head=True)
+    hid = synth.hidden(cfg, rows, 7, 3)
+    o_lg, _ = p.orc.logits(hid.astype(np.float64))
+    g_lg, g_am = p.gpu.tree_logits(to_dev(hid, torch.bfloat16))
+    g_lg, g_am = g_lg.cpu().numpy(), g_am.cpu().numpy()
+    assert max_rel_err(g_lg, o_lg) < TOL["bf16"]
+    assert np.array_equal(g_am, np.argmax(g_lg, axis=1))
