@@ -160,7 +160,7 @@ int fs_last_hip_error(void);
  *   K/V of row r stored at slot l_cache + r -> tree attention (row r sees every slot < l_glo and the draft
  *   slots l_glo + j with j an ancestor-or-self of node seg_off + r) -> output projection + residual ->
  *   RMSNorm -> SwiGLU feed-forward + residual.
- *   hidden_in / hidden_out  device [l_s, d_model], may alias
+ *   hidden_in / hidden_out  device [l_s, d_model], may alias; aligned to their element type (here and in the entry points below)
  *   parent                  HOST [seg_off + l_s], S order, parent[0] == -1 (further roots allowed: such a node
  *                           sees the context and itself only); read before the call returns
  * Precondition: l_cache == l_glo + seg_off.  l_s == 0 is a valid no-op.

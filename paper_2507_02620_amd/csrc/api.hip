@@ -503,6 +503,10 @@ static Route route_of(const fs_stage* st, int rows) {
     return rows < st->tun.mid_rows ? ROUTE_FEW : ROUTE_STREAM;
 }
 
+// Rows of the caller may begin at any element; the streaming kernel's direct-to-LDS loads want their 16 bytes aligned (the plain vector
+// loads of the other kernels and of the conversion pass do not).
+static bool lds_loadable(const void* rows) { return ((uintptr_t)rows & 15) == 0; }
+
 static hipError_t launch_proj(const fs_stage* st, int epi, const GemmPlan& p, GemmArgs& g, hipStream_t s, Route route) {
     float* part = st->at<float>(st->L.off_part);
     const int tiles = p.n_groups * p.NT;
@@ -619,7 +623,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     const int o_parts = res_parts(L.layers[0].o), down_parts = res_parts(L.layers[0].down);
     int ssp_n_first = 0;
     // (row-major input costs the streaming kernel 64-byte pieces of 16 rows per load; from 33 rows on one conversion pass is cheaper)
-    const bool to_frag = handover || (route == ROUTE_STREAM && l_s > 32);
+    const bool to_frag = handover || (route == ROUTE_STREAM && (l_s > 32 || !lds_loadable(hidden_in)));
     if (to_frag)
         HIP_TRY_K(st, FS_K_PREPARE, s,
                   launch_prenorm(hidden_in, d.d_model, l_s, d.d_model, w4 ? gains : nullptr, hb, sspa, L.ssp_stride, &ssp_n_first, s));
@@ -723,7 +727,7 @@ int fs_tree_logits(fs_stage* st, const void* hidden, int l_s, float* logits, int
     const int tiles = p.n_groups * p.NT;
     if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, tiles, p.nkt))
         route = head_few_rows(l_s, tiles, p.nkt) || !wide_fits(p.NT, tiles, l_s, p.nkt) ? ROUTE_FEW : ROUTE_WIDE;
-    if (p.w4 || route == ROUTE_WIDE) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
+    if (p.w4 || route == ROUTE_WIDE || (route == ROUTE_STREAM && !lds_loadable(hidden))) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
         void* hb = st->at<void>(st->L.off_hb);
         float* ssp = st->at<float>(st->L.off_sspa);
         const bf16_t* gain = p.w4 ? st->at<bf16_t>(st->L.off_gain) + (size_t)(2 * st->d.n_layers) * st->d.d_model : nullptr;

@@ -116,3 +116,31 @@ def test_error_codes_with_a_live_stage():
     y = p.gpu.tree_verify_stage(p.kv, cfg.l_glo, cfg.l_glo, x, 0, par[:16])
     torch.cuda.synchronize()
     assert torch.isfinite(y.float()).all()
+
+
+@pytest.mark.parametrize("rows", [16, 17, 32, 33, 64, 129])
+@pytest.mark.parametrize("shift", [1, 4])
+def test_hidden_rows_aligned_to_their_elements_only(rows, shift):
+    """hidden_in, hidden_out and the head's input at `shift` elements behind a 16-byte boundary, against the same rows on one
+    (other kernels may take the first projection: equal up to the order of sums and the bf16 rounding behind it)."""
+    import torch
+    from tests.gpu_util import TOL, max_rel_err, to_dev
+    cfg = BASE.with_(tree_size=rows, seg_len=rows, l_glo=20, vocab=1000, n_q_heads=32, n_kv_heads=32)
+    print(f"[case] rows={rows} shift={shift}", flush=True)
+    p = _pair(cfg, 9, head=True)
+    tree = synth.config_tree(cfg, 9)
+    hid = to_dev(synth.hidden(cfg, rows, 0, 9), torch.bfloat16)
+
+    def at(shift):
+        buf = torch.zeros(rows * cfg.d_model + 16, dtype=torch.bfloat16, device="cuda")
+        return buf[shift:shift + rows * cfg.d_model].view(rows, cfg.d_model)
+
+    x, y = at(shift), at(shift)
+    assert x.data_ptr() % 16 == 2 * shift
+    x.copy_(hid)
+    p.gpu.tree_verify_stage(p.kv, cfg.l_glo, cfg.l_glo, x, 0, tree.parent, y)
+    lg, am = p.gpu.tree_logits(x)
+    ref = p.gpu.tree_verify_stage(p.kv, cfg.l_glo, cfg.l_glo, hid, 0, tree.parent)
+    ref_lg, _ = p.gpu.tree_logits(hid)
+    assert max_rel_err(y.float().cpu().numpy(), ref.float().cpu().numpy()) < TOL["bf16"] / 4
+    assert max_rel_err(lg.cpu().numpy(), ref_lg.cpu().numpy()) < TOL["bf16"] / 4
