@@ -105,3 +105,27 @@ def test_sampled_accept_row_chunks_and_residual(vocab, T, n_ver, n_child):
         assert np.array_equal(g_ret, o_ret)
         seen.add(o_res.n_acc)
     assert len(seen) > 1                       # accepted and rejected candidates both occurred
+
+
+@pytest.mark.parametrize("n_child", [0, 3, 7, 8, 40])
+@pytest.mark.parametrize("vocab", [1, 63, 64, 65, 255, 256, 257, 1024, 1025, 4096, 4100])
+def test_sampled_accept_at_the_ends_of_the_passes(vocab, n_child):
+    """Vocabularies and parts of 64 and 256 entries on either side of a pass of the residual draw, few and many rejected tokens, child
+    counts that are no multiple of four; all weight on the first or the last entries in some rows."""
+    rng = np.random.default_rng(vocab * 50 + n_child)
+    T = n_child + 1
+    parent = np.array([-1] + [0] * n_child, dtype=np.int32)
+    token = rng.integers(0, vocab, T).astype(np.int32)
+    print(f"[case] vocab={vocab} children={n_child}", flush=True)
+    for step in range(6):
+        lg = (rng.standard_normal((1, vocab)) * 2).astype(np.float32)
+        if step == 1:
+            lg[0, :-1] = -np.inf
+        if step == 2:
+            lg[0, 1:] -= 30.0
+        if step >= 3:
+            lg[0, token[1:]] -= 4.0            # candidates that are mostly struck
+        o_res, o_ret = oracle.accept_sample(lg, 1.0, token, parent, 1, 31, step)
+        g_res, g_ret = _gpu(lg, 1.0, token, parent, 1, 31, step)
+        assert g_res == o_res.as_tuple(), (step, g_res, o_res.as_tuple())
+        assert np.array_equal(g_ret, o_ret)
