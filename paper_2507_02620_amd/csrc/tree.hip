@@ -21,6 +21,9 @@ hipError_t launch_rope_freq(double* inv_freq, int hd, float theta, hipStream_t s
 // Grid (16-row slice of a segment, request): latency is all it costs, so the requests of a batch share a launch and the slices of a
 // segment run side by side (two 7B layers for 32 requests of 16 rows, one launch each / one for all: 813 / 656 us; 9 requests
 // 387 / 355 us; a single 64-row segment 467 / 464 us).
+// The walk sets its bits in LDS by atomics without a result, one step behind the other at the latency of the parent link alone, and in
+// code that is short: a launch that starts cold pays for every instruction line (16 rows of a 64-node tree, mask words in
+// registers 4.4, updates of as many words as the tree has 4.4 - 4.6, in LDS 3.0 us; a chain of 32 9.0 -> 4.6).
 #define PREP_ROWS 16
 __global__ void __launch_bounds__(256) tree_prepare_kernel(const PrepArgs a) {
     const PrepReq q = a.req[blockIdx.y];
@@ -28,7 +31,11 @@ __global__ void __launch_bounds__(256) tree_prepare_kernel(const PrepArgs a) {
     if (rows <= 0) return;
     __shared__ short par[1024];
     __shared__ int pos[PREP_ROWS];
+    __shared__ unsigned long long mask[PREP_ROWS][FS_ANC_WORDS + 1];  // an odd stride: the rows' words in banks of their own
     const int T = q.seg_off + r0 + rows;  // nodes up to the slice's last one
+    const int mr = threadIdx.x / FS_ANC_WORDS, mw = threadIdx.x % FS_ANC_WORDS;
+    static_assert(PREP_ROWS * FS_ANC_WORDS == 256, "one mask word per thread");
+    mask[mr][mw] = 0;
     for (int i = threadIdx.x; i < T; i += blockDim.x) {
         const int p = a.wide ? (int)((const unsigned short*)a.par)[q.par0 + i] : (int)a.par[q.par0 + i];
         par[i] = (short)(p == i ? -1 : p);
@@ -36,23 +43,17 @@ __global__ void __launch_bounds__(256) tree_prepare_kernel(const PrepArgs a) {
     __syncthreads();
     if (threadIdx.x < rows) {
         const int r = r0 + threadIdx.x;
-        uint64_t m[FS_ANC_WORDS];
-#pragma unroll
-        for (int w = 0; w < FS_ANC_WORDS; ++w) m[w] = 0;
         int depth = -1;
         // parent[i] < i was checked on the host, so the walk ends after at most T steps
         for (int j = q.seg_off + r; j >= 0; j = par[j]) {
-#pragma unroll
-            for (int w = 0; w < FS_ANC_WORDS; ++w)
-                if (w == (j >> 6)) m[w] |= 1ull << (j & 63);
+            atomicOr(&mask[threadIdx.x][j >> 6], 1ull << (j & 63));  // no result: nothing waits for it
             ++depth;
         }
-#pragma unroll
-        for (int w = 0; w < FS_ANC_WORDS; ++w) a.anc[(size_t)(q.row0 + r) * FS_ANC_WORDS + w] = m[w];
         pos[threadIdx.x] = q.l_glo + depth;
         a.krow[q.row0 + r] = q.base + (unsigned long long)(q.slot0 + r) * a.tok_bytes;
     }
     __syncthreads();
+    if (mr < rows) a.anc[(size_t)(q.row0 + r0 + mr) * FS_ANC_WORDS + mw] = mask[mr][mw];
     const int half = a.hd >> 1;
     for (int i = threadIdx.x; i < rows * half; i += blockDim.x) {
         const int r = i / half, t = i % half;

@@ -42,7 +42,7 @@ struct PrepArgs {
     unsigned long long tok_bytes;
     int hd, wide;              // parent entries of 16 bits, else of 8 (trees of at most 256 nodes); a root's entry is its own index
     PrepReq req[PREP_MAX_REQ];
-    unsigned char par[PREP_BYTES];
+    alignas(2) unsigned char par[PREP_BYTES];
 };
 // Collects requests into launches.
 struct PrepBatch {

@@ -108,3 +108,34 @@ def test_deep_tree_as_one_item_of_a_batch():
         assert max_rel_err(got, want) < TOL["f32"]
         L = lg + len(par)
         assert max_rel_err(kv[:, :, :, lg:L].cpu().numpy(), orc.kv[:, :, :, lg:L]) < TOL["f32"]
+
+
+@pytest.mark.parametrize("T,seg", [(1, 1), (16, 15), (33, 17), (64, 64), (65, 33), (256, 16), (257, 48), (1024, 1000)])
+@pytest.mark.parametrize("kind", ["tree", "forest", "levels"])
+def test_short_tree_masks_bit_exact(T, seg, kind):
+    """The walk of a tree of at most 32 levels: 16-row slices and their remainders, the ends of mask words, byte and 16-bit parent
+    entries, further roots, and a tree whose every node lies as deep as this kernel takes it (32 levels below the root)."""
+    from oracle import oracle
+    from tests.gpu_util import Pair
+    if kind == "levels":
+        parent = np.array([i - 1 if i < 33 else 32 * (i // 32) - 1 - (i % 3) for i in range(T)], dtype=np.int32)
+        depth = np.zeros(T, dtype=np.int64)
+        for i in range(1, T):
+            parent[i] = parent[i] if depth[parent[i]] < 32 else 31
+            depth[i] = depth[parent[i]] + 1
+        assert depth.max() == min(T - 1, 32)
+    else:
+        parent = synth.random_tree(T, 9, 4, 32000, 3, forest=kind == "forest").parent
+    cfg = BASE.with_(l_glo=5, seg_len=seg)
+    print(f"[case] mask {kind} T={T} seg={seg}", flush=True)
+    p = Pair(cfg, 1, max_tree=T, max_seg=seg)
+    anc_o, depth_o = oracle.tree_ancestors(parent)
+    want = _mask_bits(anc_o)[:, :T]
+    inv_freq = cfg.rope_theta ** (-2.0 * np.arange(cfg.head_dim // 2) / cfg.head_dim)
+    for off, n in synth.segments(T, seg):
+        anc, rope = p.gpu.tree_mask(cfg.l_glo, off, n, parent[: off + n])
+        got = _mask_bits(anc.cpu().numpy())
+        assert (got[:, :T] == want[off:off + n]).all() and not got[:, T:].any(), off
+        ang = (cfg.l_glo + depth_o[off:off + n, None]) * inv_freq[None, :]
+        r = rope.cpu().numpy().astype(np.float64)
+        assert np.abs(r[:, :, 0] - np.cos(ang)).max() < 2e-6 and np.abs(r[:, :, 1] - np.sin(ang)).max() < 2e-6
