@@ -19,10 +19,10 @@ def _chain(n):
     (synth.StageConfig("pf-bf16-1024", "bf16", 1, 512, 4, 4, 128, 1024, 0, 0, 1024, 1024, 1024, 1), 1024),
     # feature counts that are not multiples of a workgroup's 256 features: padding tiles in every epilogue and in the K-split fix-up
     (synth.StageConfig("pf-bf16-odd-widths", "bf16", 2, 480, 6, 3, 64, 1056, 0, 33, 150, 150, 150, 1, qkv_bias=True), 150),
-    # one partly filled row block of the many-row kernel (65 .. 127 rows), K slices for the residual projections
+    # 65 .. 127 rows: the kernel that streams weights and activations through LDS, K slices for the residual projections
     (synth.StageConfig("pf-bf16-96", "bf16", 2, 1024, 8, 8, 128, 2816, 0, 60, 96, 96, 96, 1), 96),
     (synth.StageConfig("pf-bf16-81-gqa", "bf16", 2, 512, 8, 2, 64, 1408, 0, 100, 81, 81, 81, 1, qkv_bias=True), 81),
-    # 17 .. 64 rows: gate/up and down projection through one 64-row block, the rest through the few-row kernel
+    # 17 .. 64 rows: the same kernel with 64-row and 32-row blocks, QKV (few tiles) through the few-row kernel
     (synth.StageConfig("pf-bf16-50", "bf16", 2, 1024, 8, 8, 128, 2816, 0, 60, 50, 50, 50, 1), 50),
     (synth.StageConfig("pf-bf16-20-odd-widths", "bf16", 2, 480, 6, 3, 64, 1056, 0, 33, 20, 20, 20, 1, qkv_bias=True), 20),
 ])
@@ -95,3 +95,15 @@ def test_chain_at_bench_width():
     err = max_rel_err(g, o)
     print(f"  hidden max-rel-err {err:.3e}", flush=True)
     assert err < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows", [65, 128])
+def test_chain_segment_through_one_row_block_of_the_many_row_kernel(rows, monkeypatch):
+    """The many-row kernel with its only row block partly filled and full, as the knob for its first row count gives it."""
+    from tests.gpu_util import TOL, Pair, max_rel_err
+    monkeypatch.setenv("FLOWSPEC_WIDE_ROWS", "65")
+    cfg = synth.StageConfig(f"pf-bf16-knob-{rows}", "bf16", 2, 480, 6, 3, 64, 1056, 0, 33, rows, rows, rows, 1, qkv_bias=True)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=4)
+    o, g = pair.verify_tree(_chain(rows), synth.hidden(cfg, rows, 0, 4), rows)
+    assert max_rel_err(g, o) < TOL["bf16"]

@@ -76,10 +76,11 @@ def test_sampled_accept_errors():
 
 
 @pytest.mark.parametrize("vocab,T,n_ver,n_child", [
-    (4096, 40, 40, 3), (4097, 40, 33, 8),      # one launch per row / the smallest chunked row, with a scalar tail
-    (10007, 90, 90, 60),                       # odd row length: unaligned rows, most of the tree below one node
-    (32000, 1024, 1024, 1000),                 # many rows: two chunks each; a star of a thousand candidates
-    (152064, 3, 2, 2),                         # few rows of the largest vocabulary: many chunks
+    # one workgroup per row: rows on 16 bytes and not, most of the tree below one node, a star of a thousand candidates
+    (4096, 40, 40, 3), (4097, 40, 33, 8), (10007, 90, 90, 60), (32000, 1024, 1024, 1000),
+    # rows in chunks: the smallest vocabulary that is chunked (4 chunks) and the largest that is not, odd row lengths (scalar loads, a last
+    # chunk that is no multiple of four), 4 and 3 chunks of the same rows on either side of 512 rows, 38 chunks of few rows
+    (12288, 30, 5, 8), (12289, 30, 5, 8), (50257, 20, 9, 5), (32000, 600, 512, 70), (32000, 600, 513, 70), (152064, 3, 2, 2),
 ])
 def test_sampled_accept_row_chunks_and_residual(vocab, T, n_ver, n_child):
     """Row statistics cut into chunks, candidates with duplicate tokens and tokens outside the vocabulary, residual draws behind
@@ -105,6 +106,25 @@ def test_sampled_accept_row_chunks_and_residual(vocab, T, n_ver, n_child):
         assert np.array_equal(g_ret, o_ret)
         seen.add(o_res.n_acc)
     assert len(seen) > 1                       # accepted and rejected candidates both occurred
+
+
+@pytest.mark.parametrize("vocab", [1000, 32000])
+def test_sampled_accept_of_logits_off_a_16_byte_boundary(vocab):
+    """A row length that is a multiple of four behind a base that is not on 16 bytes: scalar loads, in one workgroup per row and in chunks."""
+    import torch
+    from paper_2507_02620_amd import flowspec as fs
+    parent, token = np.array([-1, 0, 0], dtype=np.int32), np.array([5, 7, 9], dtype=np.int32)
+    lg = synth.random_logits(3, vocab, 5, 9)
+    buf = torch.zeros(3 * vocab + 1, device="cuda")
+    view = buf[1:].view(3, vocab)
+    view.copy_(torch.from_numpy(lg))
+    assert view.data_ptr() % 16 == 4
+    res, retain, _ = fs.new_accept_buffers(3, 1)
+    for step in range(4):
+        o_res, o_ret = oracle.accept_sample(lg, 1.0, token, parent, 3, 12, step)
+        fs.tree_accept_sample(view, 1.0, torch.from_numpy(token).cuda(), torch.from_numpy(parent).cuda(), 3, 12, step, res, retain)
+        g_res, g_ret = fs.accept_result_to_host(res, retain, 3)
+        assert g_res.as_tuple() == o_res.as_tuple() and np.array_equal(g_ret, o_ret)
 
 
 @pytest.mark.parametrize("n_child", [0, 3, 7, 8, 40])

@@ -9,16 +9,9 @@ from paper_2507_02620_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows", [17, 32, 33, 64, 65, 113, 128])
-@pytest.mark.parametrize("d,hq,hkv,hd,f,vocab,bias", [
-    (480, 6, 3, 64, 1056, 1000, True),      # 15 and 33 k-tiles (an odd last stage), ragged feature blocks everywhere
-    (64, 1, 1, 64, 96, 40, False),          # 2 k-tiles: fewer stages than buffers
-    (1024, 64, 2, 128, 6400, 4000, False),  # QKV of 544 tiles through the kernel, gate/up of 800 tiles, several K slices
-])
-def test_rows_between_one_tile_and_a_block(rows, d, hq, hkv, hd, f, vocab, bias):
+def _check(cfg, rows):
     import torch
     from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
-    cfg = synth.StageConfig(f"stream-{d}-{rows}", "bf16", 2, d, hq, hkv, hd, f, vocab, 37, rows + 3, rows, 6, 3, qkv_bias=bias)
     print(f"[case] {cfg.name}", flush=True)
     pair = Pair(cfg, seed=rows, head=True)
     tree = synth.config_tree(cfg, seed=rows)
@@ -33,3 +26,26 @@ def test_rows_between_one_tile_and_a_block(rows, d, hq, hkv, hd, f, vocab, bias)
     lerr = max_rel_err(lg.cpu().numpy(), lo)
     print(f"  hidden {err:.2e}, K/V {kerr:.2e}, logits {lerr:.2e}", flush=True)
     assert err < TOL["bf16"] and kerr < TOL["bf16"] and lerr < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows", [17, 33, 64, 65, 81, 113, 128])
+@pytest.mark.parametrize("d,hq,hkv,f,vocab", [
+    # blocks of 6 feature tiles: QKV of 1152, gate/up of 1092 tiles (ragged last block), LM head of 1100; the down projection's 273
+    # k-tiles and the attention output's 384 take blocks of 8 tiles from 65 rows on (one wave group, one k-tile per stage, 8 buffers), in K
+    # slices, the last one shorter; 2 k-tiles elsewhere: fewer stages than buffers
+    (64, 96, 24, 8736, 17600),
+    # blocks of 8 feature tiles: QKV of 2048, gate/up of 1644, LM head of 1600; 3 k-tiles, an odd last stage
+    (96, 128, 64, 13152, 25600),
+])
+def test_blocks_of_six_and_eight_feature_tiles(rows, d, hq, hkv, f, vocab):
+    _check(synth.StageConfig(f"stream-wide-{d}-{rows}", "bf16", 2, d, hq, hkv, 128, f, vocab, 37, rows + 3, rows, 6, 3), rows)
+
+
+@pytest.mark.parametrize("rows", [17, 32, 33, 64, 65, 113, 128])
+@pytest.mark.parametrize("d,hq,hkv,hd,f,vocab,bias", [
+    (480, 6, 3, 64, 1056, 1000, True),      # 15 and 33 k-tiles (an odd last stage), ragged feature blocks everywhere
+    (64, 1, 1, 64, 96, 40, False),          # 2 k-tiles: fewer stages than buffers
+    (1024, 64, 2, 128, 6400, 4000, False),  # QKV of 544 tiles through the kernel, gate/up of 800 tiles, several K slices
+])
+def test_rows_between_one_tile_and_a_block(rows, d, hq, hkv, hd, f, vocab, bias):
+    _check(synth.StageConfig(f"stream-{d}-{rows}", "bf16", 2, d, hq, hkv, hd, f, vocab, 37, rows + 3, rows, 6, 3, qkv_bias=bias), rows)
