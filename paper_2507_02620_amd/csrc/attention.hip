@@ -897,11 +897,13 @@ static int splits_one_round(int per_split, int ntiles) { return std::max(1, std:
 // Whether the requests of a batch are alike enough for the paired form.  Its plan has half the splits of the other one's, counted as if
 // every request were the longest: what the launch then waits for is the longest walk of a workgroup, here in units of a compute unit's
 // share of all tiles that there are to walk.  Up to 1.5 (at most 8 row tiles and more than 32 K/V tiles), 3.5 (9 to 16 row tiles, where
-// the other form has two per wave) or 2.1 (more, where it has as many row blocks) the paired form was the faster one in 113 of
-// 116 batches of 2 to 32 requests, mostly ragged ones, by up to 1.8 times (three slower by 6, 8 and 13 %).  Above, the other one was in 20 of 45, by up to
-// 1.96 times (the paired one in the rest, by up to 1.4; us, other / paired: one 128-row segment behind 8k and fifteen 8-row segments behind 64 slots, 12/2 heads [20] 73 / 143; 18 requests of
-// up to 22 rows behind up to 7.7k, 28/4 heads [3.6] 112 / 138; 16 requests of 1 to 46 rows behind 50 to 3050, 28/4 heads [3.4] 56 / 65;
-// 23 requests of up to 29 rows behind up to 7.4k, 32/8 heads [1.8] 110 / 136).
+// the other form has two per wave) or 2.1 (more, where it has as many row blocks) the paired form was the faster one in 113 of 116
+// batches of 2 to 32 requests, mostly ragged ones, by up to 1.8 times (three slower by 6, 8 and 13 %).  Above, the other one was in 20 of
+// 45, by up to 1.96 times (the paired one in the rest, by up to 1.4).  us, other / paired: one 128-row segment behind 8k and fifteen
+// 8-row segments behind 64 slots, 12/2 heads [20] 73 / 143; 18 requests of up to 22 rows behind up to 7.7k, 28/4 heads [3.6] 112 / 138;
+// 16 requests of 1 to 46 rows behind 50 to 3050, 28/4 heads [3.4] 56 / 65; 23 requests of up to 29 rows behind up to 7.4k, 32/8 heads
+// [1.8] 110 / 136.  (Splits counted by the workgroups that have tiles, or by a model of rounds and merge, lost more than they gained: every
+// split writes partial results for all rows.)
 static bool pairs_balanced(const AttnReq* req, int n_req, int G, int Hkv1, int BS, int mtiles, int ntiles) {
     if (n_req == 1) return true;
     long long walk = 0;

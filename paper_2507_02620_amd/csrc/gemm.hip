@@ -373,7 +373,7 @@ hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const G
 //   * Projections too narrow to fill the chip (d_model outputs, a few row blocks) split K over `k_splits` workgroups;
 //     each writes its raw accumulator tiles (MFMA lane order, so 16 bytes per lane, contiguous per wave) to a scratch
 //     array and wide_fixup_kernel adds them up and runs the residual epilogue.
-//   * Below 129 rows only an LM head of many rounds of blocks comes here (stream_pays).
+//   * Below 129 rows only an LM head comes here that neither the streaming nor the few-row kernel takes (stream_pays, head_few_rows).
 template <int EPI, bool PARTIAL, int BMT, int WNT, int WAVES, bool STREAMW>
 __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel(const GemmArgs a, int layout_nt, int n_tiles, int n_cols, int m_blocks, int k_splits,
                                                            float* part) {
@@ -845,7 +845,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_kernel(const GemmArgs
 // (96 workgroups of 4 waves: 2.5 TB/s, through direct-to-LDS loads 4.5 TB/s).  Workgroup = WM x WN x KG waves on a block of
 // all rows (16 * WM * MT) x 16 * WN * NT features; the KG wave groups take alternate k-tiles of the block (larger wave tiles, hence
 // fewer LDS reads per MFMA, than dividing it further) and add their tiles up through LDS at the end.
-//   * A stage is the block's fragments of S k-tiles; R stage buffers, all but one of them in flight.  Loads are 16 bytes per
+//   * A stage is the block's fragments of KG k-tiles; R stage buffers, all but one of them in flight.  Loads are 16 bytes per
 //     lane straight into LDS, a fixed number per wave and stage, so the explicit wait counts are exact; stages beyond the K
 //     range are still "loaded" (one cache line, into a buffer nobody reads).
 //   * Per stage one bare barrier: before it a wave waits for its own loads of stage s + 1 and for its LDS reads of stage s;
@@ -856,7 +856,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_kernel(const GemmArgs
 // 38.3 -> 32.4, down 28.5 -> 21.1; 64 rows QKV 34.7 -> 27.2, gate/up 41 -> 33.9, down 30.1 -> 24.3; 128 rows QKV 47.9 -> 35.7, output
 // 25.5 -> 19.3, gate/up 53.9 -> 47.7, down 34.7 -> 31.2.  MFMAs, LDS reads and RMSNorm sums are hidden (128 rows QKV: 1.3 us without
 // them, the epilogue another 4); above the 19 us in which the same loads run alone it is the activations, first read beyond L2.
-template <int EPI, bool PARTIAL, int WM, int WN, int KG, int MT, int NT, int S, int R>
+template <int EPI, bool PARTIAL, int WM, int WN, int KG, int MT, int NT, int R>
 __global__ void __launch_bounds__(WM * WN * KG * 64) stream_gemm_kernel(const void* Wp, const void* X, int nkt, int ldx, int M, int flags, int n_tiles,
                                                                         int kt_per, const GemmArgs a, float* part) {
     using T = bf16_t;
@@ -865,11 +865,11 @@ __global__ void __launch_bounds__(WM * WN * KG * 64) stream_gemm_kernel(const vo
     constexpr bool NORM = (EPI != EPI_RESID);
     constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     constexpr int TPI = PAIR ? 2 : 1;
+    constexpr int S = KG;  // k-tiles per stage: one per wave and stage
     constexpr int NW = WM * WN * KG, BMT = WM * MT, BNT = WN * NT, H = MT / KG;
     constexpr int AF = S * BMT, WF = S * BNT, LA = AF / NW, LW = WF / NW, LPS = LA + LW;  // fragments per stage, loads per wave and stage
     static_assert(AF % NW == 0 && WF % NW == 0, "every wave issues the same loads");
-    static_assert(KG == 1 || (KG == 2 && S == 2 && MT % 2 == 0), "two wave groups take one k-tile of a stage each");
-    static_assert(S == KG, "one k-tile per wave and stage");
+    static_assert(KG == 1 || (KG == 2 && MT % 2 == 0), "two wave groups take one k-tile of a stage each");
     static_assert(R % 2 == 0 && R >= 4 && R <= 8, "register sets alternate with the stages; at most 8 buffers");
     static_assert(R * (AF + WF) <= 158 && LPS * (R - 1) < 64, "160 KiB of LDS, 6-bit wait counter");
     static_assert(KG == 1 || H * NT * WM * WN <= AF + WF, "exchange of half the tiles fits a stage buffer");
@@ -1233,9 +1233,9 @@ hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs&
 }
 
 // ---- launch of the 17 to 128 row kernel -----------------------------------------------------------------------------------
-template <int EPI, int WM, int WN, int KG, int MT, int NT, int S, int R>
+template <int EPI, int WM, int WN, int KG, int MT, int NT, int R>
 static hipError_t launch_stream_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
-    constexpr int BNT = WN * NT;
+    constexpr int BNT = WN * NT, S = KG;
     const int n_cols = (n_tiles + BNT - 1) / BNT, m_tiles = (a.M + 15) / 16;
     const int flags = a.x_frag | (layout_nt == 4 ? 4 : layout_nt == 2 ? 2 : 0);
     const dim3 block(WM * WN * KG * 64);
@@ -1245,7 +1245,7 @@ static hipError_t launch_stream_shape(int layout_nt, int n_tiles, const GemmArgs
         if (ks > 1) {
             const int per = ((a.nkt + ks - 1) / ks + S - 1) / S * S;
             ks = (a.nkt + per - 1) / per;
-            hipLaunchKernelGGL((stream_gemm_kernel<EPI, true, WM, WN, KG, MT, NT, S, R>), dim3(n_cols, ks), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags,
+            hipLaunchKernelGGL((stream_gemm_kernel<EPI, true, WM, WN, KG, MT, NT, R>), dim3(n_cols, ks), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags,
                                n_tiles, per, a, part);
             const dim3 grid((m_tiles * n_cols * BNT + 3) / 4);
 #define FS_FIX(k) \
@@ -1255,7 +1255,7 @@ static hipError_t launch_stream_shape(int layout_nt, int n_tiles, const GemmArgs
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((stream_gemm_kernel<EPI, false, WM, WN, KG, MT, NT, S, R>), dim3(n_cols), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags, n_tiles,
+    hipLaunchKernelGGL((stream_gemm_kernel<EPI, false, WM, WN, KG, MT, NT, R>), dim3(n_cols), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags, n_tiles,
                        (a.nkt + S - 1) / S * S, a, nullptr);
     return hipGetLastError();
 }
@@ -1308,19 +1308,19 @@ bool head_few_rows(int M, int n_tiles, int nkt) {
 template <int EPI>
 static hipError_t launch_stream_epi(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
     const int bn = stream_width(EPI, a.M, n_tiles, a.nkt);
-    if (a.M <= 32 && bn == 4) return launch_stream_shape<EPI, 1, 2, 2, 2, 2, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+    if (a.M <= 32 && bn == 4) return launch_stream_shape<EPI, 1, 2, 2, 2, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
     if (a.M <= 64) {
-        if (bn == 4) return launch_stream_shape<EPI, 2, 2, 2, 2, 2, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+        if (bn == 4) return launch_stream_shape<EPI, 2, 2, 2, 2, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
         if constexpr (EPI != EPI_RESID) {
-            if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 2, 6, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
-            return launch_stream_shape<EPI, 1, 2, 2, 4, 4, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+            if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 2, 6, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+            return launch_stream_shape<EPI, 1, 2, 2, 4, 4, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
         }
     }
-    if (bn == 4) return launch_stream_shape<EPI, 4, 1, 2, 2, 4, 2, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+    if (bn == 4) return launch_stream_shape<EPI, 4, 1, 2, 2, 4, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
     if constexpr (EPI != EPI_RESID) {
-        if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 4, 6, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
+        if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 4, 6, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
     }
-    return launch_stream_shape<EPI, 2, 2, 1, 4, 4, 1, 8>(layout_nt, n_tiles, a, part, part_bytes, s);
+    return launch_stream_shape<EPI, 2, 2, 1, 4, 4, 8>(layout_nt, n_tiles, a, part, part_bytes, s);
 }
 
 hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
@@ -1528,16 +1528,14 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     constexpr int AF = 4 * BMT, LA = AF / NW, LW = BNT / NW, LPS = LA + LW + 1;
     constexpr int SCALES = (AF + BNT) * 1024, STAGE = SCALES + NW * 256;
     static_assert(AF % NW == 0 && BNT % NW == 0, "every wave issues the same loads");
-    static_assert(R >= 3 && R <= 6 && LPS * (R - 1) < 64 && R * STAGE + ROWS * 8 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
+    static_assert((R == 3 || R == 4) && LPS * (R - 1) < 64 && R * STAGE + ROWS * 8 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
     static_assert(NT <= 8 && THREADS % ROWS == 0, "a wave's scales fit one load; whole rows per pass of the row-scale sums");
     __shared__ __align__(1024) unsigned char sb0[STAGE];
     __shared__ __align__(1024) unsigned char sb1[STAGE];
     __shared__ __align__(1024) unsigned char sb2[STAGE];
     __shared__ __align__(1024) unsigned char sb3[R > 3 ? STAGE : 16];
-    __shared__ __align__(1024) unsigned char sb4[R > 4 ? STAGE : 16];
-    __shared__ __align__(1024) unsigned char sb5[R > 5 ? STAGE : 16];
     __shared__ float rs_s[ROWS];
-    auto buf_at = [&](int j) -> unsigned char* { return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : (j == 3 ? sb3 : (j == 4 ? sb4 : sb5)))); };
+    auto buf_at = [&](int j) -> unsigned char* { return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : sb3)); };
 
     // grid (8 * row blocks, feature blocks / 8, K slices): the row blocks of a feature block are neighbours on one XCD
     const int mb = blockIdx.x >> 3, col = blockIdx.y * 8 + (blockIdx.x & 7), ks = blockIdx.z;
@@ -1620,7 +1618,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
         float tot = s_more;
 #pragma unroll
         for (int i = 0; i < SL; ++i) tot += sub + i * TPR < a.ssp_n ? sp[i] : 0.f;
-        for (int k = 0; k < TPR; ++k) {  // uniform; TPR is 2 .. 4
+        for (int k = 0; k < TPR; ++k) {  // uniform; TPR is 8 (64-row blocks) or 4
             if (sub == k) rs_s[row] = k == 0 ? tot : rs_s[row] + tot;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();

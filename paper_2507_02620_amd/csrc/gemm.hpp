@@ -87,12 +87,11 @@ hipError_t launch_prenorm(const void* X, int ldx, int M, int K, const void* gain
 // projection leaves w4_ssp_parts(M, n_tiles, nkt) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
 int w4_ssp_parts(int M, int n_tiles, int nkt);
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
-// bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block up to 64 rows).  layout_nt and n_tiles
-// describe the re-tiled weights (tiles per group, 16-feature tiles in total); normed projections need ssp_in from 384 rows on
-// (256-feature blocks; the 128-feature blocks add up the squares of the activations themselves).  `part` (may be null) is scratch for K-split partial results of the d_model-wide
-// residual projections (wide_partial_bytes gives a sufficient size for segments of up to max_rows rows and n_tiles output
-// tiles); a residual
-// projection leaves wide_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out.
+// bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block for an LM head of up to 64 rows).  layout_nt
+// and n_tiles describe the re-tiled weights (tiles per group, 16-feature tiles in total); normed projections need ssp_in from 384
+// rows on (256-feature blocks; the 128-feature blocks add up the squares of the activations themselves).  `part` (may be null) is
+// scratch for K-split partial results of the d_model-wide residual projections (wide_partial_bytes gives a sufficient size for
+// segments of up to max_rows rows and n_tiles output tiles); a residual projection leaves wide_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out.
 int wide_ssp_parts(int M, int n_tiles);
 size_t wide_partial_bytes(int max_rows, int n_tiles);
 // wide_fits: whether its 32-bit offsets reach all of the operands.
