@@ -1752,7 +1752,8 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
 // kernel with four tiles per workgroup 0.37 ns per chunk, feature tile and 32-row block.  Both sides, us (few / this): 4096 x 12288,
 // 128 rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 64 rows 51 / 60, 128 rows
 // 101 / 89.  Residual projections (two tiles per workgroup there, K slices here): 4096 x 4096, 128 rows 18 / 25, 200 rows 30 / 28;
-// 13824 x 5120, 64 rows 42 / 32; 5120 x 5120, 65 rows 23 / 26.
+// 13824 x 5120, 64 rows 42 / 32; 5120 x 5120, 65 rows 23 / 26; with a short K there are too few slices to fill the chip: 1024 x 1024, 640
+// rows 17.9 / 22.6, 1024 rows 24.5 / 25; 1536 x 1536, 512 rows 19.8 / 22.2, 640 rows less; 2048 x 2048, 300 rows 19.4 / 21.7.
 // Its offsets from the operands' bases have 32 bits: 4 GiB of codes and more stay with the few-row kernel.
 static bool block_w4_fits(int M, int n_tiles, int nkt) {
     return (unsigned long long)(n_tiles + 16) * nkt * 256ull < (1ull << 32) && (unsigned long long)(M + 16) * nkt * 64ull < (1ull << 32);
@@ -1760,7 +1761,7 @@ static bool block_w4_fits(int M, int n_tiles, int nkt) {
 static bool block_w4_pays(int epi, int M, int n_tiles, int nkt) {
     if (M <= 32 || !block_w4_fits(M, n_tiles, nkt)) return false;
     const int work = n_tiles * ((M + 31) / 32), rounds = ((n_tiles + 15) / 16 * ((M + 127) / 128) + 255) / 256;
-    if (epi == EPI_RESID) return work > (M <= 64 ? 600 : 1100);
+    if (epi == EPI_RESID) return work > (M <= 64 ? 600.0 : std::max(1100.0, 800 + 44000.0 / nkt));
     return work > (M <= 64 ? 4200 : 6000) * rounds;
 }
 

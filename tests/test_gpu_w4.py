@@ -133,7 +133,7 @@ def test_w4_random_shapes(i):
 
 
 @pytest.mark.parametrize("name,cfg,rows", [
-    # every projection in 128-row blocks (the last one holds one row tile), K slices for the residual ones
+    # QKV and gate/up in 128-row blocks, the residual projections (short K: test_w4_residual_projections_of_a_short_k) in the few-row kernel
     ("all", synth.StageConfig("w4b-all", "bf16", 2, 1024, 16, 16, 128, 3328, 0, 40, 577, 577, 577, 1, qkv_bias=True), 577),
     # residual projections and LM head in 64-row blocks, the attention output with one K slice; the others in the few-row kernel
     ("resid", synth.StageConfig("w4b-resid", "bf16", 2, 4992, 2, 2, 64, 1152, 34000, 30, 33, 33, 5, 3), 33),
@@ -163,3 +163,15 @@ def test_w4_row_blocks(name, cfg, rows):
         lo, _ = pair.orc.logits(x.astype(np.float64))
         lg, _ = pair.gpu.tree_logits(to_dev(x, torch.bfloat16))
         assert max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows", [500, 641])
+def test_w4_residual_projections_of_a_short_k(rows):
+    """1536 input columns: few-row kernel in row blocks up to about 570 rows, beyond in 128-row blocks (the last
+    one holds a single row) with 3 K slices of 4 chunks."""
+    from tests.gpu_util import TOL, Pair, max_rel_err
+    cfg = synth.StageConfig(f"w4-short-k-{rows}", "bf16", 2, 1536, 12, 2, 128, 1536, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=6, w4=True)
+    o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, 6), rows)
+    assert max_rel_err(g, o) < TOL["bf16"]
