@@ -496,11 +496,11 @@ int fs_stage_profile_end(fs_stage* st, void* stream, double* total_ms, long long
 }
 
 // Which kernels a dense bf16 projection of so many stacked rows takes (f32: always the few-row kernel; 4-bit weights: launch_gemm_w4).
-enum Route { ROUTE_FEW = 0, ROUTE_STREAM = 1, ROUTE_WIDE = 2 };
+enum Route { ROUTE_FEW = 0, ROUTE_MID = 1, ROUTE_WIDE = 2 };
 static Route route_of(const fs_stage* st, int rows) {
     if (st->d.dtype != FS_BF16 || st->d.weight_format != FS_WFMT_DENSE) return ROUTE_FEW;
     if (rows >= st->tun.wide_rows || rows > 128) return ROUTE_WIDE;
-    return rows < st->tun.mid_rows ? ROUTE_FEW : ROUTE_STREAM;
+    return rows < st->tun.mid_rows ? ROUTE_FEW : ROUTE_MID;
 }
 
 // Rows of the caller may begin at any element; the streaming kernel's direct-to-LDS loads want their 16 bytes aligned (the plain vector
@@ -510,7 +510,11 @@ static bool lds_loadable(const void* rows) { return ((uintptr_t)rows & 15) == 0;
 static hipError_t launch_proj(const fs_stage* st, int epi, const GemmPlan& p, GemmArgs& g, hipStream_t s, Route route) {
     float* part = st->at<float>(st->L.off_part);
     const int tiles = p.n_groups * p.NT;
-    if (route == ROUTE_STREAM && stream_pays(epi, g.M, tiles, p.nkt)) return launch_gemm_stream(epi, p.NT, tiles, g, part, st->L.part_bytes, s);
+    if (route == ROUTE_MID) {
+        const MidKernel k = mid_kernel(epi, p.NT, g.M, tiles, p.nkt);
+        if (k == MID_STREAM) return launch_gemm_stream(epi, p.NT, tiles, g, part, st->L.part_bytes, s);
+        if (k == MID_WIDE) route = ROUTE_WIDE;
+    }
     if (route == ROUTE_WIDE) return launch_gemm_wide(epi, p.NT, tiles, g, part, st->L.part_bytes, st->tun.block_gemm, s);
     if (p.w4) {
         g.Sp = p.sp;
@@ -623,7 +627,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     const int o_parts = res_parts(L.layers[0].o), down_parts = res_parts(L.layers[0].down);
     int ssp_n_first = 0;
     // (row-major input costs the streaming kernel 64-byte pieces of 16 rows per load; from 33 rows on one conversion pass is cheaper)
-    const bool to_frag = handover || (route == ROUTE_STREAM && (l_s > 32 || !lds_loadable(hidden_in)));
+    const bool to_frag = handover || (route == ROUTE_MID && (l_s > 32 || !lds_loadable(hidden_in)));
     if (to_frag)
         HIP_TRY_K(st, FS_K_PREPARE, s,
                   launch_prenorm(hidden_in, d.d_model, l_s, d.d_model, w4 ? gains : nullptr, hb, sspa, L.ssp_stride, &ssp_n_first, s));
@@ -724,10 +728,11 @@ int fs_tree_logits(fs_stage* st, const void* hidden, int l_s, float* logits, int
     GemmArgs g{};
     g.X = hidden; g.ldx = st->d.d_model; g.M = l_s; g.K = p.K; g.nkt = p.nkt; g.N = p.N; g.Wp = p.wp; g.eps = st->d.rms_eps; g.logits = logits;
     Route route = route_of(st, l_s);
-    const int tiles = p.n_groups * p.NT;
-    if (route == ROUTE_STREAM && !stream_pays(EPI_LOGITS, l_s, tiles, p.nkt))
-        route = head_few_rows(l_s, tiles, p.nkt) || !wide_fits(p.NT, tiles, l_s, p.nkt) ? ROUTE_FEW : ROUTE_WIDE;
-    if (p.w4 || route == ROUTE_WIDE || (route == ROUTE_STREAM && !lds_loadable(hidden))) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
+    if (route == ROUTE_MID) {
+        const MidKernel k = mid_kernel(EPI_LOGITS, p.NT, l_s, p.n_groups * p.NT, p.nkt);
+        if (k != MID_STREAM) route = k == MID_WIDE ? ROUTE_WIDE : ROUTE_FEW;
+    }
+    if (p.w4 || route == ROUTE_WIDE || (route == ROUTE_MID && !lds_loadable(hidden))) {  // (gained) fragment-major copy of the rows + their sums of squares, as at the entry of such a stage
         void* hb = st->at<void>(st->L.off_hb);
         float* ssp = st->at<float>(st->L.off_sspa);
         const bf16_t* gain = p.w4 ? st->at<bf16_t>(st->L.off_gain) + (size_t)(2 * st->d.n_layers) * st->d.d_model : nullptr;

@@ -356,7 +356,7 @@ hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const G
 // With more than a row tile or two the projections stop being a pure weight stream: the few-row kernel re-reads the
 // activations once per workgroup and ends up bound by the path from L2 into the compute units.  This kernel shares the
 // activations between the waves instead.  Workgroup = 4 waves; block = 128 rows x 256 features (from 384 rows), 128 rows
-// x 128 features (129 .. 383 rows; LM head from 65) or 64 rows x 128 features (LM head of up to 64 rows); wave w owns a quarter of the features for
+// x 128 features (up to 383 rows) or 64 rows x 128 features (LM head and gate/up of up to 64 rows); wave w owns a quarter of the features for
 // all rows of the block (8 x 4, 8 x 2 or 4 x 2 accumulator tiles).
 //   * Weights are private to a wave, so they skip LDS: each wave streams its tiles per k-tile straight from the re-tiled
 //     copy into registers, a ring of PFW k-tiles deep (the same coalesced 1 KiB fragment loads as the few-row kernel).
@@ -373,7 +373,7 @@ hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const G
 //   * Projections too narrow to fill the chip (d_model outputs, a few row blocks) split K over `k_splits` workgroups;
 //     each writes its raw accumulator tiles (MFMA lane order, so 16 bytes per lane, contiguous per wave) to a scratch
 //     array and wide_fixup_kernel adds them up and runs the residual epilogue.
-//   * Below 129 rows only an LM head comes here that neither the streaming nor the few-row kernel takes (stream_pays, head_few_rows).
+//   * Below 129 rows only what mid_kernel sends here.
 template <int EPI, bool PARTIAL, int BMT, int WNT, int WAVES, bool STREAMW>
 __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel(const GemmArgs a, int layout_nt, int n_tiles, int n_cols, int m_blocks, int k_splits,
                                                            float* part) {
@@ -1089,7 +1089,7 @@ static int wide_narrow_rows() {
 }
 static int env_int(const char* name, int dflt) { const char* e = getenv(name); return e ? atoi(e) : dflt; }
 static WideShape wide_shape(int epi, int M) {
-    if (M <= 64 && epi == EPI_LOGITS) return WideShape{4, 2, 4};  // one 64-row block
+    if (M <= 64 && (epi == EPI_LOGITS || epi == EPI_SWIGLU)) return WideShape{4, 2, 4};  // one 64-row block
     return M < wide_narrow_rows() ? WideShape{8, 2, 4} : WideShape{8, 4, 4};
 }
 
@@ -1192,7 +1192,7 @@ static int block_gemm_width(int mode, int epi, int M, int n_tiles) {  // mode 0 
 }
 
 // the kernels address weights and activations with 32-bit byte offsets from their bases
-bool wide_fits(int layout_nt, int n_tiles, int M, int nkt) {
+static bool wide_fits(int layout_nt, int n_tiles, int M, int nkt) {
     return (unsigned long long)(n_tiles + layout_nt) * nkt * 1024ull < (1ull << 32) && (unsigned long long)(M + 16) * nkt * 64ull < (1ull << 32);
 }
 
@@ -1219,6 +1219,7 @@ hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs&
             return narrow ? launch_wide_shape<EPI_QKV, 8, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s)
                           : launch_wide_shape<EPI_QKV, 8, 4, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
         case EPI_SWIGLU:
+            if (half) return launch_wide_shape<EPI_SWIGLU, 4, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
             return narrow ? launch_wide_shape<EPI_SWIGLU, 8, 2, 4>(layout_nt, n_tiles, a, part, part_bytes, s)
                           : launch_wide_shape<EPI_SWIGLU, 8, 4, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
         case EPI_RESID:
@@ -1262,10 +1263,10 @@ static hipError_t launch_stream_shape(int layout_nt, int n_tiles, const GemmArgs
 
 // Feature tiles per block: a compute unit holds one block at a time and draws its weights and the activations for it, so a launch
 // costs rounds x (feature tiles + row tiles); the residual projections fill the chip with K slices instead, where wider blocks
-// only pay by reading a long activation block less often (128 rows x 11008: 33.5 -> 31.2 us).
+// only pay by reading a long activation block less often (128 rows x 11008: 33.5 -> 31.2 us; 64 rows x 28672, 8192 features: 86.6 -> 84.3).
 static int stream_width(int epi, int M, int n_tiles, int nkt) {
     const int bmt = M <= 64 ? 4 : 8;
-    if (epi == EPI_RESID) return (M > 64 && nkt > 256) ? 8 : 4;
+    if (epi == EPI_RESID) return (M > 64 && nkt > 256) || (M > 32 && nkt > 512) ? 8 : 4;
     int best = 4, cost = 1 << 30;
     for (int bn = 4; bn <= 8; bn += 2) {
         const int blocks = (n_tiles + bn - 1) / bn, c = (blocks + 255) / 256 * (bn + bmt);
@@ -1277,32 +1278,51 @@ static int stream_width(int epi, int M, int n_tiles, int nkt) {
     return best;
 }
 
-// Whether a projection takes this kernel at 17 to 128 rows (else: the few-row kernel, the LM head the kernel with blocks in
-// registers).  Its offsets from the operands' bases have 32 bits: matrices of 4 GiB and more stay with the few-row kernel.  Measured, this kernel / the other one, us:
-//   * LM head: while its blocks run in one round (32000 rows x 4096: 64 rows 50 / 49 + 5 for the conversion pass the other one needs);
-//     with many rounds several workgroups per compute unit hide each other's ends (152064 x 3584, 64 rows: 242 / 220 + 5).
-//   * QKV of few heads (288 tiles, 72 blocks): from 65 rows on (80 rows 34 / 43, but 48 rows 23.4 / 21.6).
-//   * gate/up with more than one round of blocks: from 33 rows on (2368 tiles: 48 rows 54.7 / 62.2, but 32 rows 53.4 / 52.4).
-//   * attention output up to 32 rows with at most one few-row workgroup per compute unit: the second launch that adds the K slices
-//     costs more than it gives while K is short (4096 x 4096: 15 / 13; but 5120 x 5120 with its 320 tiles 15.4 / 18.4, and
-//     4096 x 11008 21.1 / 28).
+// Which kernel takes a projection of 17 to 128 rows.  The streaming kernel's offsets from the operands' bases have 32 bits: matrices of
+// 4 GiB and more stay with the few-row kernel.  Measured, us, the streaming kernel / the other one unless said otherwise:
+//   * LM head: streaming while its blocks run in one round (32000 rows x 4096: 64 rows 50 / 49 + 5 for the conversion pass the other one
+//     needs); with many rounds several workgroups per compute unit hide each other's ends (152064 x 3584, 64 rows: 242 / 220 + 5).
+//     That other kernel, with blocks in registers, has one 64-row block per 128 features, a good launch if they all run at once or in
+//     many rounds, not if a few compute units get a second one.  Few-row kernel then (blocks in registers / few-row) for 257 to 384
+//     blocks up to 40 rows (33024 x 4096: 17 rows 74.7 / 60.9, 32 rows 75.6 / 67.3, 40 rows 2 % more, 48 rows 3 % less) and for 385 to
+//     511 up to 24, with a short K up to 32 (50257 x 4096: 17 rows 85.7 / 84.6, 32 rows 85 / 93; x 1024: 17 rows 33.2 / 29.8, 32 rows
+//     35.5 / 35.8; 61440 x 1024, 28 rows 38.2 / 36.3).
+//   * QKV up to 64 rows: not of few heads (288 tiles, 72 blocks: 48 rows 23.4 / 21.6; from 65 rows on 80 rows 34 / 43), and up to 32 rows
+//     not from about a round of blocks on (2016 tiles x 2048 29 / 27, 3264 tiles 48.7 / 42.8, x 5120 alike).
+//   * gate/up up to 64 rows: streaming (2368 tiles, 48 rows 54.7 / 62.2) but where 64-row blocks in registers make a nearly full first or
+//     second round (4096 tiles x 4096, 33 rows 91.6 / 88.9, x 2048 51.7 / 49.2; 1792 tiles x 4096, 32 rows 45.0 / 42.7, but 1728 x 5120 48.1 /
+//     49.2); up to 32 rows the few-row kernel from a full round of blocks on (2048 tiles x 4096 50.5 / 46.7; 2368 tiles 53.4 / 52.4)
+//     and with a short K (1728 tiles x 2048 27.8 / 26.6).
+//   * QKV and gate/up from 65 rows on: the kernel with blocks in registers runs two of the same 128-feature blocks per compute unit and
+//     wins where this one pays a whole further round for it (65 rows, gate/up of 3584 tiles x 4096 105 / 88, 4096 x 8192 215 / 174, QKV of
+//     3072 x 5120 110 / 104), or has its first one nearly full (gate/up of 1728 tiles x 8192 97 / 91); not with few blocks in the second
+//     round (gate/up x 4096, 65 rows: 2368 tiles 5 % less, 3072 tiles 3 % less).
+//   * residual projections: the second launch that adds the K slices costs more than it gives while K is short: up to 32 rows to K 2048
+//     (5120 .. 7168 features x 1024 9.6 .. 9.8 / 7.9 .. 8.7), to 4096 where the few-row kernel has at most one workgroup per compute unit or
+//     a nearly full round of them (4096 x 4096 15 / 13; 8192 x 4096 18.9 / 17.1; but 5120 x 5120 with its 320 tiles 15.4 / 18.4, and
+//     4096 x 11008 21.1 / 28); up to 64 rows to K 1024 (512 .. 8192 features: K 512 8.8 / 6.5 .. 11.2 / 9.8, K 1024 9.0 / 8.2 .. 11.8 / 11.0,
+//     K 2048 10 % less).
 static bool stream_fits(int n_tiles, int nkt) { return (unsigned long long)(n_tiles + 8) * nkt * 1024ull < (1ull << 32); }
-bool stream_pays(int epi, int M, int n_tiles, int nkt) {
-    if (!stream_fits(n_tiles, nkt)) return false;
-    if (epi == EPI_LOGITS) return M <= 64 && (n_tiles + 7) / 8 <= 256;
-    if (epi == EPI_QKV) return M > 64 || n_tiles >= 512;
-    if (epi == EPI_RESID) return M > 32 || n_tiles > 256 || nkt > 128;
-    return M > 32 || (n_tiles + 7) / 8 <= 256;
-}
-
-// LM head of 17 to 128 rows that the kernel above does not take: the kernel with blocks in registers has one 64-row block per 128
-// features, a good launch if they all run at once or in many rounds, not if a few compute units get a second one.  Few-row kernel
-// instead (us, blocks in registers / few-row) for 257 to 384 blocks up to 40 rows (33024 x 4096: 17 rows 74.7 / 60.9, 32 rows 75.6 / 67.3,
-// 40 rows 2 % more, 48 rows 3 % less) and for 385 to 511 up to 24, with a short K up to 32 (50257 x 4096: 17 rows 85.7 / 84.6, 32 rows
-// 85 / 93; x 1024: 17 rows 33.2 / 29.8, 32 rows 35.5 / 35.8; 61440 x 1024, 28 rows 38.2 / 36.3).
-bool head_few_rows(int M, int n_tiles, int nkt) {
-    const int blocks = (n_tiles + 7) / 8;
-    return blocks > 256 && blocks < 512 && M <= (blocks <= 384 ? 40 : nkt <= 64 ? 32 : 24);
+MidKernel mid_kernel(int epi, int layout_nt, int M, int n_tiles, int nkt) {
+    if (!stream_fits(n_tiles, nkt) || !wide_fits(layout_nt, n_tiles, M, nkt)) return MID_FEW;
+    const int blocks = (n_tiles + 7) / 8;  // of 128 features
+    switch (epi) {
+        case EPI_LOGITS:
+            if (M <= 64 && blocks <= 256) return MID_STREAM;
+            return blocks > 256 && blocks < 512 && M <= (blocks <= 384 ? 40 : nkt <= 64 ? 32 : 24) ? MID_FEW : MID_WIDE;
+        case EPI_RESID:
+            if (M <= 32) return nkt <= 64 || (nkt <= 128 && (n_tiles <= 256 || n_tiles >= 448)) ? MID_FEW : MID_STREAM;
+            return M <= 64 && nkt <= 32 ? MID_FEW : MID_STREAM;
+        case EPI_QKV:
+            if (M <= 64) return n_tiles < 512 || (M <= 32 && blocks >= 250) ? MID_FEW : MID_STREAM;
+            break;
+        case EPI_SWIGLU:
+            if (M <= 32 && (blocks >= 256 || (blocks > 192 && nkt <= 64))) return MID_FEW;
+            if (M <= 64) return (blocks > 464 && blocks <= 512) || (blocks >= 220 && blocks <= 256 && nkt <= 128) ? MID_WIDE : MID_STREAM;
+            break;
+    }
+    // (the producers leave no sums of squares here: only the 128-feature blocks in registers, which work them out themselves)
+    return M < wide_narrow_rows() && (blocks >= (epi == EPI_QKV ? 384 : 400) || (blocks > 192 && blocks <= 256)) ? MID_WIDE : MID_STREAM;
 }
 
 template <int EPI>
@@ -1316,11 +1336,14 @@ static hipError_t launch_stream_epi(int layout_nt, int n_tiles, const GemmArgs& 
             return launch_stream_shape<EPI, 1, 2, 2, 4, 4, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
         }
     }
-    if (bn == 4) return launch_stream_shape<EPI, 4, 1, 2, 2, 4, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
-    if constexpr (EPI != EPI_RESID) {
-        if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 4, 6, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
+    if constexpr (EPI != EPI_LOGITS) {
+        if (bn == 4) return launch_stream_shape<EPI, 4, 1, 2, 2, 4, 6>(layout_nt, n_tiles, a, part, part_bytes, s);
+        if constexpr (EPI != EPI_RESID) {
+            if (bn == 6) return launch_stream_shape<EPI, 2, 1, 2, 4, 6, 4>(layout_nt, n_tiles, a, part, part_bytes, s);
+        }
+        return launch_stream_shape<EPI, 2, 2, 1, 4, 4, 8>(layout_nt, n_tiles, a, part, part_bytes, s);
     }
-    return launch_stream_shape<EPI, 2, 2, 1, 4, 4, 8>(layout_nt, n_tiles, a, part, part_bytes, s);
+    return hipErrorInvalidValue;  // an LM head of more rows has another kernel
 }
 
 hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {

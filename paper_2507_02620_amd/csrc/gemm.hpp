@@ -87,22 +87,20 @@ hipError_t launch_prenorm(const void* X, int ldx, int M, int K, const void* gain
 // projection leaves w4_ssp_parts(M, n_tiles, nkt) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
 int w4_ssp_parts(int M, int n_tiles, int nkt);
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
-// bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block for an LM head of up to 64 rows).  layout_nt
+// bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block for an LM head or gate/up of up to 64 rows).  layout_nt
 // and n_tiles describe the re-tiled weights (tiles per group, 16-feature tiles in total); normed projections need ssp_in from 384
 // rows on (256-feature blocks; the 128-feature blocks add up the squares of the activations themselves).  `part` (may be null) is
 // scratch for K-split partial results of the d_model-wide residual projections (wide_partial_bytes gives a sufficient size for
 // segments of up to max_rows rows and n_tiles output tiles); a residual projection leaves wide_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out.
 int wide_ssp_parts(int M, int n_tiles);
 size_t wide_partial_bytes(int max_rows, int n_tiles);
-// wide_fits: whether its 32-bit offsets reach all of the operands.
-bool wide_fits(int layout_nt, int n_tiles, int M, int nkt);
 // block_mode: 0 never / 1 whenever possible / anything else: by rule — use of the 256-row kernel (both operands through LDS) from 384 rows on
 hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, int block_mode, hipStream_t s);
 // bf16, 17 to 128 rows, row-major or fragment-major activations: the kernel that streams both operands through LDS; normed projections
-// work out their own row scale, residual projections leave no sums of squares.  `part` as for launch_gemm_wide.  stream_pays: whether it
-// is the faster choice for a projection.
-bool stream_pays(int epi, int M, int n_tiles, int nkt);
-bool head_few_rows(int M, int n_tiles, int nkt);  // an LM head that it does not take: few-row kernel, else launch_gemm_wide
+// work out their own row scale, residual projections leave no sums of squares.  `part` as for launch_gemm_wide.  mid_kernel: which
+// kernel takes a projection of so many rows.
+enum MidKernel { MID_FEW, MID_STREAM, MID_WIDE };
+MidKernel mid_kernel(int epi, int layout_nt, int M, int n_tiles, int nkt);
 hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
 // MT = ceil(M/16) in {1,2,4}, NT in {1,2,4} (even for QKV / SWIGLU), waves per workgroup NW
 hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const GemmArgs& a, hipStream_t s);

@@ -34,11 +34,25 @@ def _check(cfg, rows):
     # k-tiles and the attention output's 384 take blocks of 8 tiles from 65 rows on (one wave group, one k-tile per stage, 8 buffers), in K
     # slices, the last one shorter; 2 k-tiles elsewhere: fewer stages than buffers
     (64, 96, 24, 8736, 17600),
-    # blocks of 8 feature tiles: QKV of 2048, gate/up of 1644, LM head of 1600; 3 k-tiles, an odd last stage
-    (96, 128, 64, 13152, 25600),
+    # blocks of 8 feature tiles: up to 64 rows gate/up of 1644 tiles (from 33 rows on), LM head of 1600; from 65 rows on gate/up of 3136 tiles;
+    # 3 k-tiles, an odd last stage
+    (96, 3, 3, 13152, 25600), (96, 3, 3, 25088, 40),
 ])
 def test_blocks_of_six_and_eight_feature_tiles(rows, d, hq, hkv, f, vocab):
     _check(synth.StageConfig(f"stream-wide-{d}-{rows}", "bf16", 2, d, hq, hkv, 128, f, vocab, 37, rows + 3, rows, 6, 3), rows)
+
+
+@pytest.mark.parametrize("d,hq,hkv,f,rows", [
+    # QKV of 1728 tiles: streamed, in 128-row blocks from 65 rows on; gate/up of 1792 tiles: few-row kernel, 64-row, 128-row blocks
+    *[(64, 72, 72, 14336, rows) for rows in (32, 33, 64, 65, 128)],
+    # QKV of 3072 tiles: few-row kernel, streamed, 128-row blocks; gate/up of 4096 tiles: as above; 1024 k-tiles of the down projection in
+    # blocks of 8 feature tiles from 33 rows on
+    *[(64, 128, 128, 32768, rows) for rows in (32, 33, 64, 65, 128)],
+    (2080, 1, 1, 14336, 17),  # gate/up of 1792 tiles and 65 k-tiles: one 64-row block of 32 rows
+    (32, 8, 8, 512, 33), (64, 16, 16, 1056, 64),  # residual projections of 32 and 33 k-tiles: few-row kernel and K slices
+])
+def test_projections_that_take_another_kernel_at_some_row_counts(d, hq, hkv, f, rows):
+    _check(synth.StageConfig(f"mid-{d}-{f}-{rows}", "bf16", 1, d, hq, hkv, 128, f, 40, 37, rows + 3, rows, 6, 3), rows)
 
 
 @pytest.mark.parametrize("rows", [17, 32, 33, 64, 65, 113, 128])
