@@ -1368,7 +1368,7 @@ hipError_t launch_gemm_stream(int epi, int layout_nt, int n_tiles, const GemmArg
 //   * the group's partial result is scaled once per chunk: acc += scale[n] * acc_chunk.
 // RMSNorm: the gain cannot be folded into integer codes; a normed projection gets activations that already carry
 // the gain, and the rows' sums of squares as partial sums left by the kernel that produced them.
-template <int MT, int NT, int EPI>
+template <int MT, int NT, int EPI, int SH>
 __global__ void __launch_bounds__(512) skinny_gemm_w4_kernel(const GemmArgs a) {
     using T = bf16_t;
     using E = Elem<T>;
@@ -1382,8 +1382,10 @@ __global__ void __launch_bounds__(512) skinny_gemm_w4_kernel(const GemmArgs a) {
     const int row0 = mb * MT * 16;
     const int nkc = a.nkt >> 2;                       // chunks of 4 k-tiles
     const int nsteps = (nkc - w + NW - 1) / NW;       // >= 1: the host never launches more waves than chunks
-    // the workgroup's tiles: a whole group of the re-tiled weights, or half of one (w_shift: log2 of the tiles per group)
-    const int sh = a.w_shift, tile0 = grp * NT;
+    // the workgroup's tiles: a whole group of the re-tiled weights, or half of one (SH: log2 of the tiles per group; a launch argument
+    // in its place costs 0.2 - 0.3 us)
+    constexpr int sh = SH;
+    const int tile0 = grp * NT;
     const size_t first = (((size_t)(tile0 >> sh) * nkc) << sh) + (tile0 & ((1 << sh) - 1));
     const unsigned char* wbase = (const unsigned char*)a.Wp + first * 1024 + (size_t)lane * 16;
     const bf16_t* sbase = (const bf16_t*)a.Sp + first * 16 + g * 4;
@@ -1504,25 +1506,26 @@ __global__ void __launch_bounds__(512) skinny_gemm_w4_kernel(const GemmArgs a) {
     reduce_and_store<T, MT, NT, EPI>(a, acc, ss, smem, lane, w, NW, grp, row0, resid_first);
 }
 
-template <int MT, int NT, int EPI>
+template <int MT, int NT, int EPI, int SH>
 static hipError_t launch_one_w4(int NW, int n_groups, const GemmArgs& a0, hipStream_t s) {
     GemmArgs a = a0;
     const int mblocks = (a.M + MT * 16 - 1) / (MT * 16);
     a.red_copies = reduction_copies(NW, MT, NT);
     const size_t lds = (size_t)a.red_copies * MT * NT * 1024 + (size_t)NW * MT * 16 * sizeof(float);
-    hipLaunchKernelGGL((skinny_gemm_w4_kernel<MT, NT, EPI>), dim3(n_groups, mblocks), dim3(NW * 64), lds, s, a);
+    hipLaunchKernelGGL((skinny_gemm_w4_kernel<MT, NT, EPI, SH>), dim3(n_groups, mblocks), dim3(NW * 64), lds, s, a);
     return hipGetLastError();
 }
 
 template <int EPI>
-static hipError_t launch_mt_nt_w4(int MT, int NT, int NW, int n_groups, const GemmArgs& a, hipStream_t s) {
+static hipError_t launch_mt_nt_w4(int MT, int NT, bool half, int NW, int n_groups, const GemmArgs& a, hipStream_t s) {
     constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
-#define FS_CASE(mt, nt) \
-    if (MT == mt && NT == nt) return launch_one_w4<mt, nt, EPI>(NW, n_groups, a, s);
+    if (half) return launch_one_w4<1, 2, EPI, 2>(NW, n_groups, a, s);
+#define FS_CASE(mt, nt, sh) \
+    if (MT == mt && NT == nt) return launch_one_w4<mt, nt, EPI, sh>(NW, n_groups, a, s);
     if constexpr (!PAIR) {
-        FS_CASE(1, 1) FS_CASE(2, 1)
+        FS_CASE(1, 1, 0) FS_CASE(2, 1, 0)
     }
-    FS_CASE(1, 2) FS_CASE(2, 2) FS_CASE(1, 4) FS_CASE(2, 4)
+    FS_CASE(1, 2, 1) FS_CASE(2, 2, 1) FS_CASE(1, 4, 2) FS_CASE(2, 4, 2)
 #undef FS_CASE
     return hipErrorInvalidValue;
 }
@@ -1825,28 +1828,29 @@ static hipError_t launch_block_w4(int epi, int layout_nt, int n_tiles, const Gem
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a0, float* part, size_t part_bytes, hipStream_t s) {
-    if (block_w4_pays(epi, a0.M, n_groups * NT, a0.nkt)) return launch_block_w4(epi, NT, n_groups * NT, a0, part, part_bytes, s);
+hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    if (block_w4_pays(epi, a.M, n_groups * NT, a.nkt)) return launch_block_w4(epi, NT, n_groups * NT, a, part, part_bytes, s);
     // at most 32 rows per workgroup (register budget); longer segments take further row blocks, whose passes over
     // the quarter-size weights mostly hit in L2
-    GemmArgs a = a0;
     const int MT = a.M <= 16 ? 1 : 2;
-    a.w_shift = NT == 4 ? 2 : NT == 2 ? 1 : 0;
+    bool half = false;
     if (NT == 4 && MT == 1) {
         // one row tile: half a group per workgroup where whole groups would leave a last round of few workgroups (344 of them, two
-        // rounds of 256 compute units: gate/up 20.8 -> 18.6 us)
+        // rounds of 256 compute units: gate/up 20.8 -> 18.6 us; 592, a fill of 0.77 against 0.925: 28.3 -> 26.5; but 896, 0.875 against 1:
+        // 64 -> 70)
         auto fill = [](int n) { return (double)n / ((n + 255) / 256 * 256); };
-        if (fill(2 * n_groups) > 1.2 * fill(n_groups)) {
+        if (fill(2 * n_groups) > 1.18 * fill(n_groups)) {
+            half = true;
             NT = 2;
             n_groups *= 2;
         }
     }
     if (NW > 8) NW = 8;
     if (MT * NT >= 8 && NW > 4) NW = 4;  // as in the dense launcher
-    if (epi == EPI_QKV) return launch_mt_nt_w4<EPI_QKV>(MT, NT, NW, n_groups, a, s);
-    if (epi == EPI_RESID) return launch_mt_nt_w4<EPI_RESID>(MT, NT, NW, n_groups, a, s);
-    if (epi == EPI_SWIGLU) return launch_mt_nt_w4<EPI_SWIGLU>(MT, NT, NW, n_groups, a, s);
-    if (epi == EPI_LOGITS) return launch_mt_nt_w4<EPI_LOGITS>(MT, NT, NW, n_groups, a, s);
+    if (epi == EPI_QKV) return launch_mt_nt_w4<EPI_QKV>(MT, NT, half, NW, n_groups, a, s);
+    if (epi == EPI_RESID) return launch_mt_nt_w4<EPI_RESID>(MT, NT, half, NW, n_groups, a, s);
+    if (epi == EPI_SWIGLU) return launch_mt_nt_w4<EPI_SWIGLU>(MT, NT, half, NW, n_groups, a, s);
+    if (epi == EPI_LOGITS) return launch_mt_nt_w4<EPI_LOGITS>(MT, NT, half, NW, n_groups, a, s);
     return hipErrorInvalidValue;
 }
 

@@ -24,7 +24,6 @@ struct GemmArgs {
     const float* ssp_in;   // [ssp_n][ssp_stride]: partial sums of squares per row
     int ssp_n, ssp_stride;
     int ldx, M, K, nkt;
-    int w_shift;     // 4-bit few-row kernel, set by the launcher: log2 of the re-tiled weights' tiles per group
     int red_copies;  // set by the launcher: copies of the workgroup's tiles the cross-wave reduction keeps in LDS
     int N;           // valid output features (packed order)
     float eps;
