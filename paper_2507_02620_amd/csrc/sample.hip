@@ -234,6 +234,7 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
         if (tid < n_child) {
             const int t = ctok[tid];
             bool dup = t < 0;
+#pragma unroll 1  // unrolled it is only more code to fetch by a cold launch
             for (int j = 0; j < tid && !dup; j += 4) {
                 const int4 c = *(const int4*)(ctok + j);
                 dup = c.x == t || (c.y == t && j + 1 < tid) || (c.z == t && j + 2 < tid) || (c.w == t && j + 3 < tid);
@@ -285,7 +286,7 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
         uint64_t base = 0;  // running sum below lo
         bool found = true;
         const int scan = n_rej < 8 ? 256 : 64;
-        for (int pass = 0; pass < 2 && found && hi - lo > scan; ++pass) {
+        for (int pass = vocab > scan ? 0 : 2; pass < 2 && found; ++pass) {
             const int part = ((hi - lo + SMP_WAVES - 1) / SMP_WAVES + 3) & ~3;  // a multiple of 4 elements per wave
             const int wlo = min(hi, lo + w * part), whi = min(hi, wlo + part);
             uint64_t z = 0;
@@ -309,6 +310,7 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
                 }
                 before += s;
             }
+            if (hi - lo <= scan) break;
         }
         x_new = vocab - 1;  // the definition's default (no weight left)
         for (int v0 = lo; found && v0 < hi; v0 += 64) {  // every wave does the same
