@@ -193,9 +193,9 @@ void make_layout(const fs_stage_desc* d, Layout& L) {
     const size_t ssp_bytes = d->dtype == FS_BF16 ? (size_t)(d->d_model / 16 + 4) * M * sizeof(float) : 0;
     L.off_sspa = take(ssp_bytes);
     L.off_sspb = take(ssp_bytes);
-    // many-row segments: scratch for the K-split partial results of the two residual projections
+    // scratch for the K-split partial results of the two residual projections (many rows; 4-bit weights: any number)
     L.part_bytes = 0;
-    if (d->dtype == FS_BF16 && d->max_seg > 16) L.part_bytes = wide_partial_bytes(d->max_seg, d->d_model / 16);
+    if (d->dtype == FS_BF16 && (w4 || d->max_seg > 16)) L.part_bytes = wide_partial_bytes(d->max_seg, d->d_model / 16);
     L.off_part = take(L.part_bytes);
     L.off_krow = take(M * sizeof(unsigned long long));  // cache slot address of every stacked row
     L.off_ancall = take((size_t)2 * d->max_tree * FS_ANC_WORDS * sizeof(uint64_t));  // two copies of every node's mask while a deep tree's are built
@@ -623,7 +623,7 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     float* sspa = st->at<float>(L.off_sspa);
     float* sspb = st->at<float>(L.off_sspb);
     // partial sums per row a residual epilogue leaves
-    auto res_parts = [&](const GemmPlan& p) { return wide ? wide_ssp_parts(l_s, d.d_model / 16) : w4_ssp_parts(l_s, p.n_groups * p.NT, p.nkt); };
+    auto res_parts = [&](const GemmPlan& p) { return wide ? wide_ssp_parts(l_s, d.d_model / 16) : w4_ssp_parts(p.NT, l_s, p.n_groups * p.NT, p.nkt); };
     const int o_parts = res_parts(L.layers[0].o), down_parts = res_parts(L.layers[0].down);
     int ssp_n_first = 0;
     // (row-major input costs the streaming kernel 64-byte pieces of 16 rows per load; from 33 rows on one conversion pass is cheaper)

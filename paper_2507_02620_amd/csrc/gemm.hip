@@ -1058,13 +1058,14 @@ __global__ void __launch_bounds__(WM * WN * KG * 64) stream_gemm_kernel(const vo
     }
 }
 
-// Sum of the K slices' raw tiles + residual epilogue, one wave per 16 x 16 tile.
+// Sum of the K slices' raw tiles + residual epilogue, one wave per 16 x 16 tile; a workgroup's four tiles (neighbours of one row tile:
+// nt_all is a multiple of 4) leave one partial sum of squares per row where the consumer wants them.
 template <int KS>
 __global__ void __launch_bounds__(256) stream_fixup_kernel(const GemmArgs a, int nt_all, const float* part) {
-    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4;
+    __shared__ float hs[4][16];
+    const int lane = threadIdx.x & 63, r16 = lane & 15, g = lane >> 4, wv = threadIdx.x >> 6;
     const int m_tiles = (a.M + 15) >> 4;
-    const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (unit >= m_tiles * nt_all) return;
+    const int unit = blockIdx.x * 4 + wv;
     const int mt = unit / nt_all, ptile = unit % nt_all, m = mt * 16 + r16, n = ptile * 16 + g * 4;
     f32x4 v[KS];
 #pragma unroll
@@ -1075,7 +1076,23 @@ __global__ void __launch_bounds__(256) stream_fixup_kernel(const GemmArgs a, int
 #pragma unroll
     for (int ks = 1; ks < KS; ++ks) sum += v[ks];
     const float y[1][4] = {{sum[0], sum[1], sum[2], sum[3]}};
-    epilogue_item<bf16_t, EPI_RESID>(a, y, 1.f, m, ptile, g, &pre);
+    float hsq = epilogue_item<bf16_t, EPI_RESID>(a, y, 1.f, m, ptile, g, &pre);
+    if (a.ssp_out) {
+        hsq = wave_xor_add(wave_xor_add(hsq, 16), 32);
+        if (g == 0) hs[wv][r16] = hsq;
+        __syncthreads();
+        if (wv == 0 && g == 0 && m < a.ssp_stride && ptile * 16 < a.N)  // not for padding tiles
+            a.ssp_out[(size_t)(ptile >> 2) * a.ssp_stride + m] = hs[0][r16] + hs[1][r16] + hs[2][r16] + hs[3][r16];
+    }
+}
+
+static hipError_t launch_stream_fixup(const GemmArgs& a, int nt_all, int k_splits, const float* part, hipStream_t s) {
+    const dim3 grid(((a.M + 15) / 16 * nt_all + 3) / 4);
+#define FS_FIX(k) \
+    case k: hipLaunchKernelGGL((stream_fixup_kernel<k>), grid, dim3(256), 0, s, a, nt_all, part); break;
+    switch (k_splits) { FS_FIX(1) FS_FIX(2) FS_FIX(3) FS_FIX(4) FS_FIX(5) FS_FIX(6) FS_FIX(7) FS_FIX(8) default: return hipErrorInvalidValue; }
+#undef FS_FIX
+    return hipGetLastError();
 }
 
 // Block geometry by projection kind and row count (see the kernel's header comment).
@@ -1248,12 +1265,7 @@ static hipError_t launch_stream_shape(int layout_nt, int n_tiles, const GemmArgs
             ks = (a.nkt + per - 1) / per;
             hipLaunchKernelGGL((stream_gemm_kernel<EPI, true, WM, WN, KG, MT, NT, R>), dim3(n_cols, ks), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags,
                                n_tiles, per, a, part);
-            const dim3 grid((m_tiles * n_cols * BNT + 3) / 4);
-#define FS_FIX(k) \
-    case k: hipLaunchKernelGGL((stream_fixup_kernel<k>), grid, dim3(256), 0, s, a, n_cols * BNT, part); break;
-            switch (ks) { FS_FIX(1) FS_FIX(2) FS_FIX(3) FS_FIX(4) FS_FIX(5) FS_FIX(6) FS_FIX(7) FS_FIX(8) }
-#undef FS_FIX
-            return hipGetLastError();
+            return launch_stream_fixup(a, n_cols * BNT, ks, part, s);
         }
     }
     hipLaunchKernelGGL((stream_gemm_kernel<EPI, false, WM, WN, KG, MT, NT, R>), dim3(n_cols), block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags, n_tiles,
@@ -1774,6 +1786,294 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     }
 }
 
+// ---- 4-bit weights, up to 64 rows: one pass over the codes, both operands through LDS --------------------------------------
+// At these row counts a workgroup of the few-row kernel above reads the whole activation block from L2 for its two or four feature
+// tiles, a larger operand than its codes (24 rows x 5120: 320 KiB against 170), in loads that are each waited for after two
+// 128-column chunks.  Here a block of WN * NT feature tiles and all rows goes through a ring of R direct-to-LDS stages, as in the dense
+// streaming kernel: KG wave groups take alternate chunks (the waves of a SIMD then unpack and multiply in turn), a stage is the
+// activations of KG chunks, the blocks' codes (a KiB per tile and chunk) and, per wave, the scales of its own tiles.
+//   * -136 * sum of the activations (the codes' offset) is formed first and is where the products' accumulators start; the chunk's
+//     result enters the sums times the scale.  f32 sums per chunk and f32 scaling as in the kernels beside it.
+//   * RMSNorm: a row's partial sums of squares are spread over the workgroup's threads in front of the ring's first load.
+//   * The groups' tiles meet in LDS; the items of the epilogue are dealt to the groups.  Residual projections are cut along K and
+//     summed by stream_fixup_kernel.
+// 5120-wide layer, 24 rows, before -> now, us: QKV 22.3 -> 18.5, output 14.7 -> 13.0, gate/up 32.2 -> 25.5, down 24.7 -> 18.4.  Gate/up without
+// unpacking and products takes 20.1: a compute unit draws 36 GB/s of codes and activations together.  What is above that is left over with
+// fragments read a stage ahead, with groups half a chunk apart and with raised wave priorities alike.
+template <int EPI, int WN, int KG, int MT, int NT, int R>
+__global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void* Wp, const void* X, const void* Sp, int nkc, int M, int lsh, int n_tiles,
+                                                                      int kc_per, const GemmArgs a, float* part) {
+    using T = bf16_t;
+    using E = Elem<T>;
+    using frag_t = E::frag_t;
+    constexpr bool NORM = (EPI != EPI_RESID);
+    constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
+    constexpr int TPI = PAIR ? 2 : 1;
+    constexpr int NW = WN * KG, BNT = WN * NT, ROWS = MT * 16, THREADS = NW * 64;
+    constexpr int AF = KG * 4 * MT, WF = KG * BNT, LA = (AF + NW - 1) / NW, LW = WF / NW, LPS = LA + LW + 1;
+    constexpr int SCALES = (AF + WF) * 1024, STAGE = SCALES + NW * 256;
+    constexpr int ITEMS = MT * NT / TPI;
+    static_assert(WF % NW == 0 && NT % TPI == 0 && NT <= 8, "every wave issues the same loads; its scales fit one of them");
+    static_assert(R >= 3 && R <= 6 && LPS * (R - 1) < 64 && R * STAGE + NW * ROWS * 4 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
+    static_assert((NW + 1) / 2 * MT * NT * 1024 <= STAGE, "the groups' tiles fit two stage buffers");
+    // one array per buffer: distinct objects, see block_gemm_kernel
+    __shared__ __align__(1024) unsigned char sb0[STAGE];
+    __shared__ __align__(1024) unsigned char sb1[STAGE];
+    __shared__ __align__(1024) unsigned char sb2[STAGE];
+    __shared__ __align__(1024) unsigned char sb3[R > 3 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char sb4[R > 4 ? STAGE : 16];
+    __shared__ __align__(1024) unsigned char sb5[R > 5 ? STAGE : 16];
+    __shared__ float rs_s[NORM ? NW * ROWS : 1];
+    auto buf_at = [&](int j) -> unsigned char* { return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : (j == 3 ? sb3 : (j == 4 ? sb4 : sb5)))); };
+
+    // grid (feature block, K slice); all rows are in one block
+    const int col = blockIdx.x, ks = blockIdx.y;
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6), kg = w / WN, wn = w % WN;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int kc_lo = ks * kc_per, n = min(kc_per, nkc - kc_lo);  // >= 1 (host)
+    const int ns = (n + KG - 1) / KG;
+    const int m_tiles = (M + 15) >> 4;
+
+    // RMSNorm: this lane's share of its row's partial sums of squares (the loads go out in front of the ring's)
+    constexpr int TPR = THREADS / ROWS, SL = MT == 1 ? 12 : 20;  // 320 partial sums and more without the loop below, which waits
+    float sp[SL], s_more = 0.f;
+    const int row = t % ROWS, sub = t / ROWS;
+    if (NORM) {
+        const int m = min(row, M - 1);
+#pragma unroll
+        for (int i = 0; i < SL; ++i) sp[i] = a.ssp_in[(size_t)min(sub + i * TPR, a.ssp_n - 1) * a.ssp_stride + m];
+#pragma unroll 8
+        for (int j = sub + SL * TPR; j < a.ssp_n; j += TPR) s_more += a.ssp_in[(size_t)j * a.ssp_stride + m];
+    }
+
+    // this wave's loads of a stage: fragments i * NW + w of the activations (chunk, k-tile, row tile), code tiles i * NW + w (chunk, feature
+    // tile), the scales of its own tiles.  A 32-bit offset per lane and load; tiles and rows beyond the matrix re-read the last one
+    const unsigned char* const xb = (const unsigned char*)X;
+    const unsigned char* const wb = (const unsigned char*)Wp;
+    const unsigned char* const sb = (const unsigned char*)Sp;
+    const unsigned wkc = 1024u << lsh, skc = 32u << lsh;  // bytes from one chunk to the next
+    unsigned xo[LA], wo[LW], so;
+    int xn[LA], wn_[LW];  // stages in which the load's chunk exists
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int f = min(i * NW + w, AF - 1), j = f / (4 * MT), mt = min(f % MT, m_tiles - 1);
+        xo[i] = ((unsigned)mt * (unsigned)nkc * 4u + (unsigned)(kc_lo + j) * 4u + (unsigned)(f / MT % 4)) * 1024u + (unsigned)(lane - r16 + min(r16, M - 1 - mt * 16)) * 16u;
+        xn[i] = (n - j + KG - 1) / KG;
+    }
+#pragma unroll
+    for (int i = 0; i < LW; ++i) {
+        const int f = i * NW + w, j = f / BNT, pc = min(col * BNT + f % BNT, n_tiles - 1);
+        wo[i] = ((((unsigned)(pc >> lsh) * (unsigned)nkc + (unsigned)(kc_lo + j)) << lsh) + (unsigned)(pc & ((1 << lsh) - 1))) * 1024u + (unsigned)lane * 16u;
+        wn_[i] = (n - j + KG - 1) / KG;
+    }
+    const int sn = (n - kg + KG - 1) / KG;
+    {  // 4 bytes per lane: lane = (tile of the wave, pair of rows); lanes beyond the wave's tiles repeat its last one
+        const int pc = min(col * BNT + wn * NT + min(lane >> 3, NT - 1), n_tiles - 1);
+        so = ((((unsigned)(pc >> lsh) * (unsigned)nkc + (unsigned)(kc_lo + kg)) << lsh) + (unsigned)(pc & ((1 << lsh) - 1))) * 32u + (unsigned)(lane & 7) * 4u;
+    }
+    const unsigned lane16 = (unsigned)lane * 16u;
+    int st = 0;
+    auto issue = [&](int j) {  // next stage -> buffer j; chunks beyond the range fetch the operands' first line (no branch around a load)
+        unsigned char* dst = buf_at(j);
+#pragma unroll
+        for (int i = 0; i < LW; ++i) {
+            const unsigned live = (unsigned)((st - wn_[i]) >> 31);  // uniform, all ones or zero
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(wb + (wo[i] & live)), FS_LDS_PTR(dst + (AF + i * NW + w) * 1024), 16, 0, 2);
+            wo[i] += KG * wkc;
+        }
+        __builtin_amdgcn_global_load_lds(FS_GLB_PTR(sb + (so & (unsigned)((st - sn) >> 31))), FS_LDS_PTR(dst + SCALES + w * 256), 4, 0, 0);
+        so += KG * skc;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {
+            const unsigned live = (unsigned)((st - xn[i]) >> 31);
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + min(i * NW + w, AF - 1) * 1024), 16, 0, 0);
+            xo[i] += KG * 4096u;
+        }
+        ++st;
+    };
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    frag_t koff;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) koff[e] = (bf16_t)(-136.0f);
+    // mask and exponent of the unpacking, one in a scalar and one in a vector register: a single and-or instruction takes both
+    unsigned nib = 0x000F000Fu, one28 = 0x43004300u;
+    asm volatile("" : "+s"(nib));
+    asm volatile("" : "+v"(one28));
+
+#pragma unroll
+    for (int j = 0; j + 1 < R; ++j) issue(j);
+    if (NORM) {  // a wave's share of every row's sum; the waves' shares are added up in the epilogue
+        __builtin_amdgcn_sched_barrier(0);  // their first use stays behind the ring's loads
+        float tot = s_more;
+#pragma unroll
+        for (int i = 0; i < SL; ++i) tot += sub + i * TPR < a.ssp_n ? sp[i] : 0.f;
+#pragma unroll
+        for (int sh = ROWS; sh < 64; sh *= 2) tot = wave_xor_add(tot, sh);
+        if (lane < ROWS) rs_s[w * ROWS + lane] = tot;
+    }
+    int cur = 0;  // stage being multiplied
+    auto stage = [&](int ju) {  // the next stage, in buffer ju
+        asm volatile("" ::: "memory");
+        FS_WAIT_VM_LGKM((R - 2) * LPS, 0);
+        __builtin_amdgcn_s_barrier();  // the stage is complete for every wave, and everybody is done with the one before
+        asm volatile("" ::: "memory");
+        issue((ju + R - 1) % R);
+        if (cur++ * KG + kg >= n) return;  // uniform; the last stage may hold fewer chunks
+        const unsigned char* b = buf_at(ju);
+        u32x4 c[NT];
+        bf16x4 s4[NT];
+        frag_t x[4][MT];
+        f32x4 tq[MT][NT];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) x[q][mt] = *(const frag_t*)(b + ((kg * 4 + q) * MT + mt) * 1024 + lane16);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) c[nt] = *(const u32x4*)(b + (AF + kg * BNT + wn * NT + nt) * 1024 + lane16);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) s4[nt] = *(const bf16x4*)(b + SCALES + w * 256 + nt * 32 + g * 8);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            f32x4 off{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) off = E::mma(koff, x[q][mt], off);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) tq[mt][nt] = off;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                unsigned pr[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) pr[j] = ((c[nt][q] >> (4 * j)) & nib) | one28;
+                const frag_t wf = __builtin_bit_cast(frag_t, u32x4{pr[0], pr[1], pr[2], pr[3]});
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) tq[mt][nt] = E::mma(wf, x[q][mt], tq[mt][nt]);
+            }
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float sc = (float)s4[nt][v];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) acc[mt][nt][v] += sc * tq[mt][nt][v];
+            }
+    };
+    int s0 = 0;
+    for (; s0 + R <= ns; s0 += R) {
+#pragma unroll
+        for (int ju = 0; ju < R; ++ju) stage(ju);
+    }
+#pragma unroll
+    for (int ju = 0; ju < R; ++ju) {
+        if (s0 + ju >= ns) break;
+        stage(ju);
+    }
+    // every load has landed and every wave has left the loop before LDS is reused or given back
+    FS_WAIT_VM_LGKM(0, 0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    // ---- the groups' tiles meet in two stage buffers; item i belongs to group i % KG ----
+    auto slot = [&](int ww) -> f32x4* { return (f32x4*)((ww & 1) ? sb1 : sb0) + (size_t)(ww >> 1) * MT * NT * 64 + lane; };
+    if constexpr (KG > 1) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) slot(w)[(mt * NT + nt) * 64] = acc[mt][nt];
+        __syncthreads();
+    }
+    const int pt0 = col * BNT + wn * NT;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        if (it % KG != kg) continue;
+        const int mt = it / (NT / TPI), ntp = it % (NT / TPI);
+        if (mt >= m_tiles) break;
+        f32x4 y4[TPI];
+#pragma unroll
+        for (int tt = 0; tt < TPI; ++tt) {
+            const int nt = ntp * TPI + tt;
+            if constexpr (KG > 1) {
+                y4[tt] = slot(wn)[(mt * NT + nt) * 64];
+#pragma unroll
+                for (int k = 1; k < KG; ++k) y4[tt] += slot(k * WN + wn)[(mt * NT + nt) * 64];
+            } else {
+                y4[tt] = acc[mt][nt];
+            }
+        }
+        if constexpr (EPI == EPI_RESID) {  // raw tiles: part[ks][m tile][n tile][lane]
+            ((f32x4*)part)[(((size_t)ks * m_tiles + mt) * (gridDim.x * BNT) + pt0 + ntp) * 64 + lane] = y4[0];
+        } else {
+            float sum = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < NW; ++ww) sum += rs_s[ww * ROWS + mt * 16 + r16];
+            const float rs = 1.0f / sqrtf(sum / (float)a.K + a.eps);
+            float y[TPI][4];
+#pragma unroll
+            for (int tt = 0; tt < TPI; ++tt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) y[tt][v] = y4[tt][v];
+            epilogue_item<T, EPI>(a, y, rs, mt * 16 + r16, pt0 + ntp * TPI, g);
+        }
+    }
+}
+
+template <int EPI, int WN, int KG, int MT, int NT, int R>
+static hipError_t launch_stream_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    constexpr int BNT = WN * NT;
+    const int n_cols = (n_tiles + BNT - 1) / BNT, m_tiles = (a.M + 15) / 16, nkc = a.nkt / 4;
+    const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
+    int ks = 1;
+    if constexpr (EPI == EPI_RESID) {  // K slices until there is about one workgroup per compute unit
+        ks = std::max(1, std::min(std::min(256 / n_cols, 8), nkc / (2 * KG)));
+        while (ks > 1 && (size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) --ks;
+        if ((size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) return hipErrorInvalidValue;
+    }
+    const int per = ((nkc + ks - 1) / ks + KG - 1) / KG * KG;
+    ks = (nkc + per - 1) / per;
+    hipLaunchKernelGGL((stream_gemm_w4_kernel<EPI, WN, KG, MT, NT, R>), dim3(n_cols, ks), dim3(WN * KG * 64), 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh, n_tiles,
+                       per, a, part);
+    if (EPI == EPI_RESID) return launch_stream_fixup(a, n_cols * BNT, ks, part, s);
+    return hipGetLastError();
+}
+
+template <int EPI>
+static hipError_t launch_stream_w4_epi(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    // Four or eight feature tiles per block: a compute unit holds one block at a time and draws its codes and the activations for it (24
+    // rows x 5120, four / eight: 960 tiles 18.5 / 24.3 us, 1728 tiles 31.3 / 25.5); residual projections fill the chip with K slices,
+    // where few tiles per block mean fewer slices to sum (11008 x 4096, 32 rows 15.7 / 16.9; but 13824 x 5120, 64 rows 27.3 / 25.3)
+    const int mt = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4, b4 = (n_tiles + 3) / 4, b8 = (n_tiles + 7) / 8;
+    const bool narrow = EPI == EPI_RESID ? mt < 4 : (b4 + 255) / 256 * (4 + 4 * mt) < (b8 + 255) / 256 * (8 + 4 * mt);
+#define FS_S(wn, kg, mt, r) return launch_stream_w4_shape<EPI, wn, kg, mt, 2, r>(layout_nt, n_tiles, a, part, part_bytes, s)
+    if (mt == 1) {
+        if (narrow) FS_S(2, 4, 1, 4);
+        FS_S(4, 2, 1, 6);
+    }
+    if (mt == 2) {
+        if (narrow) FS_S(2, 4, 2, 3);
+        FS_S(4, 2, 2, 4);
+    }
+    if constexpr (EPI != EPI_RESID) if (narrow) FS_S(2, 2, 4, 3);
+    FS_S(4, 2, 4, 3);
+#undef FS_S
+}
+
+static hipError_t launch_stream_w4(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    switch (epi) {
+        case EPI_QKV: return launch_stream_w4_epi<EPI_QKV>(layout_nt, n_tiles, a, part, part_bytes, s);
+        case EPI_RESID: return launch_stream_w4_epi<EPI_RESID>(layout_nt, n_tiles, a, part, part_bytes, s);
+        case EPI_SWIGLU: return launch_stream_w4_epi<EPI_SWIGLU>(layout_nt, n_tiles, a, part, part_bytes, s);
+        case EPI_LOGITS: return launch_stream_w4_epi<EPI_LOGITS>(layout_nt, n_tiles, a, part, part_bytes, s);
+    }
+    return hipErrorInvalidValue;
+}
+
 // Which 4-bit kernel: a round of this kernel's blocks takes 1.45 (64 rows) or 2.2 us (128 rows) per 128-column chunk, the few-row
 // kernel with four tiles per workgroup 0.37 ns per chunk, feature tile and 32-row block.  Both sides, us (few / this): 4096 x 12288,
 // 128 rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 64 rows 51 / 60, 128 rows
@@ -1791,7 +2091,34 @@ static bool block_w4_pays(int epi, int M, int n_tiles, int nkt) {
     return work > (M <= 64 ? 4200 : 6000) * rounds;
 }
 
-int w4_ssp_parts(int M, int n_tiles, int nkt) { return block_w4_pays(EPI_RESID, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles; }
+// The streaming kernel, up to 64 rows.  It runs one block per compute unit and time, so a launch costs whole rounds of blocks, and a residual
+// projection a second launch.  Both sides, us (few-row or block kernel / this):
+//   * residual: 4096 x 4096, 16 rows 9.3 / 10.5, 32 rows 12.0 / 11.9; 5120 x 5120, 16 rows 11.1 / 12.1, 24 rows 14.2 / 13.5; 8192 x 3072, 16 rows
+//     11.0 / 11.7, 24 rows 14.8 / 12.6; 11008 x 4096, 16 rows 16.1 / 13.5.  33 to 64 rows: 3072 x 3072 13.8 / 12.7, 2816 x 1024 9.5 / 12.9; where
+//     the few-row kernel's workgroups make one round (4096 features) 4096 x 4096 12.1 / 14.5, 11008 x 4096 21.4 / 20.0
+//   * QKV: 288 tiles x 3584, 16 rows 10.2 / 12.4, 24 rows 13.0 / 13.6; 384 x 2048 8.8 / 10.4, 24 rows 10.5 / 11.0; x 4096, 64 rows 22.2 / 23.9; 640 x
+//     8192, 16 rows 22.3 / 19.7, 24 rows 32.2 / 22.2; 768 x 4096, 16 rows 14.3 / 14.0, 24 rows 19.1 / 15.2
+//   * gate/up, head: 352 tiles x 1024, 16 rows 8.0 / 8.6, 24 rows 9.8 / 9.0; 704 x 2048 10.4 / 10.5, 24 rows 15.7 / 11.3; 1728 x 5120 27.7 /
+//     22.6, 24 rows 34.1 / 26.3, 64 rows 50.9 / 37.1; a second round of few blocks (2368 x 3584: 296) 27.8 / 30.1, 24 rows 35.5 / 36.0, of
+//     more (3144 x 3072: 393) 37.0 / 30.2, 24 rows 37.0 / 34.6, but 64 rows 48 / 52; 9504 x 3584 88.9 / 79.6, 24 rows 99.8 / 93.8
+static bool stream_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) {
+    if (M > 64 || n_tiles > 16000 || !block_w4_fits(M, n_tiles, nkt)) return false;  // (one slice's partial results of a residual projection: 64 MiB)
+    const int nkc = nkt / 4;
+    if (epi == EPI_RESID) {
+        if (M <= 16) return nkc > 64;
+        if (M <= 32) return nkc >= 40;
+        return nkc >= ((n_tiles + layout_nt - 1) / layout_nt * 2 <= 256 ? 80 : 24);
+    }
+    if (epi == EPI_QKV) return n_tiles >= 512;
+    const int b8 = (n_tiles + 7) / 8, rounds = (b8 + 255) / 256;
+    if (rounds > 1) return M <= 32 && b8 > 0.75 * 256 * rounds;
+    return n_tiles >= (M <= 16 ? 704 : 256);
+}
+
+int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {
+    if (stream_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt)) return (n_tiles + 3) / 4;
+    return block_w4_pays(EPI_RESID, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
+}
 
 template <int EPI, int WM, int WN, int MT, int NT, int R>
 static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
@@ -1829,6 +2156,7 @@ static hipError_t launch_block_w4(int epi, int layout_nt, int n_tiles, const Gem
 }
 
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
+    if (stream_w4_pays(epi, NT, a.M, n_groups * NT, a.nkt)) return launch_stream_w4(epi, NT, n_groups * NT, a, part, part_bytes, s);
     if (block_w4_pays(epi, a.M, n_groups * NT, a.nkt)) return launch_block_w4(epi, NT, n_groups * NT, a, part, part_bytes, s);
     // at most 32 rows per workgroup (register budget); longer segments take further row blocks, whose passes over
     // the quarter-size weights mostly hit in L2

@@ -83,8 +83,8 @@ void launch_pack_w4(const PackW4Args& a, hipStream_t s);
 hipError_t launch_prenorm(const void* X, int ldx, int M, int K, const void* gain, void* xg, float* ssp, int ssp_stride, int* n_slices,
                              hipStream_t s);
 // 4-bit weights, bf16 activations (fragment-major, with their sums of squares): w[n][k] = scale[n][k/128] * (code - 8).  A residual
-// projection leaves w4_ssp_parts(M, n_tiles, nkt) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
-int w4_ssp_parts(int M, int n_tiles, int nkt);
+// projection leaves w4_ssp_parts(layout_nt, M, n_tiles, nkt) partial sums of squares per row in ssp_out; `part` as for launch_gemm_wide.
+int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt);
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s);
 // bf16, fragment-major activations: the many-row kernel (128-row blocks; one 64-row block for an LM head or gate/up of up to 64 rows).  layout_nt
 // and n_tiles describe the re-tiled weights (tiles per group, 16-feature tiles in total); normed projections need ssp_in from 384

@@ -175,3 +175,21 @@ def test_w4_residual_projections_of_a_short_k(rows):
     pair = Pair(cfg, seed=6, w4=True)
     o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, 6), rows)
     assert max_rel_err(g, o) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows,ffn", [(1, 8320), (16, 8320), (17, 5248), (32, 5248), (33, 10368), (64, 10368)])
+def test_w4_streaming_kernel(rows, ffn):
+    """Up to 64 rows through the LDS-fed 4-bit kernel: QKV and gate/up in blocks of four and eight tiles, the down projection in K slices
+    of an odd number of chunks, a head whose last block is ragged; both ends of each row-tile count."""
+    import torch
+    from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
+    cfg = synth.StageConfig(f"w4s-{rows}", "bf16", 2, 256, 32, 16, 128, ffn, 11300, 20, rows, rows, 5, 3, qkv_bias=True)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, head=True, w4=True)
+    o, g = pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)
+    L = cfg.l_glo + rows
+    kerr = max_rel_err(pair.kv[:, :, :, cfg.l_glo:L].float().cpu().numpy(), pair.orc.kv[:, :, :, cfg.l_glo:L])
+    x = synth.storage(cfg, o.astype(np.float32))
+    lo, _ = pair.orc.logits(x.astype(np.float64))
+    lg, _ = pair.gpu.tree_logits(to_dev(x, torch.bfloat16))
+    assert max_rel_err(g, o) < TOL["bf16"] and kerr < TOL["bf16"] and max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
