@@ -1547,11 +1547,12 @@ static hipError_t launch_mt_nt_w4(int MT, int NT, bool half, int NW, int n_group
 // features: at a few hundred rows it is bound by both (13B layer, 389 rows: 1048 us, now 528).  Here a workgroup of WM x WN waves owns
 // 16 * WM * MT rows x 16 * WN * NT features; a stage is one 128-column chunk: the rows' fragments of its four k-tiles, the feature
 // tiles' codes (a KiB each) and scales, all by direct-to-LDS loads, R buffers.  A wave unpacks its NT code tiles once per chunk
-// into 16 operand registers each (2 VALU operations per pair of weights) and multiplies them with MT row tiles; the chunk's result
-// gets -136 * sum of the activations added (one more MFMA per row tile and k-tile, shared by the NT feature tiles) and enters the
-// accumulators times the scale.  Per chunk and wave of 4 x 4 tiles: 80 MFMAs (64 of them products), about 250 VALU operations, 20 KB
-// of LDS reads.  A 128 x 256 block takes 2.2 us per chunk, of which 1.25 us is its MFMAs with two waves per SIMD: unpacking and
-// scaling share the issue slots with them (1024 rows x 27648 features x 5120: 1171 -> 349 us, 0.83 PFLOP/s).  Same arithmetic as the
+// into 16 operand registers each (2 VALU operations per pair of weights) and multiplies them with MT row tiles; the chunk's products start
+// at -136 * sum of the activations, which the waves work out for one row tile each, a stage ahead, and share through LDS (each for its own
+// row tiles, added behind the products, before: 389 rows x 27648 features x 5120 188 -> 182 us), and enter the accumulators times the
+// scale.  Per chunk and wave of 4 x 4 tiles: 68 MFMAs (64 of them products), about 200 VALU operations, 24 KB of LDS reads.  A 128 x 256
+// block takes 2.2 us per chunk; 1.3 its MFMAs alone, 1.1 its loads alone, 1.9 everything but the loads, and none of the LDS reads, the
+// unpacking or the scaling more than 0.15 when it is left out (1024 rows x 27648 features x 5120: 0.8 PFLOP/s).  Same arithmetic as the
 // few-row kernel: exact codes, f32 sums per chunk, f32 scaling.
 template <int EPI, bool PARTIAL, int WM, int WN, int MT, int NT, int R>
 __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void* Wp, const void* X, const void* Sp, int nkc, int M, int lsh, int n_tiles,
@@ -1563,21 +1564,25 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     constexpr int TPI = PAIR ? 2 : 1;
     constexpr int NW = WM * WN, BMT = WM * MT, BNT = WN * NT, ROWS = BMT * 16, THREADS = NW * 64;
-    constexpr int AF = 4 * BMT, LA = AF / NW, LW = BNT / NW, LPS = LA + LW + 1;
+    constexpr int AF = 4 * BMT, LA = (AF + NW - 1) / NW, LW = BNT / NW, LPS = LA + LW + 1;
     constexpr int SCALES = (AF + BNT) * 1024, STAGE = SCALES + NW * 256;
-    static_assert(AF % NW == 0 && BNT % NW == 0, "every wave issues the same loads");
-    static_assert((R == 3 || R == 4) && LPS * (R - 1) < 64 && R * STAGE + ROWS * 8 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
-    static_assert(NT <= 8 && THREADS % ROWS == 0, "a wave's scales fit one load; whole rows per pass of the row-scale sums");
+    static_assert(BNT % NW == 0 && BMT <= NW, "every wave issues the same loads");
+    static_assert((R == 3 || R == 4) && LPS * (R - 1) < 64 && R * STAGE + ROWS * 12 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
+    static_assert(NT <= 8, "a wave's scales fit one load");
     __shared__ __align__(1024) unsigned char sb0[STAGE];
     __shared__ __align__(1024) unsigned char sb1[STAGE];
     __shared__ __align__(1024) unsigned char sb2[STAGE];
     __shared__ __align__(1024) unsigned char sb3[R > 3 ? STAGE : 16];
     __shared__ float rs_s[ROWS];
+    __shared__ float off_s[2][ROWS];
     auto buf_at = [&](int j) -> unsigned char* { return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : sb3)); };
 
-    // grid (8 * row blocks, feature blocks / 8, K slices): the row blocks of a feature block are neighbours on one XCD
-    const int mb = blockIdx.x >> 3, col = blockIdx.y * 8 + (blockIdx.x & 7), ks = blockIdx.z;
-    if (col * BNT >= n_tiles) return;
+    // grid (8 * row blocks, units / 8), unit = (K slice, feature block): an XCD takes neighbouring units, most of one slice, and all their
+    // row blocks, and no XCD more than its share (slices of 20 feature blocks padded to 24 instead left half the XCDs with 36 blocks for
+    // 32 compute units: 389 rows, 13824 x 5120 163 -> 93 us, 5120 x 5120 70 -> 48)
+    const int n_cols = (n_tiles + BNT - 1) / BNT, unit = (int)((blockIdx.x & 7) * gridDim.y + blockIdx.y);
+    const int mb = blockIdx.x >> 3, ks = unit / n_cols, col = unit - ks * n_cols;
+    if (ks * kc_per >= nkc) return;
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w / WN, wn = w % WN;
     const int r16 = lane & 15, g = lane >> 4;
@@ -1587,13 +1592,15 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     // RMSNorm: this thread's share of its row's partial sums of squares (the loads go out in front of the ring's)
     constexpr int TPR = THREADS / ROWS, SL = 8;
     float sp[SL], s_more = 0.f;
-    const int row = t % ROWS, sub = t / ROWS;
+    const int row = t % ROWS, sub = t / ROWS;  // (threads beyond the last whole pass over the rows have no share)
     if (NORM) {
         const int m = min(mt0 * 16 + row, M - 1);
 #pragma unroll
         for (int i = 0; i < SL; ++i) sp[i] = a.ssp_in[(size_t)min(sub + i * TPR, a.ssp_n - 1) * a.ssp_stride + m];
+        if (sub < TPR) {
 #pragma unroll 8
-        for (int j = sub + SL * TPR; j < a.ssp_n; j += TPR) s_more += a.ssp_in[(size_t)j * a.ssp_stride + m];
+            for (int j = sub + SL * TPR; j < a.ssp_n; j += TPR) s_more += a.ssp_in[(size_t)j * a.ssp_stride + m];
+        }
     }
 
     // this wave's loads of a stage: fragments i * NW + w of the activations (k-tile, row tile), code tiles i * NW + w, its own scales
@@ -1604,7 +1611,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     unsigned xo[LA], wo[LW], so;
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-        const int f = i * NW + w, mt = min(mt0 + f % BMT, m_tiles - 1);
+        const int f = min(i * NW + w, AF - 1), mt = min(mt0 + f % BMT, m_tiles - 1);
         xo[i] = ((unsigned)mt * (unsigned)nkc * 4u + (unsigned)kc_lo * 4u + (unsigned)(f / BMT)) * 1024u + (unsigned)lane * 16u;
     }
 #pragma unroll
@@ -1623,7 +1630,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
         const unsigned live = (unsigned)((st - ns) >> 31);  // uniform, all ones or zero
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
-            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + (i * NW + w) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + min(i * NW + w, AF - 1) * 1024), 16, 0, 0);
             xo[i] += 4096u;
         }
 #pragma unroll
@@ -1663,18 +1670,35 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
             asm volatile("" ::: "memory");
         }
     }
+    // -136 * sum of the activations, per row, of the chunk in buffer j: a row tile per wave, for everybody
+    auto offsets = [&](int j, int set) {
+        if (BMT < NW && w >= BMT) return;
+        const unsigned char* b = buf_at(j);
+        f32x4 o = zero;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o = E::mma(koff, *(const frag_t*)(b + (q * BMT + w) * 1024 + lane16), o);
+        if (g == 0) off_s[set][w * 16 + r16] = o[0];
+    };
+    asm volatile("" ::: "memory");
+    FS_WAIT_VM_LGKM((R - 2) * LPS, 0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    offsets(0, 0);
+    int par = 0;
     auto stage = [&](int ju) {  // the next stage, in buffer ju
         asm volatile("" ::: "memory");
-        FS_WAIT_VM_LGKM((R - 2) * LPS, 0);
-        __builtin_amdgcn_s_barrier();  // the stage is complete for every wave, and everybody is done with the one before
+        FS_WAIT_VM_LGKM((R - 3) * LPS, 0);
+        __builtin_amdgcn_s_barrier();  // the stage behind this one is complete for every wave, and everybody is done with the one before
         asm volatile("" ::: "memory");
         issue((ju + R - 1) % R);
-        if (!works) return;
+        const int set = par;
+        par ^= 1;
+        if (!works) return offsets((ju + 1) % R, par);
         const unsigned char* b = buf_at(ju);
         u32x4 c[NT];
         bf16x4 s4[NT];
         frag_t wf[2][NT], x[2][MT];
-        f32x4 tq[MT][NT], off[MT];
+        f32x4 tq[MT][NT];
         auto unpack = [&](int set, int q) {
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
@@ -1691,10 +1715,13 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) c[nt] = *(const u32x4*)(b + (AF + wn * NT + nt) * 1024 + lane16);
         read_x(0, 0);
+        float off[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) off[mt] = off_s[set][(wm * MT + mt) * 16 + r16];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) s4[nt] = *(const bf16x4*)(b + SCALES + w * 256 + nt * 32 + g * 8);
         unpack(0, 0);
-        // k-tile by k-tile: the next one's operands are read and unpacked while this one's MFMAs run
+        // k-tile by k-tile: the next one's operands are read and unpacked while this one's MFMAs run; the products start at the offsets
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int cu = q & 1, nx = cu ^ 1;
@@ -1705,25 +1732,25 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) tq[mt][nt] = E::mma(wf[cu][nt], x[cu][mt], q ? tq[mt][nt] : zero);
-                off[mt] = E::mma(koff, x[cu][mt], q ? off[mt] : zero);
+                for (int nt = 0; nt < NT; ++nt) tq[mt][nt] = E::mma(wf[cu][nt], x[cu][mt], q ? tq[mt][nt] : f32x4{off[mt], off[mt], off[mt], off[mt]});
             }
             if (q < 3) {
                 __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);  // the next k-tile's LDS reads first
 #pragma unroll
-                for (int k = 0; k < MT * (NT + 1); ++k) {
+                for (int k = 0; k < MT * NT; ++k) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, (7 * NT + MT * (NT + 1) - 1) / (MT * (NT + 1)), 0);  // its share of the unpacking
+                    __builtin_amdgcn_sched_group_barrier(0x002, (7 * NT + MT * NT - 1) / (MT * NT), 0);  // its share of the unpacking
                 }
             }
         }
+        offsets((ju + 1) % R, par);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const float sc = (float)s4[nt][v];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt][v] += sc * (tq[mt][nt][v] + off[mt][v]);
+                for (int mt = 0; mt < MT; ++mt) acc[mt][nt][v] += sc * tq[mt][nt][v];
             }
     };
     int s0 = 0;
@@ -1743,7 +1770,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
 
     const int pt0 = col * BNT + wn * NT;
     if constexpr (PARTIAL) {  // raw tiles: part[ks][m tile][n tile][lane]
-        const int nt_all = (int)gridDim.y * 8 * BNT;
+        const int nt_all = n_cols * BNT;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             const int mtile = mt0 + wm * MT + mt;
@@ -2124,21 +2151,21 @@ template <int EPI, int WM, int WN, int MT, int NT, int R>
 static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
     constexpr int BMT = WM * MT, BNT = WN * NT;
     static_assert(BNT == 16, "the residual projections' sums of squares come per 16 feature tiles");
-    const int m_tiles = (a.M + 15) / 16, m_blocks = (m_tiles + BMT - 1) / BMT, cols8 = ((n_tiles + BNT - 1) / BNT + 7) / 8, nkc = a.nkt / 4;
+    const int m_tiles = (a.M + 15) / 16, m_blocks = (m_tiles + BMT - 1) / BMT, n_cols = (n_tiles + BNT - 1) / BNT, nkc = a.nkt / 4;
     const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
     const dim3 block(WM * WN * 64);
     if constexpr (EPI == EPI_RESID) {
-        int ks = std::min(std::min(256 / ((n_tiles + BNT - 1) / BNT * m_blocks), 8), nkc / 4);
-        while (ks > 1 && (size_t)ks * m_tiles * cols8 * 8 * BNT * 1024 > part_bytes) --ks;
+        int ks = std::min(std::min(256 / (n_cols * m_blocks), 8), nkc / 4);
+        while (ks > 1 && (size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) --ks;
         if (ks > 1) {
             const int per = (nkc + ks - 1) / ks;
             ks = (nkc + per - 1) / per;
-            hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, true, WM, WN, MT, NT, R>), dim3(8 * m_blocks, cols8, ks), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh,
+            hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, true, WM, WN, MT, NT, R>), dim3(8 * m_blocks, (n_cols * ks + 7) / 8), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh,
                                n_tiles, per, a, part);
-            return launch_fixup<4>(a, cols8 * 8 * BNT, ks, part, s);
+            return launch_fixup<4>(a, n_cols * BNT, ks, part, s);
         }
     }
-    hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, false, WM, WN, MT, NT, R>), dim3(8 * m_blocks, cols8, 1), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh, n_tiles,
+    hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, false, WM, WN, MT, NT, R>), dim3(8 * m_blocks, (n_cols + 7) / 8), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh, n_tiles,
                        nkc, a, nullptr);
     return hipGetLastError();
 }

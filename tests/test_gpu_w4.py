@@ -193,3 +193,16 @@ def test_w4_streaming_kernel(rows, ffn):
     lo, _ = pair.orc.logits(x.astype(np.float64))
     lg, _ = pair.gpu.tree_logits(to_dev(x, torch.bfloat16))
     assert max_rel_err(g, o) < TOL["bf16"] and kerr < TOL["bf16"] and max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows", [140, 177, 225])
+@pytest.mark.parametrize("d,ffn", [(4864, 3072), (128, 9728)])
+def test_w4_row_blocks_of_equal_height(rows, d, ffn):
+    """128-row blocks that share the row tiles evenly (5, 6 and 8 tiles; waves of 3 + 2, 3 + 3 and 4 + 4): the down projection of 19 feature
+    blocks in K slices (4864 columns), gate/up (128 columns)."""
+    from tests.gpu_util import TOL, Pair, max_rel_err
+    cfg = synth.StageConfig(f"w4e-{rows}", "bf16", 1 if d > 128 else 2, d, 2, 1, 64, ffn, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name} {d}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, rows), rows)
+    assert max_rel_err(g, o) < TOL["bf16"]
