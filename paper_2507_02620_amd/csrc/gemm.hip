@@ -1556,7 +1556,7 @@ static hipError_t launch_mt_nt_w4(int MT, int NT, bool half, int NW, int n_group
 // few-row kernel: exact codes, f32 sums per chunk, f32 scaling.
 template <int EPI, bool PARTIAL, int WM, int WN, int MT, int NT, int R>
 __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void* Wp, const void* X, const void* Sp, int nkc, int M, int lsh, int n_tiles,
-                                                                     int kc_per, const GemmArgs a, float* part) {
+                                                                     int kc_per, int bt, const GemmArgs a, float* part) {
     using T = bf16_t;
     using E = Elem<T>;
     using frag_t = E::frag_t;
@@ -1587,7 +1587,11 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w / WN, wn = w % WN;
     const int r16 = lane & 15, g = lane >> 4;
     const int kc_lo = ks * kc_per, ns = min(kc_per, nkc - kc_lo);  // >= 1 (host)
-    const int mt0 = mb * BMT, m_tiles = (M + 15) >> 4;
+    const int mt0 = mb * bt, m_tiles = (M + 15) >> 4;
+    // the block's bt row tiles (at most BMT), half of them for each row of waves: a block of 7 rather than 8 row tiles (389 rows in four
+    // blocks) 182 -> 173 us, of 5 (140 rows in two) 91 -> 63
+    const int tb = wm * (bt - bt / 2), my = WM == 1 ? bt : wm ? bt / 2 : bt - bt / 2;
+    static_assert(WM <= 2, "");
 
     // RMSNorm: this thread's share of its row's partial sums of squares (the loads go out in front of the ring's)
     constexpr int TPR = THREADS / ROWS, SL = 8;
@@ -1611,7 +1615,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     unsigned xo[LA], wo[LW], so;
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-        const int f = min(i * NW + w, AF - 1), mt = min(mt0 + f % BMT, m_tiles - 1);
+        const int f = min(i * NW + w, AF - 1), mt = min(mt0 + min(f % BMT, bt - 1), m_tiles - 1);
         xo[i] = ((unsigned)mt * (unsigned)nkc * 4u + (unsigned)kc_lo * 4u + (unsigned)(f / BMT)) * 1024u + (unsigned)lane * 16u;
     }
 #pragma unroll
@@ -1655,7 +1659,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     unsigned nib = 0x000F000Fu, one28 = 0x43004300u;
     asm volatile("" : "+s"(nib));
     asm volatile("" : "+v"(one28));
-    const bool works = (mt0 + wm * MT) * 16 < M;  // uniform: a wave whose rows all lie beyond the matrix only loads
+    const bool works = (mt0 + tb) * 16 < M;  // uniform: a wave whose rows all lie beyond the matrix only loads
 
 #pragma unroll
     for (int j = 0; j + 1 < R; ++j) issue(j);
@@ -1685,84 +1689,91 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     asm volatile("" ::: "memory");
     offsets(0, 0);
     int par = 0;
-    auto stage = [&](int ju) {  // the next stage, in buffer ju
-        asm volatile("" ::: "memory");
-        FS_WAIT_VM_LGKM((R - 3) * LPS, 0);
-        __builtin_amdgcn_s_barrier();  // the stage behind this one is complete for every wave, and everybody is done with the one before
-        asm volatile("" ::: "memory");
-        issue((ju + R - 1) % R);
-        const int set = par;
-        par ^= 1;
-        if (!works) return offsets((ju + 1) % R, par);
-        const unsigned char* b = buf_at(ju);
-        u32x4 c[NT];
-        bf16x4 s4[NT];
-        frag_t wf[2][NT], x[2][MT];
-        f32x4 tq[MT][NT];
-        auto unpack = [&](int set, int q) {
+    auto run = [&](auto tiles) {  // tiles: the wave's row tiles
+        constexpr int MX = decltype(tiles)::value;
+        auto stage = [&](int ju) {  // the next stage, in buffer ju
+            asm volatile("" ::: "memory");
+            FS_WAIT_VM_LGKM((R - 3) * LPS, 0);
+            __builtin_amdgcn_s_barrier();  // the stage behind this one is complete for every wave, and everybody is done with the one before
+            asm volatile("" ::: "memory");
+            issue((ju + R - 1) % R);
+            const int set = par;
+            par ^= 1;
+            if (!works) return offsets((ju + 1) % R, par);
+            const unsigned char* b = buf_at(ju);
+            u32x4 c[NT];
+            bf16x4 s4[NT];
+            frag_t wf[2][NT], x[2][MX];
+            f32x4 tq[MX][NT];
+            auto unpack = [&](int set, int q) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                unsigned pr[4];
+                for (int nt = 0; nt < NT; ++nt) {
+                    unsigned pr[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) pr[j] = ((c[nt][q] >> (4 * j)) & nib) | one28;
-                wf[set][nt] = __builtin_bit_cast(frag_t, u32x4{pr[0], pr[1], pr[2], pr[3]});
-            }
-        };
-        auto read_x = [&](int set, int q) {
+                    for (int j = 0; j < 4; ++j) pr[j] = ((c[nt][q] >> (4 * j)) & nib) | one28;
+                    wf[set][nt] = __builtin_bit_cast(frag_t, u32x4{pr[0], pr[1], pr[2], pr[3]});
+                }
+            };
+            auto read_x = [&](int set, int q) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) x[set][mt] = *(const frag_t*)(b + (q * BMT + wm * MT + mt) * 1024 + lane16);
-        };
+                for (int mt = 0; mt < MX; ++mt) x[set][mt] = *(const frag_t*)(b + (q * BMT + tb + mt) * 1024 + lane16);
+            };
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) c[nt] = *(const u32x4*)(b + (AF + wn * NT + nt) * 1024 + lane16);
-        read_x(0, 0);
-        float off[MT];
+            for (int nt = 0; nt < NT; ++nt) c[nt] = *(const u32x4*)(b + (AF + wn * NT + nt) * 1024 + lane16);
+            read_x(0, 0);
+            float off[MX];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) off[mt] = off_s[set][(wm * MT + mt) * 16 + r16];
+            for (int mt = 0; mt < MX; ++mt) off[mt] = off_s[set][(tb + mt) * 16 + r16];
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) s4[nt] = *(const bf16x4*)(b + SCALES + w * 256 + nt * 32 + g * 8);
-        unpack(0, 0);
-        // k-tile by k-tile: the next one's operands are read and unpacked while this one's MFMAs run; the products start at the offsets
+            for (int nt = 0; nt < NT; ++nt) s4[nt] = *(const bf16x4*)(b + SCALES + w * 256 + nt * 32 + g * 8);
+            unpack(0, 0);
+            // k-tile by k-tile: the next one's operands are read and unpacked while this one's MFMAs run; the products start at the offsets
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int cu = q & 1, nx = cu ^ 1;
-            if (q < 3) {
-                read_x(nx, q + 1);
-                unpack(nx, q + 1);
-            }
+            for (int q = 0; q < 4; ++q) {
+                const int cu = q & 1, nx = cu ^ 1;
+                if (q < 3) {
+                    read_x(nx, q + 1);
+                    unpack(nx, q + 1);
+                }
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
+                for (int mt = 0; mt < MX; ++mt) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) tq[mt][nt] = E::mma(wf[cu][nt], x[cu][mt], q ? tq[mt][nt] : f32x4{off[mt], off[mt], off[mt], off[mt]});
-            }
-            if (q < 3) {
-                __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);  // the next k-tile's LDS reads first
+                    for (int nt = 0; nt < NT; ++nt) tq[mt][nt] = E::mma(wf[cu][nt], x[cu][mt], q ? tq[mt][nt] : f32x4{off[mt], off[mt], off[mt], off[mt]});
+                }
+                if (q < 3) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, MX, 0);  // the next k-tile's LDS reads first
 #pragma unroll
-                for (int k = 0; k < MT * NT; ++k) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // one MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, (7 * NT + MT * NT - 1) / (MT * NT), 0);  // its share of the unpacking
+                    for (int k = 0; k < MX * NT; ++k) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                  // one MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x002, (7 * NT + MX * NT - 1) / (MX * NT), 0);  // its share of the unpacking
+                    }
                 }
             }
+            offsets((ju + 1) % R, par);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float sc = (float)s4[nt][v];
+#pragma unroll
+                    for (int mt = 0; mt < MX; ++mt) acc[mt][nt][v] += sc * tq[mt][nt][v];
+                }
+        };
+        int s0 = 0;
+        for (; s0 + R <= ns; s0 += R) {
+#pragma unroll
+            for (int ju = 0; ju < R; ++ju) stage(ju);
         }
-        offsets((ju + 1) % R, par);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float sc = (float)s4[nt][v];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt][v] += sc * tq[mt][nt][v];
-            }
+        for (int ju = 0; ju < R; ++ju) {
+            if (s0 + ju >= ns) break;
+            stage(ju);
+        }
     };
-    int s0 = 0;
-    for (; s0 + R <= ns; s0 += R) {
-#pragma unroll
-        for (int ju = 0; ju < R; ++ju) stage(ju);
-    }
-#pragma unroll
-    for (int ju = 0; ju < R; ++ju) {
-        if (s0 + ju >= ns) break;
-        stage(ju);
-    }
+    if (my == MT)
+        run(std::integral_constant<int, MT>());
+    else
+        run(std::integral_constant<int, MT - 1>());
     // every load has landed and every wave has left the loop before LDS is reused or given back
     FS_WAIT_VM_LGKM(0, 0);
     __builtin_amdgcn_s_barrier();
@@ -1773,8 +1784,8 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
         const int nt_all = n_cols * BNT;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            const int mtile = mt0 + wm * MT + mt;
-            if (mtile >= m_tiles) break;
+            const int mtile = mt0 + tb + mt;
+            if (mt >= my || mtile >= m_tiles) break;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) ((f32x4*)part)[(((size_t)ks * m_tiles + mtile) * nt_all + pt0 + nt) * 64 + lane] = acc[mt][nt];
         }
@@ -1783,7 +1794,8 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     float* hs = (float*)sb0;  // residual projections: [WN feature waves][ROWS] sums of squares
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const int lr = (wm * MT + mt) * 16 + r16, m = mt0 * 16 + lr;
+        if (mt >= my) break;
+        const int lr = (tb + mt) * 16 + r16, m = mt0 * 16 + lr;
         const float rs = NORM ? 1.0f / sqrtf(rs_s[lr] / (float)a.K + a.eps) : 1.f;
         float hsq = 0.f;
 #pragma unroll
@@ -1803,7 +1815,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     if constexpr (EPI == EPI_RESID) {
         if (a.ssp_out) {
             __syncthreads();
-            for (int r = t; r < ROWS; r += THREADS) {
+            for (int r = t; r < bt * 16; r += THREADS) {
                 float sum = 0.f;
 #pragma unroll
                 for (int k = 0; k < WN; ++k) sum += hs[k * ROWS + r];
@@ -2152,21 +2164,33 @@ static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a,
     constexpr int BMT = WM * MT, BNT = WN * NT;
     static_assert(BNT == 16, "the residual projections' sums of squares come per 16 feature tiles");
     const int m_tiles = (a.M + 15) / 16, m_blocks = (m_tiles + BMT - 1) / BMT, n_cols = (n_tiles + BNT - 1) / BNT, nkc = a.nkt / 4;
+    const int bt = (m_tiles + m_blocks - 1) / m_blocks;  // row tiles per block: a round lasts as long as its tallest block
     const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
     const dim3 block(WM * WN * 64);
     if constexpr (EPI == EPI_RESID) {
-        int ks = std::min(std::min(256 / (n_cols * m_blocks), 8), nkc / 4);
-        while (ks > 1 && (size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) --ks;
+        // K slices: whole rounds of blocks, 2.2 us a chunk, against a slice's partial results, 0.5 us a MiB to write and sum (13824 x 5120, 1024
+        // rows: 160 blocks on 256 compute units 235 us, 3 slices 188)
+        int ks = 1;
+        double best = 1e30;
+        for (int k = 1; k <= std::min(8, std::max(1, nkc / 4)); ++k) {
+            const size_t bytes = (size_t)k * m_tiles * n_cols * BNT * 1024;
+            if (k > 1 && bytes > part_bytes) break;
+            const double cost = ((n_cols * k + 7) / 8 * m_blocks + 31) / 32 * ((nkc + k - 1) / k) * (2.2 / BMT * bt) + (k > 1 ? 4 + bytes * 0.5e-6 : 0);
+            if (cost < best) {
+                best = cost;
+                ks = k;
+            }
+        }
         if (ks > 1) {
             const int per = (nkc + ks - 1) / ks;
             ks = (nkc + per - 1) / per;
             hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, true, WM, WN, MT, NT, R>), dim3(8 * m_blocks, (n_cols * ks + 7) / 8), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh,
-                               n_tiles, per, a, part);
+                               n_tiles, per, bt, a, part);
             return launch_fixup<4>(a, n_cols * BNT, ks, part, s);
         }
     }
     hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, false, WM, WN, MT, NT, R>), dim3(8 * m_blocks, (n_cols + 7) / 8), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh, n_tiles,
-                       nkc, a, nullptr);
+                       nkc, bt, a, nullptr);
     return hipGetLastError();
 }
 
