@@ -247,9 +247,10 @@ __global__ void __launch_bounds__(64) argmax_final_kernel(const int32_t* __restr
     if (threadIdx.x == 0) amax[row] = b.i;
 }
 
-// From 64 rows on there are enough workgroups with one per row: a single launch, every thread with several independent
-// 16-byte loads in flight (512 rows x 32000: 35 -> 16 us; at 16 - 32 rows the two-launch form with 64 chunks per row is as
-// fast or faster).
+// One workgroup per row in a single launch, every thread with several independent 16-byte loads in flight.  From 64 rows on (512 rows x
+// 32000: 35 -> 16 us), and for any number of rows while a row's way through one compute unit is shorter than a second launch (two
+// launches / one, us, 16 rows: 1024 logits 8.3 / 6.2, 32000 8.4 / 7.5, 50304 8.4 / 7.6, 128256 9.6 / 11.4; rows that are not on 16 bytes go
+// element by element: 152066 10.2 / 54).
 __global__ void __launch_bounds__(1024) argmax_row_kernel(const float* __restrict__ logits, int vocab, int32_t* __restrict__ amax) {
     const int row = blockIdx.x;
     const float* p = logits + (size_t)row * vocab;
@@ -275,7 +276,8 @@ __global__ void __launch_bounds__(1024) argmax_row_kernel(const float* __restric
 }
 
 hipError_t launch_argmax(const float* logits, int rows, int vocab, int chunks, int32_t* work, int32_t* amax, hipStream_t s) {
-    if (rows >= 64) {
+    const bool vec = (vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0;
+    if (rows >= 64 || vocab <= (vec ? 65536 : 4096)) {
         hipLaunchKernelGGL(argmax_row_kernel, dim3(rows), dim3(1024), 0, s, logits, vocab, amax);
         return hipGetLastError();
     }

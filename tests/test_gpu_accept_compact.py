@@ -97,6 +97,11 @@ def test_argmax_from_logits_bit_exact_with_ties(rows, vocab):
     assert g_res.as_tuple() == o_res.as_tuple() and np.array_equal(g_ret, o_ret)
 
 
+@pytest.mark.parametrize("rows,vocab", [(3, 4095), (3, 4096), (3, 4097), (3, 65536), (3, 65537), (3, 65540)])
+def test_argmax_on_either_side_of_the_one_launch_form(rows, vocab):
+    test_argmax_from_logits_bit_exact_with_ties(rows, vocab)
+
+
 def _stage_for_compact(dtype, n_layers, Hkv, hd, cap):
     fs = _fs()
     cfg = synth.StageConfig("cmp", dtype, n_layers, 64 * 2, 2 * (Hkv if Hkv > 1 else 1), Hkv, hd, 64, 0, 0, 16, 16, 4, 0)

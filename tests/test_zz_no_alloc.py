@@ -33,10 +33,16 @@ def _both(T, n_ver, vocab, seed):
 
 
 def test_noalloc_accept_matches_accept_twice_in_a_row_second_call_smaller():
-    first = _both(200, 48, 32000, 11)     # 48 rows: the two-pass argmax, whose partial maxima live in the static array
+    first = _both(200, 48, 32000, 11)     # (the two-pass argmax, whose partial maxima live in the static array: next test)
     second = _both(40, 16, 1000, 12)      # smaller tree, fewer rows, smaller vocabulary: stale partials must not matter
     third = _both(300, 300, 5000, 13)     # 64 rows and more take the single-pass argmax (no scratch at all)
     print("  results:", first, second, third, flush=True)
+
+
+def test_noalloc_accept_through_the_static_array_twice_in_a_row():
+    """Fewer than 64 rows of a large vocabulary: the two-pass argmax; the second call finds the first one's partial maxima."""
+    _both(200, 48, 80000, 11)
+    _both(40, 16, 66000, 12)
 
 
 def test_noalloc_rejects_sizes_beyond_its_scratch():
