@@ -394,12 +394,11 @@ __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel
     __shared__ __align__(16) unsigned char xs[2][BMT * 1024];
     __shared__ float rs_s[BMT * 16];
 
-    // XCD-aware placement: slot s of XCD x (workgroup id = s * 8 + x) takes feature block (s / m_blocks) * 8 + x, row block s % m_blocks
-    // (with split K the slot also runs over the K slices of a block, innermost)
-    const int id = blockIdx.x, xcd = id & 7, slot = id >> 3;
-    const int per_col = m_blocks * k_splits;
-    const int col = (slot / per_col) * 8 + xcd, mb = (slot % per_col) / k_splits, ks = slot % k_splits;
-    if (col >= n_cols) return;
+    // XCD-aware placement (workgroup id = slot * 8 + XCD): an XCD takes neighbouring units, unit = (K slice, feature block), with all their row
+    // blocks: the weights are shared, a slice's part of the activations too, and no XCD gets more than its share of the units
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, units = n_cols * k_splits;
+    const int unit = (units * xcd >> 3) + slot / m_blocks, mb = slot % m_blocks, ks = unit / n_cols, col = unit % n_cols;
+    if (unit >= units * (xcd + 1) >> 3) return;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int r16 = lane & 15, g = lane >> 4;
     const int kt_lo = (int)((long long)a.nkt * ks / k_splits), nkt = (int)((long long)a.nkt * (ks + 1) / k_splits) - kt_lo;  // >= 1 (host)
@@ -1113,10 +1112,11 @@ static WideShape wide_shape(int epi, int M) {
 struct WideGrid {
     int n_cols, m_blocks, k_splits;
 };
-// K slices for the d_model-wide residual projections: until there is about one workgroup per compute unit (measured: at 512
-// rows 4 slices -> 256 workgroups take 36 / 60 us for the attention-output / down projection, 8 slices 52 / 80 us; every
-// further slice adds a full set of partial tiles to write and to sum), at least 8 k-tiles per slice, and no more than the
-// scratch array holds.
+// K slices for the d_model-wide residual projections: the number that costs least in rounds of one block per compute unit (0.43 us per
+// k-tile of a 128 x 256 block, 0.3 of a 128 x 128 one, 4 us into and out of it, 15 with the residual epilogue), partial results (0.5 us a MiB
+// to write and sum) and the launch that sums them; at least 8 k-tiles per slice, and no more than the scratch array holds.  512 rows x
+// 4096: 4 slices -> 256 workgroups 36 / 60 us for the attention-output / down projection, 8 slices 52 / 80; 13824 x 5120: 2 slices 117 us,
+// 3 slices 95; 700 rows 1 slice 172, 3 slices 129; 1024 rows x 1024 x 1024: 1 slice 31.7, 4 slices 20.3.
 static WideGrid wide_grid(const WideShape& sh, int epi, int M, int n_tiles, int nkt, size_t part_bytes) {
     WideGrid g;
     const int col_tiles = sh.waves * sh.wnt;
@@ -1125,10 +1125,16 @@ static WideGrid wide_grid(const WideShape& sh, int epi, int M, int n_tiles, int 
     g.k_splits = 1;
     if (epi == EPI_RESID) {
         const size_t per_split = (size_t)((M + 15) / 16) * g.n_cols * col_tiles * 1024;
-        static const int target = env_int("FLOWSPEC_WIDE_SPLIT_WGS", 256);
-        while (g.k_splits < 8 && g.n_cols * g.m_blocks * g.k_splits * 2 <= target && nkt / (g.k_splits * 2) >= 8 &&
-               per_split * g.k_splits * 2 <= part_bytes)
-            g.k_splits *= 2;
+        const double kt = sh.wnt == 4 ? 0.43 : 0.3;
+        double best = 1e30;
+        for (int k = 1; k <= 8 && (k == 1 || (nkt / k >= 8 && per_split * k <= part_bytes)); ++k) {
+            const int rounds = ((g.n_cols * k + 7) / 8 * g.m_blocks + 31) / 32;
+            const double cost = rounds * (nkt * kt / k + (k > 1 ? 4 : 15)) + (k > 1 ? 4 + per_split * k * 0.5e-6 : 0);
+            if (cost < best) {
+                best = cost;
+                g.k_splits = k;
+            }
+        }
     }
     return g;
 }
@@ -1151,7 +1157,7 @@ template <int EPI, int BMT, int WNT, int WAVES>
 static hipError_t launch_wide_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
     const WideShape sh{BMT, WNT, WAVES};
     const WideGrid g = wide_grid(sh, EPI, a.M, n_tiles, a.nkt, part ? part_bytes : 0);
-    const int grid = (g.n_cols + 7) / 8 * 8 * g.m_blocks * g.k_splits;
+    const int grid = (g.n_cols * g.k_splits + 7) / 8 * 8 * g.m_blocks;
     // one row block (only the narrow shape has that few rows): every weight byte is read once
     const bool stream = (WNT == 2) && g.m_blocks == 1;
     if constexpr (EPI == EPI_RESID) {
@@ -1580,9 +1586,10 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     // grid (8 * row blocks, units / 8), unit = (K slice, feature block): an XCD takes neighbouring units, most of one slice, and all their
     // row blocks, and no XCD more than its share (slices of 20 feature blocks padded to 24 instead left half the XCDs with 36 blocks for
     // 32 compute units: 389 rows, 13824 x 5120 163 -> 93 us, 5120 x 5120 70 -> 48)
-    const int n_cols = (n_tiles + BNT - 1) / BNT, unit = (int)((blockIdx.x & 7) * gridDim.y + blockIdx.y);
+    const int n_cols = (n_tiles + BNT - 1) / BNT, units = PARTIAL ? n_cols * ((nkc + kc_per - 1) / kc_per) : n_cols;
+    const int xcd = blockIdx.x & 7, unit = (units * xcd >> 3) + (int)blockIdx.y;
     const int mb = blockIdx.x >> 3, ks = unit / n_cols, col = unit - ks * n_cols;
-    if (ks * kc_per >= nkc) return;
+    if (unit >= units * (xcd + 1) >> 3) return;
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w / WN, wn = w % WN;
     const int r16 = lane & 15, g = lane >> 4;

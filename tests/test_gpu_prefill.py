@@ -107,3 +107,15 @@ def test_chain_segment_through_one_row_block_of_the_many_row_kernel(rows, monkey
     pair = Pair(cfg, seed=4)
     o, g = pair.verify_tree(_chain(rows), synth.hidden(cfg, rows, 0, 4), rows)
     assert max_rel_err(g, o) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows", [300, 389, 1024])
+def test_chain_residual_projections_in_uneven_slices(rows):
+    """1280 output features: 5 blocks of 256 features (10 of 128 up to 383 rows) times K slices, not a multiple of the 8 XCDs, slices of
+    unequal length."""
+    from tests.gpu_util import TOL, Pair, max_rel_err
+    cfg = synth.StageConfig(f"pf-bf16-slices-{rows}", "bf16", 1, 1280, 10, 2, 128, 2816, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=4)
+    o, g = pair.verify_tree(_chain(rows), synth.hidden(cfg, rows, 0, 4), rows)
+    assert max_rel_err(g, o) < TOL["bf16"]
