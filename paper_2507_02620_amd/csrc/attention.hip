@@ -978,6 +978,10 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     const int per_split = Hkv * *row_blocks;  // workgroups per KV split
     int want = (target + per_split - 1) / per_split;
     if ((deep_ring || pairs) && wgs_override <= 0) want = splits_one_round(per_split, ntiles);
+    // Few tiles for few rows: walking them one after another is shorter than the merge launch (us, merge / none: 8 heads of 64, 16 rows each,
+    // 2 / 3 / 4 tiles 9.4 / 7.3, 9.7 / 7.8, 9.9 / 9.6, 64 rows, 2 / 3 tiles 10.1 / 9.0, 10.7 / 10.0; 32 heads of 128, 16 rows, 2 tiles 9.7 / 8.6,
+    // 3 tiles, two of them masked 10.4 / 11.4, 32 rows, 2 tiles 10.4 / 9.0, 64 rows, 3 tiles 12.4 / 13.5; f32, 3 tiles 11.7 / 14.0)
+    if (elem_bytes == 2 && wgs_override <= 0 && (hd == 64 ? mtiles <= 4 && ntiles <= 3 : mtiles <= 2 && ntiles <= 2)) want = 1;
     if (want > max_splits) want = max_splits;
     if (want > ntiles) want = ntiles;
     if (want < 1) want = 1;

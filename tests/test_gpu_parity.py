@@ -207,3 +207,11 @@ def test_bf16_comparison_would_notice_a_wrong_mask(name, cfg, seg, wgs, monkeypa
     kerr = max_rel_err(p.kv[:, :, :, cfg.l_glo:L].float().cpu().numpy(), p.orc.kv[:, :, :, cfg.l_glo:L])
     print(f"  wrong-mask distance: hidden {sens:.3e} (HIP path {err:.3e}), appended K/V {ksens:.3e} (HIP path {kerr:.3e})", flush=True)
     assert err < 0.25 * sens and kerr < 0.25 * ksens
+
+
+@pytest.mark.parametrize("heads,kv,hd,rows", [(4, 2, 64, 32), (4, 4, 128, 64), (4, 4, 128, 1)])
+@pytest.mark.parametrize("slots", [65, 128, 129, 192, 193])
+def test_short_contexts_in_one_split(heads, kv, hd, rows, slots):
+    """Two and three K/V tiles (and the first slot of a fourth) with 1 to 64 rows per KV head: one workgroup walks all tiles, no merge."""
+    cfg = synth.StageConfig(f"short-{hd}-{slots}", "bf16", 1, 256, heads, kv, hd, 512, 0, slots - rows, rows, rows, 6, 4)
+    _check_stage(cfg, slots, rows)
