@@ -2120,12 +2120,13 @@ static hipError_t launch_stream_w4(int epi, int layout_nt, int n_tiles, const Ge
     return hipErrorInvalidValue;
 }
 
-// Which 4-bit kernel: a round of this kernel's blocks takes 1.45 (64 rows) or 2.2 us (128 rows) per 128-column chunk, the few-row
-// kernel with four tiles per workgroup 0.37 ns per chunk, feature tile and 32-row block.  Both sides, us (few / this): 4096 x 12288,
-// 128 rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 64 rows 51 / 60, 128 rows
-// 101 / 89.  Residual projections (two tiles per workgroup there, K slices here): 4096 x 4096, 128 rows 18 / 25, 200 rows 30 / 28;
-// 13824 x 5120, 64 rows 42 / 32; 5120 x 5120, 65 rows 23 / 26; with a short K there are too few slices to fill the chip: 1024 x 1024, 640
-// rows 17.9 / 22.6, 1024 rows 24.5 / 25; 1536 x 1536, 512 rows 19.8 / 22.2, 640 rows less; 2048 x 2048, 300 rows 19.4 / 21.7.
+// Which 4-bit kernel: a round of the block kernel takes 1.45 (64 rows) or 2.2 us (128 rows) per 128-column chunk, the few-row kernel
+// with four tiles per workgroup 0.37 ns per chunk, feature tile and 32-row block.  Both sides, us (few / block): 4096 x 12288, 128
+// rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 128 rows 101 / 89.  Residual
+// projections (two tiles per workgroup there, K slices here): 4096 x 4096, 128 rows 18.7 / 24.2, 160 rows 24.2 / 24.5; 5120 x 5120, 65 rows
+// 23.3 / 24.2; 11008 x 4096, 65 rows 37.6 / 32.5; 13824 x 5120, 65 rows 43.9 / 39.2; 18944 x 3584, 65 rows 65 / 46, 128 rows 85 / 52; 5632 x
+// 2048, 128 rows 18.3 / 25.6, 160 rows 24.2 / 24.9; with a short K there are too few slices to fill the chip: 1024 x 1024, 640 rows 17.9 /
+// 22.6, 1024 rows 24.5 / 25; 1536 x 1536, 512 rows 19.8 / 22.2, 640 rows less; 2048 x 2048, 300 rows 18.7 / 21.2.
 // Its offsets from the operands' bases have 32 bits: 4 GiB of codes and more stay with the few-row kernel.
 static bool block_w4_fits(int M, int n_tiles, int nkt) {
     return (unsigned long long)(n_tiles + 16) * nkt * 256ull < (1ull << 32) && (unsigned long long)(M + 16) * nkt * 64ull < (1ull << 32);
@@ -2133,7 +2134,7 @@ static bool block_w4_fits(int M, int n_tiles, int nkt) {
 static bool block_w4_pays(int epi, int M, int n_tiles, int nkt) {
     if (M <= 32 || !block_w4_fits(M, n_tiles, nkt)) return false;
     const int work = n_tiles * ((M + 31) / 32), rounds = ((n_tiles + 15) / 16 * ((M + 127) / 128) + 255) / 256;
-    if (epi == EPI_RESID) return work > (M <= 64 ? 600.0 : std::max(1100.0, 800 + 44000.0 / nkt));
+    if (epi == EPI_RESID) return work > (M <= 64 ? 600.0 : std::min(400 + 90000.0 / nkt, 800 + 44000.0 / nkt));
     return work > (M <= 64 ? 4200 : 6000) * rounds;
 }
 
