@@ -1550,7 +1550,7 @@ static hipError_t launch_mt_nt_w4(int MT, int NT, bool half, int NW, int n_group
 
 // ---- 4-bit weights, many rows (prompt chunks, stacked requests) ------------------------------------------------------------
 // The few-row kernel above unpacks its weights again for every 32 rows and reads the activations once per workgroup of 32 or 64
-// features: at a few hundred rows it is bound by both (13B layer, 389 rows: 1048 us, now 528).  Here a workgroup of WM x WN waves owns
+// features: at a few hundred rows it is bound by both (13B layer, 389 rows: 1048 us, now 395).  Here a workgroup of WM x WN waves owns
 // 16 * WM * MT rows x 16 * WN * NT features; a stage is one 128-column chunk: the rows' fragments of its four k-tiles, the feature
 // tiles' codes (a KiB each) and scales, all by direct-to-LDS loads, R buffers.  A wave unpacks its NT code tiles once per chunk
 // into 16 operand registers each (2 VALU operations per pair of weights) and multiplies them with MT row tiles; the chunk's products start
