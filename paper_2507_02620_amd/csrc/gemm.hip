@@ -2162,6 +2162,30 @@ static bool stream_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) 
     return n_tiles >= (M <= 16 ? 704 : 256);
 }
 
+// K slices of a residual projection in the block kernel, and its time in us: whole rounds of blocks (bt row tiles of at most 4 or 8), a
+// slice's partial results, 0.4 us a MiB to write and sum, and the launch that sums them against the residual epilogue in the blocks
+// themselves (13824 x 5120, 1024 rows: 160 blocks on 256 compute units 235 us, 3 slices 188).  A block's time grows with its rows only in
+// part, the codes are unpacked anyway: taken as proportional, and with no cost for the epilogue, short K got too few slices (1024 x 4096,
+// 300 rows: 1 slice 31, 2 slices 22; 2048 x 8192, 389 rows: 1 slice 47.6, 2 slices 37.6).  Fitted to 5000 launches of 160 shapes, rms 4 %.
+struct W4Slices {
+    int ks;
+    double us;
+};
+static W4Slices block_w4_slices(int M, int n_tiles, int nkc, size_t part_bytes) {
+    const bool small = M <= 64;
+    const int m_tiles = (M + 15) / 16, m_blocks = small ? 1 : (m_tiles + 7) / 8, bt = (m_tiles + m_blocks - 1) / m_blocks, n_cols = (n_tiles + 15) / 16;
+    const double chunk = small ? 0.15 + 0.27 * bt : 0.8 + 0.17 * bt;
+    W4Slices best{1, 1e30};
+    for (int k = 1; k <= std::min(8, std::max(1, nkc / 4)); ++k) {
+        const int per = (nkc + k - 1) / k, ks = (nkc + per - 1) / per, rounds = ((n_cols * ks + 7) / 8 * m_blocks + 31) / 32;
+        const size_t bytes = (size_t)ks * m_tiles * n_cols * 16 * 1024;
+        if (ks > 1 && bytes > part_bytes) break;
+        const double us = ks > 1 ? 10 + rounds * (1.5 + per * chunk) + bytes * 0.4e-6 : 7 + rounds * ((small ? 2 : 6.5) + nkc * chunk);
+        if (us < best.us) best = W4Slices{ks, us};
+    }
+    return best;
+}
+
 int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {
     if (stream_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt)) return (n_tiles + 3) / 4;
     return block_w4_pays(EPI_RESID, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
@@ -2176,22 +2200,9 @@ static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a,
     const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
     const dim3 block(WM * WN * 64);
     if constexpr (EPI == EPI_RESID) {
-        // K slices: whole rounds of blocks, 2.2 us a chunk, against a slice's partial results, 0.5 us a MiB to write and sum (13824 x 5120, 1024
-        // rows: 160 blocks on 256 compute units 235 us, 3 slices 188)
-        int ks = 1;
-        double best = 1e30;
-        for (int k = 1; k <= std::min(8, std::max(1, nkc / 4)); ++k) {
-            const size_t bytes = (size_t)k * m_tiles * n_cols * BNT * 1024;
-            if (k > 1 && bytes > part_bytes) break;
-            const double cost = ((n_cols * k + 7) / 8 * m_blocks + 31) / 32 * ((nkc + k - 1) / k) * (2.2 / BMT * bt) + (k > 1 ? 4 + bytes * 0.5e-6 : 0);
-            if (cost < best) {
-                best = cost;
-                ks = k;
-            }
-        }
+        const int ks = block_w4_slices(a.M, n_tiles, nkc, part_bytes).ks;
         if (ks > 1) {
             const int per = (nkc + ks - 1) / ks;
-            ks = (nkc + per - 1) / per;
             hipLaunchKernelGGL((block_gemm_w4_kernel<EPI, true, WM, WN, MT, NT, R>), dim3(8 * m_blocks, (n_cols * ks + 7) / 8), block, 0, s, a.Wp, a.X, a.Sp, nkc, a.M, lsh,
                                n_tiles, per, bt, a, part);
             return launch_fixup<4>(a, n_cols * BNT, ks, part, s);

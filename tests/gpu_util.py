@@ -64,6 +64,16 @@ class Pair:
         return o_out, g_out
 
 
+def kernel_names(fn):
+    """Names of the kernels one call of fn launches (which form of a projection or of the attention a dispatch took)."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in p.events() if "_kernel" in e.name]
+
+
 def max_rel_err(got, ref):
     """max |got - ref| / max |ref| over the whole tensor."""
     ref = np.asarray(ref, dtype=np.float64)

@@ -206,3 +206,21 @@ def test_w4_row_blocks_of_equal_height(rows, d, ffn):
     pair = Pair(cfg, seed=rows, w4=True)
     o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, rows), rows)
     assert max_rel_err(g, o) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows,d,heads,slices", [(257, 4096, 8, 2), (300, 4096, 8, 2), (300, 5120, 10, 2)])
+def test_w4_residual_projections_of_a_short_k_are_cut(rows, d, heads, slices):
+    """1024 and 1280 input columns, a few row blocks: one slice leaves most of the chip idle (31 against 22 us)."""
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err
+    cfg = synth.StageConfig(f"w4c-{rows}-{d}", "bf16", 1, d, heads, 1, 128, 128, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    hid, par = synth.hidden(cfg, rows, 0, rows), np.arange(-1, rows - 1, dtype=np.int32)
+    o = g = None
+
+    def call():
+        nonlocal o, g
+        o, g = pair.verify_tree(par, hid, rows)
+    names = kernel_names(call)
+    assert max_rel_err(g, o) < TOL["bf16"]
+    assert sum(f"wide_fixup_kernel<{slices}, 4>" in n for n in names) == 1, names   # the output projection (the down projection has one chunk)
