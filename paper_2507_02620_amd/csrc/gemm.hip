@@ -2162,6 +2162,18 @@ static bool stream_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) 
     return n_tiles >= (M <= 16 ? 704 : 256);
 }
 
+// Row tiles per block.  Equal heights, since a round lasts as long as its tallest block (5 tiles against 8: 0.9 of the time).  But where
+// three equal row blocks make a second round of at most 8 (32 compute units of an XCD) and the last one of full height has at most four
+// tiles, so that half its waves only load, the second round starts behind such blocks and runs beside the first.  us, equal / full heights:
+// 4096 x 22016, 257 rows 129.6 / 110.2, 300 rows 136 / 112.7; 7168 x 21504, 300 rows 230 / 188; 8192 x 25600 (39 blocks an XCD) 246 / 239 and
+// 262 / 240; 42 blocks, 5120 x 27648 160 / 179 and 171 / 179.  With two or four row blocks the short ones all fall to the same part of an
+// XCD and make no room elsewhere: 7168 x 33024, 129 rows 214 / 238; 4096 x 18432, 389 rows 138 / 147.
+static int block_w4_height(bool resid, int m_tiles, int m_blocks, int n_cols) {
+    const int equal = (m_tiles + m_blocks - 1) / m_blocks, cols = (n_cols + 7) / 8, over = cols * m_blocks - 32;
+    if (!resid && m_blocks == 3 && m_tiles <= 20 && over > 0 && over <= 8) return 8;
+    return equal;
+}
+
 // K slices of a residual projection in the block kernel, and its time in us: whole rounds of blocks (bt row tiles of at most 4 or 8), a
 // slice's partial results, 0.4 us a MiB to write and sum, and the launch that sums them against the residual epilogue in the blocks
 // themselves (13824 x 5120, 1024 rows: 160 blocks on 256 compute units 235 us, 3 slices 188).  A block's time grows with its rows only in
@@ -2196,7 +2208,7 @@ static hipError_t launch_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a,
     constexpr int BMT = WM * MT, BNT = WN * NT;
     static_assert(BNT == 16, "the residual projections' sums of squares come per 16 feature tiles");
     const int m_tiles = (a.M + 15) / 16, m_blocks = (m_tiles + BMT - 1) / BMT, n_cols = (n_tiles + BNT - 1) / BNT, nkc = a.nkt / 4;
-    const int bt = (m_tiles + m_blocks - 1) / m_blocks;  // row tiles per block: a round lasts as long as its tallest block
+    const int bt = block_w4_height(EPI == EPI_RESID, m_tiles, m_blocks, n_cols);
     const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
     const dim3 block(WM * WN * 64);
     if constexpr (EPI == EPI_RESID) {

@@ -224,3 +224,15 @@ def test_w4_residual_projections_of_a_short_k_are_cut(rows, d, heads, slices):
     names = kernel_names(call)
     assert max_rel_err(g, o) < TOL["bf16"]
     assert sum(f"wide_fixup_kernel<{slices}, 4>" in n for n in names) == 1, names   # the output projection (the down projection has one chunk)
+
+
+@pytest.mark.parametrize("rows", [257, 320, 321])
+def test_w4_row_blocks_of_full_height(rows):
+    """Three row blocks of 88 feature blocks: 33 an XCD.  Up to 320 rows two blocks of eight row tiles and one of 1 to 4, whose second
+    row of waves has no rows; from 321 rows on equal heights."""
+    from tests.gpu_util import TOL, Pair, max_rel_err
+    cfg = synth.StageConfig(f"w4h-{rows}", "bf16", 1, 256, 2, 1, 64, 11136, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, rows), rows)
+    assert max_rel_err(g, o) < TOL["bf16"]
