@@ -2120,6 +2120,37 @@ static hipError_t launch_stream_w4(int epi, int layout_nt, int n_tiles, const Ge
     return hipErrorInvalidValue;
 }
 
+// K slices of a residual projection in the block kernel, and its time in us: whole rounds of blocks (bt row tiles of at most 4 or 8), a
+// slice's partial results, 0.4 us a MiB to write and sum, and the launch that sums them against the residual epilogue in the blocks
+// themselves (13824 x 5120, 1024 rows: 160 blocks on 256 compute units 235 us, 3 slices 188).  A block's time grows with its rows only in
+// part, the codes are unpacked anyway: taken as proportional, and with no cost for the epilogue, short K got too few slices (1024 x 4096,
+// 300 rows: 1 slice 31, 2 slices 22; 2048 x 8192, 389 rows: 1 slice 47.6, 2 slices 37.6).  Fitted to 5000 launches of 160 shapes, rms 4 %.
+struct W4Slices {
+    int ks;
+    double us;
+};
+static W4Slices block_w4_slices(int M, int n_tiles, int nkc, size_t part_bytes) {
+    const bool small = M <= 64;
+    const int m_tiles = (M + 15) / 16, m_blocks = small ? 1 : (m_tiles + 7) / 8, bt = (m_tiles + m_blocks - 1) / m_blocks, n_cols = (n_tiles + 15) / 16;
+    const double chunk = small ? 0.15 + 0.27 * bt : 0.8 + 0.17 * bt;
+    W4Slices best{1, 1e30};
+    for (int k = 1; k <= std::min(8, std::max(1, nkc / 4)); ++k) {
+        const int per = (nkc + k - 1) / k, ks = (nkc + per - 1) / per, rounds = ((n_cols * ks + 7) / 8 * m_blocks + 31) / 32;
+        const size_t bytes = (size_t)ks * m_tiles * n_cols * 16 * 1024;
+        if (ks > 1 && bytes > part_bytes) break;
+        const double us = ks > 1 ? 10 + rounds * (1.5 + per * chunk) + bytes * 0.4e-6 : 7 + rounds * ((small ? 2 : 6.5) + nkc * chunk);
+        if (us < best.us) best = W4Slices{ks, us};
+    }
+    return best;
+}
+
+// Time of the few-row kernel in us: whole rounds of workgroups, each one group of NT feature tiles and up to 32 rows, a wave's chunks one
+// after another.  Fitted to the same shapes, rms 5 % (residual projections; those of one tile per group 8 %: two workgroups share a unit).
+static double few_w4_us(int NT, int M, int n_tiles, int nkc) {
+    const int rounds = ((n_tiles + NT - 1) / NT * ((M + 31) / 32) + 255) / 256;
+    return 5 + rounds * (NT == 1 ? 1.5 + 0.115 * nkc : NT == 2 ? 2 + 0.165 * nkc : 3 + 0.235 * nkc);
+}
+
 // Which 4-bit kernel: a round of the block kernel takes 1.45 (64 rows) or 2.2 us (128 rows) per 128-column chunk, the few-row kernel
 // with four tiles per workgroup 0.37 ns per chunk, feature tile and 32-row block.  Both sides, us (few / block): 4096 x 12288, 128
 // rows 36 / 74, 200 rows 63 / 74, 389 rows 181 / 75; 5120 x 15360, 65 rows 42 / 87; 5120 x 27648, 128 rows 101 / 89.  Residual
@@ -2127,14 +2158,21 @@ static hipError_t launch_stream_w4(int epi, int layout_nt, int n_tiles, const Ge
 // 23.3 / 24.2; 11008 x 4096, 65 rows 37.6 / 32.5; 13824 x 5120, 65 rows 43.9 / 39.2; 18944 x 3584, 65 rows 65 / 46, 128 rows 85 / 52; 5632 x
 // 2048, 128 rows 18.3 / 25.6, 160 rows 24.2 / 24.9; with a short K there are too few slices to fill the chip: 1024 x 1024, 640 rows 17.9 /
 // 22.6, 1024 rows 24.5 / 25; 1536 x 1536, 512 rows 19.8 / 22.2, 640 rows less; 2048 x 2048, 300 rows 18.7 / 21.2.
+// Between the line of a long K and the one before it the two times decide, since the few-row kernel's come in whole rounds: 4096 features, 65 to
+// 128 rows are two of them, 5632 columns, 128 rows 23.4 / 27.1, 9216 columns, 80 rows 32.8 / 28.7, 128 rows 33.6 / 33.0.
 // Its offsets from the operands' bases have 32 bits: 4 GiB of codes and more stay with the few-row kernel.
 static bool block_w4_fits(int M, int n_tiles, int nkt) {
     return (unsigned long long)(n_tiles + 16) * nkt * 256ull < (1ull << 32) && (unsigned long long)(M + 16) * nkt * 64ull < (1ull << 32);
 }
-static bool block_w4_pays(int epi, int M, int n_tiles, int nkt) {
+static bool block_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) {
     if (M <= 32 || !block_w4_fits(M, n_tiles, nkt)) return false;
     const int work = n_tiles * ((M + 31) / 32), rounds = ((n_tiles + 15) / 16 * ((M + 127) / 128) + 255) / 256;
-    if (epi == EPI_RESID) return work > (M <= 64 ? 600.0 : std::min(400 + 90000.0 / nkt, 800 + 44000.0 / nkt));
+    if (epi == EPI_RESID) {
+        if (M <= 64) return work > 600;
+        if (work > std::max(1100, 800 + 44000 / nkt)) return true;
+        return work > std::min(400 + 90000 / nkt, 800 + 44000 / nkt) &&
+               block_w4_slices(M, n_tiles, nkt / 4, (size_t)64 << 20).us < 0.97 * few_w4_us(layout_nt, M, n_tiles, nkt / 4);
+    }
     return work > (M <= 64 ? 4200 : 6000) * rounds;
 }
 
@@ -2174,33 +2212,9 @@ static int block_w4_height(bool resid, int m_tiles, int m_blocks, int n_cols) {
     return equal;
 }
 
-// K slices of a residual projection in the block kernel, and its time in us: whole rounds of blocks (bt row tiles of at most 4 or 8), a
-// slice's partial results, 0.4 us a MiB to write and sum, and the launch that sums them against the residual epilogue in the blocks
-// themselves (13824 x 5120, 1024 rows: 160 blocks on 256 compute units 235 us, 3 slices 188).  A block's time grows with its rows only in
-// part, the codes are unpacked anyway: taken as proportional, and with no cost for the epilogue, short K got too few slices (1024 x 4096,
-// 300 rows: 1 slice 31, 2 slices 22; 2048 x 8192, 389 rows: 1 slice 47.6, 2 slices 37.6).  Fitted to 5000 launches of 160 shapes, rms 4 %.
-struct W4Slices {
-    int ks;
-    double us;
-};
-static W4Slices block_w4_slices(int M, int n_tiles, int nkc, size_t part_bytes) {
-    const bool small = M <= 64;
-    const int m_tiles = (M + 15) / 16, m_blocks = small ? 1 : (m_tiles + 7) / 8, bt = (m_tiles + m_blocks - 1) / m_blocks, n_cols = (n_tiles + 15) / 16;
-    const double chunk = small ? 0.15 + 0.27 * bt : 0.8 + 0.17 * bt;
-    W4Slices best{1, 1e30};
-    for (int k = 1; k <= std::min(8, std::max(1, nkc / 4)); ++k) {
-        const int per = (nkc + k - 1) / k, ks = (nkc + per - 1) / per, rounds = ((n_cols * ks + 7) / 8 * m_blocks + 31) / 32;
-        const size_t bytes = (size_t)ks * m_tiles * n_cols * 16 * 1024;
-        if (ks > 1 && bytes > part_bytes) break;
-        const double us = ks > 1 ? 10 + rounds * (1.5 + per * chunk) + bytes * 0.4e-6 : 7 + rounds * ((small ? 2 : 6.5) + nkc * chunk);
-        if (us < best.us) best = W4Slices{ks, us};
-    }
-    return best;
-}
-
 int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {
     if (stream_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt)) return (n_tiles + 3) / 4;
-    return block_w4_pays(EPI_RESID, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
+    return block_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
 }
 
 template <int EPI, int WM, int WN, int MT, int NT, int R>
@@ -2239,7 +2253,7 @@ static hipError_t launch_block_w4(int epi, int layout_nt, int n_tiles, const Gem
 
 hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
     if (stream_w4_pays(epi, NT, a.M, n_groups * NT, a.nkt)) return launch_stream_w4(epi, NT, n_groups * NT, a, part, part_bytes, s);
-    if (block_w4_pays(epi, a.M, n_groups * NT, a.nkt)) return launch_block_w4(epi, NT, n_groups * NT, a, part, part_bytes, s);
+    if (block_w4_pays(epi, NT, a.M, n_groups * NT, a.nkt)) return launch_block_w4(epi, NT, n_groups * NT, a, part, part_bytes, s);
     // at most 32 rows per workgroup (register budget); longer segments take further row blocks, whose passes over
     // the quarter-size weights mostly hit in L2
     const int MT = a.M <= 16 ? 1 : 2;

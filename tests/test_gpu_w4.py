@@ -216,13 +216,9 @@ def test_w4_residual_projections_of_a_short_k_are_cut(rows, d, heads, slices):
     print(f"[case] {cfg.name}", flush=True)
     pair = Pair(cfg, seed=rows, w4=True)
     hid, par = synth.hidden(cfg, rows, 0, rows), np.arange(-1, rows - 1, dtype=np.int32)
-    o = g = None
-
-    def call():
-        nonlocal o, g
-        o, g = pair.verify_tree(par, hid, rows)
-    names = kernel_names(call)
-    assert max_rel_err(g, o) < TOL["bf16"]
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(par, hid, rows)))
+    assert max_rel_err(got[1], got[0]) < TOL["bf16"]
     assert sum(f"wide_fixup_kernel<{slices}, 4>" in n for n in names) == 1, names   # the output projection (the down projection has one chunk)
 
 
@@ -236,3 +232,17 @@ def test_w4_row_blocks_of_full_height(rows):
     pair = Pair(cfg, seed=rows, w4=True)
     o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, rows), rows)
     assert max_rel_err(g, o) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows,ffn,block", [(128, 5632, False), (100, 5632, False), (80, 9216, True), (65, 11008, True)])
+def test_w4_residual_projections_between_the_two_lines(rows, ffn, block):
+    """4096 features, 65 to 128 rows: two full rounds of few-row workgroups, which a K of 5632 does not make longer than the row blocks."""
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err
+    cfg = synth.StageConfig(f"w4l-{rows}-{ffn}", "bf16", 1, 4096, 1, 1, 128, ffn, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    hid, par = synth.hidden(cfg, rows, 0, rows), np.arange(-1, rows - 1, dtype=np.int32)
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(par, hid, rows)))
+    assert max_rel_err(got[1], got[0]) < TOL["bf16"]
+    assert any("block_gemm_w4_kernel<1," in n for n in names) == block, names
