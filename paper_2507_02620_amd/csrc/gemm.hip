@@ -2070,14 +2070,25 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
     }
 }
 
+// K slices of a residual projection: until there is about one workgroup per compute unit
+static int stream_w4_slices(int KG, int n_cols, int nkc) { return std::max(1, std::min(std::min(256 / n_cols, 8), nkc / (2 * KG))); }
+
+// Four or eight feature tiles per block: a compute unit holds one block at a time and draws its codes and the activations for it (24
+// rows x 5120, four / eight: 960 tiles 18.5 / 24.3 us, 1728 tiles 31.3 / 25.5); residual projections fill the chip with K slices,
+// where few tiles per block mean fewer slices to sum (11008 x 4096, 32 rows 15.7 / 16.9; but 13824 x 5120, 64 rows 27.3 / 25.3)
+static bool stream_w4_narrow(int epi, int M, int n_tiles) {
+    const int mt = M <= 16 ? 1 : M <= 32 ? 2 : 4, b4 = (n_tiles + 3) / 4, b8 = (n_tiles + 7) / 8;
+    return epi == EPI_RESID ? mt < 4 : (b4 + 255) / 256 * (4 + 4 * mt) < (b8 + 255) / 256 * (8 + 4 * mt);
+}
+
 template <int EPI, int WN, int KG, int MT, int NT, int R>
 static hipError_t launch_stream_w4_shape(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
     constexpr int BNT = WN * NT;
     const int n_cols = (n_tiles + BNT - 1) / BNT, m_tiles = (a.M + 15) / 16, nkc = a.nkt / 4;
     const int lsh = layout_nt == 4 ? 2 : layout_nt == 2 ? 1 : 0;
     int ks = 1;
-    if constexpr (EPI == EPI_RESID) {  // K slices until there is about one workgroup per compute unit
-        ks = std::max(1, std::min(std::min(256 / n_cols, 8), nkc / (2 * KG)));
+    if constexpr (EPI == EPI_RESID) {
+        ks = stream_w4_slices(KG, n_cols, nkc);
         while (ks > 1 && (size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) --ks;
         if ((size_t)ks * m_tiles * n_cols * BNT * 1024 > part_bytes) return hipErrorInvalidValue;
     }
@@ -2091,11 +2102,8 @@ static hipError_t launch_stream_w4_shape(int layout_nt, int n_tiles, const GemmA
 
 template <int EPI>
 static hipError_t launch_stream_w4_epi(int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, hipStream_t s) {
-    // Four or eight feature tiles per block: a compute unit holds one block at a time and draws its codes and the activations for it (24
-    // rows x 5120, four / eight: 960 tiles 18.5 / 24.3 us, 1728 tiles 31.3 / 25.5); residual projections fill the chip with K slices,
-    // where few tiles per block mean fewer slices to sum (11008 x 4096, 32 rows 15.7 / 16.9; but 13824 x 5120, 64 rows 27.3 / 25.3)
-    const int mt = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4, b4 = (n_tiles + 3) / 4, b8 = (n_tiles + 7) / 8;
-    const bool narrow = EPI == EPI_RESID ? mt < 4 : (b4 + 255) / 256 * (4 + 4 * mt) < (b8 + 255) / 256 * (8 + 4 * mt);
+    const int mt = a.M <= 16 ? 1 : a.M <= 32 ? 2 : 4;
+    const bool narrow = stream_w4_narrow(EPI, a.M, n_tiles);
 #define FS_S(wn, kg, mt, r) return launch_stream_w4_shape<EPI, wn, kg, mt, 2, r>(layout_nt, n_tiles, a, part, part_bytes, s)
     if (mt == 1) {
         if (narrow) FS_S(2, 4, 1, 4);
@@ -2138,17 +2146,33 @@ static W4Slices block_w4_slices(int M, int n_tiles, int nkc, size_t part_bytes) 
         const int per = (nkc + k - 1) / k, ks = (nkc + per - 1) / per, rounds = ((n_cols * ks + 7) / 8 * m_blocks + 31) / 32;
         const size_t bytes = (size_t)ks * m_tiles * n_cols * 16 * 1024;
         if (ks > 1 && bytes > part_bytes) break;
-        const double us = ks > 1 ? 10 + rounds * (1.5 + per * chunk) + bytes * 0.4e-6 : 7 + rounds * ((small ? 2 : 6.5) + nkc * chunk);
+        const double us = ks > 1 ? (small ? 8.2 : 10) + rounds * (1.5 + per * chunk) + bytes * 0.4e-6 : 7 + rounds * ((small ? 2 : 6.5) + nkc * chunk);
         if (us < best.us) best = W4Slices{ks, us};
     }
     return best;
 }
 
+// One row tile: half a group of four tiles per workgroup where whole groups would leave a last round of few workgroups (592 of them, three
+// rounds of 256 compute units, a fill of 0.77 against 0.925: gate/up 28.3 -> 26.5 us; but 896, 0.875 against 1: 64 -> 70)
+static bool few_w4_half(int NT, int M, int n_groups) {
+    auto fill = [](int n) { return (double)n / ((n + 255) / 256 * 256); };
+    return NT == 4 && M <= 16 && fill(2 * n_groups) > 1.18 * fill(n_groups);
+}
+
 // Time of the few-row kernel in us: whole rounds of workgroups, each one group of NT feature tiles and up to 32 rows, a wave's chunks one
-// after another.  Fitted to the same shapes, rms 5 % (residual projections; those of one tile per group 8 %: two workgroups share a unit).
-static double few_w4_us(int NT, int M, int n_tiles, int nkc) {
-    const int rounds = ((n_tiles + NT - 1) / NT * ((M + 31) / 32) + 255) / 256;
-    return 5 + rounds * (NT == 1 ? 1.5 + 0.115 * nkc : NT == 2 ? 2 + 0.165 * nkc : 3 + 0.235 * nkc);
+// after another.  Fitted to 2500 launches of up to 64 rows and 300 of more, rms 5 % (residual projections of one tile per group 8 %: two of
+// their workgroups share a compute unit).
+static double few_w4_us(int epi, int NT, int M, int n_tiles, int nkc) {
+    int groups = (n_tiles + NT - 1) / NT;
+    if (few_w4_half(NT, M, groups)) {
+        NT = 2;
+        groups *= 2;
+    }
+    const int rounds = (groups * ((M + 31) / 32) + 255) / 256;
+    const bool one = M <= 16, r = epi == EPI_RESID;
+    if (NT == 4) return 5 + rounds * (one ? 1.6 + 0.213 * nkc : 3 + 0.235 * nkc);
+    if (NT == 2) return 5 + rounds * (one ? 1 + 0.119 * nkc : (r ? 2 : 2.8) + (r ? 0.165 : 0.172) * nkc);
+    return 5 + rounds * (one ? (r ? 1.2 + 0.06 * nkc : 1.7 + 0.1 * nkc) : r ? 1.5 + 0.115 * nkc : 2 + 0.13 * nkc);
 }
 
 // Which 4-bit kernel: a round of the block kernel takes 1.45 (64 rows) or 2.2 us (128 rows) per 128-column chunk, the few-row kernel
@@ -2171,33 +2195,51 @@ static bool block_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) {
         if (M <= 64) return work > 600;
         if (work > std::max(1100, 800 + 44000 / nkt)) return true;
         return work > std::min(400 + 90000 / nkt, 800 + 44000 / nkt) &&
-               block_w4_slices(M, n_tiles, nkt / 4, (size_t)64 << 20).us < 0.97 * few_w4_us(layout_nt, M, n_tiles, nkt / 4);
+               block_w4_slices(M, n_tiles, nkt / 4, (size_t)64 << 20).us < 0.97 * few_w4_us(epi, layout_nt, M, n_tiles, nkt / 4);
     }
     return work > (M <= 64 ? 4200 : 6000) * rounds;
 }
 
 // The streaming kernel, up to 64 rows.  It runs one block per compute unit and time, so a launch costs whole rounds of blocks, and a residual
-// projection a second launch.  Both sides, us (few-row or block kernel / this):
-//   * residual: 4096 x 4096, 16 rows 9.3 / 10.5, 32 rows 12.0 / 11.9; 5120 x 5120, 16 rows 11.1 / 12.1, 24 rows 14.2 / 13.5; 8192 x 3072, 16 rows
-//     11.0 / 11.7, 24 rows 14.8 / 12.6; 11008 x 4096, 16 rows 16.1 / 13.5.  33 to 64 rows: 3072 x 3072 13.8 / 12.7, 2816 x 1024 9.5 / 12.9; where
-//     the few-row kernel's workgroups make one round (4096 features) 4096 x 4096 12.1 / 14.5, 11008 x 4096 21.4 / 20.0
-//   * QKV: 288 tiles x 3584, 16 rows 10.2 / 12.4, 24 rows 13.0 / 13.6; 384 x 2048 8.8 / 10.4, 24 rows 10.5 / 11.0; x 4096, 64 rows 22.2 / 23.9; 640 x
-//     8192, 16 rows 22.3 / 19.7, 24 rows 32.2 / 22.2; 768 x 4096, 16 rows 14.3 / 14.0, 24 rows 19.1 / 15.2
-//   * gate/up, head: 352 tiles x 1024, 16 rows 8.0 / 8.6, 24 rows 9.8 / 9.0; 704 x 2048 10.4 / 10.5, 24 rows 15.7 / 11.3; 1728 x 5120 27.7 /
-//     22.6, 24 rows 34.1 / 26.3, 64 rows 50.9 / 37.1; a second round of few blocks (2368 x 3584: 296) 27.8 / 30.1, 24 rows 35.5 / 36.0, of
-//     more (3144 x 3072: 393) 37.0 / 30.2, 24 rows 37.0 / 34.6, but 64 rows 48 / 52; 9504 x 3584 88.9 / 79.6, 24 rows 99.8 / 93.8
+// projection a second launch; the few-row kernel costs whole rounds of its own workgroups, which end elsewhere (256 groups of two tiles are
+// one round, 257 two).  So from a least number of tiles or chunks on the two times are worked out and compared.  With that least number
+// alone calls of a full round lost, us, few-row / this: QKV of 512 tiles x 4096, 16 rows 10.6 / 12.7, 32 rows 13.3 / 15.4, 64 rows 22.6 / 23.8, x
+// 8192 14.6 / 18.0, 18.7 / 22.7, 33.3 / 38.8; gate/up of 256 x 4096, 32 rows 12.4 / 14.8, 64 rows 12.7 / 22.5; head of 512 x 8192, 32 rows 18.5 /
+// 23.4; output projection 6144 x 6144, 32 rows 14.7 / 15.9; block kernel / this: 9216 x 6144, 40 rows 21.4 / 23.2.  Where it pays: QKV of 768 x
+// 4096, 24 rows 19.1 / 15.2; gate/up of 1728 x 5120, 16 rows 27.7 / 22.6, 24 rows 34.1 / 26.3, 64 rows 50.9 / 37.1; 11008 x 4096, 16 rows 16.1 /
+// 13.5.  The least numbers: below them both kernels are short and the estimates (fitted to 4500 launches of 70 shapes, rms 4 - 7 %) say too
+// little: head of 640 x 2048, 16 rows 9.5 / 10.2; 4096 x 1024, 24 rows 9.3 / 9.8.
 static bool stream_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) {
-    if (M > 64 || n_tiles > 16000 || !block_w4_fits(M, n_tiles, nkt)) return false;  // (one slice's partial results of a residual projection: 64 MiB)
-    const int nkc = nkt / 4;
+    // (16000 tiles: one slice's partial results of a residual projection then fit 64 MiB; a head that wide has not been measured)
+    if (M > 64 || n_tiles > 16000 || !block_w4_fits(M, n_tiles, nkt)) return false;
+    const int nkc = nkt / 4, m = M <= 16 ? 0 : M <= 32 ? 1 : 2, m_tiles = (M + 15) / 16;
+    const bool narrow = stream_w4_narrow(epi, M, n_tiles);
+    const int tiles = narrow ? 4 : 8, n_cols = (n_tiles + tiles - 1) / tiles;
+    static const double chunk_us[2][3] = {{0.34, 0.45, 0.68}, {0.185, 0.25, 0.488}};  // a block's time per chunk, eight / four tiles
+    double us;
     if (epi == EPI_RESID) {
-        if (M <= 16) return nkc > 64;
-        if (M <= 32) return nkc >= 40;
-        return nkc >= ((n_tiles + layout_nt - 1) / layout_nt * 2 <= 256 ? 80 : 24);
+        if (nkc < (m == 0 ? 65 : m == 1 ? 40 : 24)) return false;
+        const int kg = narrow ? 4 : 2, k = stream_w4_slices(kg, n_cols, nkc), per = ((nkc + k - 1) / k + kg - 1) / kg * kg, ks = (nkc + per - 1) / per;
+        const double in_out = m < 2 ? 3.7 : 3.95, mib_us = m == 0 ? 1 : m == 1 ? 0.8 : 0.67;
+        us = in_out + (n_cols * ks + 255) / 256 * (in_out + 0.93 * chunk_us[narrow][m] * per) + mib_us * ks * m_tiles * n_cols * tiles / 1024;
+    } else {
+        if (n_tiles < (epi == EPI_QKV ? 512 : m == 0 ? 704 : 256) || (m == 2 && n_cols > 256)) return false;
+        static const double round_us[2][3] = {{4.4, 6, 8}, {4.2, 4.7, 5.6}};
+        us = 2 + (n_cols + 255) / 256 * (round_us[narrow][m] + chunk_us[narrow][m] * nkc);
     }
-    if (epi == EPI_QKV) return n_tiles >= 512;
-    const int b8 = (n_tiles + 7) / 8, rounds = (b8 + 255) / 256;
-    if (rounds > 1) return M <= 32 && b8 > 0.75 * 256 * rounds;
-    return n_tiles >= (M <= 16 ? 704 : 256);
+    double other;
+    if (!block_w4_pays(epi, layout_nt, M, n_tiles, nkt))
+        other = few_w4_us(epi, layout_nt, M, n_tiles, nkc);
+    else if (epi == EPI_RESID)
+        other = block_w4_slices(M, n_tiles, nkc, (size_t)64 << 20).us;
+    else
+        other = (((n_tiles + 15) / 16 + 7) / 8 + 31) / 32 * (10 + (0.15 + 0.27 * m_tiles) * nkc);
+    return us < 0.95 * other;
+}
+
+int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {
+    if (stream_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt)) return (n_tiles + 3) / 4;
+    return block_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
 }
 
 // Row tiles per block.  Equal heights, since a round lasts as long as its tallest block (5 tiles against 8: 0.9 of the time).  But where
@@ -2210,11 +2252,6 @@ static int block_w4_height(bool resid, int m_tiles, int m_blocks, int n_cols) {
     const int equal = (m_tiles + m_blocks - 1) / m_blocks, cols = (n_cols + 7) / 8, over = cols * m_blocks - 32;
     if (!resid && m_blocks == 3 && m_tiles <= 20 && over > 0 && over <= 8) return 8;
     return equal;
-}
-
-int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {
-    if (stream_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt)) return (n_tiles + 3) / 4;
-    return block_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
 }
 
 template <int EPI, int WM, int WN, int MT, int NT, int R>
@@ -2257,17 +2294,10 @@ hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs&
     // at most 32 rows per workgroup (register budget); longer segments take further row blocks, whose passes over
     // the quarter-size weights mostly hit in L2
     const int MT = a.M <= 16 ? 1 : 2;
-    bool half = false;
-    if (NT == 4 && MT == 1) {
-        // one row tile: half a group per workgroup where whole groups would leave a last round of few workgroups (344 of them, two
-        // rounds of 256 compute units: gate/up 20.8 -> 18.6 us; 592, a fill of 0.77 against 0.925: 28.3 -> 26.5; but 896, 0.875 against 1:
-        // 64 -> 70)
-        auto fill = [](int n) { return (double)n / ((n + 255) / 256 * 256); };
-        if (fill(2 * n_groups) > 1.18 * fill(n_groups)) {
-            half = true;
-            NT = 2;
-            n_groups *= 2;
-        }
+    const bool half = few_w4_half(NT, a.M, n_groups);
+    if (half) {
+        NT = 2;
+        n_groups *= 2;
     }
     if (NW > 8) NW = 8;
     if (MT * NT >= 8 && NW > 4) NW = 4;  // as in the dense launcher

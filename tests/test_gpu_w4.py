@@ -179,19 +179,25 @@ def test_w4_residual_projections_of_a_short_k(rows):
 
 @pytest.mark.parametrize("rows,ffn", [(1, 8320), (16, 8320), (17, 5248), (32, 5248), (33, 10368), (64, 10368)])
 def test_w4_streaming_kernel(rows, ffn):
-    """Up to 64 rows through the LDS-fed 4-bit kernel: QKV and gate/up in blocks of four and eight tiles, the down projection in K slices
-    of an odd number of chunks, a head whose last block is ragged; both ends of each row-tile count."""
+    """Up to 64 rows through the LDS-fed 4-bit kernel: QKV and gate/up in blocks of four and eight tiles, up to 32 rows the down projection in
+    K slices of an odd number of chunks (33 and 64 rows: the next test), a head whose last block is ragged; both ends of each row-tile count."""
     import torch
-    from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
-    cfg = synth.StageConfig(f"w4s-{rows}", "bf16", 2, 256, 32, 16, 128, ffn, 11300, 20, rows, rows, 5, 3, qkv_bias=True)
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err, to_dev
+    cfg = synth.StageConfig(f"w4s-{rows}", "bf16", 2, 256, 36, 18, 128, ffn, 11300, 20, rows, rows, 5, 3, qkv_bias=True)
     print(f"[case] {cfg.name}", flush=True)
     pair = Pair(cfg, seed=rows, head=True, w4=True)
-    o, g = pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)))
+    o, g = got
+    assert [sum(f"stream_gemm_w4_kernel<{kind}," in n for n in names) for kind in (0, 2)] == [2, 2], names
+    assert any("stream_gemm_w4_kernel<1," in n for n in names) == (rows <= 32), names
     L = cfg.l_glo + rows
     kerr = max_rel_err(pair.kv[:, :, :, cfg.l_glo:L].float().cpu().numpy(), pair.orc.kv[:, :, :, cfg.l_glo:L])
     x = synth.storage(cfg, o.astype(np.float32))
     lo, _ = pair.orc.logits(x.astype(np.float64))
-    lg, _ = pair.gpu.tree_logits(to_dev(x, torch.bfloat16))
+    names = kernel_names(lambda: got.extend(pair.gpu.tree_logits(to_dev(x, torch.bfloat16))))
+    lg = got[2]
+    assert any("stream_gemm_w4_kernel<3," in n for n in names), names
     assert max_rel_err(g, o) < TOL["bf16"] and kerr < TOL["bf16"] and max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
 
 
@@ -246,3 +252,36 @@ def test_w4_residual_projections_between_the_two_lines(rows, ffn, block):
     names = kernel_names(lambda: got.extend(pair.verify_tree(par, hid, rows)))
     assert max_rel_err(got[1], got[0]) < TOL["bf16"]
     assert any("block_gemm_w4_kernel<1," in n for n in names) == block, names
+
+
+# the kernels of QKV, gate/up and the down projection
+_FEW, _STREAM = "skinny_gemm_w4_kernel<", "stream_gemm_w4_kernel<"
+
+
+@pytest.mark.parametrize("d,heads,kv,ffn,rows,qkv,gateup,down", [
+    # one full round of few-row workgroups: 256 groups of two tiles (QKV), 128 groups and two row blocks (gate/up)
+    (4096, 32, 16, 2048, 16, _FEW, _FEW, _FEW),
+    (4096, 32, 16, 2048, 32, _FEW, _FEW, _FEW),
+    (2560, 20, 20, 2048, 33, _FEW, _FEW, _FEW),
+    (2560, 20, 20, 2048, 64, _FEW, _FEW, _FEW),
+    # more than a round: 320 groups of two tiles (QKV), gate/up of 1312 and 1920 tiles; the down projection of 5248 and 7680 columns
+    (1024, 40, 20, 7680, 24, _STREAM, _STREAM, _STREAM),
+    (5120, 4, 4, 5248, 24, _FEW, _STREAM, _STREAM),
+    (5120, 4, 4, 5248, 33, _FEW, _STREAM, _STREAM),
+    (5120, 4, 4, 5248, 64, _FEW, _STREAM, _STREAM),
+])
+def test_w4_streaming_kernel_where_it_is_the_faster_one(d, heads, kv, ffn, rows, qkv, gateup, down):
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err
+    cfg = synth.StageConfig(f"w4r-{d}-{ffn}-{rows}", "bf16", 1, d, heads, kv, 128, ffn, 0, 20, rows, rows, 5, 3)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    hid, par = synth.hidden(cfg, rows, 0, rows), synth.config_tree(cfg, seed=rows).parent
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(par, hid, rows)))
+    assert max_rel_err(got[1], got[0]) < TOL["bf16"]
+    # template arguments: projection kind first (streaming kernel) or third (few-row kernel)
+    kinds = [(_STREAM, n.split(_STREAM)[1].split(",")[0]) if _STREAM in n else (_FEW, n.split(_FEW)[1].split(",")[2].strip())
+             for n in names if _STREAM in n or _FEW in n]
+    print("  ", kinds, flush=True)
+    assert [k for k, _ in kinds if _ == "0"] == [qkv] and [k for k, _ in kinds if _ == "2"] == [gateup]
+    assert [k for k, _ in kinds if _ == "1"][-1] == down
