@@ -394,11 +394,21 @@ __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel
     __shared__ __align__(16) unsigned char xs[2][BMT * 1024];
     __shared__ float rs_s[BMT * 16];
 
-    // XCD-aware placement (workgroup id = slot * 8 + XCD): an XCD takes neighbouring units, unit = (K slice, feature block), with all their row
-    // blocks: the weights are shared, a slice's part of the activations too, and no XCD gets more than its share of the units
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, units = n_cols * k_splits;
-    const int unit = (units * xcd >> 3) + slot / m_blocks, mb = slot % m_blocks, ks = unit / n_cols, col = unit % n_cols;
-    if (unit >= units * (xcd + 1) >> 3) return;
+    // XCD-aware placement (workgroup id = slot * 8 + XCD): the row blocks of a feature block are neighbours on one XCD, which shares its weights.
+    // Without K slices, or with a multiple of 8 feature blocks, XCD x takes the feature blocks x, x + 8, ...; K slices of other numbers go by
+    // units = (K slice, feature block), neighbours on one XCD, so that none gets more than its share.  (By units also there, us: 1024 x 1024 in
+    // 8 feature blocks and 4 slices, 200 rows 11.9 -> 12.8, 383 rows 13.0 -> 14.6.)
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    int col, mb, ks;
+    if (k_splits == 1 || (n_cols & 7) == 0) {
+        const int per_col = m_blocks * k_splits;
+        col = (slot / per_col) * 8 + xcd, mb = (slot % per_col) / k_splits, ks = slot % k_splits;
+        if (col >= n_cols) return;
+    } else {
+        const int units = n_cols * k_splits, unit = (units * xcd >> 3) + slot / m_blocks;
+        mb = slot % m_blocks, ks = unit / n_cols, col = unit % n_cols;
+        if (unit >= units * (xcd + 1) >> 3) return;
+    }
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     const int r16 = lane & 15, g = lane >> 4;
     const int kt_lo = (int)((long long)a.nkt * ks / k_splits), nkt = (int)((long long)a.nkt * (ks + 1) / k_splits) - kt_lo;  // >= 1 (host)

@@ -119,3 +119,16 @@ def test_chain_residual_projections_in_uneven_slices(rows):
     pair = Pair(cfg, seed=4)
     o, g = pair.verify_tree(_chain(rows), synth.hidden(cfg, rows, 0, 4), rows)
     assert max_rel_err(g, o) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("rows", [200, 257, 383])
+def test_chain_residual_projections_of_8_feature_blocks(rows):
+    """1024 output features below 384 rows: one feature block of 128 to an XCD, with all its K slices and row blocks."""
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err
+    cfg = synth.StageConfig(f"pf-bf16-cols-{rows}", "bf16", 1, 1024, 8, 2, 128, 1024, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=4)
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(_chain(rows), synth.hidden(cfg, rows, 0, 4), rows)))
+    assert sum("wide_fixup_kernel<" in n for n in names) == 2, names
+    assert max_rel_err(got[1], got[0]) < TOL["bf16"]
