@@ -1122,12 +1122,11 @@ static WideShape wide_shape(int epi, int M) {
 struct WideGrid {
     int n_cols, m_blocks, k_splits;
 };
-// K slices for the d_model-wide residual projections: the number that takes least time, in us, by rounds of one block per compute unit and
-// their longest slice, partial results (MiB to write and sum) and what the launch that sums them takes; at least 8 k-tiles per slice, and no
-// more than the scratch array holds.  Fitted to 5900 launches of 36 widths and depths, 129 to 1024 rows, rms 6 %; over those the number it
-// takes costs 0.5 % more than the fastest one, the largest power of two that leaves at most 256 blocks 5.7 %.  512 rows x 4096: 4 slices 36 /
-// 60 us for the attention-output / down projection, 8 slices 52 / 80; 13824 x 5120: 2 slices 117 us, 3 slices 95; 700 rows 1 slice 172, 3 slices
-// 129; 1024 rows x 1024 x 1024: 1 slice 31.7, 4 slices 20.3; 2048 x 2048, 896 rows: 2 slices 29.0, 4 slices 27.1.
+// K slices for the d_model-wide residual projections: the number that costs least in rounds of one block per compute unit (0.43 us per
+// k-tile of a 128 x 256 block, 0.3 of a 128 x 128 one, 4 us into and out of it, 15 with the residual epilogue), partial results (0.5 us a MiB
+// to write and sum) and the launch that sums them; at least 8 k-tiles per slice, and no more than the scratch array holds.  512 rows x
+// 4096: 4 slices -> 256 workgroups 36 / 60 us for the attention-output / down projection, 8 slices 52 / 80; 13824 x 5120: 2 slices 117 us,
+// 3 slices 95; 700 rows 1 slice 172, 3 slices 129; 1024 rows x 1024 x 1024: 1 slice 31.7, 4 slices 20.3.
 static WideGrid wide_grid(const WideShape& sh, int epi, int M, int n_tiles, int nkt, size_t part_bytes) {
     WideGrid g;
     const int col_tiles = sh.waves * sh.wnt;
@@ -1136,14 +1135,11 @@ static WideGrid wide_grid(const WideShape& sh, int epi, int M, int n_tiles, int 
     g.k_splits = 1;
     if (epi == EPI_RESID) {
         const size_t per_split = (size_t)((M + 15) / 16) * g.n_cols * col_tiles * 1024;
-        const bool big = sh.wnt == 4;  // blocks of 128 x 256, else 128 x 128
-        const double kt = big ? 0.403 : 0.264;
+        const double kt = sh.wnt == 4 ? 0.43 : 0.3;
         double best = 1e30;
         for (int k = 1; k <= 8 && (k == 1 || (nkt / k >= 8 && per_split * k <= part_bytes)); ++k) {
             const int rounds = ((g.n_cols * k + 7) / 8 * g.m_blocks + 31) / 32;
-            const double mib = (double)(per_split * k) / (1 << 20);
-            const double cost = k == 1 ? (big ? 7.4 : 5.6) + rounds * ((big ? 10.3 : 5.4) + nkt * kt)
-                                       : (big ? 9.9 : 8.4) + rounds * ((nkt + k - 1) / k) * kt + mib * (big ? 0.33 : 0.44);
+            const double cost = rounds * (nkt * kt / k + (k > 1 ? 4 : 15)) + (k > 1 ? 4 + per_split * k * 0.5e-6 : 0);
             if (cost < best) {
                 best = cost;
                 g.k_splits = k;
