@@ -2252,15 +2252,17 @@ int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {
     return block_w4_pays(EPI_RESID, layout_nt, M, n_tiles, nkt) ? (n_tiles + 15) / 16 : n_tiles;
 }
 
-// Row tiles per block.  Equal heights, since a round lasts as long as its tallest block (5 tiles against 8: 0.9 of the time).  But where
-// three equal row blocks make a second round of at most 8 (32 compute units of an XCD) and the last one of full height has at most four
-// tiles, so that half its waves only load, the second round starts behind such blocks and runs beside the first.  us, equal / full heights:
-// 4096 x 22016, 257 rows 129.6 / 110.2, 300 rows 136 / 112.7; 7168 x 21504, 300 rows 230 / 188; 8192 x 25600 (39 blocks an XCD) 246 / 239 and
-// 262 / 240; 42 blocks, 5120 x 27648 160 / 179 and 171 / 179.  With two or four row blocks the short ones all fall to the same part of an
-// XCD and make no room elsewhere: 7168 x 33024, 129 rows 214 / 238; 4096 x 18432, 389 rows 138 / 147.
+// Row tiles per block.  Equal heights, since a round lasts as long as its tallest block (5 tiles against 8: 0.9 of the time).  But where an
+// odd number of row blocks would leave at most 7 blocks to an XCD's last round (32 compute units) and the last row block of full height has at
+// most four tiles, so that half its waves only load, what would be the last round starts behind such blocks and runs beside the others.  us,
+// equal / full heights: 4096 x 22016, 257 rows 129.6 / 110.2, 300 rows 136 / 112.7; 7168 x 21504, 300 rows 230 / 188; 8192 x 25600 (39 blocks an
+// XCD) 262 / 240; 2048 x 11264 (66) 119 / 108, 5120 x 11008 263 / 237; 5120 x 6400, 530 rows (65 blocks in five row blocks) 263 / 235; 129 blocks
+// 199 / 180, 161 in seven row blocks 245 / 225.  With more in the last round the difference goes: 40 blocks 80.3 / 84.8, 42 160 / 179.  With an even
+// number the short blocks all fall to the same part of an XCD and make no room elsewhere: 7168 x 33024, 129 rows 214 / 238; 4096 x 18432, 389 rows
+// 138 / 147.
 static int block_w4_height(bool resid, int m_tiles, int m_blocks, int n_cols) {
-    const int equal = (m_tiles + m_blocks - 1) / m_blocks, cols = (n_cols + 7) / 8, over = cols * m_blocks - 32;
-    if (!resid && m_blocks == 3 && m_tiles <= 20 && over > 0 && over <= 8) return 8;
+    const int equal = (m_tiles + m_blocks - 1) / m_blocks, blocks = (n_cols + 7) / 8 * m_blocks, over = blocks % 32;
+    if (!resid && m_blocks % 2 && m_tiles - 8 * (m_blocks - 1) <= 4 && m_blocks > 1 && blocks > 32 && over > 0 && over < 8) return 8;
     return equal;
 }
 

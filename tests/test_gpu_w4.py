@@ -240,6 +240,24 @@ def test_w4_row_blocks_of_full_height(rows):
     assert max_rel_err(g, o) < TOL["bf16"]
 
 
+@pytest.mark.parametrize("rows,ffn", [
+    (300, 22528),   # 66 blocks an XCD in three row blocks, two rounds and two: full heights
+    (321, 22528),   # the last row block of full height would have five tiles: equal
+    (530, 6656),    # 35 blocks in five row blocks: full
+    (530, 8192),    # 40: equal
+    (385, 8448),    # four row blocks of seven tiles, the last of four: its second row of waves has no rows
+    (389, 1024),    # the same in the residual projections' slices and in gate/up
+])
+def test_w4_row_blocks_of_either_height(rows, ffn):
+    from tests.gpu_util import TOL, Pair, max_rel_err
+    d = 128 if ffn > 1024 else 2176
+    cfg = synth.StageConfig(f"w4r-{rows}-{ffn}", "bf16", 1, d, 17 if ffn == 1024 else 2, 1, 128 if ffn == 1024 else 64, ffn, 0, 20, rows, rows, rows, 1)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    o, g = pair.verify_tree(np.arange(-1, rows - 1, dtype=np.int32), synth.hidden(cfg, rows, 0, rows), rows)
+    assert max_rel_err(g, o) < TOL["bf16"]
+
+
 @pytest.mark.parametrize("rows,ffn,block", [(128, 5632, False), (100, 5632, False), (80, 9216, True), (65, 11008, True)])
 def test_w4_residual_projections_between_the_two_lines(rows, ffn, block):
     """4096 features, 65 to 128 rows: two full rounds of few-row workgroups, which a K of 5632 does not make longer than the row blocks."""
