@@ -247,10 +247,8 @@ __global__ void __launch_bounds__(64) argmax_final_kernel(const int32_t* __restr
     if (threadIdx.x == 0) amax[row] = b.i;
 }
 
-// One workgroup per row in a single launch, every thread with several independent 16-byte loads in flight.  From 64 rows on (512 rows x
-// 32000: 35 -> 16 us), and for any number of rows while a row's way through one compute unit is shorter than a second launch (two
-// launches / one, us, 16 rows: 1024 logits 8.3 / 6.2, 32000 8.4 / 7.5, 50304 8.4 / 7.6, 128256 9.6 / 11.4; rows that are not on 16 bytes go
-// element by element: 152066 10.2 / 54).
+// One workgroup per row in a single launch, every thread with several independent 16-byte loads in flight: from 64 rows on (512 rows x
+// 32000: 35 -> 16 us), and for fewer while a row's way through one compute unit is shorter than a second launch.
 __global__ void __launch_bounds__(1024) argmax_row_kernel(const float* __restrict__ logits, int vocab, int32_t* __restrict__ amax) {
     const int row = blockIdx.x;
     const float* p = logits + (size_t)row * vocab;
@@ -276,8 +274,11 @@ __global__ void __launch_bounds__(1024) argmax_row_kernel(const float* __restric
 }
 
 hipError_t launch_argmax(const float* logits, int rows, int vocab, int chunks, int32_t* work, int32_t* amax, hipStream_t s) {
+    // Both sides, us of an acceptance with logits beyond the caches (two launches / one): 1 row, 16384 logits 9.1 / 9.0, 24576 9.2 / 9.9, 61440 9.3 /
+    // 11.3; 4 rows, 24576 10.4 / 10.8; 8 rows, 24576 11.1 / 10.8, 50304 11.6 / 11.3, 57344 11.5 / 11.9; 32 rows, 50304 13.5 / 13.4, 61440 13.6 / 15.0; 40
+    // rows, 65536 15.9 / 14.8.  Rows that are not on 16 bytes go element by element: 4095, 32 rows 11.8 / 10.6; 152066, 16 rows 10.2 / 54.
     const bool vec = (vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0;
-    if (rows >= 64 || vocab <= (vec ? 65536 : 4096)) {
+    if (rows >= 64 || vocab <= (!vec ? 4096 : rows < 8 ? 20480 : rows < 40 ? 53248 : 65536)) {
         hipLaunchKernelGGL(argmax_row_kernel, dim3(rows), dim3(1024), 0, s, logits, vocab, amax);
         return hipGetLastError();
     }

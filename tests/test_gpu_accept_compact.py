@@ -102,6 +102,19 @@ def test_argmax_on_either_side_of_the_one_launch_form(rows, vocab):
     test_argmax_from_logits_bit_exact_with_ties(rows, vocab)
 
 
+@pytest.mark.parametrize("rows,vocab,one", [(1, 20480, True), (7, 20484, False), (7, 61440, False), (8, 53248, True), (39, 53252, False), (39, 61440, False),
+                                            (40, 65536, True), (63, 65540, False), (64, 65540, True), (7, 4096, True), (7, 4097, False)])
+def test_argmax_takes_the_shorter_form(rows, vocab, one):
+    """Few rows of many logits: a row's way through one compute unit is longer than a second launch (1 row x 61440 11.3 / 9.3 us)."""
+    from tests.gpu_util import kernel_names
+    lg = synth.random_logits(rows, vocab, 3, rows)
+    parent, token = np.arange(-1, rows - 1, dtype=np.int32), np.zeros(rows, dtype=np.int32)
+    got = []
+    names = kernel_names(lambda: got.append(_gpu_accept(None, token, parent, rows, logits=lg)))
+    assert np.array_equal(got[0][2][:rows], oracle.argmax_rows(lg))
+    assert any("argmax_row_kernel" in n for n in names) == one and any("argmax_final_kernel" in n for n in names) != one, names
+
+
 def _stage_for_compact(dtype, n_layers, Hkv, hd, cap):
     fs = _fs()
     cfg = synth.StageConfig("cmp", dtype, n_layers, 64 * 2, 2 * (Hkv if Hkv > 1 else 1), Hkv, hd, 64, 0, 0, 16, 16, 4, 0)
