@@ -212,6 +212,17 @@ def test_bf16_comparison_would_notice_a_wrong_mask(name, cfg, seg, wgs, monkeypa
 @pytest.mark.parametrize("heads,kv,hd,rows", [(4, 2, 64, 32), (4, 4, 128, 64), (4, 4, 128, 1)])
 @pytest.mark.parametrize("slots", [65, 128, 129, 192, 193])
 def test_short_contexts_in_one_split(heads, kv, hd, rows, slots):
-    """Two and three K/V tiles (and the first slot of a fourth) with 1 to 64 rows per KV head: one workgroup walks all tiles, no merge."""
+    """Two and three K/V tiles (and the first slot of a fourth): 64 rows per KV head of 64 (up to three tiles) and one row per head of 128 (up to
+    two) in one split, without a merge; 64 rows per head of 128 and everything longer in several."""
     cfg = synth.StageConfig(f"short-{hd}-{slots}", "bf16", 1, 256, heads, kv, hd, 512, 0, slots - rows, rows, rows, 6, 4)
     _check_stage(cfg, slots, rows)
+
+
+@pytest.mark.parametrize("heads,kv,hd,rows,slots,one", [
+    (4, 4, 128, 17, 65, True), (4, 4, 128, 32, 128, True), (8, 4, 128, 16, 128, True), (4, 4, 128, 32, 129, False), (4, 4, 128, 33, 128, False),
+    (4, 2, 64, 32, 192, True), (4, 2, 64, 32, 193, False), (4, 2, 64, 33, 192, False)])
+def test_short_contexts_up_to_both_ends_of_the_rule(heads, kv, hd, rows, slots, one):
+    from tests.gpu_util import kernel_names
+    cfg = synth.StageConfig(f"ends-{hd}-{rows}-{slots}", "bf16", 1, 256, heads, kv, hd, 512, 0, slots - rows, rows, rows, 6, 4)
+    names = kernel_names(lambda: _check_stage(cfg, slots, rows))
+    assert any("tree_attn" in n for n in names) and any("attn_merge_kernel" in n for n in names) != one, names

@@ -138,10 +138,10 @@ def test_w4_random_shapes(i):
     # residual projections and LM head in 64-row blocks, the attention output with one K slice; the others in the few-row kernel
     ("resid", synth.StageConfig("w4b-resid", "bf16", 2, 4992, 2, 2, 64, 1152, 34000, 30, 33, 33, 5, 3), 33),
     ("resid", synth.StageConfig("w4b-resid", "bf16", 1, 4992, 2, 2, 64, 1152, 34000, 30, 64, 64, 5, 3), 64),
-    # gate/up only: 64-row blocks, and 128-row blocks whose last one holds a single row
+    # gate/up only: 64-row blocks, and 128-row blocks (161 rows: 6 and 5 row tiles, the last one with a single row)
     ("gateup", synth.StageConfig("w4b-gu", "bf16", 2, 128, 2, 1, 64, 17024, 0, 30, 64, 64, 5, 3), 64),
     ("gateup", synth.StageConfig("w4b-gu", "bf16", 2, 128, 2, 1, 64, 9728, 0, 30, 161, 161, 161, 1), 161),
-    # one row tile, 344 groups of four gate/up tiles: half a group per workgroup
+    # one row tile, gate/up of 1376 tiles (half groups: the next test)
     ("half", synth.StageConfig("w4b-half", "bf16", 1, 128, 2, 1, 64, 11008, 0, 30, 16, 16, 5, 3), 16),
 ])
 def test_w4_row_blocks(name, cfg, rows):
@@ -165,10 +165,37 @@ def test_w4_row_blocks(name, cfg, rows):
         assert max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
 
 
+@pytest.mark.parametrize("rows", [1, 16])
+def test_w4_half_groups(rows):
+    """One row tile, gate/up of 592 groups of four tiles: half a group per workgroup."""
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err
+    cfg = synth.StageConfig(f"w4-half-{rows}", "bf16", 1, 256, 2, 2, 128, 18944, 0, 30, rows, rows, 5, 3)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)))
+    assert max_rel_err(got[1], got[0]) < TOL["bf16"]
+    assert any("skinny_gemm_w4_kernel<1, 2, 2, 2>" in n for n in names), names   # two of a group's four tiles
+
+
+@pytest.mark.parametrize("rows,ffn,wn", [(33, 5504, 2), (64, 5504, 2), (33, 11008, 4), (64, 11008, 4)])
+def test_w4_streaming_kernel_behind_a_few_row_producer(rows, ffn, wn):
+    """4096 columns: the output projection leaves 256 partial sums of squares, more than a thread of gate/up loads ahead of the ring."""
+    from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err
+    cfg = synth.StageConfig(f"w4-ssp-{rows}-{ffn}", "bf16", 1, 4096, 1, 1, 128, ffn, 0, 20, rows, rows, 5, 3)
+    print(f"[case] {cfg.name}", flush=True)
+    pair = Pair(cfg, seed=rows, w4=True)
+    got = []
+    names = kernel_names(lambda: got.extend(pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)))
+    assert max_rel_err(got[1], got[0]) < TOL["bf16"]
+    assert any(f"stream_gemm_w4_kernel<2, {wn}, 2, 4" in n for n in names), names
+    assert any("skinny_gemm_w4_kernel" in n and ", 1, " in n for n in names), names   # the output projection
+
+
 @pytest.mark.parametrize("rows", [500, 641])
 def test_w4_residual_projections_of_a_short_k(rows):
-    """1536 input columns: few-row kernel in row blocks up to about 570 rows, beyond in 128-row blocks (the last
-    one holds a single row) with 3 K slices of 4 chunks."""
+    """1536 input columns: few-row kernel in row blocks up to about 570 rows, beyond in 128-row blocks (6 or 5 row
+    tiles, the last one with a single row) in K slices."""
     from tests.gpu_util import TOL, Pair, max_rel_err
     cfg = synth.StageConfig(f"w4-short-k-{rows}", "bf16", 2, 1536, 12, 2, 128, 1536, 0, 20, rows, rows, rows, 1)
     print(f"[case] {cfg.name}", flush=True)
