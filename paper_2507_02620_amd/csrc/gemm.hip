@@ -1156,10 +1156,10 @@ int wide_ssp_parts(int M, int n_tiles) {  // one per workgroup column of the res
 }
 
 size_t wide_partial_bytes(int max_rows, int n_tiles) {
-    // slices * row tiles * feature tiles KiB: at most 8 slices of the whole result, and, with slices * blocks bounded by the
-    // split rule, at most 512 blocks' worth of tiles (largest block shape)
+    // slices * row tiles * feature tiles KiB: 8 slices of the whole result, and at most 64 MiB; the launches take fewer slices where those do
+    // not fit
     const size_t whole = (size_t)8 * ((max_rows + 15) / 16) * (size_t)(n_tiles + 15) * 1024;
-    const size_t cap = (size_t)512 * 8 * 4 * 4 * 1024;
+    const size_t cap = (size_t)64 << 20;
     return whole < cap ? whole : cap;
 }
 
@@ -1580,11 +1580,11 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     constexpr int TPI = PAIR ? 2 : 1;
     constexpr int NW = WM * WN, BMT = WM * MT, BNT = WN * NT, ROWS = BMT * 16, THREADS = NW * 64;
-    constexpr int AF = 4 * BMT, LA = (AF + NW - 1) / NW, LW = BNT / NW, LPS = LA + LW + 1;
+    constexpr int AF = 4 * BMT, LA = AF / NW, LW = BNT / NW, LPS = LA + LW + 1;
     constexpr int SCALES = (AF + BNT) * 1024, STAGE = SCALES + NW * 256;
-    static_assert(BNT % NW == 0 && BMT <= NW, "every wave issues the same loads");
+    static_assert(AF % NW == 0 && BNT % NW == 0 && BMT <= NW, "every wave issues the same loads");
     static_assert((R == 3 || R == 4) && LPS * (R - 1) < 64 && R * STAGE + ROWS * 12 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
-    static_assert(NT <= 8, "a wave's scales fit one load");
+    static_assert(NT <= 8 && THREADS % ROWS == 0, "a wave's scales fit one load; whole rows per pass of the row-scale sums");
     __shared__ __align__(1024) unsigned char sb0[STAGE];
     __shared__ __align__(1024) unsigned char sb1[STAGE];
     __shared__ __align__(1024) unsigned char sb2[STAGE];
@@ -1613,15 +1613,13 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     // RMSNorm: this thread's share of its row's partial sums of squares (the loads go out in front of the ring's)
     constexpr int TPR = THREADS / ROWS, SL = 8;
     float sp[SL], s_more = 0.f;
-    const int row = t % ROWS, sub = t / ROWS;  // (threads beyond the last whole pass over the rows have no share)
+    const int row = t % ROWS, sub = t / ROWS;
     if (NORM) {
         const int m = min(mt0 * 16 + row, M - 1);
 #pragma unroll
         for (int i = 0; i < SL; ++i) sp[i] = a.ssp_in[(size_t)min(sub + i * TPR, a.ssp_n - 1) * a.ssp_stride + m];
-        if (sub < TPR) {
 #pragma unroll 8
-            for (int j = sub + SL * TPR; j < a.ssp_n; j += TPR) s_more += a.ssp_in[(size_t)j * a.ssp_stride + m];
-        }
+        for (int j = sub + SL * TPR; j < a.ssp_n; j += TPR) s_more += a.ssp_in[(size_t)j * a.ssp_stride + m];
     }
 
     // this wave's loads of a stage: fragments i * NW + w of the activations (k-tile, row tile), code tiles i * NW + w, its own scales
@@ -1632,7 +1630,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     unsigned xo[LA], wo[LW], so;
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-        const int f = min(i * NW + w, AF - 1), mt = min(mt0 + min(f % BMT, bt - 1), m_tiles - 1);
+        const int f = i * NW + w, mt = min(mt0 + min(f % BMT, bt - 1), m_tiles - 1);
         xo[i] = ((unsigned)mt * (unsigned)nkc * 4u + (unsigned)kc_lo * 4u + (unsigned)(f / BMT)) * 1024u + (unsigned)lane * 16u;
     }
 #pragma unroll
@@ -1651,7 +1649,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
         const unsigned live = (unsigned)((st - ns) >> 31);  // uniform, all ones or zero
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
-            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + min(i * NW + w, AF - 1) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + (i * NW + w) * 1024), 16, 0, 0);
             xo[i] += 4096u;
         }
 #pragma unroll
@@ -1866,10 +1864,10 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
     constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
     constexpr int TPI = PAIR ? 2 : 1;
     constexpr int NW = WN * KG, BNT = WN * NT, ROWS = MT * 16, THREADS = NW * 64;
-    constexpr int AF = KG * 4 * MT, WF = KG * BNT, LA = (AF + NW - 1) / NW, LW = WF / NW, LPS = LA + LW + 1;
+    constexpr int AF = KG * 4 * MT, WF = KG * BNT, LA = AF / NW, LW = WF / NW, LPS = LA + LW + 1;
     constexpr int SCALES = (AF + WF) * 1024, STAGE = SCALES + NW * 256;
     constexpr int ITEMS = MT * NT / TPI;
-    static_assert(WF % NW == 0 && NT % TPI == 0 && NT <= 8, "every wave issues the same loads; its scales fit one of them");
+    static_assert(AF % NW == 0 && WF % NW == 0 && KG > 1 && NT % TPI == 0 && NT <= 8, "every wave issues the same loads; its scales fit one of them");
     static_assert(R >= 3 && R <= 6 && LPS * (R - 1) < 64 && R * STAGE + NW * ROWS * 4 <= 160 * 1024, "6-bit wait counter, 160 KiB of LDS");
     static_assert((NW + 1) / 2 * MT * NT * 1024 <= STAGE, "the groups' tiles fit two stage buffers");
     // one array per buffer: distinct objects, see block_gemm_kernel
@@ -1892,7 +1890,8 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
     const int m_tiles = (M + 15) >> 4;
 
     // RMSNorm: this lane's share of its row's partial sums of squares (the loads go out in front of the ring's)
-    constexpr int TPR = THREADS / ROWS, SL = MT == 1 ? 12 : 20;  // 320 partial sums and more without the loop below, which waits
+    constexpr int TPR = THREADS / ROWS, SL = MT == 1 ? 12 : 20;
+    // (TPR * SL partial sums without the loop below, which waits: 384 up to 16 rows, 320 up to 32, 160 or 80 up to 64)
     float sp[SL], s_more = 0.f;
     const int row = t % ROWS, sub = t / ROWS;
     if (NORM) {
@@ -1913,7 +1912,7 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
     int xn[LA], wn_[LW];  // stages in which the load's chunk exists
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
-        const int f = min(i * NW + w, AF - 1), j = f / (4 * MT), mt = min(f % MT, m_tiles - 1);
+        const int f = i * NW + w, j = f / (4 * MT), mt = min(f % MT, m_tiles - 1);
         xo[i] = ((unsigned)mt * (unsigned)nkc * 4u + (unsigned)(kc_lo + j) * 4u + (unsigned)(f / MT % 4)) * 1024u + (unsigned)(lane - r16 + min(r16, M - 1 - mt * 16)) * 16u;
         xn[i] = (n - j + KG - 1) / KG;
     }
@@ -1943,7 +1942,7 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const unsigned live = (unsigned)((st - xn[i]) >> 31);
-            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + min(i * NW + w, AF - 1) * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(FS_GLB_PTR(xb + (xo[i] & live)), FS_LDS_PTR(dst + (i * NW + w) * 1024), 16, 0, 0);
             xo[i] += KG * 4096u;
         }
         ++st;
@@ -2038,13 +2037,11 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
 
     // ---- the groups' tiles meet in two stage buffers; item i belongs to group i % KG ----
     auto slot = [&](int ww) -> f32x4* { return (f32x4*)((ww & 1) ? sb1 : sb0) + (size_t)(ww >> 1) * MT * NT * 64 + lane; };
-    if constexpr (KG > 1) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) slot(w)[(mt * NT + nt) * 64] = acc[mt][nt];
-        __syncthreads();
-    }
+        for (int nt = 0; nt < NT; ++nt) slot(w)[(mt * NT + nt) * 64] = acc[mt][nt];
+    __syncthreads();
     const int pt0 = col * BNT + wn * NT;
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
@@ -2055,13 +2052,9 @@ __global__ void __launch_bounds__(WN * KG * 64) stream_gemm_w4_kernel(const void
 #pragma unroll
         for (int tt = 0; tt < TPI; ++tt) {
             const int nt = ntp * TPI + tt;
-            if constexpr (KG > 1) {
-                y4[tt] = slot(wn)[(mt * NT + nt) * 64];
+            y4[tt] = slot(wn)[(mt * NT + nt) * 64];
 #pragma unroll
-                for (int k = 1; k < KG; ++k) y4[tt] += slot(k * WN + wn)[(mt * NT + nt) * 64];
-            } else {
-                y4[tt] = acc[mt][nt];
-            }
+            for (int k = 1; k < KG; ++k) y4[tt] += slot(k * WN + wn)[(mt * NT + nt) * 64];
         }
         if constexpr (EPI == EPI_RESID) {  // raw tiles: part[ks][m tile][n tile][lane]
             ((f32x4*)part)[(((size_t)ks * m_tiles + mt) * (gridDim.x * BNT) + pt0 + ntp) * 64 + lane] = y4[0];
