@@ -2212,6 +2212,7 @@ static bool block_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) {
 // 4096, 24 rows 19.1 / 15.2; gate/up of 1728 x 5120, 16 rows 27.7 / 22.6, 24 rows 34.1 / 26.3, 64 rows 50.9 / 37.1; 11008 x 4096, 16 rows 16.1 /
 // 13.5.  The least numbers: below them both kernels are short and the estimates (fitted to 4500 launches of 70 shapes, rms 4 - 7 %) say too
 // little: head of 640 x 2048, 16 rows 9.5 / 10.2; 4096 x 1024, 24 rows 9.3 / 9.8.
+// (Near a tie the estimates still choose well, and a margin for the few-row kernel gives calls away: QKV of 960 x 5120, 24 rows 15.3 / 17.3.)
 static bool stream_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) {
     // (16000 tiles: one slice's partial results of a residual projection then fit 64 MiB; a head that wide has not been measured)
     if (M > 64 || n_tiles > 16000 || !block_w4_fits(M, n_tiles, nkt)) return false;
@@ -2237,7 +2238,7 @@ static bool stream_w4_pays(int epi, int layout_nt, int M, int n_tiles, int nkt) 
         other = block_w4_slices(M, n_tiles, nkc, (size_t)64 << 20).us;
     else
         other = (((n_tiles + 15) / 16 + 7) / 8 + 31) / 32 * (10 + (0.15 + 0.27 * m_tiles) * nkc);
-    return us < 0.95 * other;
+    return us < other;
 }
 
 int w4_ssp_parts(int layout_nt, int M, int n_tiles, int nkt) {

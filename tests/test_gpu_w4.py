@@ -206,8 +206,8 @@ def test_w4_residual_projections_of_a_short_k(rows):
 
 @pytest.mark.parametrize("rows,ffn", [(1, 8320), (16, 8320), (17, 5248), (32, 5248), (33, 10368), (64, 10368)])
 def test_w4_streaming_kernel(rows, ffn):
-    """Up to 64 rows through the LDS-fed 4-bit kernel: QKV and gate/up in blocks of four and eight tiles, up to 32 rows the down projection in
-    K slices of an odd number of chunks (33 and 64 rows: the next test), a head whose last block is ragged; both ends of each row-tile count."""
+    """Up to 64 rows through the LDS-fed 4-bit kernel: QKV and gate/up in blocks of four and eight tiles, the down projection in
+    K slices of an odd number of chunks, a head whose last block is ragged; both ends of each row-tile count."""
     import torch
     from tests.gpu_util import TOL, Pair, kernel_names, max_rel_err, to_dev
     cfg = synth.StageConfig(f"w4s-{rows}", "bf16", 2, 256, 36, 18, 128, ffn, 11300, 20, rows, rows, 5, 3, qkv_bias=True)
@@ -217,7 +217,7 @@ def test_w4_streaming_kernel(rows, ffn):
     names = kernel_names(lambda: got.extend(pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)))
     o, g = got
     assert [sum(f"stream_gemm_w4_kernel<{kind}," in n for n in names) for kind in (0, 2)] == [2, 2], names
-    assert any("stream_gemm_w4_kernel<1," in n for n in names) == (rows <= 32), names
+    assert any("stream_gemm_w4_kernel<1," in n for n in names), names
     L = cfg.l_glo + rows
     kerr = max_rel_err(pair.kv[:, :, :, cfg.l_glo:L].float().cpu().numpy(), pair.orc.kv[:, :, :, cfg.l_glo:L])
     x = synth.storage(cfg, o.astype(np.float32))
@@ -311,6 +311,8 @@ _FEW, _STREAM = "skinny_gemm_w4_kernel<", "stream_gemm_w4_kernel<"
     (2560, 20, 20, 2048, 64, _FEW, _FEW, _FEW),
     # more than a round: 320 groups of two tiles (QKV), gate/up of 1312 and 1920 tiles; the down projection of 5248 and 7680 columns
     (1024, 40, 20, 7680, 24, _STREAM, _STREAM, _STREAM),
+    # close to each other: QKV of 960 tiles, 15.3 against 17.3 us
+    (5120, 40, 40, 2048, 24, _STREAM, _FEW, _FEW),
     (5120, 4, 4, 5248, 24, _FEW, _STREAM, _STREAM),
     (5120, 4, 4, 5248, 33, _FEW, _STREAM, _STREAM),
     (5120, 4, 4, 5248, 64, _FEW, _STREAM, _STREAM),
