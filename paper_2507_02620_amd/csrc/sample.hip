@@ -37,6 +37,7 @@ static __device__ __forceinline__ uint64_t exp_weight(float z, float m) {
     p = fmaf(p, f, 1.0f);
     const unsigned bits = __float_as_uint(p);
     const int sh = 127 - (int)(bits >> 23) - (int)n;  // 0 .. 64 places below 2^32 (p = 2 only with n <= -1)
+    // (the shift in 32 bits, with the cases of no and of more than 32 places apart, makes the sums' launch 12.8 -> 14.2 us)
     return ((uint64_t)((bits & 0x7FFFFFu) | 0x800000u) << 9) >> min(sh, 63);
 }
 
@@ -48,32 +49,33 @@ static __device__ __forceinline__ unsigned max_key(float m) {
 }
 static __device__ __forceinline__ float key_max(unsigned k) { return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k); }
 
-// Visits the elements [lo, hi) of a row with all threads of the group, adjacent threads on adjacent 16 bytes (four loads in flight
-// per thread) where the row allows it (lo a multiple of 4).
-template <typename F>
+// Visits the elements [lo, hi) of a row with all threads of the group, adjacent threads on adjacent 16 bytes (U loads in flight per
+// thread) where the row allows it (lo a multiple of 4).  fn(x, live).  CLAMP: a last round repeats the last 16 bytes instead of going
+// one load at a time (live is false for repeats): shorter where a round is most of the work, longer where it is little of it.
+template <int U, bool CLAMP, typename F>
 static __device__ __forceinline__ void for_row(const float* __restrict__ p, int lo, int hi, int t, int nt, bool vec, F&& fn) {
     int v = lo;
     if (vec) {
         const int n4 = (hi - lo) >> 2;
         const f32x4* p4 = (const f32x4*)(p + lo);
         int i = t;
-        for (; i + 3 * nt < n4; i += 4 * nt) {
-            f32x4 x[4];
+        for (; CLAMP ? i < n4 : i + (U - 1) * nt < n4; i += U * nt) {
+            f32x4 x[U];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) x[k] = p4[i + k * nt];
+            for (int k = 0; k < U; ++k) x[k] = p4[CLAMP ? min(i + k * nt, n4 - 1) : i + k * nt];
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
+            for (int k = 0; k < U; ++k)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) fn(x[k][e]);
+                for (int e = 0; e < 4; ++e) fn(x[k][e], !CLAMP || i + k * nt < n4);
         }
         for (; i < n4; i += nt) {
             const f32x4 x = p4[i];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) fn(x[e]);
+            for (int e = 0; e < 4; ++e) fn(x[e], true);
         }
         v = lo + 4 * n4;
     }
-    for (int i = v + t; i < hi; i += nt) fn(p[i]);
+    for (int i = v + t; i < hi; i += nt) fn(p[i], true);
 }
 
 static __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
@@ -85,7 +87,7 @@ static __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 // Row statistics of the verified rows: m = max z and Z = sum of the integer weights, which needs m first.  A compute unit draws 25 - 45 GB/s
 // from memory, so one workgroup per row leaves most of the chip idle (80 rows x 152064: 351 us in one launch with scalar loads);
 // here every row is cut into gridDim.x chunks and the chunks of a row meet in an atomic maximum and an atomic (integer: order does
-// not matter) sum: 1.6 + 15 + 13 us, 48.7 MB read twice at 3.2 - 3.7 TB/s.
+// not matter) sum: 1.6 + 11 + 13 us, 48.7 MB read twice at 4.4 and 3.7 TB/s (the weights' arithmetic alone is about 9 us of the second pass).
 __global__ void __launch_bounds__(256) sample_clear_kernel(unsigned* __restrict__ rowm, unsigned long long* __restrict__ rowZ, int rows) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < rows) {
@@ -94,13 +96,14 @@ __global__ void __launch_bounds__(256) sample_clear_kernel(unsigned* __restrict_
     }
 }
 
+template <int U>
 __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_max_kernel(const float* __restrict__ logits, int vocab, float inv_temp, int chunk, bool vec,
                                                                       unsigned* __restrict__ rowm) {
     __shared__ float shm[SMP_STAT_THREADS / 64];
     const float* p = logits + (size_t)blockIdx.y * vocab;
     const int lo = blockIdx.x * chunk, hi = min(vocab, lo + chunk);
     float m = -INFINITY;
-    for_row(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
+    for_row<U, true>(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, FS_WAVE));
     if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = m;
     __syncthreads();
@@ -110,6 +113,7 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_max_kernel(const floa
     }
 }
 
+template <int U>
 __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_sum_kernel(const float* __restrict__ logits, int vocab, float inv_temp, int chunk, bool vec,
                                                                       const unsigned* __restrict__ rowm, unsigned long long* __restrict__ rowZ) {
     __shared__ uint64_t shz[SMP_STAT_THREADS / 64];
@@ -117,7 +121,7 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_sum_kernel(const floa
     const int lo = blockIdx.x * chunk, hi = min(vocab, lo + chunk);
     const float m = key_max(rowm[blockIdx.y]);
     uint64_t z = 0;
-    for_row(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { z += exp_weight(__fmul_rn(x, inv_temp), m); });
+    for_row<U, true>(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool live) { z += live ? exp_weight(__fmul_rn(x, inv_temp), m) : 0; });
     z = wave_sum_u64(z);
     if ((threadIdx.x & 63) == 0) shz[threadIdx.x >> 6] = z;
     __syncthreads();
@@ -135,14 +139,14 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_rowstats_kernel(const
     __shared__ uint64_t shz[SMP_STAT_THREADS / 64];
     const float* p = logits + (size_t)blockIdx.x * vocab;
     float m = -INFINITY;
-    for_row(p, 0, vocab, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
+    for_row<4, false>(p, 0, vocab, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, FS_WAVE));
     if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = m;
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < SMP_STAT_THREADS / 64; ++w) m = fmaxf(m, shm[w]);
     uint64_t z = 0;
-    for_row(p, 0, vocab, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x) { z += exp_weight(__fmul_rn(x, inv_temp), m); });
+    for_row<4, false>(p, 0, vocab, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool live) { z += live ? exp_weight(__fmul_rn(x, inv_temp), m) : 0; });
     z = wave_sum_u64(z);
     if ((threadIdx.x & 63) == 0) shz[threadIdx.x >> 6] = z;
     __syncthreads();
@@ -155,6 +159,7 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_rowstats_kernel(const
 
 #define SMP_THREADS 1024 /* one node of the tree per thread */
 #define SMP_WAVES (SMP_THREADS / 64)
+#define SMP_PENDING (-2)  /* x_new while the residual draw is still to come */
 
 // Rank of this thread among the threads whose flag is set, and their number (two barriers).
 static __device__ __forceinline__ int block_rank(bool flag, int* sh, int* total) {
@@ -174,24 +179,26 @@ static __device__ __forceinline__ int block_rank(bool flag, int* sh, int* total)
     return before + __popcll(b & ((1ull << lane) - 1));
 }
 
-// One workgroup walks the tree.  Latency is what it costs, so per accepted node everything that can be parallel is: the children
-// are gathered by ballots, their weights fetched together and their duplicate tests run side by side; one lane then only takes
+// One workgroup walks the tree.  Latency is what it costs, so everything that can be parallel is: every node's weight under its parent's
+// row and every row's sum are fetched before the walk (one round of memory latency for the whole tree instead of two per accepted
+// node), the children of a node are gathered by ballots and their duplicate tests run side by side; one lane then only takes
 // the decisions from LDS.  The residual draw narrows the vocabulary down in up to three coalesced passes (a sixteenth per wave, a
 // sixteenth of that per wave, then 64 elements at a time) with the rejected tokens' weights taken off the sums; what is down to
 // 256 elements (64 behind many rejected tokens, which every step of the last pass looks through) goes to the last one at once: two
 // barriers of 16 waves cost more than its three further steps (one node, 200 entries, whole call 11.0 -> 6.9 us).
-// (Three accepted nodes and a residual draw over 152064 entries: 420 -> 40 us, of which the 608 KB row through one compute unit is
-// the larger part; 16 rows x 32000 below a star of 16 nodes, whole call: 338 -> 35 us.)
+// (16 rows x 32000 below a star of 16 nodes, whole call: 338 -> 35 us.)  Where sample_draw_kernel follows (`pending`), the draw's target is
+// left to it: three accepted nodes and a draw over 152064 entries 40 us in here, of which the 608 KB row through one compute unit was the
+// larger part, now 8 here and 10.6 there.
 __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float* __restrict__ logits, int vocab, float inv_temp, bool vec,
-                                                                    const unsigned* __restrict__ rowm, const unsigned long long* __restrict__ rowZ,
+                                                                    const unsigned* __restrict__ rowm, const unsigned long long* rowZ,
                                                                     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, int T,
                                                                     int n_ver, uint64_t seed, uint64_t step, AcceptResultDev* __restrict__ res,
-                                                                    int32_t* __restrict__ retain) {
+                                                                    int32_t* __restrict__ retain, unsigned long long* pending) {
     __shared__ short child[1024], jump[2][1024];
     __shared__ unsigned char keep[1024], reach[2][1024], skip[1024];
     __shared__ __align__(16) int ctok[1024];
     __shared__ int rej[1024], sh[SMP_WAVES];
-    __shared__ uint64_t cw[1024], rejw[1024], sums[SMP_WAVES];
+    __shared__ uint64_t cw[1024], rejw[1024], zrow[1024], sums[SMP_WAVES];
     __shared__ int s_next, s_nrej;
     __shared__ uint64_t s_draw, s_target;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -211,15 +218,14 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
         return;
     }
 
+    const bool in_vocab = tid < T && tok >= 0 && tok < vocab;
+    const uint64_t wt = in_vocab && par >= 0 && par < n_ver ? exp_weight(__fmul_rn(logits[(size_t)par * vocab + tok], inv_temp), key_max(rowm[par])) : 0;
+    if (tid < n_ver) zrow[tid] = rowZ[tid];
+
     int u = 0, n_acc = 0, x_new = -1, n_new = -1;  // uniform over the workgroup
     for (;;) {  // one iteration per accepted node: at most T of them
-        const float* row = logits + (size_t)u * vocab;
-        const float m = key_max(rowm[u]);
-        const uint64_t Z = rowZ[u];
         // children of u in ascending order, their tokens and weights
         const bool is_child = tid < T && par == u;
-        const bool in_vocab = is_child && tok >= 0 && tok < vocab;
-        const uint64_t wt = in_vocab ? exp_weight(__fmul_rn(row[tok], inv_temp), m) : 0;
         int n_child;
         const int rank = block_rank(is_child, sh, &n_child);
         if (is_child) {
@@ -243,7 +249,7 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
         }
         __syncthreads();
         if (tid == 0) {
-            uint64_t R = Z, draw = s_draw;
+            uint64_t R = zrow[u], draw = s_draw;
             int n_rej = 0, next = -1;
             for (int k = 0; k < n_child && next < 0; ++k) {
                 if (skip[k]) continue;
@@ -280,6 +286,16 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
         }
         // Residual draw: the first v whose running sum of unstruck weights exceeds the target.  Integer sums: any grouping gives
         // the same token.
+        if (pending) {  // left to the launches behind this one
+            if (tid == 0) {
+                pending[0] = s_target;
+                pending[1] = 0;
+            }
+            x_new = SMP_PENDING;
+            break;
+        }
+        const float* row = logits + (size_t)u * vocab;
+        const float m = key_max(rowm[u]);
         const uint64_t target = s_target;
         const int n_rej = s_nrej;
         int lo = 0, hi = vocab;
@@ -290,7 +306,7 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
             const int part = ((hi - lo + SMP_WAVES - 1) / SMP_WAVES + 3) & ~3;  // a multiple of 4 elements per wave
             const int wlo = min(hi, lo + w * part), whi = min(hi, wlo + part);
             uint64_t z = 0;
-            for_row(row, wlo, whi, lane, 64, vec, [&](float x) { z += exp_weight(__fmul_rn(x, inv_temp), m); });
+            for_row<4, false>(row, wlo, whi, lane, 64, vec, [&](float x, bool live) { z += live ? exp_weight(__fmul_rn(x, inv_temp), m) : 0; });
             for (int j = lane; j < n_rej; j += 64)
                 if (rej[j] >= wlo && rej[j] < whi) z -= rejw[j];
             z = wave_sum_u64(z);
@@ -357,29 +373,174 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
     if (tid == 0) *res = AcceptResultDev{n_acc, x_new, n_new, n_new >= 0, total, prv};
 }
 
+// ---- residual draw of a large vocabulary -----------------------------------------------------------------------------------
+// One compute unit takes 24 us for a row of 152064 logits.  Spread over the chip every workgroup sums one chunk of the row, and the one that
+// arrives last finds the token in the chunk that holds the target (two launches instead: 5.4 + 5.6 us against 10.6, but a call whose
+// walk ends without a draw then pays for two that do nothing, 2.3 us each).  Nobody waits for anybody: the last to arrive is told by a
+// counter.  All children of the last accepted node were rejected, so the struck tokens are read off the tree again.
+#define DRAW_THREADS 256
+#define DRAW_EACH 16  /* consecutive logits per thread */
+#define DRAW_BLOCK (DRAW_THREADS * DRAW_EACH)
+
+// Bit e of word t: entry lo + 16 t + e is struck (a child of u carries it).  Ends with a barrier.
+static __device__ __forceinline__ void struck_bits(unsigned* bits, const int32_t* __restrict__ token, const int32_t* __restrict__ parent, int T, int u, int lo,
+                                                   int hi) {
+    const int tid = threadIdx.x;
+    __syncthreads();
+    bits[tid] = 0;
+    __syncthreads();
+    for (int i = u + 1 + tid; i < T; i += DRAW_THREADS) {
+        const int par = parent[i], tok = token[i];
+        if (par == u && tok >= lo && tok < hi) atomicOr(&bits[(tok - lo) / DRAW_EACH], 1u << ((tok - lo) % DRAW_EACH));
+    }
+    __syncthreads();
+}
+
+// This thread's 16 logits of the block at lo (those at hi and beyond come as -inf: no weight).
+static __device__ __forceinline__ void draw_load(const float* __restrict__ row, int lo, int hi, bool vec, float (&x)[DRAW_EACH]) {
+    const int v = lo + threadIdx.x * DRAW_EACH;
+    if (vec && v + DRAW_EACH <= hi) {
+#pragma unroll
+        for (int k = 0; k < DRAW_EACH / 4; ++k) {
+            const f32x4 q = *(const f32x4*)(row + v + 4 * k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * k + e] = q[e];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < DRAW_EACH; ++e) x[e] = v + e < hi ? row[v + e] : -INFINITY;
+    }
+}
+
+// Running sum of v over the lanes, this lane's included.
+static __device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {
+    const int lane = threadIdx.x & 63;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint64_t below = __shfl_up(v, o, FS_WAVE);
+        if (lane >= o) v += below;
+    }
+    return v;
+}
+
+// draw: {target, workgroups that are done (0 before the launch), sums of the chunks}
+__global__ void __launch_bounds__(DRAW_THREADS) sample_draw_kernel(const float* __restrict__ logits, int vocab, float inv_temp, bool vec, int chunk,
+                                                                   const unsigned* __restrict__ rowm, const int32_t* __restrict__ token,
+                                                                   const int32_t* __restrict__ parent, int T, AcceptResultDev* res,
+                                                                   const int32_t* __restrict__ retain, unsigned long long* draw) {
+    __shared__ unsigned bits[DRAW_THREADS];
+    __shared__ uint64_t shz[DRAW_THREADS / 64];
+    __shared__ int s_last, s_x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, chunks = gridDim.x;
+    const int n_acc = res->n_acc;
+    if (n_acc < 1 || res->x_new != SMP_PENDING) return;
+    const int u = retain[n_acc - 1];  // nothing is retained behind the accepted path
+    const float* row = logits + (size_t)u * vocab;
+    const float m = key_max(rowm[u]);
+    auto weights = [&](int lo, int hi, float (&x)[DRAW_EACH], unsigned& b) {  // this thread's sum of the block at lo
+        draw_load(row, lo, hi, vec, x);
+        struck_bits(bits, token, parent, T, u, lo, hi);
+        b = bits[tid];
+        uint64_t z = 0;
+#pragma unroll
+        for (int e = 0; e < DRAW_EACH; ++e) z += (b >> e) & 1 ? 0 : exp_weight(__fmul_rn(x[e], inv_temp), m);
+        return z;
+    };
+    float x[DRAW_EACH];
+    unsigned b;
+    uint64_t z = 0;
+    for (int lo = blockIdx.x * chunk, c_hi = min(vocab, lo + chunk); lo < c_hi; lo += DRAW_BLOCK) z += weights(lo, min(c_hi, lo + DRAW_BLOCK), x, b);
+    z = wave_sum_u64(z);
+    if (lane == 0) shz[w] = z;
+    __syncthreads();
+    if (tid == 0) {
+        for (int k = 1; k < DRAW_THREADS / 64; ++k) z += shz[k];
+        __hip_atomic_store(&draw[2 + blockIdx.x], z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = __hip_atomic_fetch_add(&draw[1], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned long long)(chunks - 1);
+    }
+    __syncthreads();
+    if (!s_last) return;
+    // the first chunk whose running sum exceeds the target (at most 64 chunks; every wave does the same)
+    const uint64_t target = draw[0], own = lane < chunks ? __hip_atomic_load(&draw[2 + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    const uint64_t upto = wave_scan_u64(own);
+    const unsigned long long hit = __ballot(lane < chunks && upto > target);
+    int x_new = vocab - 1;  // the definition's default (no weight left)
+    if (hit) {
+        const int c = __ffsll(hit) - 1;
+        uint64_t base = __shfl(upto - own, c, FS_WAVE);
+        for (int lo = c * chunk, c_hi = min(vocab, lo + chunk); lo < c_hi; lo += DRAW_BLOCK) {
+            if (tid == 0) s_x = -1;
+            z = weights(lo, min(c_hi, lo + DRAW_BLOCK), x, b);
+            const uint64_t run = wave_scan_u64(z);
+            if (lane == 63) shz[w] = run;
+            __syncthreads();
+            uint64_t before = base;
+#pragma unroll
+            for (int k = 0; k < DRAW_THREADS / 64; ++k) {
+                before += k < w ? shz[k] : 0;
+                base += shz[k];
+            }
+            before += run - z;
+            if (before <= target && target < before + z) {  // at most one thread
+                int at = -1;
+#pragma unroll
+                for (int e = 0; e < DRAW_EACH; ++e) {
+                    before += (b >> e) & 1 ? 0 : exp_weight(__fmul_rn(x[e], inv_temp), m);
+                    if (at < 0 && before > target) at = e;
+                }
+                s_x = lo + tid * DRAW_EACH + at;
+            }
+            __syncthreads();
+            if (s_x >= 0) {
+                x_new = s_x;
+                break;
+            }
+        }
+    }
+    if (tid == 0) res->x_new = x_new;
+}
+
 hipError_t launch_accept_sample(const float* logits, int vocab, float inv_temp, const int32_t* token, const int32_t* parent, int T, int n_ver,
                                 uint64_t seed, uint64_t step, AcceptResultDev* res, int32_t* retain, void* work, hipStream_t s) {
     unsigned* rowm = (unsigned*)work;
     unsigned long long* rowZ = (unsigned long long*)((char*)work + (((size_t)n_ver * sizeof(float) + 15) / 16) * 16);
     const bool vec = (vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0;  // every row starts on 16 bytes
     if (n_ver > 0) {
-        // Chunks of a row: about 2048 workgroups in all, at least 4096 elements each.  From four chunks on the three launches
-        // beat one workgroup per row (whole call, chunked / single: 256 x 32000 135 / 141 us, 16 x 32000 35 / 36, 16 x 152064
-        // 78 / 104), with fewer they do not (600 x 32000 331 / 283, 16 x 8192 24 / 21).
-        int chunks = std::min((vocab + 4095) / 4096, std::max(1, 2048 / n_ver));
+        // Chunks of a row: about 512 workgroups in all, up to 1024 while they have 12288 elements each, at least 4096 elements each and
+        // four chunks up to 512 rows.  From four chunks on the three launches beat one workgroup per row (whole call, chunked / single:
+        // 256 x 32000 135 / 141 us, 16 x 32000 35 / 36, 16 x 152064 78 / 104), with fewer they do not (600 x 32000 331 / 283, 16 x 8192 24 / 21).
+        // Twice to four times as many, smaller workgroups cost more to start than their loads take (x 152064: 40 rows 43.0 -> 32.7 us, 80 rows
+        // 47.4 -> 42.4).
+        const int smallest = (vocab + 4095) / 4096;
+        int chunks = std::min(smallest, std::max(std::max(512 / n_ver, std::min(1024 / n_ver, (vocab + 12287) / 12288)), n_ver <= 512 ? 4 : 1));
         if (chunks >= 4) {
             const int chunk = ((vocab + chunks - 1) / chunks + 3) & ~3;
             chunks = (vocab + chunk - 1) / chunk;
             hipLaunchKernelGGL(sample_clear_kernel, dim3((n_ver + 255) / 256), dim3(256), 0, s, rowm, rowZ, n_ver);
-            hipLaunchKernelGGL(sample_max_kernel, dim3(chunks, n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
-            hipLaunchKernelGGL(sample_sum_kernel, dim3(chunks, n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
+            const dim3 grid(chunks, n_ver), block(SMP_STAT_THREADS);
+            if (chunk <= 4 * 4 * SMP_STAT_THREADS) {  // one round of four loads per thread
+                hipLaunchKernelGGL(sample_max_kernel<4>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
+                hipLaunchKernelGGL(sample_sum_kernel<4>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
+            } else {
+                hipLaunchKernelGGL(sample_max_kernel<8>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
+                hipLaunchKernelGGL(sample_sum_kernel<8>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
+            }
         } else {
             hipLaunchKernelGGL(sample_rowstats_kernel, dim3(n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, vec, rowm, rowZ);
         }
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
+    // Residual draw in a launch of its own: its target, counter and the chunks' sums take the places of the row sums, which nobody needs
+    // behind the walk.  From 12 chunks on, us of the whole call with the draw inside / outside of the walk: 16 rows x 50257 35.1 / 31.2, 40 rows x
+    // 100000 47 / 36, 80 rows x 152064 66 / 48; a call without a draw pays 2.3 us for the empty launch and has as much from the walk.
+    const int draw_chunks = std::min(std::min((vocab + DRAW_BLOCK - 1) / DRAW_BLOCK, 64), n_ver - 2);
+    const bool draw = draw_chunks >= 12;
     hipLaunchKernelGGL(accept_sample_kernel, dim3(1), dim3(SMP_THREADS), 0, s, logits, vocab, inv_temp, vec, rowm, rowZ, token, parent, T, n_ver, seed,
-                       step, res, retain);
+                       step, res, retain, draw ? rowZ : nullptr);
+    if (draw) {
+        const int chunk = ((vocab + draw_chunks - 1) / draw_chunks + DRAW_BLOCK - 1) / DRAW_BLOCK * DRAW_BLOCK, chunks = (vocab + chunk - 1) / chunk;
+        hipLaunchKernelGGL(sample_draw_kernel, dim3(chunks), dim3(DRAW_THREADS), 0, s, logits, vocab, inv_temp, vec, chunk, rowm, token, parent, T, res, retain,
+                           rowZ);
+    }
     return hipGetLastError();
 }

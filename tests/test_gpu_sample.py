@@ -149,3 +149,35 @@ def test_sampled_accept_at_the_ends_of_the_passes(vocab, n_child):
         g_res, g_ret = _gpu(lg, 1.0, token, parent, 1, 31, step)
         assert g_res == o_res.as_tuple(), (step, g_res, o_res.as_tuple())
         assert np.array_equal(g_ret, o_ret)
+
+
+@pytest.mark.parametrize("vocab,T,n_ver,n_child", [
+    # one entry on either side of the 12 chunks of 4096 from which the draw has a launch of its own, and one row on either side of
+    # the 14 whose sums leave room for them
+    (45056, 40, 20, 3), (45057, 40, 20, 3), (152064, 40, 13, 2), (152064, 40, 14, 2),
+    # rows off 16 bytes, several blocks per chunk (12 chunks of 152064 entries), a last chunk of 1024, as many chunks as there may be and
+    # more blocks than that, all of the tree below the root
+    (50257, 60, 60, 1), (152064, 16, 16, 5), (300000, 100, 100, 40), (262145, 80, 70, 1), (65536, 1024, 64, 1000),
+])
+def test_sampled_accept_draw_in_its_own_launch(vocab, T, n_ver, n_child):
+    """Residual draws spread over the chip: chunks and blocks of every length, tokens struck in them, bit for bit as the oracle."""
+    test_sampled_accept_row_chunks_and_residual(vocab, T, n_ver, n_child)
+
+
+@pytest.mark.parametrize("place", [0, 15, 16, 4095, 4096, 8191, 98303, 98304, 99999])
+def test_sampled_accept_draw_finds_an_entry_at_the_ends(place):
+    """All weight on one entry at the end of a thread's, a block's, a chunk's or the row's entries; then that entry struck, with the
+    definition's default where no weight is left."""
+    vocab, n_ver = 100000, 16
+    parent = np.full(n_ver, 0, dtype=np.int32)
+    parent[0] = -1
+    for tok in ((place + 7) % vocab, place):
+        token = np.full(n_ver, tok, dtype=np.int32)
+        lg = np.full((n_ver, vocab), -np.inf, dtype=np.float32)
+        lg[0, place] = 1.0
+        lg[0, (place + 70000) % vocab] = -12.0
+        for step in range(3):
+            o_res, o_ret = oracle.accept_sample(lg, 1.0, token, parent, n_ver, 8, step)
+            g_res, g_ret = _gpu(lg, 1.0, token, parent, n_ver, 8, step)
+            assert g_res == o_res.as_tuple(), (tok, step, g_res, o_res.as_tuple())
+            assert np.array_equal(g_ret, o_ret)
