@@ -56,12 +56,29 @@ static __device__ __forceinline__ f32x4 prefetch_resid(const GemmArgs& a, int w,
     return v;
 }
 
+// What the QKV epilogue reads for a row and a pair of tiles, fetched before the K loop: behind it, the rotary table and the cache row's
+// address are two rounds of memory latency in front of the stores (4096-wide layer, 16 rows 21.0 -> 20.6 us).
+struct QkvPre {
+    float2 cs[4];             // rotary table of the lane's features
+    unsigned long long krow;  // cache row (K and V heads)
+};
+static __device__ __forceinline__ QkvPre prefetch_qkv(const GemmArgs& a, int m, int ptile, int g) {
+    QkvPre p;
+    const int tph = a.hd >> 4, mc = min(m, a.M - 1);
+    const float2* cs = a.rope + (size_t)mc * (a.hd >> 1) + ((ptile % tph) >> 1) * 16 + g * 4;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) p.cs[v] = cs[v];
+    p.krow = a.krow[mc];
+    return p;
+}
+
 // Fused epilogue for one "item": one 16x16 result tile (RESID, LOGITS) or a pair of tiles (QKV, SWIGLU) in the
 // MFMA result layout — this lane holds features g*4 + v of row m; rs is the row's RMSNorm scale.
 // Returns this lane's share of the sum of squares of the new residual-stream values (RESID), else 0.
 template <typename T, int EPI>
 static __device__ __forceinline__ float epilogue_item(const GemmArgs& a, const float (&y)[(EPI == EPI_QKV || EPI == EPI_SWIGLU) ? 2 : 1][4],
-                                                      float rs, int m, int ptile, int g, const f32x4* resid_pre = nullptr) {
+                                                      float rs, int m, int ptile, int g, const f32x4* resid_pre = nullptr,
+                                                      const QkvPre* qkv_pre = nullptr) {
     using E = Elem<T>;
     float hsq = 0.f;
     if constexpr (EPI != EPI_RESID) {
@@ -119,7 +136,7 @@ static __device__ __forceinline__ float epilogue_item(const GemmArgs& a, const f
             float olo[4], ohi[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                float2 c = cs[v];
+                const float2 c = qkv_pre ? qkv_pre->cs[v] : cs[v];
                 olo[v] = lo[v] * c.x - hi[v] * c.y;
                 ohi[v] = hi[v] * c.x + lo[v] * c.y;
             }
@@ -127,7 +144,7 @@ static __device__ __forceinline__ float epilogue_item(const GemmArgs& a, const f
             if (head < a.Hq)
                 dst = (T*)a.q_out + (size_t)m * (a.Hq * a.hd) + (size_t)head * a.hd;
             else
-                dst = (T*)a.krow[m] + a.layer_off + (size_t)(head - a.Hq) * a.stride_head;
+                dst = (T*)(qkv_pre ? qkv_pre->krow : a.krow[m]) + a.layer_off + (size_t)(head - a.Hq) * a.stride_head;
             *(typename E::out4_t*)(dst + t) = E::pack4(olo[0], olo[1], olo[2], olo[3]);
             *(typename E::out4_t*)(dst + t + half) = E::pack4(ohi[0], ohi[1], ohi[2], ohi[3]);
         } else if (head < a.Hq + 2 * a.Hkv) {
@@ -305,6 +322,105 @@ __global__ void __launch_bounds__(512) skinny_gemm_kernel(const void* Wp, const 
     reduce_and_store<T, MT, NT, EPI>(a, acc, ss, smem, lane, w, NW, grp, row0, resid_first);
 }
 
+// QKV of up to 16 rows where every rotary pair of query / key tiles has a value tile to go with it (as many KV heads as query heads): the
+// workgroup takes pair i and value tile i.  Bound by the weight stream, and a launch lasts as long as its most loaded compute unit: 768 tiles
+// of a 4096-wide layer are 384 pairs on 256 compute units, four tiles on half of them, where this is three on each.  16 rows, us, groups
+// of two (four) tiles -> this: 2816 wide 19.8 -> 16.1, 3072 20.4 -> 16.7, 4096 23.6 -> 20.6 (4.9 TB/s), 4096 in f32 45.6 -> 40.6, 8192 columns x
+// 12288 46.8 -> 39.6; groups of four: 5632 50.0 -> 43.1, 6144 52.8 -> 46.5, 7168 61.5 -> 58.
+template <typename T>
+__global__ void __launch_bounds__(512) skinny_qkv_kernel(const void* Wp, const void* X, int nkt_, int ldx_, int M_, int flags, const GemmArgs a) {
+    using E = Elem<T>;
+    using frag_t = typename E::frag_t;
+    constexpr int NT = 3, PF = 8;
+    __shared__ __align__(16) float red[8 * NT * 256];
+    __shared__ float ssr[8 * 16];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, NW = blockDim.x >> 6;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int x_frag = flags & 1, lsh = flags >> 1;  // log2 of the weights' tiles per group
+    const int nsteps = (nkt_ - w + NW - 1) / NW;  // >= 1: the host never launches more waves than k-tiles
+    const int pair = blockIdx.x, vtile = 2 * gridDim.x + blockIdx.x;  // gridDim.x pairs, then as many value tiles
+    auto first = [&](int pt) {
+        return (const unsigned char*)Wp + ((((size_t)(pt >> lsh) * nkt_) << lsh) + (pt & ((1 << lsh) - 1))) * 1024 + (size_t)lane * 16;
+    };
+    const unsigned char* const wb[NT] = {first(2 * pair), first(2 * pair + 1), first(vtile)};
+    const T* xrow;
+    const size_t xstep = x_frag ? (size_t)64 * E::EPF : (size_t)E::KT;
+    if (x_frag)
+        xrow = (const T*)X + (size_t)lane * E::EPF;
+    else
+        xrow = (const T*)X + (size_t)min(r16, M_ - 1) * ldx_ + g * E::EPF;
+
+    const QkvPre pre = prefetch_qkv(a, r16, 2 * pair, g);
+    f32x4 acc[NT];
+    float ss = 0.f;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    frag_t bq[PF][NT], aq[PF];
+    auto issue = [&](int s, int step) {
+        const int kt = w + min(step, nsteps - 1) * NW;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) bq[s][nt] = load_w<T>(wb[nt] + ((size_t)kt << (10 + lsh)));
+        aq[s] = *(const frag_t*)(xrow + (size_t)kt * xstep);
+    };
+    auto consume = [&](int s, int step) {
+        const frag_t av = step >= nsteps ? E::zero() : aq[s];
+        ss += E::sumsq(av);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[nt] = E::mma(bq[s][nt], av, acc[nt]);
+    };
+#pragma unroll
+    for (int s = 0; s < PF; ++s) issue(s, s);
+    const int nrounds = (nsteps + PF - 1) / PF;
+    for (int rd = 0; rd + 1 < nrounds; ++rd) {
+#pragma unroll
+        for (int s = 0; s < PF; ++s) {
+            consume(s, rd * PF + s);
+            issue(s, (rd + 1) * PF + s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < PF; ++s) consume(s, (nrounds - 1) * PF + s);
+
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[((w * NT + nt) * 4 + v) * 64 + lane] = acc[nt][v];
+    ss = wave_xor_add(wave_xor_add(ss, 16), 32);
+    if (lane < 16) ssr[w * 16 + lane] = ss;
+    __syncthreads();
+    if (w > 1 && NW > 1) return;
+    float s = 0.f;
+    for (int k = 0; k < NW; ++k) s += ssr[k * 16 + r16];
+    const float rs = 1.0f / sqrtf(s / (float)a.K + a.eps);
+    auto tile_sum = [&](int nt, float (&y)[4]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            y[v] = 0.f;
+            for (int k = 0; k < NW; ++k) y[v] += red[((k * NT + nt) * 4 + v) * 64 + lane];
+        }
+    };
+    // wave 0 finishes the pair, wave 1 the value tile
+    if (w == 0) {
+        float y[2][4];
+        tile_sum(0, y[0]);
+        tile_sum(1, y[1]);
+        epilogue_item<T, EPI_QKV>(a, y, rs, r16, 2 * pair, g, nullptr, &pre);
+    }
+    if ((w == 1 || NW == 1) && r16 < a.M) {
+        float y[4];
+        tile_sum(2, y);
+        const int tph = a.hd >> 4, head = vtile / tph, t = vtile % tph * 16 + g * 4;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            y[v] *= rs;
+            if (a.bias) y[v] += a.bias[vtile * 16 + g * 4 + v];
+        }
+        T* dst = (T*)pre.krow + a.layer_off + a.stride_kv + (size_t)(head - a.Hq - a.Hkv) * a.stride_head;
+        *(typename E::out4_t*)(dst + t) = E::pack4(y[0], y[1], y[2], y[3]);
+    }
+}
+
 // copies of the workgroup's tiles the cross-wave reduction keeps in LDS: as many as there are waves, within about 48 KiB
 static int reduction_copies(int nw, int mt, int nt) {
     const int fit = 48 / (mt * nt);  // 1 KiB per tile and copy
@@ -340,6 +456,20 @@ hipError_t launch_gemm(int dtype, int epi, int NT, int NW, int n_groups, const G
     // other's start-up and epilogue; 8 waves: QKV 42 -> 44 us, gate/up 50 -> 53 us at 64 rows).  Two 32-row blocks per
     // group instead were slower as well (gate/up 54 -> 61 us).
     const int MT = a.M <= 16 ? 1 : (a.M <= 32 ? 2 : 4);
+    if (epi == EPI_QKV && MT == 1 && a.Hq == a.Hkv) {
+        // pairs with a value tile where that leaves fewer tiles on the most loaded compute unit; with two full rounds of them (its 8 waves
+        // leave no registers for a second workgroup on the unit) groups of four are the faster ones all the same (512 pairs 76.0 / 70.3 us)
+        const int pairs = a.Hq * a.hd / 16;
+        if (pairs < 480 && (pairs + 255) / 256 * 3 < (n_groups + 255) / 256 * NT) {
+            const int flags = a.x_frag | (NT == 4 ? 4 : 2);
+            const dim3 grid(pairs), block(std::min(NW, 8) * 64);
+            if (dtype == 0)
+                hipLaunchKernelGGL(skinny_qkv_kernel<float>, grid, block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags, a);
+            else
+                hipLaunchKernelGGL(skinny_qkv_kernel<bf16_t>, grid, block, 0, s, a.Wp, a.X, a.nkt, a.ldx, a.M, flags, a);
+            return hipGetLastError();
+        }
+    }
     if (MT == 4 && NW > 4) NW = 4;
     if (MT * NT >= 8 && NW > 4) NW = 4;  // 8 tiles per workgroup: 4 waves keep a copy each in LDS without reduction rounds
 #define FS_EPI(e)                                                                      \
