@@ -996,11 +996,15 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     if (ring > *tiles_per_split) ring = *tiles_per_split;
     *nset = ring < 1 ? 1 : ring;
     // The direct-to-LDS kernel where it measured faster: one workgroup per compute unit on a long context with three tile
-    // buffers (16k context, 64 rows: 54.6 -> 53.0 us with the merge; two or four buffers 56.7 / 55.2), and grids of two and more
-    // workgroups per compute unit with two buffers, two workgroups sharing a unit's LDS (16 / 24 / 32 stacked requests of a
-    // 1k context: 55.5 -> 49.9, 81.1 -> 78.0, 107.9 -> 99.0 us; three buffers: slower than the register ring).
+    // buffers (16k context, 64 rows: 54.6 -> 53.0 us with the merge; two or four buffers 56.7 / 55.2), and more workgroups than compute
+    // units with two buffers, two workgroups sharing a unit's LDS (16 / 24 / 32 stacked requests of a 1k context: 55.5 -> 49.9,
+    // 81.1 -> 78.0, 107.9 -> 99.0 us; three buffers: slower than the register ring).  A few workgroups beyond 256 are what gains most: with
+    // three buffers they are a round of their own (us, three / two buffers: 9 requests x 32 heads, 500 / 1k / 2k / 4k context 31.3 / 22.8,
+    // 46.3 / 33.6, 85.5 / 60.9, 143.9 / 100.3, 15 requests 34.4 / 28.5 .. 154.2 / 150.9; 272 batches of 257 to 511 workgroups, half of them
+    // ragged: 270 faster, two 3 and 4 % slower).
     if (dma_override == 0 && dma_shape && mtw == 1 && nw <= 4 && *tiles_per_split >= 6) {
-        if ((long long)per_split * *n_splits >= 512)
+        const long long wgs = (long long)per_split * *n_splits;
+        if (wgs >= 512 || (deep_ring && wgs > 256))
             dma_bufs = 2;
         else if (deep_ring)
             dma_bufs = 3;

@@ -202,3 +202,33 @@ def test_tiles_in_pairs_over_a_ragged_batch(name, hq, hkv, specs, knob, monkeypa
     for kv, orc, l_glo, seg_off, l_s in caches:
         rows = slice(l_glo + seg_off, l_glo + seg_off + l_s)
         assert max_rel_err(kv[0][:, :, rows].float().cpu().numpy(), orc.kv[0][:, :, rows]) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("heads,kv,n,rows,bufs", [
+    (64, 64, 4, 16, 3),    # 256 attention workgroups: a round of one per compute unit, three tile buffers
+    (43, 43, 6, 16, 2),    # 258: two to a unit, two buffers
+    (64, 64, 7, 40, 2),    # 448, three row tiles
+    (128, 64, 5, 9, 2),    # two query heads per KV head
+    (73, 73, 7, 1, 2),     # 511
+])
+def test_attention_of_a_few_more_workgroups_than_compute_units(heads, kv, n, rows, bufs):
+    """Ragged batches on either side of one workgroup per compute unit; the attention form that the plan takes, and each request's rows."""
+    from tests.gpu_util import TOL, kernel_names, max_rel_err, to_dev
+    specs = [(700 + 131 * i, rows + 8, 5, 3, 8, rows - i % min(rows, 3)) for i in range(n)]
+    cfg = synth.StageConfig(f"b-over-{heads}-{n}", "bf16", 1, 64, heads, kv, 128, 256, 0, max(s[0] for s in specs), rows + 8,
+                            max(64, sum(s[5] for s in specs)), 5, 3)
+    print(f"[case] {cfg.name}: {n} requests, {sum(s[5] for s in specs)} stacked rows", flush=True)
+    got, want, caches, cfg = _run_batch(cfg, specs, seed=3)
+    row = 0
+    for r, w in enumerate(want):
+        err = max_rel_err(got[row:row + w.shape[0]], w)
+        print(f"  request {r}: hidden max-rel-err {err:.3e}", flush=True)
+        assert err < TOL["bf16"]
+        row += w.shape[0]
+    from tests.gpu_util import Pair
+    pair = Pair(cfg, seed=3)
+    items = [(kv_, l_glo, l_glo + off, off, l_s, synth.random_tree(rows + 8, 5, 3, 1000, 3, stream=10 + r).parent[:off + l_s])
+             for r, (kv_, _, l_glo, off, l_s) in enumerate(caches)]
+    x = to_dev(np.zeros((row, 64), dtype=np.float32), pair.tdtype)
+    names = kernel_names(lambda: pair.gpu.tree_verify_batch(items, x))
+    assert any(f"tree_attn_dma_kernel<{bufs}," in k for k in names), names
