@@ -210,6 +210,7 @@ def test_tiles_in_pairs_over_a_ragged_batch(name, hq, hkv, specs, knob, monkeypa
     (64, 64, 7, 40, 2),    # 448, three row tiles
     (128, 64, 5, 9, 2),    # two query heads per KV head
     (73, 73, 7, 1, 2),     # 511
+    (64, 64, 9, 5, 2),     # 576: more than a round of two to a unit, the longest contexts first
 ])
 def test_attention_of_a_few_more_workgroups_than_compute_units(heads, kv, n, rows, bufs):
     """Ragged batches on either side of one workgroup per compute unit; the attention form that the plan takes, and each request's rows."""
