@@ -101,9 +101,16 @@ static __device__ __forceinline__ float epilogue_item(const GemmArgs& a, const f
         }
     } else if constexpr (EPI == EPI_LOGITS) {
         const int n = ptile * 16 + g * 4;
+        float* dst = a.logits + (size_t)m * a.N + n;
+        // Four stores of a float each, every one into 64 pieces of memory, held up the ends of the launches (us, one by one -> together: 16 rows x
+        // 32000 48.0 -> 46.3, 128 rows 61.8 -> 56.2, with K 1024 28.9 -> 22.9; 128 rows x 152064 275 -> 250; 4-bit, 128 rows x 32000 101 -> 89).
+        if (a.logits_vec) {
+            if (n < a.N) *(f32x4*)dst = f32x4{rs * y[0][0], rs * y[0][1], rs * y[0][2], rs * y[0][3]};
+        } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (n + v < a.N) a.logits[(size_t)m * a.N + n + v] = rs * y[0][v];
+            for (int v = 0; v < 4; ++v)
+                if (n + v < a.N) dst[v] = rs * y[0][v];
+        }
     } else if constexpr (EPI == EPI_SWIGLU) {
         const int f = (ptile >> 1) * 16 + g * 4;
         if (f < a.F) {

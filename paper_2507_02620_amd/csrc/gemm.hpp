@@ -48,6 +48,7 @@ struct GemmArgs {
     int F;
     // EPI_LOGITS
     float* logits;  // [M][vocab]
+    int logits_vec;  // rows on 16 bytes: base and vocab
 };
 
 struct PackArgs {

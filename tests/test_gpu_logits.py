@@ -54,3 +54,26 @@ def test_head_of_17_to_48_rows_at_the_edges_of_its_routes(vocab, rows):
     g_lg, g_am = g_lg.cpu().numpy(), g_am.cpu().numpy()
     assert max_rel_err(g_lg, o_lg) < TOL["bf16"]
     assert np.array_equal(g_am, np.argmax(g_lg, axis=1))
+
+
+@pytest.mark.parametrize("dtype,w4,rows,vocab,shift", [
+    ("bf16", False, 16, 1004, 0), ("bf16", False, 5, 1004, 1), ("bf16", False, 40, 996, 0), ("bf16", False, 128, 2004, 0), ("bf16", False, 128, 2004, 2),
+    ("bf16", False, 300, 1000, 0), ("bf16", False, 17, 1003, 0), ("bf16", True, 24, 1004, 0), ("bf16", True, 100, 1004, 3), ("f32", False, 16, 1004, 0),
+    ("f32", False, 7, 1002, 0), ("f32", False, 3, 4, 0),
+])
+def test_logits_in_rows_on_16_bytes_and_not(dtype, w4, rows, vocab, shift):
+    """Vocabularies that are and are not a multiple of four, inside the last tile, and a buffer off 16 bytes; nothing beyond the rows is written."""
+    import torch
+    from tests.gpu_util import TOL, Pair, max_rel_err, to_dev
+    cfg = synth.StageConfig(f"lg-vec-{vocab}", dtype, 1, 256, 2, 2, 128, 256, vocab, 8, 16, rows, 4, 3)
+    print(f"[case] {cfg.name} {dtype} w4={w4} rows={rows} shift={shift}", flush=True)
+    p = Pair(cfg, 3, head=True, w4=w4)
+    hid = synth.hidden(cfg, rows, 7, 3)
+    o_lg, _ = p.orc.logits(hid.astype(np.float64))
+    buf = torch.full((rows * vocab + 64,), -7.0, device="cuda")
+    view = buf[shift:shift + rows * vocab].view(rows, vocab)
+    _, am = p.gpu.tree_logits(to_dev(hid, p.tdtype), view, torch.empty(rows, dtype=torch.int32, device="cuda"))
+    got = view.cpu().numpy()
+    assert max_rel_err(got, o_lg) < TOL[dtype]
+    assert np.array_equal(am.cpu().numpy(), np.argmax(got, axis=1))
+    assert bool((buf[:shift] == -7.0).all()) and bool((buf[shift + rows * vocab:] == -7.0).all())
