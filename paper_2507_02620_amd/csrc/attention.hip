@@ -86,7 +86,11 @@ static __device__ __forceinline__ void merge_row_chunk(const AttnArgs& a, int kv
         E::pack4(o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
 }
 
-template <typename T, int HD, int MTW, int NWAVES, int NSET, bool STREAM>
+// SLOTW (f32): one row tile, whose tiles of slots are divided over the waves (a wave takes the slots of one P fragment) instead of computed by
+// one wave while the others only stage; the waves' sums meet in LDS at the end.  An f32 tile of 64 slots x 64 is 128 matrix instructions
+// of 32 cycles, 2 us for one wave.  16 rows, with the merge, us: 4 heads of 64, 160 / 1k / 16k slots 12.0 / 12.9 / 27.0 -> 10.4 / 12.0 / 21.6, 8 heads of
+// 128, 16k 47.5 -> 43.5.  bf16 has an eighth of the matrix time per tile and gains nothing (32 heads, 1k 13.0 -> 13.2).
+template <typename T, int HD, int MTW, int NWAVES, int NSET, bool STREAM, bool SLOTW = false>
 __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_eu(2))) tree_attn_kernel(int row_blocks, const AttnArgs a) {
     using E = Elem<T>;
     using frag_t = typename E::frag_t;
@@ -105,6 +109,8 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
     constexpr int NTHR = NWAVES * 64; // every thread stages; waves beyond the compute waves do nothing else
     constexpr int CPT = CH / NTHR;    // chunks per thread (K and V each)
     static_assert(CH % NTHR == 0, "tile must split evenly over the workgroup");
+    static_assert(!SLOTW || (MTW == 1 && NPF > 1 && NPF <= NWAVES), "one row tile, a wave per P fragment");
+    constexpr int JN = SLOTW ? NSUB : BS / 16, PN = SLOTW ? 1 : NPF;  // sub-tiles of slots and P fragments per wave
     __shared__ __align__(16) T Ks[BS * KROW];
     __shared__ __align__(16) T Vt[VTR ? BS * VROW : HD * VROW];
 
@@ -122,14 +128,15 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
     const int ntiles = dead ? 0 : (L + BS - 1) / BS;
     const int t0 = split * a.tiles_per_split, t1 = min(ntiles, t0 + a.tiles_per_split);
     // waves beyond the compute waves (or whose rows all lie beyond R) only help staging
-    const bool computes = (w < a.nwc) && ((rb * a.nwc + w) * MTW * 16 < R);
+    const int rw = SLOTW ? 0 : w, j0 = SLOTW ? w * NSUB : 0;  // row tile and first sub-tile of the wave
+    const bool computes = SLOTW ? w < NPF && !dead : (w < a.nwc) && ((rb * a.nwc + w) * MTW * 16 < R);
 
     int rho[MTW], seg_r[MTW];
     bool rok[MTW];
     frag_t qf[MTW][NKT];
 #pragma unroll
     for (int i = 0; i < MTW; ++i) {
-        rho[i] = ((rb * a.nwc + w) * MTW + i) * 16 + r16;
+        rho[i] = ((rb * a.nwc + rw) * MTW + i) * 16 + r16;
         rok[i] = computes && rho[i] < R;
         const int rr = rok[i] ? rho[i] : 0;
         seg_r[i] = row0 + rr % M;  // row of the stacked arrays
@@ -248,21 +255,21 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
                 }
                 if (valid < 64) m &= (1ull << valid) - 1;
                 if (!rok[i]) m = 0;
-                vm[i] = m >> (g * 4);
+                vm[i] = m >> (g * 4 + j0 * 16);
                 any |= (m != 0);
             }
             if (__ballot(any) == 0) return;  // wave-uniform; the staging is already done
         }
 
         // ---- S^T = K . Q^T ----
-        f32x4 st[MTW][BS / 16];
+        f32x4 st[MTW][JN];
 #pragma unroll
-        for (int j = 0; j < BS / 16; ++j) {
+        for (int j = 0; j < JN; ++j) {
 #pragma unroll
             for (int i = 0; i < MTW; ++i) st[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kt = 0; kt < NKT; ++kt) {
-                frag_t kf = *(const frag_t*)(&Ks[(j * 16 + r16) * KROW + kt * KT + g * EPF]);
+                frag_t kf = *(const frag_t*)(&Ks[((j0 + j) * 16 + r16) * KROW + kt * KT + g * EPF]);
 #pragma unroll
                 for (int i = 0; i < MTW; ++i) st[i][j] = E::mma(kf, qf[i][kt], st[i][j]);
             }
@@ -271,13 +278,13 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
         // ---- mask, online softmax ----
         // Tiles below l_glo (almost all of a long context) take the short form: no visibility test, scale folded into the
         // exponent's multiply-add.  The running sums are rescaled only when some row's maximum moved (wave-uniform test).
-        frag_t pf[MTW][NPF];
+        frag_t pf[MTW][PN];
 #pragma unroll
         for (int i = 0; i < MTW; ++i) {
             float mx = NEG_BIG;
             if (need_mask) {
 #pragma unroll
-                for (int j = 0; j < BS / 16; ++j)
+                for (int j = 0; j < JN; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         float s = st[i][j][v] * a.scale_log2;
@@ -288,7 +295,7 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
                     }
             } else {
 #pragma unroll
-                for (int j = 0; j < BS / 16; ++j)
+                for (int j = 0; j < JN; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) mx = fmaxf(mx, st[i][j][v]);
                 mx *= a.scale_log2;  // the scale is positive: the maximum commutes with it
@@ -305,10 +312,10 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
                 mrun[i] = mnew;
             }
             float psum = 0.f;
-            float p[BS / 16][4];
+            float p[JN][4];
             if (need_mask) {
 #pragma unroll
-                for (int j = 0; j < BS / 16; ++j)
+                for (int j = 0; j < JN; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const float s = st[i][j][v];
@@ -318,7 +325,7 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
                     }
             } else {
 #pragma unroll
-                for (int j = 0; j < BS / 16; ++j)
+                for (int j = 0; j < JN; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(st[i][j][v], a.scale_log2, -mnew));
@@ -328,26 +335,26 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
             }
             lrun[i] += psum;
 #pragma unroll
-            for (int jj = 0; jj < NPF; ++jj)
+            for (int jj = 0; jj < PN; ++jj)
 #pragma unroll
                 for (int e = 0; e < EPF; ++e) pf[i][jj][e] = E::from_f(p[jj * NSUB + e / 4][e % 4]);
         }
 
         // ---- O^T += V^T . P^T ----
 #pragma unroll
-        for (int jj = 0; jj < NPF; ++jj)
+        for (int jj = 0; jj < PN; ++jj)
 #pragma unroll
             for (int nt = 0; nt < NHT; ++nt) {
                 frag_t vf;
                 if constexpr (VTR) {
                     // Transpose load: within each group of 16 lanes, lane i addresses 4 consecutive head-dim elements of
                     // slot row (i >> 2); lane j receives element j of the group's 16 columns for 4 consecutive slots.
-                    const T* vp = &Vt[(jj * NSUB * 16 + g * 4 + (r16 >> 2)) * VROW + nt * 16 + (r16 & 3) * 4];
+                    const T* vp = &Vt[((j0 + jj * NSUB) * 16 + g * 4 + (r16 >> 2)) * VROW + nt * 16 + (r16 & 3) * 4];
                     const s16x4 t0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)vp);
                     const s16x4 t1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(vp + 16 * VROW));
                     vf = __builtin_bit_cast(frag_t, __builtin_shufflevector(t0, t1, 0, 1, 2, 3, 4, 5, 6, 7));
                 } else {
-                    const T* vr = &Vt[(nt * 16 + r16) * VROW + jj * NSUB * 16 + g * 4];
+                    const T* vr = &Vt[(nt * 16 + r16) * VROW + (j0 + jj * NSUB) * 16 + g * 4];
 #pragma unroll
                     for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
@@ -411,6 +418,35 @@ __global__ void __launch_bounds__(NWAVES * 64) __attribute__((amdgpu_waves_per_e
         }
     }
 
+    if constexpr (SLOTW) {  // the other waves' sums join those of wave 0, through the tile's place
+        f32x4* const po = (f32x4*)Ks;
+        float2* const pml = (float2*)(po + (NPF - 1) * NHT * 64);
+        static_assert((NPF - 1) * 64 * (NHT * sizeof(f32x4) + sizeof(float2)) <= sizeof(Ks), "the waves' sums fit the place of a tile");
+        __syncthreads();
+        if (w > 0 && w < NPF) {
+#pragma unroll
+            for (int nt = 0; nt < NHT; ++nt) po[((w - 1) * NHT + nt) * 64 + lane] = acc[0][nt];
+            pml[(w - 1) * 64 + lane] = make_float2(mrun[0], lrun[0]);
+        }
+        __syncthreads();
+        if (w > 0) return;
+        float mn = mrun[0];
+#pragma unroll
+        for (int k = 0; k + 1 < NPF; ++k) mn = fmaxf(mn, pml[k * 64 + lane].x);
+        const float w0 = exp2f(mrun[0] - mn);
+        mrun[0] = mn;
+        lrun[0] *= w0;
+#pragma unroll
+        for (int nt = 0; nt < NHT; ++nt) acc[0][nt] *= w0;
+#pragma unroll
+        for (int k = 0; k + 1 < NPF; ++k) {
+            const float2 o = pml[k * 64 + lane];
+            const float wk = exp2f(o.x - mn);
+            lrun[0] += o.y * wk;
+#pragma unroll
+            for (int nt = 0; nt < NHT; ++nt) acc[0][nt] += po[(k * NHT + nt) * 64 + lane] * wk;
+        }
+    }
     // ---- write out ----
 #pragma unroll
     for (int i = 0; i < MTW; ++i) {
@@ -860,6 +896,15 @@ static hipError_t launch_hd(const AttnArgs& a, int MTW, int row_blocks, hipStrea
             done = true;
         }
     }
+    if constexpr (sizeof(T) == 4) {  // one row tile (the plan's row blocks are then one): its tiles of slots divided over the waves
+        if (MTW == 1 && a.nwc == 1) {
+            if (deep)
+                hipLaunchKernelGGL((tree_attn_kernel<T, HD, 1, 4, 2, true, true>), grid, block, 0, s, row_blocks, a);
+            else
+                hipLaunchKernelGGL((tree_attn_kernel<T, HD, 1, 4, 1, true, true>), grid, block, 0, s, row_blocks, a);
+            done = true;
+        }
+    }
     if (done) {
     } else if (MTW == 1 && nw == 4 && deep)
         hipLaunchKernelGGL((tree_attn_kernel<T, HD, 1, 4, 2, true>), grid, block, 0, s, row_blocks, a);
@@ -980,8 +1025,10 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     if ((deep_ring || pairs) && wgs_override <= 0) want = splits_one_round(per_split, ntiles);
     // Few tiles for few rows: walking them one after another is shorter than the merge launch (us, merge / none: 8 heads of 64, 16 rows each,
     // 2 / 3 / 4 tiles 9.4 / 7.3, 9.7 / 7.8, 9.9 / 9.6, 64 rows, 2 / 3 tiles 10.1 / 9.0, 10.7 / 10.0; 32 heads of 128, 16 rows, 2 tiles 9.7 / 8.6,
-    // 3 tiles, two of them masked 10.4 / 11.4, 32 rows, 2 tiles 10.4 / 9.0, 64 rows, 3 tiles 12.4 / 13.5; f32, 3 tiles 11.7 / 14.0)
-    if (elem_bytes == 2 && wgs_override <= 0 && (hd == 64 ? mtiles <= 4 && ntiles <= 3 : mtiles <= 2 && ntiles <= 2)) want = 1;
+    // 3 tiles, two of them masked 10.4 / 11.4, 32 rows, 2 tiles 10.4 / 9.0, 64 rows, 3 tiles 12.4 / 13.5; f32, up to 16 rows per head, heads of 64,
+    // 2 / 3 / 4 tiles 10.5 / 9.3, 11.2 / 10.4, 10.9 / 12.5, of 128, 2 / 4 tiles 11.1 / 10.2, 11.4 / 14.4)
+    const bool few_tiles = elem_bytes == 2 ? (hd == 64 ? mtiles <= 4 && ntiles <= 3 : mtiles <= 2 && ntiles <= 2) : mtiles == 1 && ntiles <= (hd == 64 ? 3 : 2);
+    if (wgs_override <= 0 && few_tiles) want = 1;
     if (want > max_splits) want = max_splits;
     if (want > ntiles) want = ntiles;
     if (want < 1) want = 1;
