@@ -165,6 +165,113 @@ static __device__ __forceinline__ float epilogue_item(const GemmArgs& a, const f
     return hsq;
 }
 
+// Two neighbouring items of a wave at once (bf16; ptile a multiple of 4, so that both belong to one head or one k-tile of the activations): lanes
+// g and g ^ 1 trade four features of one item against four of the other, and every lane stores 16 bytes of one item, features
+// (g >> 1) * 8 .. + 7, where epilogue_item stores 8 of each.  permlane16_swap trades the second 16 lanes of its first operand against the first 16
+// of its second one, the fourth against the third: exactly that.
+static __device__ __forceinline__ u32x4 trade_halves(const float (&p)[4], const float (&q)[4]) {
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 u = __builtin_bit_cast(u32x2, Elem<bf16_t>::pack4(p[0], p[1], p[2], p[3]));
+    const u32x2 v = __builtin_bit_cast(u32x2, Elem<bf16_t>::pack4(q[0], q[1], q[2], q[3]));
+    const auto x = __builtin_amdgcn_permlane16_swap(u[0], v[0], false, false), y = __builtin_amdgcn_permlane16_swap(u[1], v[1], false, false);
+    return u32x4{x[0], y[0], x[1], y[1]};
+}
+template <int EPI>
+static __device__ __forceinline__ void epilogue_two(const GemmArgs& a, const float (&y0)[2][4], const float (&y1)[2][4], float rs, int m, int ptile, int g) {
+    using T = bf16_t;
+    static_assert(EPI == EPI_QKV || EPI == EPI_SWIGLU, "paired epilogues");
+    const int odd = g & 1, k8 = (g >> 1) * 8;  // which item, and which half of its features, this lane stores
+    if (m >= a.M) return;  // the four lanes of a row together
+    if constexpr (EPI == EPI_SWIGLU) {
+        float o0[4], o1[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float g0 = rs * y0[0][v], g1 = rs * y1[0][v];
+            o0[v] = g0 / (1.0f + expf(-g0)) * (rs * y0[1][v]);
+            o1[v] = g1 / (1.0f + expf(-g1)) * (rs * y1[1][v]);
+        }
+        const u32x4 o = trade_halves(o0, o1);
+        const int f = (ptile >> 1) * 16 + odd * 16 + k8;
+        if (f < a.F) *(u32x4*)((T*)a.act_out + frag_major_index<T>(m, f, a.F / 32)) = o;
+    } else {
+        const int tph = a.hd >> 4, head = ptile / tph, tih = ptile % tph;
+        if (head >= a.Hq + 2 * a.Hkv) return;  // padding tiles of the last group
+        float lo0[4], hi0[4], lo1[4], hi1[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            lo0[v] = rs * y0[0][v], hi0[v] = rs * y0[1][v], lo1[v] = rs * y1[0][v], hi1[v] = rs * y1[1][v];
+            if (a.bias) {
+                const float* b = a.bias + ptile * 16 + g * 4 + v;
+                lo0[v] += b[0], hi0[v] += b[16], lo1[v] += b[32], hi1[v] += b[48];
+            }
+        }
+        if (head < a.Hq + a.Hkv) {  // features t and t + hd/2 per item, t = (tih / 2) * 16 + g * 4 + v, and 16 on
+            const int t = (tih >> 1) * 16, half = a.hd >> 1;
+            const float2* cs = a.rope + (size_t)m * half + t + g * 4;
+            float p0[4], q0[4], p1[4], q1[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float2 c = cs[v], d = cs[16 + v];
+                p0[v] = lo0[v] * c.x - hi0[v] * c.y;
+                q0[v] = hi0[v] * c.x + lo0[v] * c.y;
+                p1[v] = lo1[v] * d.x - hi1[v] * d.y;
+                q1[v] = hi1[v] * d.x + lo1[v] * d.y;
+            }
+            T* dst = head < a.Hq ? (T*)a.q_out + (size_t)m * (a.Hq * a.hd) + (size_t)head * a.hd
+                                 : (T*)a.krow[m] + a.layer_off + (size_t)(head - a.Hq) * a.stride_head;
+            dst += t + odd * 16 + k8;
+            *(u32x4*)dst = trade_halves(p0, p1);
+            *(u32x4*)(dst + half) = trade_halves(q0, q1);
+        } else {  // natural tile order, no rotation
+            T* dst = (T*)a.krow[m] + a.layer_off + a.stride_kv + (size_t)(head - a.Hq - a.Hkv) * a.stride_head + tih * 16 + odd * 16 + k8;
+            *(u32x4*)dst = trade_halves(lo0, hi0);
+            *(u32x4*)(dst + 32) = trade_halves(lo1, hi1);
+        }
+    }
+}
+
+// The items of a wave's NT tiles of one row tile, two at a time where they begin on a multiple of four tiles; returns as epilogue_item.  Us of
+// launches of 1024 rows, one at a time -> so: QKV 28.0 -> 24.7 (1024 wide), 67.5 -> 64.0 (3584), 101.1 -> 99.6 (4096), 146.8 -> 145.2 (5120);
+// gate/up 172.9 -> 172.1 (4096).
+template <int EPI, int NT>
+static __device__ __forceinline__ float epilogue_row(const GemmArgs& a, const f32x4 (&acc)[NT], float rs, int m, int ptile, int g) {
+    constexpr int TPI = (EPI == EPI_QKV || EPI == EPI_SWIGLU) ? 2 : 1;
+    float hsq = 0.f;
+    auto one = [&](int i) __attribute__((always_inline)) {
+        float y[TPI][4];
+#pragma unroll
+        for (int tt = 0; tt < TPI; ++tt)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) y[tt][v] = acc[i * TPI + tt][v];
+        hsq += epilogue_item<bf16_t, EPI>(a, y, rs, m, ptile + i * TPI, g);
+    };
+    if constexpr (TPI == 2 && NT >= 4) {
+        auto two = [&](int i) __attribute__((always_inline)) {
+            float y0[2][4], y1[2][4];
+#pragma unroll
+            for (int tt = 0; tt < 2; ++tt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    y0[tt][v] = acc[i * 2 + tt][v];
+                    y1[tt][v] = acc[i * 2 + 2 + tt][v];
+                }
+            epilogue_two<EPI>(a, y0, y1, rs, m, ptile + i * 2, g);
+        };
+        static_assert(NT == 4 || NT == 6, "a wave's first tile is a multiple of NT");
+        if (NT == 4 || (ptile & 3) == 0) {  // uniform
+            two(0);
+            if constexpr (NT == 6) one(2);
+        } else if constexpr (NT == 6) {
+            one(0);
+            two(1);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NT / TPI; ++i) one(i);
+    }
+    return hsq;
+}
+
 // Cross-wave reduction through LDS and the fused epilogue, shared by the dense and the 4-bit kernels.
 template <typename T, int MT, int NT, int EPI>
 static __device__ __forceinline__ void reduce_and_store(const GemmArgs& a, f32x4 (&acc)[MT][NT], float (&ss)[MT], unsigned char* smem,
@@ -519,8 +626,6 @@ __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel
     using E = Elem<T>;
     using frag_t = E::frag_t;
     constexpr bool NORM = (EPI != EPI_RESID);
-    constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
-    constexpr int TPI = PAIR ? 2 : 1;
     // Weight fragments are fetched PFW k-tiles ahead and activation pieces XD k-tiles ahead.  Loads retire in order, so
     // waiting for an activation piece also waits for every weight fetch issued before it: XD, not PFW, is the latency
     // budget of a weight fetch, and PFW > XD + 1 only adds loads in flight.  (With XD = 2 a k-tile took 0.7 us whenever
@@ -710,16 +815,7 @@ __global__ void __launch_bounds__(WAVES * 64, BMT == 8 ? 2 : 3) wide_gemm_kernel
     for (int mt = 0; mt < BMT; ++mt) {
         const int m = (mt0 + mt) * 16 + r16;
         const float rs = NORM ? rs_s[mt * 16 + r16] : 1.f;
-        float hsq = 0.f;
-#pragma unroll
-        for (int ntp = 0; ntp < WNT / TPI; ++ntp) {
-            float y[TPI][4];
-#pragma unroll
-            for (int tt = 0; tt < TPI; ++tt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) y[tt][v] = acc[mt][ntp * TPI + tt][v];
-            hsq += epilogue_item<T, EPI>(a, y, rs, m, pt0 + ntp * TPI, g);
-        }
+        float hsq = epilogue_row<EPI, WNT>(a, acc[mt], rs, m, pt0, g);
         if constexpr (EPI == EPI_RESID) {
             if (a.ssp_out) {
                 hsq = wave_xor_add(wave_xor_add(hsq, 16), 32);
@@ -822,7 +918,6 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_kernel(const GemmArgs
     using frag_t = E::frag_t;
     constexpr bool NORM = (EPI != EPI_RESID);
     constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
-    constexpr int TPI = PAIR ? 2 : 1;
     constexpr int NWAVES = WM * WN;
     constexpr int BMT = WM * MT, BNT = WN * NT, FR = BMT + BNT;  // row tiles, feature tiles, fragments (KiB) per stage
     constexpr int DIST = STAGES - 1;                             // k-tiles between a stage's loads and its MFMAs
@@ -955,16 +1050,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_kernel(const GemmArgs
         const int lr = (wm * MT + mt) * 16 + r16;  // row within the block
         const int m = mt0 * 16 + lr;
         const float rs = NORM ? rs_s[lr] : 1.f;
-        float hsq = 0.f;
-#pragma unroll
-        for (int ntp = 0; ntp < NT / TPI; ++ntp) {
-            float y[TPI][4];
-#pragma unroll
-            for (int tt = 0; tt < TPI; ++tt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) y[tt][v] = acc[mt][ntp * TPI + tt][v];
-            hsq += epilogue_item<T, EPI>(a, y, rs, m, pt0 + ntp * TPI, g);
-        }
+        float hsq = epilogue_row<EPI, NT>(a, acc[mt], rs, m, pt0, g);
         if constexpr (EPI == EPI_RESID) {
             if (a.ssp_out) {
                 hsq = wave_xor_add(wave_xor_add(hsq, 16), 32);
@@ -1010,8 +1096,6 @@ __global__ void __launch_bounds__(WM * WN * KG * 64) stream_gemm_kernel(const vo
     using E = Elem<T>;
     using frag_t = E::frag_t;
     constexpr bool NORM = (EPI != EPI_RESID);
-    constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
-    constexpr int TPI = PAIR ? 2 : 1;
     constexpr int S = KG;  // k-tiles per stage: one per wave and stage
     constexpr int NW = WM * WN * KG, BMT = WM * MT, BNT = WN * NT, H = MT / KG;
     constexpr int AF = S * BMT, WF = S * BNT, LA = AF / NW, LW = WF / NW, LPS = LA + LW;  // fragments per stage, loads per wave and stage
@@ -1192,15 +1276,7 @@ __global__ void __launch_bounds__(WM * WN * KG * 64) stream_gemm_kernel(const vo
             for (int nt = 0; nt < NT; ++nt) ((f32x4*)part)[(((size_t)ks * m_tiles + mt) * (gridDim.x * BNT) + pt0 + nt) * 64 + lane] = own[h][nt];
         } else {
             const float rs = NORM ? 1.0f / sqrtf(so[h] / (float)a.K + a.eps) : 1.f;
-#pragma unroll
-            for (int ntp = 0; ntp < NT / TPI; ++ntp) {
-                float y[TPI][4];
-#pragma unroll
-                for (int tt = 0; tt < TPI; ++tt)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) y[tt][v] = own[h][ntp * TPI + tt][v];
-                epilogue_item<T, EPI>(a, y, rs, mt * 16 + r16, pt0 + ntp * TPI, g);
-            }
+            epilogue_row<EPI, NT>(a, own[h], rs, mt * 16 + r16, pt0, g);
         }
     }
 }
@@ -1715,8 +1791,6 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
     using E = Elem<T>;
     using frag_t = E::frag_t;
     constexpr bool NORM = (EPI != EPI_RESID);
-    constexpr bool PAIR = (EPI == EPI_QKV || EPI == EPI_SWIGLU);
-    constexpr int TPI = PAIR ? 2 : 1;
     constexpr int NW = WM * WN, BMT = WM * MT, BNT = WN * NT, ROWS = BMT * 16, THREADS = NW * 64;
     constexpr int AF = 4 * BMT, LA = AF / NW, LW = BNT / NW, LPS = LA + LW + 1;
     constexpr int SCALES = (AF + BNT) * 1024, STAGE = SCALES + NW * 256;
@@ -1950,16 +2024,7 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_w4_kernel(const void*
         if (mt >= my) break;
         const int lr = (tb + mt) * 16 + r16, m = mt0 * 16 + lr;
         const float rs = NORM ? 1.0f / sqrtf(rs_s[lr] / (float)a.K + a.eps) : 1.f;
-        float hsq = 0.f;
-#pragma unroll
-        for (int ntp = 0; ntp < NT / TPI; ++ntp) {
-            float y[TPI][4];
-#pragma unroll
-            for (int tt = 0; tt < TPI; ++tt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) y[tt][v] = acc[mt][ntp * TPI + tt][v];
-            hsq += epilogue_item<T, EPI>(a, y, rs, m, pt0 + ntp * TPI, g);
-        }
+        float hsq = epilogue_row<EPI, NT>(a, acc[mt], rs, m, pt0, g);
         if constexpr (EPI == EPI_RESID) {
             hsq = wave_xor_add(wave_xor_add(hsq, 16), 32);
             if (g == 0) hs[wn * ROWS + lr] = hsq;
