@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_rowstats_kernel(const
 
 #define SMP_THREADS 1024 /* one node of the tree per thread */
 #define SMP_WAVES (SMP_THREADS / 64)
-#define SMP_PENDING (-2)  /* x_new while the residual draw is still to come */
+#define SMP_PENDING (-2)  /* x_new = SMP_PENDING - u while the residual draw at node u is still to come */
 
 // Rank of this thread among the threads whose flag is set, and their number (two barriers).
 static __device__ __forceinline__ int block_rank(bool flag, int* sh, int* total) {
@@ -188,7 +188,7 @@ static __device__ __forceinline__ int block_rank(bool flag, int* sh, int* total)
 // barriers of 16 waves cost more than its three further steps (one node, 200 entries, whole call 11.0 -> 6.9 us).
 // (16 rows x 32000 below a star of 16 nodes, whole call: 338 -> 35 us.)  Where sample_draw_kernel follows (`pending`), the draw's target is
 // left to it: three accepted nodes and a draw over 152064 entries 40 us in here, of which the 608 KB row through one compute unit was the
-// larger part, now 8 here and 10.6 there.
+// larger part, now 8 here and 10 there.
 __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float* __restrict__ logits, int vocab, float inv_temp, bool vec,
                                                                     const unsigned* __restrict__ rowm, const unsigned long long* rowZ,
                                                                     const int32_t* __restrict__ token, const int32_t* __restrict__ parent, int T,
@@ -291,7 +291,7 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
                 pending[0] = s_target;
                 pending[1] = 0;
             }
-            x_new = SMP_PENDING;
+            x_new = SMP_PENDING - u;
             break;
         }
         const float* row = logits + (size_t)u * vocab;
@@ -375,24 +375,23 @@ __global__ void __launch_bounds__(SMP_THREADS) accept_sample_kernel(const float*
 
 // ---- residual draw of a large vocabulary -----------------------------------------------------------------------------------
 // One compute unit takes 24 us for a row of 152064 logits.  Spread over the chip every workgroup sums one chunk of the row, and the one that
-// arrives last finds the token in the chunk that holds the target (two launches instead: 5.4 + 5.6 us against 10.6, but a call whose
+// arrives last finds the token in the chunk that holds the target: about 10 us (two launches instead: 5.4 + 5.6, but a call whose
 // walk ends without a draw then pays for two that do nothing, 2.3 us each).  Nobody waits for anybody: the last to arrive is told by a
 // counter.  All children of the last accepted node were rejected, so the struck tokens are read off the tree again.
 #define DRAW_THREADS 256
 #define DRAW_EACH 16  /* consecutive logits per thread */
 #define DRAW_BLOCK (DRAW_THREADS * DRAW_EACH)
 
-// Bit e of word t: entry lo + 16 t + e is struck (a child of u carries it).  Ends with a barrier.
-static __device__ __forceinline__ void struck_bits(unsigned* bits, const int32_t* __restrict__ token, const int32_t* __restrict__ parent, int T, int u, int lo,
-                                                   int hi) {
+// Bit e of word t: entry lo + 16 t + e is struck: tok[] are the tokens of this thread's nodes that are children of u, -1 else.  Ends with a barrier.
+#define DRAW_NODES (1024 / DRAW_THREADS) /* nodes per thread */
+static __device__ __forceinline__ void struck_bits(unsigned* bits, const int (&tok)[DRAW_NODES], int lo, int hi) {
     const int tid = threadIdx.x;
     __syncthreads();
     bits[tid] = 0;
     __syncthreads();
-    for (int i = u + 1 + tid; i < T; i += DRAW_THREADS) {
-        const int par = parent[i], tok = token[i];
-        if (par == u && tok >= lo && tok < hi) atomicOr(&bits[(tok - lo) / DRAW_EACH], 1u << ((tok - lo) % DRAW_EACH));
-    }
+#pragma unroll
+    for (int k = 0; k < DRAW_NODES; ++k)
+        if (tok[k] >= lo && tok[k] < hi) atomicOr(&bits[(tok[k] - lo) / DRAW_EACH], 1u << ((tok[k] - lo) % DRAW_EACH));
     __syncthreads();
 }
 
@@ -426,19 +425,27 @@ static __device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {
 __global__ void __launch_bounds__(DRAW_THREADS) sample_draw_kernel(const float* __restrict__ logits, int vocab, float inv_temp, bool vec, int chunk,
                                                                    const unsigned* __restrict__ rowm, const int32_t* __restrict__ token,
                                                                    const int32_t* __restrict__ parent, int T, AcceptResultDev* res,
-                                                                   const int32_t* __restrict__ retain, unsigned long long* draw) {
+                                                                   unsigned long long* draw) {
     __shared__ unsigned bits[DRAW_THREADS];
     __shared__ uint64_t shz[DRAW_THREADS / 64];
     __shared__ int s_last, s_x;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, chunks = gridDim.x;
-    const int n_acc = res->n_acc;
-    if (n_acc < 1 || res->x_new != SMP_PENDING) return;
-    const int u = retain[n_acc - 1];  // nothing is retained behind the accepted path
+    int par[DRAW_NODES], tok[DRAW_NODES];  // before anything is known of u: one round of memory latency less
+#pragma unroll
+    for (int k = 0; k < DRAW_NODES; ++k) {
+        const int i = min(tid + k * DRAW_THREADS, T - 1);
+        par[k] = parent[i];
+        tok[k] = token[i];
+    }
+    const int n_acc = res->n_acc, u = SMP_PENDING - res->x_new;
+    if (n_acc < 1 || u < 0) return;
+#pragma unroll
+    for (int k = 0; k < DRAW_NODES; ++k) tok[k] = par[k] == u && tid + k * DRAW_THREADS < T ? tok[k] : -1;
     const float* row = logits + (size_t)u * vocab;
     const float m = key_max(rowm[u]);
     auto weights = [&](int lo, int hi, float (&x)[DRAW_EACH], unsigned& b) {  // this thread's sum of the block at lo
         draw_load(row, lo, hi, vec, x);
-        struck_bits(bits, token, parent, T, u, lo, hi);
+        struck_bits(bits, tok, lo, hi);
         b = bits[tid];
         uint64_t z = 0;
 #pragma unroll
@@ -539,8 +546,7 @@ hipError_t launch_accept_sample(const float* logits, int vocab, float inv_temp, 
                        step, res, retain, draw ? rowZ : nullptr);
     if (draw) {
         const int chunk = ((vocab + draw_chunks - 1) / draw_chunks + DRAW_BLOCK - 1) / DRAW_BLOCK * DRAW_BLOCK, chunks = (vocab + chunk - 1) / chunk;
-        hipLaunchKernelGGL(sample_draw_kernel, dim3(chunks), dim3(DRAW_THREADS), 0, s, logits, vocab, inv_temp, vec, chunk, rowm, token, parent, T, res, retain,
-                           rowZ);
+        hipLaunchKernelGGL(sample_draw_kernel, dim3(chunks), dim3(DRAW_THREADS), 0, s, logits, vocab, inv_temp, vec, chunk, rowm, token, parent, T, res, rowZ);
     }
     return hipGetLastError();
 }
