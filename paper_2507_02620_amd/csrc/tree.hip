@@ -217,14 +217,33 @@ static __device__ Best block_best(Best b) {
     return r;
 }
 
+// The maximum of a chunk of a row.  Loads of a round go out together; past the chunk's end they repeat its last ones.
+template <bool VEC>
 __global__ void __launch_bounds__(256) argmax_partial_kernel(const float* __restrict__ logits, int vocab, int chunk_len, int32_t* __restrict__ work) {
     const int row = blockIdx.y, c = blockIdx.x;
-    const int lo = c * chunk_len, hi = min(vocab, lo + chunk_len);
+    const int lo = min(vocab, c * chunk_len), hi = min(vocab, lo + chunk_len);
     const float* p = logits + (size_t)row * vocab;
     Best b{-INFINITY, lo < vocab ? lo : 0};
-    for (int i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-        const float v = p[i];
-        if (v > b.v) b = Best{v, i};
+    constexpr int E = VEC ? 4 : 1, U = 8;  // chunk_len and vocab are multiples of 4 where VEC
+    const int n = (hi - lo) / E;
+    for (int i = threadIdx.x; i < n; i += U * 256) {
+        float v[U][E];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float* q = p + lo + min(i + u * 256, n - 1) * E;
+            if constexpr (VEC) {
+                const f32x4 x = *(const f32x4*)q;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][e] = x[e];
+            } else {
+                v[u][0] = *q;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (v[u][e] > b.v) b = Best{v[u][e], lo + min(i + u * 256, n - 1) * E + e};
     }
     b = block_best(b);
     if (threadIdx.x == 0) {
@@ -282,8 +301,14 @@ hipError_t launch_argmax(const float* logits, int rows, int vocab, int chunks, i
         hipLaunchKernelGGL(argmax_row_kernel, dim3(rows), dim3(1024), 0, s, logits, vocab, amax);
         return hipGetLastError();
     }
-    const int chunk_len = (vocab + chunks - 1) / chunks;
-    hipLaunchKernelGGL(argmax_partial_kernel, dim3(chunks, rows), dim3(256), 0, s, logits, vocab, chunk_len, work);
+    // about 1024 workgroups: many smaller ones cost more to start than their loads take (chunks of a 64th and scalar loads one after another
+    // before: 32 / 40 / 63 rows x 152064 17.2 / 22.1 / 24.4 us -> 14.6 / 14.8 / 18.5, 63 rows x 50257 16.7 -> 14.0)
+    chunks = max(1, min(chunks, 1024 / rows));
+    const int chunk_len = ((vocab + chunks - 1) / chunks + 3) & ~3;
+    if (vec)
+        hipLaunchKernelGGL(argmax_partial_kernel<true>, dim3(chunks, rows), dim3(256), 0, s, logits, vocab, chunk_len, work);
+    else
+        hipLaunchKernelGGL(argmax_partial_kernel<false>, dim3(chunks, rows), dim3(256), 0, s, logits, vocab, chunk_len, work);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(argmax_final_kernel, dim3(rows), dim3(64), 0, s, work, chunks, amax);

@@ -212,3 +212,12 @@ def test_seg_prune_bit_exact(dtype):
         assert n == ref.shape[0]
         got = out.view(torch.int16 if dtype == torch.bfloat16 else torch.int32).cpu().numpy()[:n]
         assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("rows,vocab", [
+    (1, 20484), (1, 30001), (17, 53252), (39, 60000), (39, 60002), (40, 65540), (63, 65541), (63, 152064), (16, 262144),
+    (7, 4098), (63, 5003),   # rows off 16 bytes: chunks shorter than a round of loads
+])
+def test_argmax_in_chunks(rows, vocab):
+    """Two launches: as many chunks as there may be and fewer, chunks that end inside a round of loads, rows on and off 16 bytes."""
+    test_argmax_from_logits_bit_exact_with_ties(rows, vocab)
