@@ -938,9 +938,15 @@ __global__ void __launch_bounds__(WM * WN * 64) block_gemm_kernel(const GemmArgs
     auto stage_buf = [&](int j) -> unsigned char* { return j == 0 ? sb0 : (j == 1 ? sb1 : (j == 2 ? sb2 : sb3)); };
 
     const int id = blockIdx.x, xcd = id & 7, slot = id >> 3;
-    const int per_col = m_blocks * k_splits;
-    const int col = (slot / per_col) * 8 + xcd, mb = (slot % per_col) / k_splits, ks = slot % k_splits;
-    if (col >= n_cols) return;
+    int col, mb, ks;
+    if constexpr (PARTIAL) {  // units (K slice, feature block), neighbours on one XCD: none gets more than its share
+        const int units = n_cols * k_splits, unit = (units * xcd >> 3) + slot / m_blocks;
+        mb = slot % m_blocks, ks = unit / n_cols, col = unit % n_cols;
+        if (unit >= units * (xcd + 1) >> 3) return;
+    } else {
+        col = (slot / m_blocks) * 8 + xcd, mb = slot % m_blocks, ks = 0;
+        if (col >= n_cols) return;
+    }
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6), wm = w / WN, wn = w % WN;  // wave-uniform: scalar address arithmetic below
     const int r16 = lane & 15, g = lane >> 4;
@@ -1335,6 +1341,7 @@ static WideShape wide_shape(int epi, int M) {
 
 struct WideGrid {
     int n_cols, m_blocks, k_splits;
+    double us;  // residual projections: estimate
 };
 // K slices for the d_model-wide residual projections: the number that costs least in rounds of one block per compute unit (0.43 us per
 // k-tile of a 128 x 256 block, 0.3 of a 128 x 128 one, 4 us into and out of it, 15 with the residual epilogue), partial results (0.5 us a MiB
@@ -1347,15 +1354,16 @@ static WideGrid wide_grid(const WideShape& sh, int epi, int M, int n_tiles, int 
     g.n_cols = (n_tiles + col_tiles - 1) / col_tiles;
     g.m_blocks = (M + sh.bmt * 16 - 1) / (sh.bmt * 16);
     g.k_splits = 1;
+    g.us = 0;
     if (epi == EPI_RESID) {
         const size_t per_split = (size_t)((M + 15) / 16) * g.n_cols * col_tiles * 1024;
         const double kt = sh.wnt == 4 ? 0.43 : 0.3;
-        double best = 1e30;
+        g.us = 1e30;
         for (int k = 1; k <= 8 && (k == 1 || (nkt / k >= 8 && per_split * k <= part_bytes)); ++k) {
             const int rounds = ((g.n_cols * k + 7) / 8 * g.m_blocks + 31) / 32;
             const double cost = rounds * (nkt * kt / k + (k > 1 ? 4 : 15)) + (k > 1 ? 4 + per_split * k * 0.5e-6 : 0);
-            if (cost < best) {
-                best = cost;
+            if (cost < g.us) {
+                g.us = cost;
                 g.k_splits = k;
             }
         }
@@ -1424,8 +1432,8 @@ static hipError_t launch_block(int layout_nt, int n_tiles, const GemmArgs& a, hi
 // 192 blocks of 256 features or 256 blocks of 192).  It wins when that is most of the chip while the 128-row kernel would have to
 // give some compute units a second pair of blocks (measured, 1024 rows: QKV 111 -> 97 us; 512 rows: gate/up 108 -> 92 us); with
 // more than 256 blocks its second round costs more than it saves (1024 rows: gate/up 159 -> 187 us), with few blocks the 128-row
-// kernel's finer grain fills more compute units (512 rows: QKV 66 -> 92 us), and the K slices of the d_model-wide residual
-// projections do no better either (1024 rows: 51 -> 58 us, 95 -> 96 us).
+// kernel's finer grain fills more compute units (512 rows: QKV 66 -> 92 us).  The d_model-wide residual
+// projections come by a rule of their own (launch_gemm_wide).
 static int block_gemm_width(int mode, int epi, int M, int n_tiles) {  // mode 0 / 1 / 2: never / always 16 tiles / always 12 tiles (tuning knob)
     if (epi == EPI_RESID || mode == 0) return 0;
     if (mode == 1) return 16;
@@ -1436,6 +1444,22 @@ static int block_gemm_width(int mode, int epi, int M, int n_tiles) {  // mode 0 
     if (b12 <= 256 && b12 >= 144) return 12;  // the narrower block has more blocks: closer to one per compute unit
     if (b16 <= 256 && b16 >= 144) return 16;
     return 0;
+}
+
+// K slices of a residual projection in 256-row blocks of 16 feature tiles, one round of them (32 blocks on an XCD's compute units) and at least 24
+// k-tiles per slice; 0 if none is estimated below `other` us: 0.8 us per k-tile, 0.45 us a MiB of partial results to write and sum, 4 us.
+static int block_slices(int n_cols, int M, int nkt, size_t part_bytes, double other) {
+    const int m_blocks = (M + 255) / 256;
+    const size_t per_split = (size_t)((M + 15) / 16) * n_cols * 16 * 1024;
+    int best = 0;
+    for (int k = 2; k <= 8 && (n_cols * k + 7) / 8 * m_blocks <= 32 && nkt / k >= 24 && per_split * k <= part_bytes; ++k) {
+        const double us = 4 + per_split * k * 0.45e-6 + 0.8 * ((nkt + k - 1) / k);
+        if (us < other) {
+            other = us;
+            best = k;
+        }
+    }
+    return best;
 }
 
 // the kernels address weights and activations with 32-bit byte offsets from their bases
@@ -1459,6 +1483,21 @@ hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs&
             case EPI_QKV: return launch_block<EPI_QKV, 4, 2, 4, 6>(layout_nt, n_tiles, a, s);
             case EPI_SWIGLU: return launch_block<EPI_SWIGLU, 4, 2, 4, 6>(layout_nt, n_tiles, a, s);
             case EPI_LOGITS: return launch_block<EPI_LOGITS, 4, 2, 4, 6>(layout_nt, n_tiles, a, s);
+        }
+    }
+    if (epi == EPI_RESID && !narrow && part && block_mode != 0) {
+        // 256-row blocks where their estimate is 3 % below the 128-row kernel's, which runs 5 % over its own with nearly every compute unit busy.
+        // us, 128-row blocks -> 256-row blocks: 5120 x 5120, 1024 rows 95.5 -> 78.7; 11008 x 4096, 700 rows 91.7 -> 84; 14336 x 4096, 700 rows
+        // 116.5 -> 100.6; 18944 x 3584, 1024 rows 159.8 -> 148.3; 16384 x 6144, 512 rows 136 -> 115; 22016 x 8192, 389 .. 1024 rows 186 .. 340 -> 172 ..
+        // 319.  A short K, or a second round on some XCD, is worse: 2048 x 2048, 512 rows 21.9 / 24.9; 18944 x 3584, 700 rows in 84 units 122 / 161.
+        const WideGrid g = wide_grid(sh, epi, a.M, n_tiles, a.nkt, part_bytes);
+        const bool full = g.n_cols * g.k_splits * g.m_blocks > 216 && g.n_cols * g.k_splits * g.m_blocks <= 256;
+        const int ks = block_slices(g.n_cols, a.M, a.nkt, part_bytes, block_mode > 0 ? 1e30 : g.us * (full ? 1.02 : 0.97));
+        if (ks > 1) {
+            const int m_blocks = (a.M + 255) / 256, grid = (g.n_cols * ks + 7) / 8 * 8 * m_blocks;
+            hipLaunchKernelGGL((block_gemm_kernel<EPI_RESID, true, 2, 4, 8, 4, 4>), dim3(grid), dim3(512), 0, s, a, layout_nt, n_tiles, g.n_cols, m_blocks, ks,
+                               part);
+            return launch_fixup<4>(a, g.n_cols * 16, ks, part, s);
         }
     }
     switch (epi) {

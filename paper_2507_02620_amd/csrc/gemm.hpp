@@ -94,7 +94,7 @@ hipError_t launch_gemm_w4(int epi, int NT, int NW, int n_groups, const GemmArgs&
 // segments of up to max_rows rows and n_tiles output tiles); a residual projection leaves wide_ssp_parts(M, n_tiles) partial sums of squares per row in ssp_out.
 int wide_ssp_parts(int M, int n_tiles);
 size_t wide_partial_bytes(int max_rows, int n_tiles);
-// block_mode: 0 never / 1 whenever possible / anything else: by rule — use of the 256-row kernel (both operands through LDS) from 384 rows on
+// block_mode: 0 never / 1, 2 whenever possible / negative: by rule — use of the 256-row kernel (both operands through LDS) from 384 rows on
 hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs& a, float* part, size_t part_bytes, int block_mode, hipStream_t s);
 // bf16, 17 to 128 rows, row-major or fragment-major activations: the kernel that streams both operands through LDS; normed projections
 // work out their own row scale, residual projections leave no sums of squares.  `part` as for launch_gemm_wide.  mid_kernel: which
