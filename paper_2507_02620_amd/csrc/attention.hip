@@ -1023,6 +1023,14 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     const int per_split = Hkv * *row_blocks;  // workgroups per KV split
     int want = (target + per_split - 1) / per_split;
     if ((deep_ring || pairs) && wgs_override <= 0) want = splits_one_round(per_split, ntiles);
+    // Few KV heads, 16-bit K/V: 29 to 128 tiles come at least two to a split and go into at most 32.  A split of one tile costs its way in and out
+    // and a partial result of every row for the merge, which 64 of them make the longer part.  us with the merge, as many splits as workgroups
+    // were wanted / so: 8 heads x 64 rows, 2k / 4k / 8k slots 17.4 / 15.4, 25.5 / 19.1, 27.6 / 22.7, x 4 rows 12.5 / 11.8, 17.6 / 13.9, 19.8 / 17; 4 heads
+    // x 28 rows 12.4 / 12.2, 16.7 / 13.6, 18.1 / 16.4; 8 heads of 64, 4k 16.5 / 12.4.  Elsewhere one tile each is the faster one: 17 tiles (8 heads x
+    // 16 rows 10.8 / 11.2), more than 128 (2 heads x 96 rows, 16k 24.4 / 26.1), one or two heads (6 rows 12.1 / 12.7), f32, whose tiles take several
+    // times as long (2 heads x 48 rows, 4k 17.5 / 19.3).
+    else if (wgs_override <= 0 && elem_bytes == 2 && per_split >= 4 && ntiles > 28 && ntiles <= 128)
+        want = std::min(want, std::min(32, (ntiles + 1) / 2));
     // Few tiles for few rows: walking them one after another is shorter than the merge launch (us, merge / none: 8 heads of 64, 16 rows each,
     // 2 / 3 / 4 tiles 9.4 / 7.3, 9.7 / 7.8, 9.9 / 9.6, 64 rows, 2 / 3 tiles 10.1 / 9.0, 10.7 / 10.0; 32 heads of 128, 16 rows, 2 tiles 9.7 / 8.6,
     // 3 tiles, two of them masked 10.4 / 11.4, 32 rows, 2 tiles 10.4 / 9.0, 64 rows, 3 tiles 12.4 / 13.5; f32, up to 16 rows per head, heads of 64,
