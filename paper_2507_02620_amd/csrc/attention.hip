@@ -997,6 +997,12 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
         dma_bufs = dma_override;
         mtw = 1;
     }
+    // Four row tiles on 4 to 8 KV heads behind 29 to 128 tiles: a wave each and two tile buffers of the direct-to-LDS kernel, instead of two row
+    // tiles for two waves and registers (4 heads x 49 rows, 7k slots 18.9 -> 17.0 us with the merge, 8 heads x 64 rows, 2k / 4k / 7k 16.4 / 18.6 /
+    // 21.8 -> 15.4 / 17.8 / 20.0; 16 heads gain nothing, 7k 25.4 -> 25.6, and three row tiles lose: 8 heads x 48 rows, 4k 15.9 -> 16.6).
+    const bool few_heads = dma_shape && mtiles == 4 && !deep_ring && Hkv >= 4 && Hkv <= 8 && ntiles > 28 && ntiles <= 128 && dma_override == 0 &&
+                           wgs_override <= 0 && mtw_override <= 0 && nwc_override <= 0 && nset_override <= 0;
+    if (few_heads) mtw = 1;
     // Tiles in pairs, 128 rows per workgroup (tree_attn_dma_kernel with two groups): from 5 row tiles on, where a context of at
     // least 12 tiles gives one workgroup per compute unit 4 of them.  us with the merge, tile by tile -> in pairs (tiles to walk per
     // workgroup in brackets): 32 heads, 1024 rows: 1k context [16] 64 -> 52, 4k 146 -> 108; 700 rows, 1k 59 -> 42; 256 rows, 4k
@@ -1064,6 +1070,7 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
         else if (deep_ring)
             dma_bufs = 3;
     }
+    if (few_heads && !pairs) dma_bufs = 2;
     *dma = dma_bufs;
 }
 
