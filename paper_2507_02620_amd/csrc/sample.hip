@@ -49,33 +49,59 @@ static __device__ __forceinline__ unsigned max_key(float m) {
 }
 static __device__ __forceinline__ float key_max(unsigned k) { return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k); }
 
-// Visits the elements [lo, hi) of a row with all threads of the group, adjacent threads on adjacent 16 bytes (U loads in flight per
-// thread) where the row allows it (lo a multiple of 4).  fn(x, live).  CLAMP: a last round repeats the last 16 bytes instead of going
-// one load at a time (live is false for repeats): shorter where a round is most of the work, longer where it is little of it.
+// Visits n pieces of E floats with all threads of the group, adjacent threads on adjacent pieces, U loads in flight per thread.  fn(x, live).
+// CLAMP: what a thread has left behind its full rounds goes out together too and repeats the last piece (live is false for repeats) instead of
+// one load at a time: shorter where a round is most of the work, longer where it is little of it.
+template <int U, bool CLAMP, int E, typename F>
+static __device__ __forceinline__ void for_pieces(const float* __restrict__ p, int n, int t, int nt, F&& fn) {
+    auto load = [&](int i, float (&x)[E]) __attribute__((always_inline)) {
+        if constexpr (E == 4) {
+            const f32x4 q = *(const f32x4*)(p + (size_t)i * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = q[e];
+        } else {
+            x[0] = p[i];
+        }
+    };
+    int i = t;
+    for (; i + (U - 1) * nt < n; i += U * nt) {
+        float x[U][E];
+#pragma unroll
+        for (int k = 0; k < U; ++k) load(i + k * nt, x[k]);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int e = 0; e < E; ++e) fn(x[k][e], true);
+    }
+    if constexpr (CLAMP) {
+        if (i < n) {
+            float x[U][E];
+#pragma unroll
+            for (int k = 0; k < U; ++k) load(min(i + k * nt, n - 1), x[k]);
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+                for (int e = 0; e < E; ++e) fn(x[k][e], i + k * nt < n);
+        }
+    } else {
+        for (; i < n; i += nt) {
+            float x[E];
+            load(i, x);
+#pragma unroll
+            for (int e = 0; e < E; ++e) fn(x[e], true);
+        }
+    }
+}
+
+// The elements [lo, hi) of a row: by 16 bytes where the row allows it (lo a multiple of 4), the rest by elements.
 template <int U, bool CLAMP, typename F>
 static __device__ __forceinline__ void for_row(const float* __restrict__ p, int lo, int hi, int t, int nt, bool vec, F&& fn) {
     int v = lo;
     if (vec) {
-        const int n4 = (hi - lo) >> 2;
-        const f32x4* p4 = (const f32x4*)(p + lo);
-        int i = t;
-        for (; CLAMP ? i < n4 : i + (U - 1) * nt < n4; i += U * nt) {
-            f32x4 x[U];
-#pragma unroll
-            for (int k = 0; k < U; ++k) x[k] = p4[CLAMP ? min(i + k * nt, n4 - 1) : i + k * nt];
-#pragma unroll
-            for (int k = 0; k < U; ++k)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) fn(x[k][e], !CLAMP || i + k * nt < n4);
-        }
-        for (; i < n4; i += nt) {
-            const f32x4 x = p4[i];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) fn(x[e], true);
-        }
-        v = lo + 4 * n4;
+        for_pieces<U, CLAMP, 4>(p + lo, (hi - lo) >> 2, t, nt, fn);
+        v = lo + ((hi - lo) & ~3);
     }
-    for (int i = v + t; i < hi; i += nt) fn(p[i], true);
+    for_pieces<U, CLAMP, 1>(p + v, hi - v, t, nt, fn);
 }
 
 static __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
@@ -96,14 +122,13 @@ __global__ void __launch_bounds__(256) sample_clear_kernel(unsigned* __restrict_
     }
 }
 
-template <int U>
 __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_max_kernel(const float* __restrict__ logits, int vocab, float inv_temp, int chunk, bool vec,
                                                                       unsigned* __restrict__ rowm) {
     __shared__ float shm[SMP_STAT_THREADS / 64];
     const float* p = logits + (size_t)blockIdx.y * vocab;
     const int lo = blockIdx.x * chunk, hi = min(vocab, lo + chunk);
     float m = -INFINITY;
-    for_row<U, true>(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
+    for_row<4, true>(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool) { m = fmaxf(m, __fmul_rn(x, inv_temp)); });
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, FS_WAVE));
     if ((threadIdx.x & 63) == 0) shm[threadIdx.x >> 6] = m;
     __syncthreads();
@@ -113,7 +138,6 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_max_kernel(const floa
     }
 }
 
-template <int U>
 __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_sum_kernel(const float* __restrict__ logits, int vocab, float inv_temp, int chunk, bool vec,
                                                                       const unsigned* __restrict__ rowm, unsigned long long* __restrict__ rowZ) {
     __shared__ uint64_t shz[SMP_STAT_THREADS / 64];
@@ -121,7 +145,7 @@ __global__ void __launch_bounds__(SMP_STAT_THREADS) sample_sum_kernel(const floa
     const int lo = blockIdx.x * chunk, hi = min(vocab, lo + chunk);
     const float m = key_max(rowm[blockIdx.y]);
     uint64_t z = 0;
-    for_row<U, true>(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool live) { z += live ? exp_weight(__fmul_rn(x, inv_temp), m) : 0; });
+    for_row<4, true>(p, lo, hi, threadIdx.x, SMP_STAT_THREADS, vec, [&](float x, bool live) { z += live ? exp_weight(__fmul_rn(x, inv_temp), m) : 0; });
     z = wave_sum_u64(z);
     if ((threadIdx.x & 63) == 0) shz[threadIdx.x >> 6] = z;
     __syncthreads();
@@ -506,31 +530,32 @@ __global__ void __launch_bounds__(DRAW_THREADS) sample_draw_kernel(const float* 
     if (tid == 0) res->x_new = x_new;
 }
 
+// Workgroups that share a row's statistics.  Up to 256 rows: about 512 in all, up to 1024 while they have 12288 elements each, at least 4096
+// elements each and four to a row; twice to four times as many, smaller ones cost more to start than their loads take (us of a call without a
+// draw, 2048 in all / so: x 152064 40 rows 38.0 / 28.1, 80 rows 41.1 / 36.5, 120 rows 44.8 / 42.6; x 152065, off 16 bytes, 40 rows 37.8 / 29.1,
+// 120 rows 49.3 / 45.8).  More rows: about 2048 (1024 / 2048: 400 rows x 152064 98.3 / 96.2, x 100000 71.5 / 70.0, x 32000 38.0 / 35.4).  From
+// four chunks on the three launches beat one workgroup per row (256 x 32000 30.0 / 30.8, 80 x 32000 22.7 / 25.1, 80 x 152064 36.5 / 81.3), with
+// fewer they do not (600 x 32000, five chunks 44.1 / 42.3).
+extern "C" int sample_chunks(int vocab, int n_ver) {
+    const int smallest = (vocab + 4095) / 4096;
+    if (n_ver > 256) return std::min(smallest, std::max(1, 2048 / n_ver));
+    return std::min(smallest, std::max(std::max(512 / n_ver, std::min(1024 / n_ver, (vocab + 12287) / 12288)), 4));
+}
+
 hipError_t launch_accept_sample(const float* logits, int vocab, float inv_temp, const int32_t* token, const int32_t* parent, int T, int n_ver,
                                 uint64_t seed, uint64_t step, AcceptResultDev* res, int32_t* retain, void* work, hipStream_t s) {
     unsigned* rowm = (unsigned*)work;
     unsigned long long* rowZ = (unsigned long long*)((char*)work + (((size_t)n_ver * sizeof(float) + 15) / 16) * 16);
     const bool vec = (vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0;  // every row starts on 16 bytes
     if (n_ver > 0) {
-        // Chunks of a row: about 512 workgroups in all, up to 1024 while they have 12288 elements each, at least 4096 elements each and
-        // four chunks up to 512 rows.  From four chunks on the three launches beat one workgroup per row (whole call, chunked / single:
-        // 256 x 32000 135 / 141 us, 16 x 32000 35 / 36, 16 x 152064 78 / 104), with fewer they do not (600 x 32000 331 / 283, 16 x 8192 24 / 21).
-        // Twice to four times as many, smaller workgroups cost more to start than their loads take (x 152064: 40 rows 43.0 -> 32.7 us, 80 rows
-        // 47.4 -> 42.4).
-        const int smallest = (vocab + 4095) / 4096;
-        int chunks = std::min(smallest, std::max(std::max(512 / n_ver, std::min(1024 / n_ver, (vocab + 12287) / 12288)), n_ver <= 512 ? 4 : 1));
+        int chunks = sample_chunks(vocab, n_ver);
         if (chunks >= 4) {
             const int chunk = ((vocab + chunks - 1) / chunks + 3) & ~3;
             chunks = (vocab + chunk - 1) / chunk;
             hipLaunchKernelGGL(sample_clear_kernel, dim3((n_ver + 255) / 256), dim3(256), 0, s, rowm, rowZ, n_ver);
             const dim3 grid(chunks, n_ver), block(SMP_STAT_THREADS);
-            if (chunk <= 4 * 4 * SMP_STAT_THREADS) {  // one round of four loads per thread
-                hipLaunchKernelGGL(sample_max_kernel<4>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
-                hipLaunchKernelGGL(sample_sum_kernel<4>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
-            } else {
-                hipLaunchKernelGGL(sample_max_kernel<8>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
-                hipLaunchKernelGGL(sample_sum_kernel<8>, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
-            }
+            hipLaunchKernelGGL(sample_max_kernel, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm);
+            hipLaunchKernelGGL(sample_sum_kernel, grid, block, 0, s, logits, vocab, inv_temp, chunk, vec, rowm, rowZ);
         } else {
             hipLaunchKernelGGL(sample_rowstats_kernel, dim3(n_ver), dim3(SMP_STAT_THREADS), 0, s, logits, vocab, inv_temp, vec, rowm, rowZ);
         }

@@ -181,3 +181,9 @@ def test_sampled_accept_draw_finds_an_entry_at_the_ends(place):
             g_res, g_ret = _gpu(lg, 1.0, token, parent, n_ver, 8, step)
             assert g_res == o_res.as_tuple(), (tok, step, g_res, o_res.as_tuple())
             assert np.array_equal(g_ret, o_ret)
+
+
+@pytest.mark.parametrize("vocab,rows", [(12289, 256), (12289, 257), (20001, 300), (16385, 40), (13315, 17)])
+def test_sampled_accept_rows_off_16_bytes(vocab, rows):
+    """Element-wise rounds of four loads and what is left behind them: chunks of 3076 to 5004 elements, a last one of a few elements less."""
+    test_sampled_accept_row_chunks_and_residual(vocab, rows, rows, 5)
