@@ -611,12 +611,19 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     int aMTW, aRB;
     attn_plan(st->elem, hd, max_M, G, d.n_kv_heads, max_L, at.req, n_live, kMaxSplits, st->tun.attn_wgs, st->tun.attn_mtw, st->tun.attn_nset,
               st->tun.attn_nwc, st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma, &at.pair);
-    // Workgroups start in the table's order, so where they come in more than one round the longest contexts go first and what runs at the
-    // end is short (32 requests of contexts between 512 and 1024, 32 heads: 82.5 -> 76.8 us; 17 between 1500 and 3000: 129 -> 109; of 306 batches
-    // of 14 to 32 requests 74 faster by 2 to 16 %, four slower by 2 to 3 %).  A single round is better left alone (9 requests: 27.4 -> 28.8
-    // sorted), and the merge of splits looks a row's request up by ascending rows.
-    if (at.n_splits == 1 && (long long)n_live * d.n_kv_heads * aRB > 512)
-        std::stable_sort(at.req, at.req + n_live, [](const AttnReq& x, const AttnReq& y) { return x.L > y.L; });
+    // More workgroups than run at once (two per compute unit; one of 8 waves or of tiles in pairs): the longest contexts first where that is
+    // estimated the shorter launch.  A single round is better left alone (9 requests: 27.4 -> 28.8 sorted), and the merge of splits looks a row's
+    // request up by ascending rows.
+    if (at.n_splits == 1 && (long long)n_live * d.n_kv_heads * aRB > 512) {
+        const int bs = attn_tile_slots(st->elem, hd), block = at.nwc * aMTW * 16;
+        int tiles[FS_MAX_BATCH], wgs[FS_MAX_BATCH];
+        for (int i = 0; i < n_live; ++i) {
+            tiles[i] = (at.req[i].L + bs - 1) / bs;
+            wgs[i] = (G * at.req[i].M + block - 1) / block * d.n_kv_heads;
+        }
+        if (attn_longest_first(tiles, wgs, n_live, at.pair || at.nwc > 4 ? 256 : 512))
+            std::stable_sort(at.req, at.req + n_live, [](const AttnReq& x, const AttnReq& y) { return x.L > y.L; });
+    }
 
     // 4-bit stages: activations entering a normed projection carry the norm's gain, and the rows' sums of squares
     // travel beside them as partial sums (see GemmArgs::gain_next).  The many-row kernels of dense stages use the same hand-over of

@@ -1074,6 +1074,50 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     *dma = dma_bufs;
 }
 
+// When the last of a launch's workgroups ends: wgs[i] of them walk tiles[i] tiles each, started in the order of i on whichever of the chip's
+// `slots` places is free first.  A workgroup's way in and out counts as 6 tiles.
+static int launch_end(const int* tiles, const int* wgs, const int* order, int n, int slots) {
+    struct {
+        int t, n;
+    } free_at[ATTN_MAX_REQ + 2] = {{0, slots}};  // ascending; a request adds at most one entry
+    int groups = 1, end = 0;
+    for (int r = 0; r < n; ++r) {
+        for (int left = wgs[order[r]]; left > 0;) {
+            const int take = std::min(left, free_at[0].n), e = free_at[0].t + tiles[order[r]] + 6;
+            left -= take;
+            end = std::max(end, e);
+            if (take == free_at[0].n)
+                std::copy(free_at + 1, free_at + groups--, free_at);
+            else
+                free_at[0].n -= take;
+            int i = 0;
+            while (i < groups && free_at[i].t < e) ++i;
+            if (i < groups && free_at[i].t == e) {
+                free_at[i].n += take;
+            } else {
+                std::copy_backward(free_at + i, free_at + groups, free_at + groups + 1);
+                ++groups;
+                free_at[i] = {e, take};
+            }
+        }
+    }
+    return end;
+}
+
+// Whether a batch's workgroups, which start in the table's order, should start with the longest contexts: where that ends the launch 3 % sooner
+// (32 requests of contexts between 512 and 1024, 32 heads: 82.5 -> 76.8 us; 17 between 1500 and 3000: 129 -> 109).  Longest first is not always
+// shorter: its second round pairs long with short, so that all places fall free at once, and a few workgroups beyond two rounds (26 x 40 = 1040)
+// are a third one (26 requests, 40 heads, contexts up to 1.1k / 2.9k 77.8 -> 84.3, 205 -> 220).  Of 271 batches of more than 512 workgroups, sorting
+// all made 31 slower by over 2 % (up to 8 %); of those chosen so 7 are (up to 5 %), at the same mean.
+extern "C" int attn_longest_first(const int* tiles, const int* wgs, int n, int slots) {
+    int order[ATTN_MAX_REQ];
+    for (int i = 0; i < n; ++i) order[i] = i;
+    const int given = launch_end(tiles, wgs, order, n, slots);
+    for (int i = 1; i < n; ++i)  // insertion sort, stable
+        for (int j = i; j > 0 && tiles[order[j]] > tiles[order[j - 1]]; --j) std::swap(order[j], order[j - 1]);
+    return launch_end(tiles, wgs, order, n, slots) * 100ll < given * 97ll;
+}
+
 hipError_t launch_attention(int dtype, const AttnArgs& a, int MTW, int row_blocks, hipStream_t s) {
     if (a.hd == 64) return dtype == 0 ? launch_hd<float, 64>(a, MTW, row_blocks, s) : launch_hd<bf16_t, 64>(a, MTW, row_blocks, s);
     if (a.hd == 128) return dtype == 0 ? launch_hd<float, 128>(a, MTW, row_blocks, s) : launch_hd<bf16_t, 128>(a, MTW, row_blocks, s);
