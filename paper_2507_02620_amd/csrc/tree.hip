@@ -217,14 +217,14 @@ static __device__ Best block_best(Best b) {
     return r;
 }
 
-// The maximum of a chunk of a row.  Loads of a round go out together; past the chunk's end they repeat its last ones.
-template <bool VEC>
+// The maximum of a chunk of a row.  The U loads of a round go out together; past the chunk's end they repeat its last ones.
+template <bool VEC, int U>
 __global__ void __launch_bounds__(256) argmax_partial_kernel(const float* __restrict__ logits, int vocab, int chunk_len, int32_t* __restrict__ work) {
     const int row = blockIdx.y, c = blockIdx.x;
     const int lo = min(vocab, c * chunk_len), hi = min(vocab, lo + chunk_len);
     const float* p = logits + (size_t)row * vocab;
     Best b{-INFINITY, lo < vocab ? lo : 0};
-    constexpr int E = VEC ? 4 : 1, U = 8;  // chunk_len and vocab are multiples of 4 where VEC
+    constexpr int E = VEC ? 4 : 1;  // chunk_len and vocab are multiples of 4 where VEC
     const int n = (hi - lo) / E;
     for (int i = threadIdx.x; i < n; i += U * 256) {
         float v[U][E];
@@ -293,22 +293,29 @@ __global__ void __launch_bounds__(1024) argmax_row_kernel(const float* __restric
 }
 
 hipError_t launch_argmax(const float* logits, int rows, int vocab, int chunks, int32_t* work, int32_t* amax, hipStream_t s) {
-    // Both sides, us of an acceptance with logits beyond the caches (two launches / one): 1 row, 16384 logits 9.1 / 9.0, 24576 9.2 / 9.9, 61440 9.3 /
-    // 11.3; 4 rows, 24576 10.4 / 10.8; 8 rows, 24576 11.1 / 10.8, 50304 11.6 / 11.3, 57344 11.5 / 11.9; 32 rows, 50304 13.5 / 13.4, 61440 13.6 / 15.0; 40
-    // rows, 65536 15.9 / 14.8.  Rows that are not on 16 bytes go element by element: 4095, 32 rows 11.8 / 10.6; 152066, 16 rows 10.2 / 54.
+    // Both sides, us of an acceptance with logits beyond the caches (two launches / one): 1 row, 16384 logits 9.4 / 9.1, 24576 9.5 / 9.8, 57344 9.7 /
+    // 11.2; 4 rows, 16384 10.7 / 10.0, 24576 10.6 / 10.7, 57344 11.1 / 12.2; 32 rows, 24576 11.6 / 11.3, 57344 12.4 / 14.4; 128 rows x 152064 24.6 / 24.0, 256
+    // rows 37.5 / 35.3.  Off 16 bytes a row goes element by element: 4094, 32 rows 11.3 / 10.4; 152066, 16 rows 13.4 / 83.4.
+    // The lines were drawn with two launches of smaller chunks, one load in flight each.  As they are now they would be the shorter way
+    // also for 40 to 96 rows on 16 bytes of 32000 logits and more (63 rows x 40000 12.9 / 13.8, x 65536 13.6 / 15.0, 64 rows x 152064 18.6 / 22.2)
+    // and for any number of rows off 16 bytes (64 rows x 152066 17.7 / 83.8).
     const bool vec = (vocab & 3) == 0 && ((uintptr_t)logits & 15) == 0;
     if (rows >= 64 || vocab <= (!vec ? 4096 : rows < 8 ? 20480 : rows < 40 ? 53248 : 65536)) {
         hipLaunchKernelGGL(argmax_row_kernel, dim3(rows), dim3(1024), 0, s, logits, vocab, amax);
         return hipGetLastError();
     }
     // about 1024 workgroups: many smaller ones cost more to start than their loads take (chunks of a 64th and scalar loads one after another
-    // before: 32 / 40 / 63 rows x 152064 17.2 / 22.1 / 24.4 us -> 14.6 / 14.8 / 18.5, 63 rows x 50257 16.7 -> 14.0)
+    // before: 32 / 40 / 63 rows x 152064 17.3 / 22.1 / 24.5 us -> 14.6 / 14.9 / 18.4, 63 rows x 50257 16.8 -> 13.5).  As many loads per round as a
+    // thread has, so that few are repeats (always eight: 1 row x 24576 9.5 -> 9.4, 16 rows x 152064 13.6 -> 12.8)
     chunks = max(1, min(chunks, 1024 / rows));
     const int chunk_len = ((vocab + chunks - 1) / chunks + 3) & ~3;
+    const int loads = (chunk_len / (vec ? 4 : 1) + 255) / 256;  // per thread
+    const dim3 grid(chunks, rows), block(256);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, logits, vocab, chunk_len, work); };
     if (vec)
-        hipLaunchKernelGGL(argmax_partial_kernel<true>, dim3(chunks, rows), dim3(256), 0, s, logits, vocab, chunk_len, work);
+        loads <= 2 ? go(argmax_partial_kernel<true, 2>) : loads <= 4 ? go(argmax_partial_kernel<true, 4>) : go(argmax_partial_kernel<true, 8>);
     else
-        hipLaunchKernelGGL(argmax_partial_kernel<false>, dim3(chunks, rows), dim3(256), 0, s, logits, vocab, chunk_len, work);
+        loads <= 2 ? go(argmax_partial_kernel<false, 2>) : loads <= 4 ? go(argmax_partial_kernel<false, 4>) : go(argmax_partial_kernel<false, 8>);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(argmax_final_kernel, dim3(rows), dim3(64), 0, s, work, chunks, amax);
