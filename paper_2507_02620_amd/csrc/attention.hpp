@@ -38,7 +38,7 @@ static inline int attn_tile_slots(int elem_bytes, int hd) { return elem_bytes * 
 // the K/V tiles in flight per workgroup (tuning knobs); dma_override: 0 = plan's choice, 1 = never the direct-to-LDS kernel, 2 .. 4 = that
 // kernel with so many tile buffers wherever its shape allows, 5 = its form that takes tiles in pairs.  M and L are the batch's longest
 // segment and context, req its n_req requests, Hkv1 the KV heads of one request.
-void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const AttnReq* req, int n_req, int max_splits, int wgs_override, int mtw_override,
+extern "C" void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const AttnReq* req, int n_req, int max_splits, int wgs_override, int mtw_override,
                int nset_override, int nwc_override, int dma_override, int* NWC, int* MTW, int* row_blocks, int* n_splits, int* tiles_per_split, int* nset, int* dma, int* pair);
 extern "C" int attn_longest_first(const int* tiles, const int* wgs, int n, int slots);  // n <= ATTN_MAX_REQ
 hipError_t launch_attention(int dtype, const AttnArgs& a, int MTW, int row_blocks, hipStream_t s);

@@ -79,7 +79,8 @@ def _profiled(fn):
 def kernel_names(fn):
     """Names of the kernels one call of fn launches (which form of a projection or of the attention a dispatch took).  A profile now and then
     lacks its records, the first one of a process above all: a small one of its own comes first until it has some, and fn is called again
-    only where its profile shows no kernel of the library at all."""
+    (up to three times) only where its profile shows no kernel of the library at all.  A list without any is an error, so that a form's absence
+    from it means that another one ran."""
     x = torch.zeros(64, device="cuda")
     for _ in range(5):
         if _profiled(lambda: x.add_(1)):
@@ -87,8 +88,8 @@ def kernel_names(fn):
     for _ in range(4):
         names = _profiled(fn)
         if any("at::" not in n for n in names):
-            break
-    return names
+            return names
+    raise AssertionError(f"no kernel of the library in four profiles: {names}")
 
 
 def max_rel_err(got, ref):

@@ -30,3 +30,5 @@ def test_residual_projection_in_256_row_blocks(d, ffn, rows, taken, monkeypatch)
     x = to_dev(hid, pair.tdtype)
     names = kernel_names(lambda: pair.gpu.tree_verify_stage(pair.kv, 20, 20, x, 0, tree.parent))
     assert any("block_gemm_kernel<1" in n or "block_gemm_kernelILi1" in n for n in names) == taken, names
+    if not taken:   # the same projections in 128-row blocks with K slices
+        assert any("wide_gemm_kernel<1, true" in n or "wide_gemm_kernelILi1ELb1" in n for n in names), names

@@ -37,3 +37,5 @@ def test_value_tile_beside_every_pair(dtype, d, heads, kv, hd, max_seg, rows, bi
     x = to_dev(hid[:rows], pair.tdtype)
     names = kernel_names(lambda: pair.gpu.tree_verify_stage(pair.kv, cfg.l_glo, cfg.l_glo, x, 0, tree.parent[:rows]))
     assert any("skinny_qkv_kernel" in n for n in names) == taken, names
+    if not taken:   # the QKV form (0) of the kernels in groups of tiles
+        assert any("skinny_gemm_kernel" in n and (", 0>(" in n or "Li0EEv" in n) or "stream_gemm_kernel<0," in n for n in names), names

@@ -215,7 +215,7 @@ def test_w4_streaming_kernel(rows, ffn):
     pair = Pair(cfg, seed=rows, head=True, w4=True)
     got = []
     names = kernel_names(lambda: got.extend(pair.verify_tree(synth.config_tree(cfg, seed=rows).parent, synth.hidden(cfg, rows, 0, rows), rows)))
-    o, g = got
+    o, g = got[:2]   # (more where the profile had to be taken again)
     assert [sum(f"stream_gemm_w4_kernel<{kind}," in n for n in names) for kind in (0, 2)] == [2, 2], names
     assert any("stream_gemm_w4_kernel<1," in n for n in names), names
     L = cfg.l_glo + rows
@@ -223,7 +223,7 @@ def test_w4_streaming_kernel(rows, ffn):
     x = synth.storage(cfg, o.astype(np.float32))
     lo, _ = pair.orc.logits(x.astype(np.float64))
     names = kernel_names(lambda: got.extend(pair.gpu.tree_logits(to_dev(x, torch.bfloat16))))
-    lg = got[2]
+    lg = got[-2]
     assert any("stream_gemm_w4_kernel<3," in n for n in names), names
     assert max_rel_err(g, o) < TOL["bf16"] and kerr < TOL["bf16"] and max_rel_err(lg.cpu().numpy(), lo) < TOL["bf16"]
 

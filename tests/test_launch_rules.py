@@ -49,3 +49,31 @@ def test_a_few_workgroups_beyond_two_rounds_keep_their_order():
     tiles = [9 + (7 * i) % 10 for i in range(26)]
     assert not _longest_first(tiles, [40] * 26, 512)
     assert _longest_first([9 + (7 * i) % 10 for i in range(32)], [32] * 32, 512)
+
+
+def _plan(M, G, kv, slots, hd=128, elem=2):
+    """The attention plan of one request of M rows, G query heads to each of kv KV heads."""
+    out = [C.c_int() for _ in range(8)]
+    req = C.create_string_buffer(64)   # not looked at: one request's tiles in pairs are balanced
+    fs.lib().attn_plan(elem, hd, M, G, kv, slots, req, 1, 64, 0, 0, 0, 0, 0, *(C.byref(o) for o in out))
+    return dict(zip(("waves", "row_tiles", "row_blocks", "splits", "tiles_per_split", "ring", "dma", "pair"), (o.value for o in out)))
+
+
+@pytest.mark.parametrize("M,G,kv,hd,slots,splits", [
+    (16, 2, 4, 128, 28 * 64, 28), (16, 2, 4, 128, 28 * 64 + 1, 15), (16, 2, 4, 128, 33 * 64 - 1, 17), (16, 2, 4, 128, 65 * 64, 22),
+    (16, 2, 4, 128, 128 * 64, 32), (16, 2, 4, 128, 128 * 64 + 1, 43), (5, 1, 4, 64, 29 * 64, 15), (5, 1, 4, 64, 29 * 32, 15),
+    (7, 3, 2, 128, 29 * 64, 29),                                             # two KV heads: a tile to a split
+])
+def test_splits_of_few_kv_heads(M, G, kv, hd, slots, splits):
+    p = _plan(M, G, kv, slots, hd)
+    assert p["splits"] == splits and not p["pair"], p
+    assert p["splits"] * p["tiles_per_split"] * 64 >= slots
+
+
+@pytest.mark.parametrize("M,G,kv,slots,dma", [
+    (16, 4, 4, 28 * 64, False), (16, 4, 4, 28 * 64 + 1, True), (13, 4, 8, 128 * 64, True), (16, 4, 8, 128 * 64 + 1, False),
+    (12, 4, 4, 64 * 64, False), (17, 4, 4, 64 * 64, False), (16, 4, 3, 64 * 64, False), (16, 4, 9, 64 * 64, False),
+])
+def test_four_row_tiles_on_few_kv_heads(M, G, kv, slots, dma):
+    p = _plan(M, G, kv, slots)
+    assert (p["dma"] == 2 and p["row_tiles"] == 1 and p["waves"] == 4) == dma, p
