@@ -1486,13 +1486,18 @@ hipError_t launch_gemm_wide(int epi, int layout_nt, int n_tiles, const GemmArgs&
         }
     }
     if (epi == EPI_RESID && !narrow && part && block_mode != 0) {
-        // 256-row blocks where their estimate is 3 % below the 128-row kernel's, which runs 5 % over its own with nearly every compute unit busy.
-        // us, 128-row blocks -> 256-row blocks: 5120 x 5120, 1024 rows 95.5 -> 78.7; 11008 x 4096, 700 rows 91.7 -> 84; 14336 x 4096, 700 rows
-        // 116.5 -> 100.6; 18944 x 3584, 1024 rows 159.8 -> 148.3; 16384 x 6144, 512 rows 136 -> 115; 22016 x 8192, 389 .. 1024 rows 186 .. 340 -> 172 ..
-        // 319.  A short K, or a second round on some XCD, is worse: 2048 x 2048, 512 rows 21.9 / 24.9; 18944 x 3584, 700 rows in 84 units 122 / 161.
+        // 256-row blocks where their estimate is 3 % below the 128-row kernel's: with up to 216 of its blocks 6 to 20 % faster in all of 30 launches
+        // (us, 128-row blocks -> 256-row blocks: 5120 x 5120, 1024 rows 91.0 -> 75.8; 14336 x 4096, 700 rows 114 -> 97.5; 16384 x 6144, 512 rows
+        // 137 -> 109).  217 to 256 blocks, nearly every compute unit at once, take up to 18 % more than estimated behind a long K: up to 2 % above it
+        // the 256-row blocks are still 2 to 11 % faster in all of 26 (22016 x 8192, 900 rows 364 -> 332, estimates 311 and 306; 14336 x 4096, 960 rows
+        // 132 -> 121; from 2 to 4 % above 0.95 .. 1.02, further up mostly slower).  Two rounds of short slices overlap, which the estimate does not
+        // know: 4608 x 4608 in slices of 36 k-tiles, 769 rows 58.2 / 59.9, 850 rows 60.7 / 62.6; of 100 and more 11 % faster to 1 %
+        // (12288 x 4608, 1024 rows 138.6 -> 131.3).  A short K, or a second round on some XCD, is worse: 2048 x 2048, 512 rows 21.9 / 32.1;
+        // 18944 x 3584, 850 rows 128.8 / 137.5.
         const WideGrid g = wide_grid(sh, epi, a.M, n_tiles, a.nkt, part_bytes);
-        const bool full = g.n_cols * g.k_splits * g.m_blocks > 216 && g.n_cols * g.k_splits * g.m_blocks <= 256;
-        const int ks = block_slices(g.n_cols, a.M, a.nkt, part_bytes, block_mode > 0 ? 1e30 : g.us * (full ? 1.02 : 0.97));
+        const int blocks = g.n_cols * g.k_splits * g.m_blocks;
+        const bool full = blocks > 216 && blocks <= 256, overlap = blocks > 256 && a.nkt / g.k_splits < 64;
+        const int ks = block_slices(g.n_cols, a.M, a.nkt, part_bytes, block_mode > 0 ? 1e30 : overlap ? 0 : g.us * (full ? 1.02 : 0.97));
         if (ks > 1) {
             const int m_blocks = (a.M + 255) / 256, grid = (g.n_cols * ks + 7) / 8 * 8 * m_blocks;
             hipLaunchKernelGGL((block_gemm_kernel<EPI_RESID, true, 2, 4, 8, 4, 4>), dim3(grid), dim3(512), 0, s, a, layout_nt, n_tiles, g.n_cols, m_blocks, ks,

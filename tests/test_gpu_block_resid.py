@@ -32,3 +32,27 @@ def test_residual_projection_in_256_row_blocks(d, ffn, rows, taken, monkeypatch)
     assert any("block_gemm_kernel<1" in n or "block_gemm_kernelILi1" in n for n in names) == taken, names
     if not taken:   # the same projections in 128-row blocks with K slices
         assert any("wide_gemm_kernel<1, true" in n or "wide_gemm_kernelILi1ELb1" in n for n in names), names
+
+
+@pytest.mark.parametrize("d,ffn,rows,taken", [
+    (4608, 256, 769, 0), (4608, 256, 850, 0),   # output projection in 504 128-row blocks of 36 k-tiles: two rounds that overlap
+    (4608, 256, 960, 1),                        # in 144
+    (4608, 12288, 900, 2),                      # the same, and the down projection in 432 blocks of 128 k-tiles
+])
+def test_residual_projection_takes_the_shorter_form(d, ffn, rows, taken):
+    """Which of the layer's two residual projections go into 256-row blocks by the estimates."""
+    import numpy as np
+    import torch
+    from paper_2507_02620_amd import flowspec as fs
+    from tests.gpu_util import kernel_names
+    w = lambda n, k: torch.randn(n, k, device="cuda").mul_(0.02).bfloat16()  # noqa: E731
+    ones = torch.ones(d, dtype=torch.bfloat16, device="cuda")
+    layer = dict(rms_attn=ones, rms_ffn=ones, wq=w(d, d), wk=w(128, d), wv=w(128, d), wo=w(d, d), w_gate=w(ffn, d), w_up=w(ffn, d), w_down=w(d, ffn))
+    st = fs.Stage(n_layers=1, d_model=d, n_q_heads=d // 128, n_kv_heads=1, head_dim=128, d_ffn=ffn, vocab=0, dtype=fs.FS_BF16, rms_eps=1e-5, rope_theta=1e4,
+                  kv_capacity=rows, max_tree=rows, max_seg=rows, layers=[layer])
+    kv, x, out = st.new_kv_cache(), w(rows, d), torch.empty(rows, d, dtype=torch.bfloat16, device="cuda")
+    parent = np.arange(-1, rows - 1, dtype=np.int32)
+    print(f"[case] {d} x {ffn}, {rows} rows", flush=True)
+    names = kernel_names(lambda: st.tree_verify_stage(kv, 0, 0, x, 0, parent, out))
+    assert sum("block_gemm_kernel<1" in n or "block_gemm_kernelILi1" in n for n in names) == taken, names
+    st.close()
