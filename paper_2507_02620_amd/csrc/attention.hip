@@ -999,7 +999,8 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     }
     // Four row tiles on 4 to 8 KV heads behind 29 to 128 tiles: a wave each and two tile buffers of the direct-to-LDS kernel, instead of two row
     // tiles for two waves and registers (4 heads x 49 rows, 7k slots 18.9 -> 17.0 us with the merge, 8 heads x 64 rows, 2k / 4k / 7k 16.4 / 18.6 /
-    // 21.8 -> 15.4 / 17.8 / 20.0; 16 heads gain nothing, 7k 25.4 -> 25.6, and three row tiles lose: 8 heads x 48 rows, 4k 15.9 -> 16.6).
+    // 21.8 -> 15.4 / 17.8 / 20.0; 16 heads gain nothing, 7k 25.4 -> 25.6).  Three row tiles have a wave each either way, so only the way of staging would change, and
+    // loses: 8 heads x 48 rows, 4k 15.9 -> 16.6.
     const bool few_heads = dma_shape && mtiles == 4 && !deep_ring && Hkv >= 4 && Hkv <= 8 && ntiles > 28 && ntiles <= 128 && dma_override == 0 &&
                            wgs_override <= 0 && mtw_override <= 0 && nwc_override <= 0 && nset_override <= 0;
     if (few_heads) mtw = 1;
@@ -1029,14 +1030,20 @@ void attn_plan(int elem_bytes, int hd, int M, int G, int Hkv1, int L, const Attn
     const int per_split = Hkv * *row_blocks;  // workgroups per KV split
     int want = (target + per_split - 1) / per_split;
     if ((deep_ring || pairs) && wgs_override <= 0) want = splits_one_round(per_split, ntiles);
-    // Few KV heads, 16-bit K/V: 29 to 128 tiles come at least two to a split and go into at most 32.  A split of one tile costs its way in and out
-    // and a partial result of every row for the merge, which 64 of them make the longer part.  us with the merge, as many splits as workgroups
-    // were wanted / so: 8 heads x 64 rows, 2k / 4k / 8k slots 17.4 / 15.4, 25.5 / 19.1, 27.6 / 22.7, x 4 rows 12.5 / 11.8, 17.6 / 13.9, 19.8 / 17; 4 heads
-    // x 28 rows 12.4 / 12.2, 16.7 / 13.6, 18.1 / 16.4; 8 heads of 64, 4k 16.5 / 12.4.  Elsewhere one tile each is the faster one: 17 tiles (8 heads x
-    // 16 rows 10.8 / 11.2), more than 128 (2 heads x 96 rows, 16k 24.4 / 26.1), one or two heads (6 rows 12.1 / 12.7), f32, whose tiles take several
-    // times as long (2 heads x 48 rows, 4k 17.5 / 19.3).
-    else if (wgs_override <= 0 && elem_bytes == 2 && per_split >= 4 && ntiles > 28 && ntiles <= 128)
-        want = std::min(want, std::min(32, (ntiles + 1) / 2));
+    // Few KV heads, 16-bit K/V: of 29 to 128 tiles two come to a split up to 64, three up to 96 (one row tile: all, two: 112), then four.  A split of
+    // one tile costs its way in and out and a partial result of every row for the merge, which 64 of them make the longer part.  us with
+    // the merge, as many splits as workgroups were wanted / so: 8 heads x 64 rows, 2k / 4k / 8k slots 17.4 / 15.4, 23.2 / 17.4, 24.7 / 20.5; 4 heads x 28
+    // rows, 2k / 4k / 8k 12.4 / 12.2, 16.7 / 13.6, 18.1 / 16.2; 8 heads of 64, 4k 16.5 / 12.4.  With fewer rows there is less to merge (100 tiles, three /
+    // four to a split: 4 heads x 16 rows 14.4 / 15.6, x 28 rows 14.9 / 16.2, 8 heads x 64 rows 21.7 / 19.7; 128 tiles: 4 heads x 16 rows 15.1 / 15.7, 8 heads
+    // x 28 rows 18.8 / 17.3).  Elsewhere one tile each is the faster one: 17 tiles (8 heads x 16 rows 10.8 / 11.2), more than 128 (2 heads x 96
+    // rows, 16k 24.4 / 26.1), one or two heads (6 rows 12.1 / 12.7), f32, whose tiles take several times as long (2 heads x 48 rows, 4k 17.5 /
+    // 19.3).  Of workgroups of eight waves a compute unit holds one: a few beyond 256 would be a second round (4 heads x 360 rows, 66 / 70 / 76 tiles, 264
+    // / 288 / 312 workgroups 28.2 / 28.7 / 29.4, in one round 23.6 / 25.2 / 24.2; two tiles to a split 27.0 / 26.6 / 28.6).
+    else if (wgs_override <= 0 && elem_bytes == 2 && per_split >= 4 && ntiles > 28 && ntiles <= 128) {
+        const int walk = ntiles <= 64 ? 2 : (ntiles <= (mtiles == 1 ? 128 : mtiles == 2 ? 112 : 96) ? 3 : 4);
+        want = std::min(want, (ntiles + walk - 1) / walk);
+        if (nw > 4 && per_split * want > 256 && per_split * want <= 320) want = splits_one_round(per_split, ntiles);
+    }
     // Few tiles for few rows: walking them one after another is shorter than the merge launch (us, merge / none: 8 heads of 64, 16 rows each,
     // 2 / 3 / 4 tiles 9.4 / 7.3, 9.7 / 7.8, 9.9 / 9.6, 64 rows, 2 / 3 tiles 10.1 / 9.0, 10.7 / 10.0; 32 heads of 128, 16 rows, 2 tiles 9.7 / 8.6,
     // 3 tiles, two of them masked 10.4 / 11.4, 32 rows, 2 tiles 10.4 / 9.0, 64 rows, 3 tiles 12.4 / 13.5; f32, up to 16 rows per head, heads of 64,

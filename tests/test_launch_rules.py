@@ -60,8 +60,11 @@ def _plan(M, G, kv, slots, hd=128, elem=2):
 
 
 @pytest.mark.parametrize("M,G,kv,hd,slots,splits", [
-    (16, 2, 4, 128, 28 * 64, 28), (16, 2, 4, 128, 28 * 64 + 1, 15), (16, 2, 4, 128, 33 * 64 - 1, 17), (16, 2, 4, 128, 65 * 64, 22),
-    (16, 2, 4, 128, 128 * 64, 32), (16, 2, 4, 128, 128 * 64 + 1, 43), (5, 1, 4, 64, 29 * 64, 15), (5, 1, 4, 64, 29 * 32, 15),
+    (16, 2, 4, 128, 28 * 64, 28), (16, 2, 4, 128, 28 * 64 + 1, 15), (16, 2, 4, 128, 33 * 64 - 1, 17), (16, 2, 4, 128, 64 * 64, 32),
+    (16, 2, 4, 128, 65 * 64, 22), (16, 2, 4, 128, 112 * 64, 38), (16, 2, 4, 128, 113 * 64, 29), (16, 3, 4, 128, 96 * 64, 32), (16, 3, 4, 128, 97 * 64, 25),
+    (16, 2, 4, 128, 128 * 64, 32), (16, 2, 4, 128, 128 * 64 + 1, 43), (5, 1, 4, 64, 29 * 64, 15), (5, 1, 4, 64, 81 * 64, 27),
+    (16, 1, 12, 128, 80 * 64, 27), (16, 1, 12, 128, 100 * 64, 34), (1, 1, 5, 128, 128 * 64, 43),   # one row tile (12 heads: 43 wanted)
+    (45, 8, 4, 128, 36 * 64, 18), (45, 8, 4, 128, 66 * 64, 17), (45, 8, 4, 128, 76 * 64, 19), (45, 8, 4, 128, 80 * 64, 27),   # 12 workgroups of 8 waves
     (7, 3, 2, 128, 29 * 64, 29),                                             # two KV heads: a tile to a split
 ])
 def test_splits_of_few_kv_heads(M, G, kv, hd, slots, splits):
