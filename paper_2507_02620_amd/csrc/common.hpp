@@ -31,11 +31,13 @@ struct Elem<float> {
     using out4_t = f32x4;
     static constexpr int EPF = 4;
     static constexpr int KT = 16;
+    static constexpr int STEPS = 4;  // matrix instructions per fragment pair, each of which needs the one before it
+    static __device__ __forceinline__ f32x4 mma_step(int e, frag_t a, frag_t b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    }
     static __device__ __forceinline__ f32x4 mma(frag_t a, frag_t b, f32x4 c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[0], b[0], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[1], b[1], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[2], b[2], c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[3], b[3], c, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < STEPS; ++e) c = mma_step(e, a, b, c);
         return c;
     }
     static __device__ __forceinline__ frag_t zero() { return frag_t{0.f, 0.f, 0.f, 0.f}; }
@@ -51,6 +53,8 @@ struct Elem<bf16_t> {
     using out4_t = bf16x4;
     static constexpr int EPF = 8;
     static constexpr int KT = 32;
+    static constexpr int STEPS = 1;
+    static __device__ __forceinline__ f32x4 mma_step(int, frag_t a, frag_t b, f32x4 c) { return mma(a, b, c); }
     static __device__ __forceinline__ f32x4 mma(frag_t a, frag_t b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
