@@ -611,9 +611,10 @@ static int verify_batch(fs_stage* st, const fs_batch_item* items, int n, const v
     int aMTW, aRB;
     attn_plan(st->elem, hd, max_M, G, d.n_kv_heads, max_L, at.req, n_live, kMaxSplits, st->tun.attn_wgs, st->tun.attn_mtw, st->tun.attn_nset,
               st->tun.attn_nwc, st->tun.attn_dma, &at.nwc, &aMTW, &aRB, &at.n_splits, &at.tiles_per_split, &at.nset, &at.dma, &at.pair);
-    // More workgroups than run at once (two per compute unit; one of 8 waves or of tiles in pairs): the longest contexts first where that is
-    // estimated the shorter launch.  A single round is better left alone (9 requests: 27.4 -> 28.8 sorted), and the merge of splits looks a row's
-    // request up by ascending rows.
+    // More than two workgroups per compute unit: the longest contexts first where that is estimated the shorter launch, with two running at once
+    // on a unit, or one where they have 8 waves or take tiles in pairs (such workgroups come in rounds from 257 on; between there and 512 the order
+    // as given was kept unmeasured).  A single round is better left alone (9 requests: 27.4 -> 28.8 sorted), and the merge of splits looks a
+    // row's request up by ascending rows.
     if (at.n_splits == 1 && (long long)n_live * d.n_kv_heads * aRB > 512) {
         const int bs = attn_tile_slots(st->elem, hd), block = at.nwc * aMTW * 16;
         int tiles[FS_MAX_BATCH], wgs[FS_MAX_BATCH];

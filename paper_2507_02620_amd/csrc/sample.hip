@@ -564,7 +564,9 @@ hipError_t launch_accept_sample(const float* logits, int vocab, float inv_temp, 
     }
     // Residual draw in a launch of its own: its target, counter and the chunks' sums take the places of the row sums, which nobody needs
     // behind the walk.  From 12 chunks on, us of the whole call with the draw inside / outside of the walk: 16 rows x 50257 35.1 / 31.2, 40 rows x
-    // 100000 47 / 36, 80 rows x 152064 66 / 48; a call without a draw pays 2.3 us for the empty launch and has as much from the walk.
+    // 100000 47 / 36, 80 rows x 152064 66 / 48; a call without a draw pays 2 us for the empty launch.  A row sum's place holds one chunk's sum, so
+    // 12 chunks also need 14 rows: that line is the scratch's, not a measured one, and with fewer rows the draw stays in the walk (24 us of
+    // one compute unit for 152064 logits).
     const int draw_chunks = std::min(std::min((vocab + DRAW_BLOCK - 1) / DRAW_BLOCK, 64), n_ver - 2);
     const bool draw = draw_chunks >= 12;
     hipLaunchKernelGGL(accept_sample_kernel, dim3(1), dim3(SMP_THREADS), 0, s, logits, vocab, inv_temp, vec, rowm, rowZ, token, parent, T, n_ver, seed,
